@@ -27,8 +27,8 @@
  *     that enqueues several kernels may by then have enqueued the earlier ones, so treat its
  *     outputs and workspace as undefined. No call aborts or throws.
  *   - GQA: G = Hq / Hkv must be an integer; query head h reads KV head h / G.
- *   - Supported: dtype bf16 (MFMA kernels, d in {64, 128}, G <= 16) and fp32 (plain
- *     correctness kernels, d <= 256). Innermost dimension contiguous; base pointers and
+ *   - Supported: dtype bf16 (MFMA kernels, d in {64, 128}, G <= 16) and fp32 (fp32 MFMA
+ *     kernels, d <= 256). Innermost dimension contiguous; base pointers and
  *     row strides 16-byte aligned. Output dtype = input dtype; all running state is fp32.
  */
 #ifndef PARALLAX_H
@@ -102,7 +102,8 @@ typedef struct {
  *   use_r     1 = Parallax; 0 = softmax-only twin (r may be NULL, correction branch skipped)
  *   num_splits 0 = library heuristic, else the number of key-range splits to use
  *   workspace fp32 scratch for split partials, >= parallax_decode_workspace_bytes(...);
- *             may be NULL only when num_splits == 1
+ *             may be NULL only when num_splits == 1 (bf16). fp32 calls use as many splits as it
+ *             has room for, one without it
  *
  * Several query rows (Tq > 1; speculative rows or a short chunk, the causal set of Sec. 2.1 at
  * absolute positions): q, r, o are [B, Hq, Tq, d] and the rows are the LAST Tq positions of the
@@ -330,7 +331,7 @@ plx_status parallax_decode_mla(const plx_decode_mla_args *args, void *hip_stream
  * heads of its group. Every tensor 16-byte aligned with the head dimension innermost and
  * contiguous; *_stride are element strides {batch, head, row} as in plx_prefill_args, an all-zero
  * triple meaning the dense [B, H, T, d] layout (row_stats is always dense). bf16 (d = 64 or 128;
- * MFMA kernels) or fp32 (d <= 256, plain untuned path, vbar in fp32 too, dense layout only). causal, Tkv and window as in the forward (window > 0 needs causal != 0; the row cache
+ * MFMA kernels) or fp32 (d <= 256, fp32 MFMA kernels, vbar in fp32 too, dense layout only). causal, Tkv and window as in the forward (window > 0 needs causal != 0; the row cache
  * must come from a forward call with the same window).
  *   workspace  fp32 scratch, >= parallax_prefill_backward_workspace_bytes(B, Hq, T) = 16 bytes
  *              per query row (four row scalars built from lse, ubar, tau = dO.o, beta = dO.vbar;

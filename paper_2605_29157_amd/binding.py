@@ -327,9 +327,11 @@ def parallax_decode(q, r, k, v, scale, seq_lens=None, use_r=True, num_splits=0, 
         Lmax = int(max_len) if max_len is not None else block_table.shape[1] * k.shape[2]
     if out is None:
         out = torch.empty_like(q)
-    if workspace is None and num_splits != 1 and q.dtype == torch.bfloat16:
+    if workspace is None and num_splits != 1:
         # (with a window the library may pick fewer splits than for Lmax, never more)
-        S = num_splits or parallax_decode_num_splits(B, Hq, Hkv, Lmax, d)
+        # (fp32: one record per 128 keys is the most that the library asks for)
+        S = num_splits or (parallax_decode_num_splits(B, Hq, Hkv, Lmax, d) if q.dtype == torch.bfloat16
+                           else min(PLX_MAX_SPLITS, Lmax // 128))
         if S > 1:
             workspace = torch.empty(B * Hq * Tq * S * (2 * d + 4), dtype=torch.float32,
                                     device=q.device)
