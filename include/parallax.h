@@ -377,6 +377,24 @@ size_t parallax_prefill_backward_workspace_bytes(int32_t B, int32_t Hq, int32_t 
 plx_status parallax_prefill_backward(const plx_prefill_bwd_args *args, void *hip_stream);
 
 /*
+ * The lists of plx_prefill_args / plx_prefill_bwd_args from a block mask on the device. mask
+ * [lists, n_row_blocks, n_tiles] bytes, nonzero = row block x key tile is listed (lists = sparse_batch *
+ * sparse_heads, n_row_blocks = ceil(T / 128), n_tiles = ceil(Tkv / 64)).
+ *   row_ptr   [lists * n_row_blocks + 1], tile_idx [lists * n_row_blocks * n_tiles]: written
+ *   col_ptr   [lists * ceil(n_tiles / 2) + 1], col_idx [lists * ceil(n_tiles / 2) * n_row_blocks]:
+ *             written, or both NULL
+ *   counts    scratch, lists * (n_row_blocks + ceil(n_tiles / 2)) int32
+ * Entries behind the last one listed are left as they are. Two kernels, no synchronisation.
+ */
+typedef struct {
+    const uint8_t *mask;
+    int32_t lists, n_row_blocks, n_tiles;
+    int32_t *counts, *row_ptr, *tile_idx, *col_ptr, *col_idx;
+} plx_block_list_args;
+
+plx_status parallax_block_lists(const plx_block_list_args *args, void *hip_stream);
+
+/*
  * RMSNorm over the head dimension, then rotary position embedding, on up to three tensors of one
  * layer (q, rho, k) in one launch -- what the paper's language-model runs apply in front of the
  * attention call (Sec. 5 experiment setup, backbone appendix: RMSNorm on q, k and rho; RoPE with

@@ -26,7 +26,7 @@ EXPORTED_SYMBOLS = (
     "parallax_decode_static", "parallax_decode_static_scratch_bytes",
     "parallax_decode_mla", "parallax_decode_mla_workspace_bytes", "parallax_decode_mla_num_splits",
     "parallax_prefill", "parallax_prefill_backward", "parallax_prefill_backward_workspace_bytes",
-    "parallax_norm_rope", "parallax_rope_table", "parallax_util_copy", "parallax_util_read",
+    "parallax_block_lists", "parallax_norm_rope", "parallax_rope_table", "parallax_util_copy", "parallax_util_read",
     "parallax_util_read_grid", "parallax_util_read_sink_slots", "parallax_util_mfma", "parallax_strerror", "parallax_version",
 )
 
@@ -125,6 +125,12 @@ class plx_decode_mla_args(ctypes.Structure):
     ]
 
 
+class plx_block_list_args(ctypes.Structure):
+    _fields_ = [("mask", ctypes.c_void_p), ("lists", ctypes.c_int32), ("n_row_blocks", ctypes.c_int32),
+                ("n_tiles", ctypes.c_int32), ("counts", ctypes.c_void_p), ("row_ptr", ctypes.c_void_p),
+                ("tile_idx", ctypes.c_void_p), ("col_ptr", ctypes.c_void_p), ("col_idx", ctypes.c_void_p)]
+
+
 class plx_norm_rope_tensor(ctypes.Structure):
     _fields_ = [("x", ctypes.c_void_p), ("y", ctypes.c_void_p), ("gamma", ctypes.c_void_p),
                 ("H", ctypes.c_int32), ("rope", ctypes.c_int32)]
@@ -173,6 +179,8 @@ def load_library() -> ctypes.CDLL:
         lib.parallax_prefill_backward.restype = ctypes.c_int
         lib.parallax_prefill_backward_workspace_bytes.argtypes = [ctypes.c_int32] * 3
         lib.parallax_prefill_backward_workspace_bytes.restype = ctypes.c_size_t
+        lib.parallax_block_lists.argtypes = [ctypes.POINTER(plx_block_list_args), ctypes.c_void_p]
+        lib.parallax_block_lists.restype = ctypes.c_int
         lib.parallax_norm_rope.argtypes = [ctypes.POINTER(plx_norm_rope_args), ctypes.c_void_p]
         lib.parallax_norm_rope.restype = ctypes.c_int
         lib.parallax_rope_table.argtypes = [ctypes.c_void_p, ctypes.c_int32, ctypes.c_int32, ctypes.c_float,
@@ -464,6 +472,40 @@ def block_mask_column_lists(block_mask):
     return col_ptr, col_idx
 
 
+def attach_block_lists(a, block_mask, device, stream=None, columns=False):
+    """Build the lists of a block mask on the device (current stream) and point the prefill (columns:
+    backward) arguments `a` at them, for a launch on `stream`. Returns the buffer that holds them:
+    keep it until the call has been enqueued."""
+    m = block_mask.to(device=device, dtype=torch.bool)
+    while m.dim() < 4:
+        m = m.unsqueeze(0)
+    Bs, Hs, nrb, nkt = m.shape
+    m = m.contiguous()
+    rows, cols, ncb = Bs * Hs * nrb, 0, (nkt + 1) // 2
+    if columns:
+        cols = Bs * Hs * ncb
+    # [row_ptr | col_ptr | counts | tile_idx | col_idx]
+    sizes = [rows + 1, cols + 1 if columns else 0, rows + cols, rows * nkt, cols * nrb]
+    buf = torch.empty(sum(sizes), dtype=torch.int32, device=device)
+    at = [buf.data_ptr() + 4 * sum(sizes[:i]) for i in range(5)]
+    la = plx_block_list_args()
+    la.mask, la.lists, la.n_row_blocks, la.n_tiles = m.data_ptr(), Bs * Hs, nrb, nkt
+    la.row_ptr, la.counts, la.tile_idx = at[0], at[2], at[3]
+    a.sparse_row_ptr, a.sparse_tile_idx, a.sparse_batch, a.sparse_heads = at[0], at[3], Bs, Hs
+    if columns:
+        la.col_ptr, la.col_idx = at[1], at[4]
+        a.sparse_col_ptr, a.sparse_col_idx = at[1], at[4]
+    current = torch.cuda.current_stream()
+    st = load_library().parallax_block_lists(ctypes.byref(la), current.cuda_stream)
+    if st != PLX_OK:
+        raise ParallaxError(st, "parallax_block_lists")
+    if stream is not None and stream.cuda_stream != current.cuda_stream:
+        other = torch.cuda.ExternalStream(stream.cuda_stream)
+        other.wait_stream(current)
+        buf.record_stream(other)
+    return buf
+
+
 def parallax_prefill(q, r, k, v, scale, causal=True, use_r=True, out=None, stream=None, window=0,
                      save_for_backward=False, block_mask=None, prep=None):
     """Parallax prefill forward over T query rows and Tkv keys (causal: the rows are the last
@@ -483,9 +525,7 @@ def parallax_prefill(q, r, k, v, scale, causal=True, use_r=True, out=None, strea
         nrb, nkt = -(-q.shape[2] // BLOCK_ROWS), -(-k.shape[2] // BLOCK_KEYS)
         if tuple(block_mask.shape[-2:]) != (nrb, nkt):
             raise ValueError("block_mask must end in [ceil(T/128), ceil(Tkv/64)] = [%d, %d]" % (nrb, nkt))
-        row_ptr, tile_idx, Bs, Hs = block_mask_lists(block_mask.to(q.device))
-        a.sparse_row_ptr, a.sparse_tile_idx = row_ptr.data_ptr(), tile_idx.data_ptr()
-        a.sparse_batch, a.sparse_heads = Bs, Hs
+        lists = attach_block_lists(a, block_mask, q.device, stream)  # alive until the launch below
     if prep is not None:
         a.prep = prep
     if save_for_backward:
@@ -542,11 +582,7 @@ def parallax_prefill_backward(q, r, k, v, o, vbar, row_stats, d_o, scale, causal
         nrb, nkt = -(-q.shape[2] // BLOCK_ROWS), -(-k.shape[2] // BLOCK_KEYS)
         if tuple(block_mask.shape[-2:]) != (nrb, nkt):
             raise ValueError("block_mask must end in [ceil(T/128), ceil(Tkv/64)] = [%d, %d]" % (nrb, nkt))
-        row_ptr, tile_idx, Bs, Hs = block_mask_lists(block_mask.to(q.device))
-        col_ptr, col_idx = block_mask_column_lists(block_mask.to(q.device))
-        a.sparse_row_ptr, a.sparse_tile_idx = row_ptr.data_ptr(), tile_idx.data_ptr()
-        a.sparse_col_ptr, a.sparse_col_idx = col_ptr.data_ptr(), col_idx.data_ptr()
-        a.sparse_batch, a.sparse_heads = Bs, Hs
+        lists = attach_block_lists(a, block_mask, q.device, stream, columns=True)  # alive until the launch below
     st = load_library().parallax_prefill_backward(ctypes.byref(a), _stream_ptr(stream))
     if st != PLX_OK:
         raise ParallaxError(st, "parallax_prefill_backward")

@@ -1,0 +1,110 @@
+// Block mask -> the lists that the block-sparse kernels walk (index bookkeeping of the sparsity
+// patterns of the paper's Sec. 5, no arithmetic).
+//
+// A line is a row block (entries: its listed key tiles) or a key block of two key tiles (entries:
+// 4 * row block + flags); lines are independent but for where their entries go, so one launch
+// counts and a second places: every workgroup adds up the counts in front of its lines itself
+// (reads that the L2 holds) instead of a third launch scanning them. What bounds it is the two
+// launches; the host never learns the number of entries, so nothing waits for the GPU. Built from
+// tensor operations instead (a scan, a compaction whose size the host reads back, casts: 40 launches
+// and three waits per training step), the lists took 310 us of a 537 us step over 2 sequences x
+// 2048 rows, 16 heads, a quarter of the cells; now 12 us of 228.
+#include "plx_device.h"
+#include "plx_kernels.h"
+
+namespace plx {
+
+namespace {
+constexpr int kLinesPerGroup = 4;  // one wave each
+
+// Entry n of a line: 0 = not listed, else 1 + the value that goes into the list.
+struct LineReader {
+    const uint8_t *cells;
+    int64_t step;
+    int n, second;  // second: bytes from a cell to its neighbour tile (0: row line, -1: none exists)
+    __device__ LineReader(const BlockListParams &p, int64_t line) {
+        const int64_t row_lines = (int64_t)p.lists * p.n_row_blocks;
+        if (line < row_lines) {
+            cells = p.mask + line * p.n_tiles, step = 1, n = p.n_tiles, second = 0;
+        } else {
+            const int n_cb = (p.n_tiles + 1) / 2;
+            const int64_t l = line - row_lines, list = l / n_cb;
+            const int tile = 2 * (int)(l % n_cb);
+            cells = p.mask + list * p.n_row_blocks * p.n_tiles + tile;
+            step = p.n_tiles, n = p.n_row_blocks, second = tile + 1 < p.n_tiles ? 1 : -1;
+        }
+    }
+    __device__ int entry(int i) const {
+        if (i >= n) return 0;
+        const uint8_t *at = cells + i * step;
+        if (second == 0) return *at ? 1 + i : 0;
+        const int flags = (at[0] ? 1 : 0) | (second > 0 && at[1] ? 2 : 0);
+        return flags ? 1 + 4 * i + flags : 0;
+    }
+};
+
+__device__ __forceinline__ int64_t line_total(const BlockListParams &p) {
+    const int64_t rows = (int64_t)p.lists * p.n_row_blocks;
+    return p.col_ptr ? rows + (int64_t)p.lists * ((p.n_tiles + 1) / 2) : rows;
+}
+
+__global__ __launch_bounds__(64 * kLinesPerGroup) void block_list_count_kernel(BlockListParams p) {
+    const int64_t line = (int64_t)blockIdx.x * kLinesPerGroup + (threadIdx.x >> 6);
+    if (line >= line_total(p)) return;
+    const int lane = threadIdx.x & 63;
+    const LineReader in(p, line);
+    int count = 0;
+    for (int i = lane; i - lane < in.n; i += 64) count += __popcll(__ballot(in.entry(i) != 0));
+    if (lane == 0) p.counts[line] = count;
+}
+
+__global__ __launch_bounds__(64 * kLinesPerGroup) void block_list_place_kernel(BlockListParams p) {
+    __shared__ int part[kLinesPerGroup];
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int64_t total = line_total(p), rows = (int64_t)p.lists * p.n_row_blocks;
+    const int64_t line0 = (int64_t)blockIdx.x * kLinesPerGroup, line = line0 + w;
+    // entries in front of the workgroup's first line, of its kind (row lines and key lines are separate
+    // lists; a workgroup may hold the last of one and the first of the other)
+    const int64_t kind0 = line0 < rows ? 0 : rows;
+    int before = 0;
+    for (int64_t i = kind0 + threadIdx.x; i < line0; i += 64 * kLinesPerGroup) before += p.counts[i];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) before += __shfl_xor(before, off, 64);
+    if (lane == 0) part[w] = before;
+    __syncthreads();
+    if (line >= total) return;
+    const bool row_line = line < rows;
+    int at = 0;
+    if (row_line == (line0 < rows))
+        for (int i = 0; i < kLinesPerGroup; ++i) at += part[i];
+    for (int64_t i = row_line ? line0 : (line0 > rows ? line0 : rows); i < line; ++i) at += p.counts[i];
+
+    int32_t *ptr = row_line ? p.row_ptr : p.col_ptr;
+    int32_t *idx = row_line ? p.tile_idx : p.col_idx;
+    const int64_t e = row_line ? line : line - rows;
+    const LineReader in(p, line);
+    if (lane == 0) {
+        ptr[e] = at;
+        if (line + 1 == (row_line ? rows : total)) ptr[e + 1] = at + p.counts[line];
+    }
+    for (int i = lane; i - lane < in.n; i += 64) {
+        const int x = in.entry(i);
+        const unsigned long long hits = __ballot(x != 0);
+        if (x != 0) idx[at + __popcll(hits & ((1ull << lane) - 1ull))] = x - 1;
+        at += __popcll(hits);
+    }
+}
+}  // namespace
+
+hipError_t launch_block_lists(const BlockListParams &p, hipStream_t stream) {
+    const int64_t lines = (int64_t)p.lists * p.n_row_blocks + (p.col_ptr ? (int64_t)p.lists * ((p.n_tiles + 1) / 2) : 0);
+    const int64_t groups = (lines + kLinesPerGroup - 1) / kLinesPerGroup;
+    if (groups > (1 << 23)) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)groups), block(64 * kLinesPerGroup);
+    hipLaunchKernelGGL(block_list_count_kernel, grid, block, 0, stream, p);
+    if (hipError_t err = hipGetLastError()) return err;
+    hipLaunchKernelGGL(block_list_place_kernel, grid, block, 0, stream, p);
+    return hipGetLastError();
+}
+
+}  // namespace plx

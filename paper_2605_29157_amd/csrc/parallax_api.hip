@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 
 #include <atomic>
+#include <initializer_list>
 #include <mutex>
 
 #include "plx_kernels.h"
@@ -538,6 +539,23 @@ plx_status parallax_decode_mla(const plx_decode_mla_args *a, void *hip_stream) {
     }
     return plx::launch_decode_mla(p, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? PLX_OK
                                                                                          : PLX_ERR_LAUNCH;
+}
+
+plx_status parallax_block_lists(const plx_block_list_args *a, void *hip_stream) {
+    if (!a || !a->mask || !a->counts || !a->row_ptr || !a->tile_idx) return PLX_ERR_NULL;
+    if ((a->col_ptr != nullptr) != (a->col_idx != nullptr)) return PLX_ERR_NULL;
+    if (a->lists < 1 || a->n_row_blocks < 1 || a->n_tiles < 1) return PLX_ERR_SHAPE;
+    // (entries are counted in 32 bits; a key list holds at most as many as the mask has cells)
+    if ((int64_t)a->lists * a->n_row_blocks > 0x7fffffffLL / a->n_tiles || a->n_row_blocks > 0x1fffffff ||
+        (int64_t)a->lists * ((int64_t)a->n_row_blocks + (a->n_tiles + 1) / 2) > (1 << 25))
+        return PLX_ERR_SHAPE;
+    for (const int32_t *ptr : {a->counts, a->row_ptr, a->tile_idx, a->col_ptr, a->col_idx})
+        if (reinterpret_cast<uintptr_t>(ptr) & 3u) return PLX_ERR_ALIGN;
+    plx::BlockListParams p{};
+    p.mask = a->mask, p.lists = a->lists, p.n_row_blocks = a->n_row_blocks, p.n_tiles = a->n_tiles;
+    p.counts = a->counts, p.row_ptr = a->row_ptr, p.tile_idx = a->tile_idx;
+    p.col_ptr = a->col_ptr, p.col_idx = a->col_idx;
+    return plx::launch_block_lists(p, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? PLX_OK : PLX_ERR_LAUNCH;
 }
 
 size_t parallax_prefill_backward_workspace_bytes(int32_t B, int32_t Hq, int32_t T) {

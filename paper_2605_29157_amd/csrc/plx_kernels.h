@@ -100,6 +100,15 @@ struct PrefillBwdParams {
     int32_t sparse_batch, sparse_heads;
 };
 
+// Block mask [lists, n_row_blocks, n_tiles] (bytes, nonzero = listed) -> the lists of PrefillParams and,
+// unless col_ptr is NULL, those by columns of PrefillBwdParams. counts: one int32 per line (lists *
+// n_row_blocks, and lists * ceil(n_tiles / 2) more with col_ptr).
+struct BlockListParams {
+    const uint8_t *mask;
+    int32_t lists, n_row_blocks, n_tiles;
+    int32_t *counts, *row_ptr, *tile_idx, *col_ptr, *col_idx;
+};
+
 // RMSNorm + RoPE on up to three contiguous [B, H, T, d] tensors of one (B, T, d).
 struct NormRopeTensor {
     const void *x;
@@ -125,6 +134,7 @@ hipError_t launch_prefill_bwd_bf16(const PrefillBwdParams &p, hipStream_t stream
 hipError_t launch_prefill_bwd_f32(const PrefillBwdParams &p, hipStream_t stream);
 hipError_t launch_decode_f32(const DecodeParams &p, hipStream_t stream);
 hipError_t launch_prefill_f32(const PrefillParams &p, hipStream_t stream);
+hipError_t launch_block_lists(const BlockListParams &p, hipStream_t stream);
 hipError_t launch_norm_rope(const NormRopeParams &p, bool f32, hipStream_t stream);
 hipError_t launch_rope_table(float *table, int n_pos, int d, float theta, hipStream_t stream);
 hipError_t launch_decode_mla(const MlaDecodeParams &p, hipStream_t stream);

@@ -269,3 +269,38 @@ def test_backward_at_the_benchmark_launch(plx, synth, masked):
                                       y["scale"], dense)
         for name, got, ref, hs in zip(("dq", "dr", "dk", "dv"), grads, want, (qs, qs, ks, ks)):
             assert_gradient_close(name, host(got[b:b + 1, hs]), ref, BF16_REL_L2, (b, hk))
+
+
+@pytest.mark.parametrize("lists,nrb,nkt", [((1, 1), 1, 1), ((1, 1), 3, 5), ((2, 1), 1, 64), ((1, 3), 65, 7), ((3, 2), 5, 129),
+                                           ((4, 16), 16, 32)])
+@pytest.mark.parametrize("density", [0.0, 0.3, 1.0])
+def test_lists_built_on_the_device(plx, lists, nrb, nkt, density):
+    """Rows and columns against the same lists from tensor operations: lines of one cell, lines longer
+    than a wave, a workgroup that holds the last row line and the first key line, empty masks."""
+    gen = torch.Generator().manual_seed(nrb * nkt)
+    mask = torch.rand(*lists, nrb, nkt, generator=gen) < density
+    want = plx.block_mask_lists(mask)[:2] + plx.block_mask_column_lists(mask)
+    a = plx.plx_prefill_bwd_args()
+    buf = plx.attach_block_lists(a, mask, torch.device(DEV), columns=True).cpu()
+    assert (a.sparse_batch, a.sparse_heads) == lists
+    base = a.sparse_row_ptr
+    for at, ref, n in zip((a.sparse_row_ptr, a.sparse_tile_idx, a.sparse_col_ptr, a.sparse_col_idx), want,
+                          (len(want[0]), int(want[0][-1]), len(want[2]), int(want[2][-1]))):
+        first = (at - base) // 4
+        assert torch.equal(buf[first:first + n], ref[:n])
+    rows_only = plx.plx_prefill_args()
+    buf = plx.attach_block_lists(rows_only, mask, torch.device(DEV)).cpu()
+    first = (rows_only.sparse_tile_idx - rows_only.sparse_row_ptr) // 4
+    assert torch.equal(buf[:len(want[0])], want[0]) and torch.equal(buf[first:first + int(want[0][-1])], want[1][:int(want[0][-1])])
+
+
+def test_masked_call_on_another_stream(plx, synth):
+    """The lists are built on the current stream and walked on the caller's."""
+    y = synth.prefill_inputs(1, 4, 2, 700, 128, seed=6611, device=DEV)
+    mask = torch.rand(6, 11, generator=torch.Generator().manual_seed(3)) < 0.5
+    want = plx.parallax_prefill(y["q"], y["r"], y["k"], y["v"], y["scale"], block_mask=mask)
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    got = plx.parallax_prefill(y["q"], y["r"], y["k"], y["v"], y["scale"], block_mask=mask, stream=side)
+    torch.cuda.synchronize()
+    assert torch.equal(got, want)
