@@ -269,6 +269,20 @@ typedef struct {
 plx_status parallax_prefill(const plx_prefill_args *args, void *hip_stream);
 
 /*
+ * parallax_prefill for launches that leave compute units idle (a short prompt, a few hundred rows
+ * behind a long cache): row blocks with many keys are cut into key ranges, one workgroup each, whose
+ * unnormalised fp32 records go to the workspace and are merged by a second kernel (App. C). bf16,
+ * dense forms only; the split is chosen from the shape, and where none pays the call is
+ * parallax_prefill.
+ *   parallax_prefill_workspace_bytes  what the split of this call takes, 0 = the call is not split
+ *                                     (or its arguments are not valid)
+ *   workspace   NULL, or 16-byte aligned device memory; smaller than that: the call runs unsplit
+ */
+size_t parallax_prefill_workspace_bytes(const plx_prefill_args *args);
+plx_status parallax_prefill_split(const plx_prefill_args *args, void *workspace, size_t workspace_bytes,
+                                  void *hip_stream);
+
+/*
  * Decode over an MLA-style latent cache (the closing discussion names multi-head latent
  * attention as structurally compatible; this is its absorbed-projection decode form). Every
  * cached token is ONE row [latent d_latent | rope part d_rope] shared by all heads: the key of

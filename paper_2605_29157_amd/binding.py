@@ -25,7 +25,7 @@ EXPORTED_SYMBOLS = (
     "parallax_decode_partials", "parallax_decode_combine", "parallax_decode_fused",
     "parallax_decode_static", "parallax_decode_static_scratch_bytes",
     "parallax_decode_mla", "parallax_decode_mla_workspace_bytes", "parallax_decode_mla_num_splits",
-    "parallax_prefill", "parallax_prefill_backward", "parallax_prefill_backward_workspace_bytes",
+    "parallax_prefill", "parallax_prefill_split", "parallax_prefill_workspace_bytes", "parallax_prefill_backward", "parallax_prefill_backward_workspace_bytes",
     "parallax_block_lists", "parallax_norm_rope", "parallax_rope_table", "parallax_util_copy", "parallax_util_read",
     "parallax_util_read_grid", "parallax_util_read_sink_slots", "parallax_util_mfma", "parallax_strerror", "parallax_version",
 )
@@ -175,6 +175,11 @@ def load_library() -> ctypes.CDLL:
             getattr(lib, name).restype = ctypes.c_int
         lib.parallax_prefill.argtypes = [ctypes.POINTER(plx_prefill_args), ctypes.c_void_p]
         lib.parallax_prefill.restype = ctypes.c_int
+        lib.parallax_prefill_workspace_bytes.argtypes = [ctypes.POINTER(plx_prefill_args)]
+        lib.parallax_prefill_workspace_bytes.restype = ctypes.c_size_t
+        lib.parallax_prefill_split.argtypes = [ctypes.POINTER(plx_prefill_args), ctypes.c_void_p, ctypes.c_size_t,
+                                               ctypes.c_void_p]
+        lib.parallax_prefill_split.restype = ctypes.c_int
         lib.parallax_prefill_backward.argtypes = [ctypes.POINTER(plx_prefill_bwd_args), ctypes.c_void_p]
         lib.parallax_prefill_backward.restype = ctypes.c_int
         lib.parallax_prefill_backward_workspace_bytes.argtypes = [ctypes.c_int32] * 3
@@ -233,6 +238,16 @@ def _stream_ptr(stream) -> int:
     if stream is None:
         stream = torch.cuda.current_stream()
     return int(stream.cuda_stream)
+
+
+def _used_on(buf, stream_ptr):
+    """Tell the allocator that `buf`, allocated on the current stream, is used on another one (then
+    returned), so that its memory is not handed out again before that stream is through with it."""
+    if stream_ptr == torch.cuda.current_stream().cuda_stream:
+        return None
+    other = torch.cuda.ExternalStream(stream_ptr, device=buf.device)
+    buf.record_stream(other)
+    return other
 
 
 def parallax_rope_table(n_pos, d, theta=1.0e6, device="cuda:0", stream=None):
@@ -499,10 +514,9 @@ def attach_block_lists(a, block_mask, device, stream=None, columns=False):
     st = load_library().parallax_block_lists(ctypes.byref(la), current.cuda_stream)
     if st != PLX_OK:
         raise ParallaxError(st, "parallax_block_lists")
-    if stream is not None and stream.cuda_stream != current.cuda_stream:
-        other = torch.cuda.ExternalStream(stream.cuda_stream)
+    other = _used_on(buf, _stream_ptr(stream))
+    if other is not None:
         other.wait_stream(current)
-        buf.record_stream(other)
     return buf
 
 
@@ -532,7 +546,14 @@ def parallax_prefill(q, r, k, v, scale, causal=True, use_r=True, out=None, strea
         vbar = torch.empty_like(out)
         row_stats = torch.empty(q.shape[:3] + (2,), dtype=torch.float32, device=q.device)
         a.vbar, a.row_stats = vbar.data_ptr(), row_stats.data_ptr()
-    st = load_library().parallax_prefill(ctypes.byref(a), _stream_ptr(stream))
+    lib, where = load_library(), _stream_ptr(stream)
+    split_bytes = lib.parallax_prefill_workspace_bytes(ctypes.byref(a))
+    if split_bytes:  # few row blocks, many keys: split over key ranges
+        workspace = torch.empty(split_bytes // 4, dtype=torch.float32, device=q.device)
+        _used_on(workspace, where)
+        st = lib.parallax_prefill_split(ctypes.byref(a), workspace.data_ptr(), split_bytes, where)
+    else:
+        st = lib.parallax_prefill(ctypes.byref(a), where)
     if st != PLX_OK:
         raise ParallaxError(st, "parallax_prefill")
     return (out, vbar, row_stats) if save_for_backward else out

@@ -379,7 +379,10 @@ plx_status parallax_decode_combine(const plx_decode_args *a, void *hip_stream) {
                : PLX_ERR_LAUNCH;
 }
 
-plx_status parallax_prefill(const plx_prefill_args *a, void *hip_stream) {
+namespace {
+
+// Validation of a prefill call; fills the launch parameters.
+plx_status prepare_prefill(const plx_prefill_args *a, plx::PrefillParams *out) {
     if (!a) return PLX_ERR_NULL;
     if (!a->q || !a->k || !a->v || !a->o) return PLX_ERR_NULL;
     if (a->use_r && !a->r) return PLX_ERR_NULL;
@@ -417,7 +420,8 @@ plx_status parallax_prefill(const plx_prefill_args *a, void *hip_stream) {
         p.os[j] = a->o_stride[j];
     }
     p.scale = a->scale, p.causal = a->causal ? 1 : 0, p.use_r = a->use_r ? 1 : 0;
-    p.window = a->window;
+    // a window that reaches back past the first key is no window
+    p.window = a->window < Tk ? a->window : 0;
     if ((a->sparse_row_ptr != nullptr) != (a->sparse_tile_idx != nullptr)) return PLX_ERR_NULL;
     if (a->sparse_row_ptr) {
         if (a->dtype != PLX_BF16) return PLX_ERR_DTYPE;
@@ -440,10 +444,35 @@ plx_status parallax_prefill(const plx_prefill_args *a, void *hip_stream) {
         if (!aligned16(a->vbar) || (reinterpret_cast<uintptr_t>(a->row_stats) & 7u)) return PLX_ERR_ALIGN;
         p.vbar = a->vbar, p.row_stats = a->row_stats;
     }
+    *out = p;
+    return PLX_OK;
+}
+
+}  // namespace
+
+plx_status parallax_prefill(const plx_prefill_args *a, void *hip_stream) {
+    return parallax_prefill_split(a, nullptr, 0, hip_stream);
+}
+
+size_t parallax_prefill_workspace_bytes(const plx_prefill_args *a) {
+    plx::PrefillParams p{};
+    if (prepare_prefill(a, &p) != PLX_OK || a->dtype != PLX_BF16) return 0;
+    return plx::plan_prefill_split_bf16(p, query_num_cus());
+}
+
+plx_status parallax_prefill_split(const plx_prefill_args *a, void *workspace, size_t workspace_bytes,
+                                  void *hip_stream) {
+    plx::PrefillParams p{};
+    plx_status st = prepare_prefill(a, &p);
+    if (st != PLX_OK) return st;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    hipError_t err = a->dtype == PLX_F32 ? plx::launch_prefill_f32(p, stream)
-                                         : plx::launch_prefill_bf16(p, stream);
-    return err == hipSuccess ? PLX_OK : PLX_ERR_LAUNCH;
+    if (a->dtype == PLX_F32) return plx::launch_prefill_f32(p, stream) == hipSuccess ? PLX_OK : PLX_ERR_LAUNCH;
+    if (workspace) {
+        if (!aligned16(workspace)) return PLX_ERR_WORKSPACE;
+        const size_t need = plx::plan_prefill_split_bf16(p, query_num_cus());
+        if (need > 0 && workspace_bytes >= need) p.ws = static_cast<float *>(workspace);
+    }
+    return plx::launch_prefill_bf16(p, stream) == hipSuccess ? PLX_OK : PLX_ERR_LAUNCH;
 }
 
 size_t parallax_decode_mla_workspace_bytes(int32_t B, int32_t Hq) {

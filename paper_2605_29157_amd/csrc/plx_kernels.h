@@ -58,6 +58,10 @@ struct PrefillParams {
     const int32_t *sparse_row_ptr, *sparse_tile_idx;
     int32_t sparse_batch, sparse_heads;
     QrPrep prep;
+    // bf16, launches with idle compute units: records of row blocks whose keys are split over workgroups
+    // (ws != nullptr: take this form, at most split_tiles 64-key tiles per range)
+    float *ws;
+    int32_t split_tiles, items_per_head;
 };
 
 // Decode over an MLA-style latent cache: one row [latent 512 | rope 64] per token shared by all
@@ -130,6 +134,8 @@ struct NormRopeParams {
 hipError_t launch_decode_bf16(const DecodeParams &p, hipStream_t stream);
 hipError_t launch_decode_combine(const DecodeParams &p, hipStream_t stream);
 hipError_t launch_prefill_bf16(const PrefillParams &p, hipStream_t stream);
+// Plans the split of a call over key ranges: 0 = not split, else the bytes of p.ws that its launch takes
+size_t plan_prefill_split_bf16(PrefillParams &p, int num_cus);
 hipError_t launch_prefill_bwd_bf16(const PrefillBwdParams &p, hipStream_t stream);
 hipError_t launch_prefill_bwd_f32(const PrefillBwdParams &p, hipStream_t stream);
 hipError_t launch_decode_f32(const DecodeParams &p, hipStream_t stream);

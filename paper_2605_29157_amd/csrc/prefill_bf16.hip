@@ -39,6 +39,7 @@
 // exp2 domain the sums overflow to inf/NaN; this is detected at the end of the pass and the
 // workgroup redoes its rows with the textbook online update (max, alpha rescale) -- slower, and
 // in practice never taken for attention logits, but it keeps the softmax safe for every input.
+#include <algorithm>
 #include <type_traits>
 
 #include "plx_device.h"
@@ -52,19 +53,37 @@ namespace plx {
 constexpr int kBC = 64;   // keys per LDS tile
 constexpr int kKB = 32;   // keys per inner block (one MFMA row block)
 
+// Key ranges of a row block that sees `keys` keys: as few ranges of at most max_tiles tiles as will do,
+// of equal length up to the last
+struct PrefillRanges {
+    int count, tiles;
+    __host__ __device__ PrefillRanges(int keys, int max_tiles) {
+        const int all = (keys + kBC - 1) / kBC;
+        count = (all + max_tiles - 1) / max_tiles;
+        tiles = (all + count - 1) / count;
+        count = (all + tiles - 1) / tiles;  // (no empty range at the end)
+    }
+};
+// Split records of 32 rows: O1, O2 (2 * 32 * D floats) and five row scalars
+__host__ __device__ constexpr int64_t prefill_record_floats(int d) { return 64 * (int64_t)d + 5 * 32; }
+
 
 
 // RW: sub-blocks of 32 query rows per wave (the workgroup covers 128 * RW rows).
+// SPLIT: a row block with many key tiles is cut into key ranges of at most p.split_tiles tiles, each a
+// workgroup of its own that writes unnormalised records instead of output rows (the split-KV form of
+// App. C, merged by prefill_combine_kernel) -- for launches with fewer row blocks than compute units.
 // PREP: RMSNorm + RoPE on the wave's Q and R rows in their LDS landing zones, before the MFMA
 // fragments are read (the operations the paper's language-model runs put in front of the attention
 // call: Sec. 5 experiment setup and the backbone appendix; same formulas and order of operations as
 // norm_rope.hip, the rotation taken from a table of (cos, sin) per position and pair).
 template <int D, bool USE_R, bool CAUSAL, bool WINDOW, bool STATS = false, bool SPARSE = false, int RW = 1,
-          bool PREP = false>
+          bool PREP = false, bool SPLIT = false>
 __global__ __launch_bounds__(256, 1) void prefill_bf16_kernel(PrefillParams p) {
     static_assert(!PREP || (USE_R && !WINDOW && !STATS && !SPARSE), "q / rho preparation: dense forward only");
     static_assert(RW == 1 || (RW == 2 && D == 64), "two row sub-blocks per wave fit the registers at d = 64 only");
     static_assert(!SPARSE || RW == 1, "block-sparse lists are per 128 query rows");
+    static_assert(!SPLIT || (!WINDOW && !SPARSE && !PREP), "key ranges: dense forward only");
     constexpr int WROWS = 32 * RW;  // query rows per wave
     constexpr int kBR = 4 * WROWS;  // query rows per workgroup
     static_assert(CAUSAL || !WINDOW, "a sliding window needs the rows' positions");
@@ -112,7 +131,7 @@ __global__ __launch_bounds__(256, 1) void prefill_bf16_kernel(PrefillParams p) {
     const int T = p.T, G = p.G;  // query rows
     const int nrb = (T + kBR - 1) / kBR;
     const int pairs = p.B * p.Hkv;
-    int rbi, pair, hg;
+    int rbi, pair, hg;  // (SPLIT: rbi numbers the (row block, key range) items of a head)
     {
         const int id = blockIdx.x;
         if (pairs % 8 == 0) {
@@ -130,12 +149,27 @@ __global__ __launch_bounds__(256, 1) void prefill_bf16_kernel(PrefillParams p) {
             hg = rem % G;
         }
     }
+    const int item = rbi;
+    int n_ranges = 1, range = 0, range_tiles = 0;
+    if constexpr (SPLIT) {  // (few row blocks: the host splits launches smaller than the chip)
+        rbi = 0, range = item;
+        for (;; ++rbi) {
+            const PrefillRanges r(CAUSAL ? min(p.Tk, (nrb - rbi) * kBR + (p.Tk - T)) : p.Tk, p.split_tiles);
+            n_ranges = r.count, range_tiles = r.tiles;
+            if (range < n_ranges || rbi == nrb - 1) break;
+            range -= n_ranges;
+        }
+    }
     const int rb = CAUSAL ? nrb - 1 - rbi : rbi;
     // Sliding window: row i sees the keys i + off - window + 1 .. i + off. The key tiles before
     // the first key of the workgroup's first row are skipped by moving the K / V base; from
     // here on key positions, Tk and off are relative to that first tile.
-    const int kt_skip = WINDOW ? max(rb * kBR + (p.Tk - T) - p.window + 1, 0) / kBC : 0;
+    // (SPLIT skips the tiles before its key range the same way.)
+    const int kt_skip = WINDOW  ? max(rb * kBR + (p.Tk - T) - p.window + 1, 0) / kBC
+                        : SPLIT ? range * range_tiles
+                                : 0;
     const int Tk = p.Tk - kt_skip * kBC;  // keys
+    const int Tv = SPLIT ? min(Tk, range_tiles * kBC) : Tk;  // keys this workgroup looks at
     const int off = Tk - T;               // causal: row i sits at key position i + off
     const int b = pair / p.Hkv, hk = pair - b * p.Hkv;
     const int hq = hk * G + hg;
@@ -199,7 +233,7 @@ __global__ __launch_bounds__(256, 1) void prefill_bf16_kernel(PrefillParams p) {
     const __bf16 *kbase = (const __bf16 *)p.k + b * p.ks[0] + hk * p.ks[1] + (int64_t)kt_skip * kBC * p.ks[2];
     const __bf16 *vbase = (const __bf16 *)p.v + b * p.vs[0] + hk * p.vs[1] + (int64_t)kt_skip * kBC * p.vs[2];
 
-    const int key_end = CAUSAL ? min(Tk, (rb + 1) * kBR + off) : Tk;  // keys this workgroup may need
+    const int key_end = CAUSAL ? min(Tv, (rb + 1) * kBR + off) : Tv;  // keys this workgroup may need
     // Block-sparse: the workgroup visits only the key tiles its row block lists (ascending tile
     // indices, caller's arrays); the ring position i and the key tile tile_at(i) then differ.
     // Entries are clamped to existing tiles, listed tiles past the causal limit are dropped.
@@ -251,7 +285,7 @@ __global__ __launch_bounds__(256, 1) void prefill_bf16_kernel(PrefillParams p) {
     // (block-sparse: leading list entries; the entry prefetched two ahead is then not the last
     // one, the only one that may be the partial tile)
     const int n_full = SPARSE ? max(0, min(n_list_full, n_list - kDist))
-                              : max(0, min(CAUSAL ? (rb * kBR + off + 1) / kBC : Tk / kBC, Tk / kBC - kDist));
+                              : max(0, min(CAUSAL ? min((rb * kBR + off + 1) / kBC, Tv / kBC) : Tv / kBC, Tk / kBC - kDist));
     // sliding window: first key this lane's row sees, and the leading tiles that hold a key
     // some row of the workgroup does not see (its last row starts latest)
     int row_lo[RW];
@@ -363,7 +397,7 @@ __global__ __launch_bounds__(256, 1) void prefill_bf16_kernel(PrefillParams p) {
     // accumulator register r of an S^T block <-> key key_base + 8*(r/4) + 4*h + r%4
     auto key_ok = [&](int key_base, int r, int a) __attribute__((always_inline)) {
         const int key = key_base + 8 * (r >> 2) + 4 * h + (r & 3);
-        return key < Tk && (!CAUSAL || key <= my_row(a) + off) && (!WINDOW || key >= row_lo[a]) && !no_tiles;
+        return key < Tv && (!CAUSAL || key <= my_row(a) + off) && (!WINDOW || key >= row_lo[a]) && !no_tiles;
     };
 
     // d1 / d2 are accumulated by MFMAs as well: Ones(32 x 16 keys) x P^T gives a block whose
@@ -501,7 +535,7 @@ __global__ __launch_bounds__(256, 1) void prefill_bf16_kernel(PrefillParams p) {
 
     // does this wave see any key of the block starting at key_base?
     auto block_visible = [&](int key_base) __attribute__((always_inline)) {
-        return key_base < Tk && (!CAUSAL || key_base <= row0 + WROWS - 1 + off) &&
+        return key_base < Tv && (!CAUSAL || key_base <= row0 + WROWS - 1 + off) &&
                (!WINDOW || key_base + kKB > row0 + off - p.window + 1);
     };
 
@@ -559,7 +593,7 @@ __global__ __launch_bounds__(256, 1) void prefill_bf16_kernel(PrefillParams p) {
     // last key this lane's row may see
     int row_lim[RW];
 #pragma unroll
-    for (int a = 0; a < RW; ++a) row_lim[a] = no_tiles ? -1 : (CAUSAL ? min(my_row(a) + off, Tk - 1) : Tk - 1);
+    for (int a = 0; a < RW; ++a) row_lim[a] = no_tiles ? -1 : (CAUSAL ? min(my_row(a) + off, Tv - 1) : Tv - 1);
     // The 8 * RW chains (row sub-block a, register r0 + u) of a phase, one after the other.
     auto exp_stages = [&](auto masked_tag, auto sums_tag, f32x16(&s1)[RW], f32x16(&s2)[RW], int r0, int slot,
                           int slot0, int n_slots, const float(&neg_m)[RW], const int(&lim)[RW], const int(&lo)[RW],
@@ -951,7 +985,7 @@ __global__ __launch_bounds__(256, 1) void prefill_bf16_kernel(PrefillParams p) {
 #pragma unroll
             for (int r = 0; r < 16; ++r) tmax = fmaxf(tmax, key_ok(kb0, r, a) ? sa1[a][r] : kNegInf);
             tmax = halves_max(tmax);
-            if constexpr (WINDOW || SPARSE) {
+            if constexpr (WINDOW || SPARSE || SPLIT) {
                 // a row whose window starts behind this block takes the block's plain maximum: any
                 // finite reference will do (the check after the loops catches one that was too far off)
                 float tall = sa1[a][0];
@@ -1042,7 +1076,7 @@ __global__ __launch_bounds__(256, 1) void prefill_bf16_kernel(PrefillParams p) {
     static_assert(OROW == KROW, "the staging tile is the wave's Q tile");
     u32x4 *otile = lds + QZONE + w * WAVE_TILE_CHUNKS;
     unsigned short *otile16 = (unsigned short *)otile;
-    float inv[RW], dsum1[RW];
+    float inv[RW], dsum1[RW], dsum2s[RW];
     auto stage_outputs = [&]() __attribute__((always_inline)) {
         float chk = 0.f;
 #pragma unroll
@@ -1058,6 +1092,7 @@ __global__ __launch_bounds__(256, 1) void prefill_bf16_kernel(PrefillParams p) {
                 dsum2 = halves_sum(rsum2[a] + vsum2[a][0] + vsum2[a][1]);
             }
             if constexpr (PREP) dsum2 *= r_gain[a];
+            if constexpr (SPLIT) dsum2s[a] = dsum2;
             inv[a] = dsum1[a] > 0.f ? 1.f / dsum1[a] : 0.f;  // empty key set: zeros
             const float gain = inv[a] * (1.f + dsum2 * inv[a]);
             const float inv2 = PREP ? inv[a] * r_gain[a] : inv[a];
@@ -1080,14 +1115,16 @@ __global__ __launch_bounds__(256, 1) void prefill_bf16_kernel(PrefillParams p) {
         return chk;
     };
     float chk = stage_outputs();
-    if constexpr (WINDOW || SPARSE) {
+    if constexpr (WINDOW || SPARSE || SPLIT) {
         // the reference of a row may come from keys outside its window; if it was so far above
         // the row's own scores that the sum underflowed, take the exact path as well
         // (block-sparse: only for rows that do see a listed key -- the list is ascending, so that
         // is decided by its first tile)
 #pragma unroll
         for (int a = 0; a < RW; ++a)
-            if (my_row(a) < T && (!SPARSE || tile_at(0) * kBC <= row_lim[a]) && !(dsum1[a] > 1e-30f)) chk = 1.f;
+            if (my_row(a) < T && (!SPARSE || tile_at(0) * kBC <= row_lim[a]) && (!SPLIT || row_lim[a] >= 0) &&
+                !(dsum1[a] > 1e-30f))
+                chk = 1.f;
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // tile loads past the end have landed
     const bool overflow = __syncthreads_or(chk != 0.f);  // NaN != 0 is true; all waves agree
@@ -1147,6 +1184,41 @@ __global__ __launch_bounds__(256, 1) void prefill_bf16_kernel(PrefillParams p) {
         (void)stage_outputs();
     }
 
+    // ---- SPLIT, more than one key range: the record of every row ----------------------------
+    // Laid out by accumulator: [float4 block (O1, O2; dimension block n, q4)][half-wave][row], so that
+    // every store of a wave is one contiguous KB, then the row scalars.
+    if constexpr (SPLIT)
+        if (n_ranges > 1) {
+            const int64_t slot = ((int64_t)b * p.Hq + hq) * p.items_per_head + item;
+#pragma unroll
+            for (int a = 0; a < RW; ++a) {
+                if (row0 + 32 * a >= T) continue;  // (wave-uniform) no such rows
+                float *rec = p.ws + ((slot * 4 + w) * RW + a) * prefill_record_floats(D);
+                f32x4 *ob = (f32x4 *)rec + 32 * h + col;
+#pragma unroll
+                for (int n = 0; n < NDB; ++n)
+#pragma unroll
+                    for (int q4 = 0; q4 < 4; ++q4) {
+                        ob[64 * (4 * n + q4)] = f32x4{o1[a][n][4 * q4], o1[a][n][4 * q4 + 1], o1[a][n][4 * q4 + 2], o1[a][n][4 * q4 + 3]};
+                        if constexpr (USE_R)
+                            ob[64 * (4 * (NDB + n) + q4)] = f32x4{o2[a][n][4 * q4], o2[a][n][4 * q4 + 1], o2[a][n][4 * q4 + 2], o2[a][n][4 * q4 + 3]};
+                    }
+                float fsum1 = 0.f, fsum2 = 0.f;  // row cache: sums of the unrounded P1, P2 (see msum1)
+                if constexpr (STATS) {
+                    fsum1 = halves_sum(vsum1[a][0] + vsum1[a][1] + msum1[a][0] + msum1[a][1]);
+                    fsum2 = halves_sum(vsum2[a][0] + vsum2[a][1] + msum2[a][0] + msum2[a][1]);
+                }
+                if (h == 0) {
+                    float *row = rec + 64 * D + col;  // [m | d1 | d2 | sums of the unrounded P1 | P2][32 rows]
+                    row[0] = dsum1[a] > 0.f ? m_ref[a] : kNegInf;
+                    row[32] = dsum1[a];
+                    row[64] = dsum2s[a];
+                    if constexpr (STATS) row[96] = fsum1, row[128] = fsum2;
+                }
+            }
+            return;
+        }
+
     // ---- epilogue: the staged rows go out as whole rows ------------------------------------
     {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -1204,6 +1276,150 @@ __global__ __launch_bounds__(256, 1) void prefill_bf16_kernel(PrefillParams p) {
     }
 }
 
+
+// Merge of the key ranges of a SPLIT launch (App. C) and the closing formula. A wave finishes one
+// block of 32 output dimensions of 32 rows: lane (row, h) holds dimensions 8 q4 + 4 h .. + 3, as the
+// records do, so every load is one contiguous KB. Row blocks with one range were written by the
+// prefill kernel itself. Memory bound: the records travel twice, 2 x 1 KB per row and range at d = 128
+// (512 rows over 16384 keys, 16 heads: 8192 rows x 4 ranges, 34 MB each way).
+template <int D, bool USE_R, bool STATS, int RW>
+__global__ __launch_bounds__(256) void prefill_combine_kernel(PrefillParams p) {
+    constexpr int NDB = D / 32, ROWS = 128 * RW;
+    const int lane = threadIdx.x & 63, col = lane & 31, h = lane >> 5;
+    const int nrb = (p.T + ROWS - 1) / ROWS;
+    int64_t id = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);  // (batch, head, row block, 32 rows, n)
+    const int n = (int)(id % NDB);
+    id /= NDB;
+    const int sub = (int)(id % (4 * RW));
+    id /= 4 * RW;
+    const int rbi = (int)(id % nrb);
+    const int64_t bh = id / nrb;
+    if (bh >= (int64_t)p.B * p.Hq) return;  // (whole waves)
+    const int rb = p.causal ? nrb - 1 - rbi : rbi;
+    const int row = rb * ROWS + 32 * sub + col;
+    if (rb * ROWS + 32 * sub >= p.T) return;
+    int item0 = 0, n_ranges = 1;
+    for (int i = 0; i <= rbi; ++i) {
+        item0 += i > 0 ? n_ranges : 0;
+        const PrefillRanges r(p.causal ? min(p.Tk, (nrb - i) * ROWS + (p.Tk - p.T)) : p.Tk, p.split_tiles);
+        n_ranges = r.count;
+    }
+    if (n_ranges == 1) return;
+    auto record = [&](int i) {
+        return p.ws + ((bh * p.items_per_head + item0 + i) * (4 * RW) + sub) * prefill_record_floats(D);
+    };
+    float m = kNegInf;
+#pragma unroll 8
+    for (int i = 0; i < n_ranges; ++i) m = fmaxf(m, record(i)[64 * D + col]);
+    const float m_use = m == kNegInf ? 0.f : m;
+    float d1 = 0.f, d2 = 0.f, f1 = 0.f, f2 = 0.f;
+    f32x4 o1[4], o2[4];
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4) o1[q4] = o2[q4] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+    for (int i = 0; i < n_ranges; ++i) {
+        const float *rec = record(i), *sc = rec + 64 * D + col;
+        const f32x4 *ob = (const f32x4 *)rec + 32 * h + col;
+        const float wt = fast_exp2(sc[0] - m_use);  // 0 where the range shows the row nothing
+        d1 += wt * sc[32], d2 += wt * sc[64];
+        if constexpr (STATS) f1 += wt * sc[96], f2 += wt * sc[128];
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+            o1[q4] += wt * ob[64 * (4 * n + q4)];
+            if constexpr (USE_R) o2[q4] += wt * ob[64 * (4 * (NDB + n) + q4)];
+        }
+    }
+    if (row >= p.T) return;
+    const float inv = d1 > 0.f ? 1.f / d1 : 0.f, gain = inv * (1.f + d2 * inv);
+    const int64_t b = bh / p.Hq, hq = bh % p.Hq, at = b * p.os[0] + hq * p.os[1] + (int64_t)row * p.os[2] + 32 * n + 4 * h;
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4) {
+        f32x4 y = o1[q4] * gain;
+        if constexpr (USE_R) y -= o2[q4] * inv;
+        *(u32x2 *)((__bf16 *)p.o + at + 8 * q4) = u32x2{pack_bf16(y[0], y[1]), pack_bf16(y[2], y[3])};
+        if constexpr (STATS) {
+            const f32x4 v = o1[q4] * inv;
+            *(u32x2 *)((__bf16 *)p.vbar + at + 8 * q4) = u32x2{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
+        }
+    }
+    if constexpr (STATS)
+        if (n == 0 && h == 0) {
+            float *st = p.row_stats + (bh * p.T + row) * 2;
+            st[0] = f1 > 0.f ? m_use + log2f(f1) : -kNegInf;
+            st[1] = f1 > 0.f ? f2 / f1 : 0.f;
+        }
+}
+
+// Key ranges of a launch that leaves compute units idle: the tiles per range with the smallest
+// estimate, in units of one 64-key tile of a workgroup (1.6 us at d = 128; twice as many rows with
+// twice the work per key weigh the same at d = 64): 4 to start and finish a workgroup, one workgroup
+// per compute unit at a time; what a launch with more items than units loses at its end is taken as half
+// an item. Merging costs a launch (3) and twice the records' bytes at about 4.5 TB/s (7.2 MB per unit).
+// 0 = leave the launch whole (also when the gain would be under a tenth). Measured us against the number
+// of ranges of the longest row block, 16 heads, d = 128: 512 rows over 16384 keys whole 267, 2 160, 3 128,
+// 4 (the rule) 121, 5 160, 8 135; 1024 over 16384 whole 302, 2 (the rule) 218, 3 250, 4 226; square
+// prompts of 400 ... 3000 rows whole (the rule) 17 ... 75, 2 25 ... 108; 17 over 5000 whole 88, 8 33, 16
+// (the rule) 38; d = 64, 8 heads, 3000 square whole 69, 2 54, 4 (the rule) 45, 8 58.
+static int choose_split_tiles(const PrefillParams &p, int num_cus, int *items_per_head) {
+    const int rows = p.d == 64 ? 256 : 128, nrb = (p.T + rows - 1) / rows;
+    const int64_t heads = (int64_t)p.B * p.Hq;
+    *items_per_head = nrb;
+    if (heads * nrb >= 2 * (int64_t)num_cus || nrb > 64) return 0;
+    auto keys = [&](int rbi) { return p.causal ? std::min(p.Tk, (nrb - rbi) * rows + (p.Tk - p.T)) : p.Tk; };
+    const int longest = (keys(0) + kBC - 1) / kBC;
+    auto estimate = [&](int tiles, int *items) {
+        double work = 0, widest = 0;
+        int64_t n = 0, records = 0;  // records: of 32 rows
+        for (int i = 0; i < nrb; ++i) {
+            const PrefillRanges r(keys(i), tiles);
+            const int rb = p.causal ? nrb - 1 - i : i, subs = (std::min(rows, p.T - rb * rows) + 31) / 32;
+            work += r.count * (4.0 + r.tiles);
+            widest = std::max(widest, 4.0 + r.tiles);
+            n += r.count, records += r.count > 1 ? r.count * subs : 0;
+        }
+        *items = (int)n;
+        double t = std::max(widest, (double)heads * work / num_cus + (heads * n > num_cus ? 0.5 * widest : 0.0));
+        if (records > 0) t += 3.0 + (double)(heads * records) * (2.0 * 32 * (2 * p.d + 5) * 4.0 / 7.2e6);
+        return t;
+    };
+    int items = 0, best = 0;
+    double best_cost = 0.9 * estimate(longest, &items);
+    for (int ranges = 2; ranges <= 32; ++ranges) {
+        const int tiles = (longest + ranges - 1) / ranges;
+        if (tiles < 2) break;
+        const double t = estimate(tiles, &items);
+        if (t < best_cost) best_cost = t, best = tiles, *items_per_head = items;
+    }
+    return best;
+}
+
+size_t plan_prefill_split_bf16(PrefillParams &p, int num_cus) {
+    p.split_tiles = 0;
+    if (p.sparse_row_ptr != nullptr || p.window > 0 || p.prep.gamma_q != nullptr) return 0;
+    p.split_tiles = choose_split_tiles(p, num_cus, &p.items_per_head);
+    if (p.split_tiles == 0) return 0;
+    return (size_t)p.B * p.Hq * p.items_per_head * (p.d == 64 ? 8 : 4) * prefill_record_floats(p.d) * sizeof(float);
+}
+
+template <int D, int RW>
+static hipError_t launch_prefill_split(const PrefillParams &p, hipStream_t stream) {
+    const long long total = (long long)p.items_per_head * p.Hq * p.B;
+    const int rows = 128 * RW;
+    const long long waves = (long long)((p.T + rows - 1) / rows) * p.Hq * p.B * (4 * RW) * (D / 32);
+    const dim3 grid((unsigned)total), merge((unsigned)((waves + 3) / 4)), block(256);
+    auto run = [&](auto use_r, auto causal, auto stats) {
+        constexpr bool R = decltype(use_r)::value, C = decltype(causal)::value, ST = decltype(stats)::value;
+        hipLaunchKernelGGL((prefill_bf16_kernel<D, R, C, false, ST, false, RW, false, true>), grid, block, 0, stream, p);
+        if (hipError_t err = hipGetLastError()) return err;
+        hipLaunchKernelGGL((prefill_combine_kernel<D, R, ST, RW>), merge, block, 0, stream, p);
+        return hipGetLastError();
+    };
+    const std::true_type yes;
+    const std::false_type no;
+    if (p.row_stats != nullptr) return p.causal ? run(yes, yes, yes) : run(yes, no, yes);
+    if (p.use_r) return p.causal ? run(yes, yes, no) : run(yes, no, no);
+    return p.causal ? run(no, yes, no) : run(no, no, no);
+}
 
 // Block-sparse tile iterator (use_r, no window): lists per 128 query rows.
 template <int D>
@@ -1266,6 +1482,8 @@ static hipError_t launch_prefill_dense(const PrefillParams &p, hipStream_t strea
 }
 
 hipError_t launch_prefill_bf16(const PrefillParams &p, hipStream_t stream) {
+    if (p.ws != nullptr)  // (planned and sized by plan_prefill_split_bf16)
+        return p.d == 128 ? launch_prefill_split<128, 1>(p, stream) : launch_prefill_split<64, 2>(p, stream);
     if (p.sparse_row_ptr != nullptr)
         return p.d == 128 ? launch_prefill_sparse<128>(p, stream) : launch_prefill_sparse<64>(p, stream);
     return p.d == 128 ? launch_prefill_dense<128, 1>(p, stream) : launch_prefill_dense<64, 2>(p, stream);
