@@ -418,7 +418,7 @@ def backward_line(torch, plx, synth, dev, opt):
                    "forward_with_row_cache_plus_backward_TFLOPs": round(train_tf, 1)},
         "roofline": {"bound": "mfma", "achieved": round(tf, 1), "peak": MFMA_BF16_PEAK_TFLOPS,
                      "unit": "TFLOP/s", "frac": round(tf / MFMA_BF16_PEAK_TFLOPS, 4), "traffic": None,
-                     "kernel": "bwd_dq_dr_kernel<%d,true,false> + bwd_dk_dv_kernel<%d,true,false>" % (d, d),
+                     "kernel": "bwd_passes_kernel<%d,true,false,false>" % d,
                      "kernel_us": round(us, 1)},
     }
 
@@ -971,7 +971,7 @@ def extra_measurements(torch, plx, synth, lib, dev, sptr, sets, ws, out):
                    "us": round(us, 1), "TFLOPs": round(flops / us / 1e6, 1),
                    "frac_of_bf16_mfma_peak": round(flops / us / 1e6 / MFMA_BF16_PEAK_TFLOPS, 4)}
             if B == 4:
-                # the backward over the same lists (three kernels; 22 d flops per allowed pair)
+                # the backward over the same lists (two kernels; 22 d flops per allowed pair)
                 vbar = torch.empty_like(po)
                 stats = torch.empty(B, Hq, T, 2, dtype=torch.float32, device=dev)
                 a.vbar, a.row_stats = vbar.data_ptr(), stats.data_ptr()

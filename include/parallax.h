@@ -350,7 +350,7 @@ plx_status parallax_decode_mla(const plx_decode_mla_args *args, void *hip_stream
  *   workspace  fp32 scratch, >= parallax_prefill_backward_workspace_bytes(B, Hq, T) = 16 bytes
  *              per query row (four row scalars built from lse, ubar, tau = dO.o, beta = dO.vbar;
  *              contents are private to the library)
- * Three kernels are enqueued (row scalars; dQ, dR; dK, dV); nothing is accumulated with atomics,
+ * Two kernels are enqueued (row scalars; both passes, dK, dV and dQ, dR); nothing is accumulated with atomics,
  * so results are deterministic and the outputs need no zeroing.
  */
 typedef struct {
