@@ -146,10 +146,22 @@ __device__ __forceinline__ void merge_records(const float *const (&rec0)[NROW], 
     }
 }
 
+// How a wave finds the K / V rows of its 32-key tile.
+//   kContiguous, kPagedRuns  the rows of each half tile (16 aligned keys) follow each other in memory --
+//             a contiguous cache, or pages of a multiple of 16 keys -- so a load is a wave-uniform base
+//             plus a 32-bit lane offset (two vector instructions). The bases of a paged cache are looked
+//             up 32 tiles at a time, two lanes per tile, and handed out by lane reads.
+//   kRows     any page size and any row stride: every lane finds its own rows (eight lookups, divisions
+//             and 64-bit products per tile and lane).
+// With few workgroups the address arithmetic is what a paged tile costs: 2 sequences x 20000 keys, 8
+// key heads, one workgroup each: row by row 315 us, by runs 212, contiguous 183 (190 with the row-by-row
+// arithmetic); 24 sequences x 3000 - 6000 keys in pages of 16: 104 -> 86 us.
+enum CacheForm { kContiguous, kPagedRuns, kRows };
+
 // RANGE: the launch covers the query rows [row0, row0 + rows) of Tq only (calls with more than 16
 // columns); its own instantiation, so that the one-launch kernel stays as it is.
 // PREP: RMSNorm + RoPE on the q / rho rows after they are loaded (own instantiations as well).
-template <int D, bool USE_R, bool PAGED, bool RANGE = false, bool PREP = false>
+template <int D, bool USE_R, int CACHE, bool RANGE = false, bool PREP = false>
 __global__ __launch_bounds__(256, 2) void decode_bf16_kernel(DecodeParams p) {
     constexpr int CPR = D / 8;            // 16-byte chunks per K/V row
     constexpr int KPI = 64 / CPR;         // rows covered by one wave-wide 16-byte load
@@ -204,45 +216,88 @@ __global__ __launch_bounds__(256, 2) void decode_bf16_kernel(DecodeParams p) {
         }
     }
 
-    // paged cache: the batch stride is the page stride and is applied per row below
-    const __bf16 *kbase = (const __bf16 *)p.k + (PAGED ? 0 : (int64_t)b * p.ksb) + (int64_t)hk * p.ksh;
-    const __bf16 *vbase = (const __bf16 *)p.v + (PAGED ? 0 : (int64_t)b * p.vsb) + (int64_t)hk * p.vsh;
+    // a paged cache's batch stride is its page stride and is applied below
+    const bool batch_rows = CACHE == kContiguous || (CACHE == kRows && p.block_table == nullptr);
+    const __bf16 *kbase = (const __bf16 *)p.k + (batch_rows ? (int64_t)b * p.ksb : 0) + (int64_t)hk * p.ksh;
+    const __bf16 *vbase = (const __bf16 *)p.v + (batch_rows ? (int64_t)b * p.vsb : 0) + (int64_t)hk * p.vsh;
     u32x4 *ldsK = lds + w * (2 * TILE_CHUNKS);
     u32x4 *ldsV = ldsK + TILE_CHUNKS;
     const unsigned short *ldsV16 = (const unsigned short *)ldsV;
 
     const int ld_row = lane / CPR, ld_chunk = lane % CPR;  // this lane's place in a load
     u32x4 kst[NLD], vst[NLD];
-    // paged cache: page numbers of this lane's rows, looked up one tile before the rows
-    // themselves are fetched so that the table read is off the critical path
+    const int32_t *table = p.block_table + (int64_t)b * p.table_stride;  // (paged forms only)
+    // kRows: page numbers of this lane's rows, looked up one tile before the rows themselves are
+    // fetched so that the table read is off the critical path
     int32_t pg[NLD];
-    const int32_t *table = PAGED ? p.block_table + (int64_t)b * p.table_stride : nullptr;
     auto lookup_pages = [&](int tk0) {
-        if constexpr (PAGED) {
+        if constexpr (CACHE == kRows)
+            if (p.block_table != nullptr)
 #pragma unroll
-            for (int i = 0; i < NLD; ++i) pg[i] = table[min(tk0 + i * KPI + ld_row, Lb - 1) / p.page_size];
+                for (int i = 0; i < NLD; ++i) pg[i] = table[min(tk0 + i * KPI + ld_row, Lb - 1) / p.page_size];
+    };
+    // kPagedRuns: element offsets of the first rows of this wave's next 32 tiles' halves, lane 2 * j + half
+    const int last16 = (Lb - 1) & ~15;  // first key of the last half tile that exists
+    int run_k[2] = {0, 0}, run_v[2] = {0, 0}, run_slot = 0;
+    auto lookup_runs = [&](int tk0) {
+        if constexpr (CACHE == kPagedRuns) {
+            const int key = min(tk0 + (lane >> 1) * (kWaves * kTileKeys) + 16 * (lane & 1), last16);
+            const int page_no = key / p.page_size, row = key - page_no * p.page_size;
+            const int64_t page = min(max(table[page_no], 0), p.num_pages - 1);
+            const int64_t ko = page * p.ksb + (int64_t)row * p.ksl, vo = page * p.vsb + (int64_t)row * p.vsl;
+            run_k[0] = (int)ko, run_k[1] = (int)(ko >> 32);
+            run_v[0] = (int)vo, run_v[1] = (int)(vo >> 32);
+            run_slot = 0;
         }
     };
+    const uint32_t k_row_bytes = (uint32_t)p.ksl * 2u, v_row_bytes = (uint32_t)p.vsl * 2u;
     auto issue_loads = [&](int tk0) {
+        if constexpr (CACHE != kRows) {
+            if constexpr (CACHE == kPagedRuns)
+                if (run_slot == 64) lookup_runs(tk0);  // (uniform)
 #pragma unroll
-        for (int i = 0; i < NLD; ++i) {
-            // rows past the sequence end re-read its last row (finite data, masked below)
-            const int key = min(tk0 + i * KPI + ld_row, Lb - 1);
-            int64_t koff = (int64_t)key * p.ksl, voff = (int64_t)key * p.vsl;
-            if constexpr (PAGED) {
-                const int64_t page = min(max(pg[i], 0), p.num_pages - 1);
-                const int row = key % p.page_size;
-                koff = page * p.ksb + (int64_t)row * p.ksl;
-                voff = page * p.vsb + (int64_t)row * p.vsl;
+            for (int hf = 0; hf < 2; ++hf) {
+                const int key0 = __builtin_amdgcn_readfirstlane(min(tk0 + 16 * hf, last16));
+                int64_t ko = (int64_t)key0 * p.ksl, vo = (int64_t)key0 * p.vsl;
+                if constexpr (CACHE == kPagedRuns) {
+                    auto pick = [&](const int(&x)[2]) {
+                        return ((int64_t)__builtin_amdgcn_readlane(x[1], run_slot + hf) << 32) |
+                               (uint32_t)__builtin_amdgcn_readlane(x[0], run_slot + hf);
+                    };
+                    ko = pick(run_k), vo = pick(run_v);
+                }
+                const char *kp = (const char *)(kbase + ko), *vp = (const char *)(vbase + vo);
+                const int last = Lb - 1 - key0;  // rows past the sequence end re-read its last row (finite data, masked below)
+#pragma unroll
+                for (int i = 0; i < NLD / 2; ++i) {
+                    const uint32_t row = (uint32_t)min(i * KPI + ld_row, last);
+                    kst[hf * (NLD / 2) + i] = *(const u32x4 *)(kp + (__umul24(row, k_row_bytes) + 16u * ld_chunk));
+                    vst[hf * (NLD / 2) + i] = *(const u32x4 *)(vp + (__umul24(row, v_row_bytes) + 16u * ld_chunk));
+                }
             }
-            kst[i] = *(const u32x4 *)(kbase + koff + ld_chunk * 8);
-            vst[i] = *(const u32x4 *)(vbase + voff + ld_chunk * 8);
+            run_slot += 2;
+        } else {
+#pragma unroll
+            for (int i = 0; i < NLD; ++i) {
+                const int key = min(tk0 + i * KPI + ld_row, Lb - 1);
+                int64_t koff = (int64_t)key * p.ksl, voff = (int64_t)key * p.vsl;
+                if (p.block_table != nullptr) {
+                    const int64_t page = min(max(pg[i], 0), p.num_pages - 1);
+                    const int row = key % p.page_size;
+                    koff = page * p.ksb + (int64_t)row * p.ksl;
+                    voff = page * p.vsb + (int64_t)row * p.vsl;
+                }
+                kst[i] = *(const u32x4 *)(kbase + koff + ld_chunk * 8);
+                vst[i] = *(const u32x4 *)(vbase + voff + ld_chunk * 8);
+            }
         }
     };
-
-    if constexpr (PREP && PAGED) {  // (the first tile's page numbers travel with the weights)
+    {  // (the first tiles' pages travel with the query rows, in front of everything else)
         const int tk_first = key_lo + w * kTileKeys;
-        if (tk_first < key_hi) lookup_pages(tk_first);
+        if (tk_first < key_hi) {
+            if constexpr (CACHE == kRows) lookup_pages(tk_first);
+            if constexpr (CACHE == kPagedRuns) lookup_runs(tk_first);
+        }
     }
     // ---- RMSNorm + RoPE on the q / rho rows in their operand registers (the operations the
     // paper's language-model runs apply in front of the attention call; formulas of
@@ -331,7 +386,6 @@ __global__ __launch_bounds__(256, 2) void decode_bf16_kernel(DecodeParams p) {
         asm volatile("" : "+v"(tk) : "v"(qf[KSTEPS - 1][3]), "v"(rf[KSTEPS - 1][3]));
     }
     if (tk < key_hi) {
-        if constexpr (!(PREP && PAGED)) lookup_pages(tk);
         issue_loads(tk);
         if (tk + kWaves * kTileKeys < key_hi) lookup_pages(tk + kWaves * kTileKeys);
     }
@@ -572,25 +626,29 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(DecodeParams p) {
     merge_records<D, false, 1>(recs, p.S, outs, threadIdx.x, &sm);
 }
 
-template <int D, bool USE_R>
-static void launch_decode_variant(const DecodeParams &p, dim3 grid, hipStream_t stream) {
+template <int D, bool USE_R, int CACHE>
+static void launch_decode_form(const DecodeParams &p, dim3 grid, hipStream_t stream) {
     if (p.prep.gamma_q != nullptr) {  // q / rho prepared in the kernel (the row-range form serves every call)
         DecodeParams pr = p;
         if (pr.rows == 0) pr.row0 = 0, pr.rows = pr.Tq;
-        if (p.block_table)
-            hipLaunchKernelGGL((decode_bf16_kernel<D, USE_R, true, true, true>), grid, dim3(256), 0, stream, pr);
-        else
-            hipLaunchKernelGGL((decode_bf16_kernel<D, USE_R, false, true, true>), grid, dim3(256), 0, stream, pr);
+        hipLaunchKernelGGL((decode_bf16_kernel<D, USE_R, CACHE, true, true>), grid, dim3(256), 0, stream, pr);
     } else if (p.rows > 0) {  // a range of the query rows
-        if (p.block_table)
-            hipLaunchKernelGGL((decode_bf16_kernel<D, USE_R, true, true>), grid, dim3(256), 0, stream, p);
-        else
-            hipLaunchKernelGGL((decode_bf16_kernel<D, USE_R, false, true>), grid, dim3(256), 0, stream, p);
-    } else if (p.block_table) {
-        hipLaunchKernelGGL((decode_bf16_kernel<D, USE_R, true>), grid, dim3(256), 0, stream, p);
+        hipLaunchKernelGGL((decode_bf16_kernel<D, USE_R, CACHE, true>), grid, dim3(256), 0, stream, p);
     } else {
-        hipLaunchKernelGGL((decode_bf16_kernel<D, USE_R, false>), grid, dim3(256), 0, stream, p);
+        hipLaunchKernelGGL((decode_bf16_kernel<D, USE_R, CACHE>), grid, dim3(256), 0, stream, p);
     }
+}
+
+template <int D, bool USE_R>
+static void launch_decode_variant(const DecodeParams &p, dim3 grid, hipStream_t stream) {
+    // (24-bit products of a row number below 16 and the row stride in bytes)
+    const bool short_rows = p.ksl < (1 << 23) && p.vsl < (1 << 23);
+    if (short_rows && p.block_table == nullptr)
+        launch_decode_form<D, USE_R, kContiguous>(p, grid, stream);
+    else if (short_rows && p.page_size % 16 == 0)
+        launch_decode_form<D, USE_R, kPagedRuns>(p, grid, stream);
+    else
+        launch_decode_form<D, USE_R, kRows>(p, grid, stream);
 }
 
 hipError_t launch_decode_bf16(const DecodeParams &p, hipStream_t stream) {

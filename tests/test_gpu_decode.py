@@ -457,3 +457,29 @@ def test_block_sparse_decode_is_a_block_table_of_selected_pages(plx, synth, orac
         ref = oracle.forward(q[b:b + 1, :, None], r[b:b + 1, :, None], k[b:b + 1][:, :, cols],
                              v[b:b + 1][:, :, cols], x["scale"])[0, :, 0]
         assert rel_l2(host(out)[b], ref) <= BF16_REL_L2, b
+
+
+@pytest.mark.parametrize("page_size", [16, 80])
+@pytest.mark.parametrize("lens", [[9000, 4097, 33], [4112, 8193, 1]])
+@pytest.mark.parametrize("S,d", [(1, 128), (2, 64)])
+def test_paged_runs_beyond_one_lookup(plx, synth, page_size, lens, S, d):
+    """A wave looks the pages of its next 32 tiles up at once (4096 keys of a split): lengths on both
+    sides of that, last halves of one key and of sixteen; same bits as the contiguous cache."""
+    x = synth.decode_inputs(3, 4, 2, 9000, d, seed=600 + page_size, device=DEV)
+    x["seq_lens"] = torch.tensor(lens, dtype=torch.int32, device=DEV)
+    kp, vp, table = synth.paged_cache(x, page_size, seed=601)
+    want = plx.parallax_decode(x["q"], x["r"], x["k"], x["v"], x["scale"], seq_lens=x["seq_lens"], num_splits=S)
+    got = plx.parallax_decode(x["q"], x["r"], kp, vp, x["scale"], seq_lens=x["seq_lens"], block_table=table, max_len=9000,
+                              num_splits=S)
+    assert torch.equal(got, want)
+
+
+def test_rows_too_far_apart_for_lane_offsets(plx, synth):
+    """Row strides of 2^23 elements and more take the row-by-row form; same bits as a dense cache."""
+    x = synth.decode_inputs(1, 4, 1, 41, 128, seed=610, device=DEV)
+    wide = torch.empty(2, 1, 1, 41, 1 << 23, dtype=torch.bfloat16, device=DEV)
+    k, v = wide[0][..., :128], wide[1][..., :128]
+    k.copy_(x["k"])
+    v.copy_(x["v"])
+    want = plx.parallax_decode(x["q"], x["r"], x["k"], x["v"], x["scale"])
+    assert torch.equal(plx.parallax_decode(x["q"], x["r"], k, v, x["scale"]), want)
