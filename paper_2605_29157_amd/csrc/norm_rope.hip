@@ -9,10 +9,14 @@
 // formed and reduced modulo 2 pi in double precision (pos * frequency reaches 1e5 and more, where
 // fp32 would lose the fraction), sine and cosine are taken in single precision -- once per
 // (position, pair), for all heads of all tensors.
+#include <cmath>
+
 #include "plx_device.h"
 #include "plx_kernels.h"
 
 namespace plx {
+
+constexpr int kNormRopeTripHeads = 4;
 
 template <typename T>
 struct Chunk;  // 16 bytes of a row
@@ -31,29 +35,52 @@ struct Chunk<float> {
     __device__ void set_pair(int j, float a, float b) { raw[2 * j] = a, raw[2 * j + 1] = b; }
 };
 
-// A wave owns 64 / (lanes per row) consecutive positions of one sequence and walks over a chunk
-// of the heads of every tensor at those positions: sine and cosine of a (position, pair) are
-// computed once per wave. With many positions a wave takes all heads (the trigonometry is then
-// done once per position); with few (a decode step has one row per sequence) the heads are
-// dealt over more waves, because a wave that walks 40 heads alone is a chain of 10 dependent
-// memory round trips (measured: 22 us for 8 x 16 x 1 rows, against 4 us in chunks of 4 heads).
+// A wave owns 64 / (lanes per row) consecutive positions of one sequence and walks over some of the
+// trips there, a trip being four heads of one tensor, all four in flight (the first trip's loads are
+// issued before the trigonometry).
+// With many positions a wave takes all trips: sine and cosine of a (position, pair) are then computed
+// once. With few (a decode step has one row per sequence) the trips are dealt over more waves,
+// because a wave that walks 40 heads alone is a chain of 10 dependent memory round trips.
+// q, rho [1,16,777,128] and k [1,8,777,128]: 11.2 -> 7.0 us; one row each, 10.3 -> 5.2 us; [4,..,4096,128] 66.
 template <typename T>
 __global__ __launch_bounds__(256) void norm_rope_kernel(NormRopeParams p) {
     constexpr int E = Chunk<T>::E;
-    constexpr int UNROLL = 4;                      // heads in flight per lane
+    constexpr int UNROLL = kNormRopeTripHeads;     // heads in flight per lane
+    using raw_t = decltype(Chunk<T>::raw);
     const int lpr = p.d / E;                       // lanes per row (a power of two <= 64)
     const int rows_per_wave = 64 / lpr;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int lr = lane % lpr;                     // this lane's chunk of its row
     const int t_per_seq = (p.T + rows_per_wave - 1) / rows_per_wave;  // position groups per sequence
     const int64_t wid_all = (int64_t)blockIdx.x * 4 + wave;
-    if (wid_all >= (int64_t)p.B * t_per_seq * p.head_chunks) return;   // whole waves only: no barrier below
-    const int hchunk = (int)(wid_all % p.head_chunks);
-    const int64_t wid = wid_all / p.head_chunks;
+    if (wid_all >= (int64_t)p.B * t_per_seq * p.trip_chunks) return;   // whole waves only: no barrier below
+    const int first_trip = (int)(wid_all % p.trip_chunks) * p.trips_per_wave;
+    const int64_t wid = wid_all / p.trip_chunks;
     const int b = (int)(wid / t_per_seq);
     const int t = (int)(wid % t_per_seq) * rows_per_wave + lane / lpr;
     const bool live = t < p.T;
     const int ld_t = live ? t : p.T - 1;
+
+    // trip -> tensor and first head; loads of its heads (heads past the last re-read that one)
+    int ten_i = 0, h0 = first_trip * UNROLL;
+    for (; ten_i < p.n_tensors && h0 >= p.t[ten_i].H; ++ten_i) h0 -= (p.t[ten_i].H + UNROLL - 1) / UNROLL * UNROLL;
+    if (ten_i >= p.n_tensors) return;
+    Chunk<T> c[UNROLL];
+    float gam[E];
+    NormRopeTensor ten;
+    auto load_trip = [&]() {
+        const raw_t *src = (const raw_t *)ten.x;
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u)
+            c[u].raw = src[(((int64_t)b * ten.H + min(h0 + u, ten.H - 1)) * p.T + ld_t) * lpr + lr];
+    };
+    auto take_tensor = [&]() {
+        ten = p.t[ten_i];
+#pragma unroll
+        for (int e = 0; e < E; ++e) gam[e] = ten.gamma[lr * E + e];
+    };
+    take_tensor();
+    load_trip();
 
     float cs[E / 2], sn[E / 2];
     if (p.table != nullptr) {  // (uniform) from the caller's table: E floats = this lane's E / 2 pairs
@@ -65,53 +92,49 @@ __global__ __launch_bounds__(256) void norm_rope_kernel(NormRopeParams p) {
             cs[j] = v[0], sn[j] = v[1], cs[j + 1] = v[2], sn[j + 1] = v[3];
         }
     } else {
+        // theta^(-dim/d) for this lane's first pair, then pair by pair times theta^(-2/d) (both in double
+        // precision: at most three roundings more than a power per pair, 4e-16 of the angle)
         const double pos = (double)((p.pos0 ? p.pos0[b] : 0) + ld_t);
-        const double log2_theta = log2((double)p.theta);
+        double freq = exp2(-(double)(lr * E) / (double)p.d * p.log2_theta);
 #pragma unroll
         for (int j = 0; j < E / 2; ++j) {
-            const int dim = lr * E + 2 * j;  // even dimension of the pair
-            double ang = pos * exp2(-(double)dim / (double)p.d * log2_theta);
+            double ang = pos * freq;
             ang -= floor(ang * 0.15915494309189535) * 6.283185307179586;  // modulo 2 pi
             sincosf((float)ang, &sn[j], &cs[j]);
+            freq *= p.pair_ratio;
         }
     }
     const float inv_d = 1.0f / (float)p.d;
-    for (int i = 0; i < p.n_tensors; ++i) {
-        const NormRopeTensor ten = p.t[i];
-        float gam[E];
+    for (int n = 0; n < p.trips_per_wave; ++n) {
+        raw_t *dst = (raw_t *)ten.y;
 #pragma unroll
-        for (int e = 0; e < E; ++e) gam[e] = ten.gamma[lr * E + e];
-        const decltype(Chunk<T>::raw) *src = (const decltype(Chunk<T>::raw) *)ten.x;
-        decltype(Chunk<T>::raw) *dst = (decltype(Chunk<T>::raw) *)ten.y;
-        const int h_end = min(ten.H, (hchunk + 1) * p.heads_per_wave);
-        for (int h0 = hchunk * p.heads_per_wave; h0 < h_end; h0 += UNROLL) {
-            Chunk<T> c[UNROLL];
+        for (int u = 0; u < UNROLL; ++u) {
+            float ss = 0.f;
 #pragma unroll
-            for (int u = 0; u < UNROLL; ++u) {  // all loads of the trip first
-                const int h = min(h0 + u, h_end - 1);
-                c[u].raw = src[(((int64_t)b * ten.H + h) * p.T + ld_t) * lpr + lr];
-            }
+            for (int e = 0; e < E; ++e) ss = fmaf(c[u].get(e), c[u].get(e), ss);
+            for (int off = 1; off < lpr; off <<= 1) ss += __shfl_xor(ss, off, 64);
+            const float rinv = 1.0f / sqrtf(ss * inv_d + p.eps);
 #pragma unroll
-            for (int u = 0; u < UNROLL; ++u) {
-                float ss = 0.f;
-#pragma unroll
-                for (int e = 0; e < E; ++e) ss = fmaf(c[u].get(e), c[u].get(e), ss);
-                for (int off = 1; off < lpr; off <<= 1) ss += __shfl_xor(ss, off, 64);
-                const float rinv = 1.0f / sqrtf(ss * inv_d + p.eps);
-#pragma unroll
-                for (int j = 0; j < E / 2; ++j) {
-                    float y0 = c[u].get(2 * j) * rinv * gam[2 * j];
-                    float y1 = c[u].get(2 * j + 1) * rinv * gam[2 * j + 1];
-                    if (ten.rope) {
-                        const float r0 = y0 * cs[j] - y1 * sn[j], r1 = y0 * sn[j] + y1 * cs[j];
-                        y0 = r0, y1 = r1;
-                    }
-                    c[u].set_pair(j, y0, y1);
+            for (int j = 0; j < E / 2; ++j) {
+                float y0 = c[u].get(2 * j) * rinv * gam[2 * j];
+                float y1 = c[u].get(2 * j + 1) * rinv * gam[2 * j + 1];
+                if (ten.rope) {
+                    const float r0 = y0 * cs[j] - y1 * sn[j], r1 = y0 * sn[j] + y1 * cs[j];
+                    y0 = r0, y1 = r1;
                 }
-                if (live && h0 + u < h_end)
-                    dst[(((int64_t)b * ten.H + h0 + u) * p.T + t) * lpr + lr] = c[u].raw;
+                c[u].set_pair(j, y0, y1);
             }
+            if (live && h0 + u < ten.H)
+                dst[(((int64_t)b * ten.H + h0 + u) * p.T + t) * lpr + lr] = c[u].raw;
         }
+        if (n + 1 == p.trips_per_wave) break;  // (all uniform)
+        h0 += UNROLL;
+        if (h0 >= ten.H) {
+            if (++ten_i >= p.n_tensors) break;
+            h0 = 0;
+            take_tensor();
+        }
+        load_trip();
     }
 }
 
@@ -143,16 +166,19 @@ hipError_t launch_norm_rope(const NormRopeParams &p_in, bool f32, hipStream_t st
     const int elems = f32 ? 4 : 8;
     const int rows_per_wave = 64 / (p.d / elems);
     const int64_t groups = (int64_t)p.B * ((p.T + rows_per_wave - 1) / rows_per_wave);
-    // heads per wave: all of them when there are position groups enough to fill the chip
-    // (about four waves per SIMD), else chunks, down to the four heads a wave has in flight
-    int max_h = 1;
-    for (int i = 0; i < p.n_tensors; ++i) max_h = p.t[i].H > max_h ? p.t[i].H : max_h;
-    int hpw = max_h;
-    while (hpw > 4 && groups * ((max_h + hpw - 1) / hpw) < 4096) hpw = (hpw + 1) / 2;
-    hpw = (hpw + 3) / 4 * 4;
-    p.heads_per_wave = hpw;
-    p.head_chunks = (max_h + hpw - 1) / hpw;
-    const int64_t waves = groups * p.head_chunks;
+    // trips per wave: all of them when there are position groups enough for four waves per SIMD, else
+    // as many as leave eight waves per SIMD, down to one. Measured us, 16 / 16 / 8 heads, d = 128, for
+    // 2048, 4096, 8192, 16384 waves aimed at: 4096 positions 21.4, 20.0, 17.8, 19.4; 4444 24.8, 21.3,
+    // 19.0, 21.6; 16384 (4096 groups: one wave each 66.6, two 68.8).
+    int trips = 0;
+    for (int i = 0; i < p.n_tensors; ++i) trips += (p.t[i].H + kNormRopeTripHeads - 1) / kNormRopeTripHeads;
+    int64_t chunks = groups >= 4096 ? 1 : (8192 + groups - 1) / groups;
+    if (chunks > trips) chunks = trips;
+    p.trips_per_wave = (trips + (int)chunks - 1) / (int)chunks;
+    p.trip_chunks = (trips + p.trips_per_wave - 1) / p.trips_per_wave;
+    p.log2_theta = std::log2((double)p.theta);
+    p.pair_ratio = std::exp2(-2.0 / (double)p.d * p.log2_theta);
+    const int64_t waves = groups * p.trip_chunks;
     const int64_t blocks = (waves + 3) / 4;
     if (blocks <= 0 || blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     if (f32)

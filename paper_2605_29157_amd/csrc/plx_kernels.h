@@ -127,7 +127,8 @@ struct NormRopeParams {
     float eps, theta;
     const float *table;   // optional (cos, sin) per (position, pair); NULL = evaluate in the kernel
     int32_t n_pos;        // positions in the table
-    int32_t heads_per_wave, head_chunks;  // set by the launcher
+    int32_t trips_per_wave, trip_chunks;  // set by the launcher, like
+    double log2_theta, pair_ratio;        // ... log2(theta) and theta^(-2/d)
 };
 
 // Each returns hipSuccess or the launch error. No allocation, no synchronisation.

@@ -295,3 +295,20 @@ def test_norm_rope_from_the_table_matches_the_in_kernel_evaluation(plx, nr):
     st = plx.load_library().parallax_norm_rope(ctypes.byref(a), int(torch.cuda.current_stream().cuda_stream))
     assert st == plx.PLX_ERR_ALIGN
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("B,T", [(1, 3), (2, 5001), (1, 16390)])
+def test_heads_dealt_over_waves(plx, nr, B, T):
+    """Trips of four heads: one per wave, two per wave across the end of a tensor, all in one wave; head
+    counts that are no multiple of four."""
+    d = 128
+    ts = [_rand((B, H, T, d), 950 + H, torch.bfloat16) for H in (6, 5, 1)]
+    gs = [1.0 + 0.2 * _rand((d,), 960 + i, torch.float32) for i in range(3)]
+    outs = plx.parallax_norm_rope([(ts[0], gs[0], True), (ts[1], gs[1], False), (ts[2], gs[2], True)])
+    rows = sorted({0, 1, T // 2, T - 2, T - 1})
+    pos = np.array(rows)[None, None, :]
+    for x, g, out, rope in zip(ts, gs, outs, (True, False, True)):
+        raw = host(x[:, :, rows])
+        ref = nr.norm_rope(raw, host(g), pos) if rope else nr.rms_norm(raw, host(g))
+        assert rel_l2(host(out[:, :, rows]), ref) <= BF16_REL_L2
+        assert torch.isfinite(out).all() and float((out.float() ** 2).mean()) > 0.5  # every row was written
