@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 
 import torch  # imported before the library so both share one HIP runtime
 
@@ -143,6 +144,33 @@ class plx_norm_rope_args(ctypes.Structure):
                 ("dtype", ctypes.c_int), ("rope_table", ctypes.c_void_p), ("table_positions", ctypes.c_int32)]
 
 
+# The same layouts for struct.pack: a call fills its arguments in one go (30 - 60 assignments of
+# ctypes fields and arrays cost 4 - 12 us of host time, as much as a small step takes on the GPU).
+_PREP = "4P3if"
+_PACK = {
+    plx_decode_args: struct.Struct("@6P5i6qf2iPNiP3i2iP" + _PREP + "0P"),
+    plx_prefill_args: struct.Struct("@5P5i15qf5i2P2P2i" + _PREP + "0P"),
+    plx_prefill_bwd_args: struct.Struct("@12P6if3iPN33q4P2i0P"),
+    plx_decode_mla_args: struct.Struct("@5P3i3i2qfiPNP3i2i0P"),
+    plx_norm_rope_args: struct.Struct("@" + 3 * "3P2i" + "4iP2fiPi0P"),
+}
+for _args, _format in _PACK.items():
+    assert _format.size == ctypes.sizeof(_args), _args
+_NO_PREP = (0,) * 8
+
+
+def _filled(args, *values):
+    return args.from_buffer_copy(_PACK[args].pack(*values))
+
+
+def _f32(x) -> float:  # (as a C float takes it: too large becomes infinite, not an error here)
+    return ctypes.c_float(float(x)).value
+
+
+def _i32(x) -> int:  # (as a C int takes it)
+    return ctypes.c_int32(int(x)).value
+
+
 class ParallaxError(RuntimeError):
     def __init__(self, status: int, where: str):
         self.status = status
@@ -234,16 +262,31 @@ def _dtype_code(t: torch.Tensor) -> int:
     raise TypeError("Parallax kernels take bfloat16 or float32 tensors, got %s" % t.dtype)
 
 
+# (the stream's handle without the stream object around it, which takes 2.5 us to build)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_raw_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream_ptr(stream) -> int:
     if stream is None:
+        if _raw_stream is not None and _raw_device is not None:
+            return _raw_stream(_raw_device())
         stream = torch.cuda.current_stream()
     return int(stream.cuda_stream)
+
+
+def _bytes(t) -> int:
+    return t.numel() * t.element_size()
+
+
+def _ptr(t) -> int:
+    return 0 if t is None else t.data_ptr()
 
 
 def _used_on(buf, stream_ptr):
     """Tell the allocator that `buf`, allocated on the current stream, is used on another one (then
     returned), so that its memory is not handed out again before that stream is through with it."""
-    if stream_ptr == torch.cuda.current_stream().cuda_stream:
+    if stream_ptr == _stream_ptr(None):
         return None
     other = torch.cuda.ExternalStream(stream_ptr, device=buf.device)
     buf.record_stream(other)
@@ -295,33 +338,17 @@ def decode_args(q, r, k, v, out, scale, seq_lens=None, use_r=True, num_splits=0,
     with block_table [B, pages per sequence] (int32), page pools [num_pages, Hkv, page_size, d]
     (max_len = largest logical length, default: pages per sequence x page_size).
     q, r, out may also be [B, Hq, Tq, d]: Tq query rows, the last Tq positions of each sequence."""
-    Tq = 1
-    if q.dim() == 4:
-        Tq = q.shape[2]
+    Tq = q.shape[2] if q.dim() == 4 else 1
     B, Hq, d = q.shape[0], q.shape[1], q.shape[-1]
-    _, Hkv, Lmax, _ = k.shape
+    num_pages, Hkv, Lmax, _ = k.shape
+    paged = (0, 0, 0, 0)
     if block_table is not None:
-        Lmax = int(max_len) if max_len is not None else block_table.shape[1] * k.shape[2]
-    a = plx_decode_args()
-    a.q, a.k, a.v, a.o = q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr()
-    a.r = r.data_ptr() if r is not None else None
-    a.seq_lens = seq_lens.data_ptr() if seq_lens is not None else None
-    a.B, a.Hq, a.Hkv, a.Lmax, a.d = B, Hq, Hkv, Lmax, d
-    a.k_stride_b, a.k_stride_h, a.k_stride_l = k.stride(0), k.stride(1), k.stride(2)
-    a.v_stride_b, a.v_stride_h, a.v_stride_l = v.stride(0), v.stride(1), v.stride(2)
-    a.scale = float(scale)
-    a.use_r = 1 if use_r else 0
-    a.num_splits = int(num_splits)
-    if workspace is not None:
-        a.workspace = workspace.data_ptr()
-        a.workspace_bytes = workspace.numel() * workspace.element_size()
-    a.dtype = _dtype_code(q)
-    a.Tq = Tq
-    a.window = int(window)
-    if block_table is not None:
-        a.block_table = block_table.data_ptr()
-        a.page_size, a.block_table_stride, a.num_pages = k.shape[2], block_table.stride(0), k.shape[0]
-    return a
+        paged = (block_table.data_ptr(), Lmax, block_table.stride(0), num_pages)
+        Lmax = _i32(max_len if max_len is not None else block_table.shape[1] * Lmax)
+    return _filled(plx_decode_args, q.data_ptr(), _ptr(r), k.data_ptr(), v.data_ptr(), out.data_ptr(), _ptr(seq_lens),
+                   B, Hq, Hkv, Lmax, d, *k.stride()[:3], *v.stride()[:3], _f32(scale), 1 if use_r else 0, _i32(num_splits),
+                   _ptr(workspace), 0 if workspace is None else _bytes(workspace), _dtype_code(q), *paged, Tq,
+                   _i32(window), 0, *_NO_PREP)
 
 
 def parallax_decode(q, r, k, v, scale, seq_lens=None, use_r=True, num_splits=0, workspace=None,
@@ -331,9 +358,8 @@ def parallax_decode(q, r, k, v, scale, seq_lens=None, use_r=True, num_splits=0, 
     (allocation only; all arithmetic is in the library). With `split_counters` (zeroed int32
     device tensor, >= B * Hkv entries) the call goes to parallax_decode_fused: one launch, the
     last split of every group to arrive merges inside the kernel."""
-    for t in (q, k, v) + ((r,) if r is not None else ()):
-        if not t.is_cuda:
-            raise ValueError("parallax_decode needs device tensors")
+    if not (q.is_cuda and k.is_cuda and v.is_cuda and (r is None or r.is_cuda)):
+        raise ValueError("parallax_decode needs device tensors")
     if q.stride(-1) != 1 or k.stride(-1) != 1 or v.stride(-1) != 1 or not q.is_contiguous() or (
             r is not None and not r.is_contiguous()):
         raise ValueError("q, r must be contiguous and k, v contiguous in the last dimension")
@@ -427,20 +453,11 @@ def prefill_args(q, r, k, v, out, scale, causal=True, use_r=True, window=0):
     """Fill a plx_prefill_args from tensors: q, r, out [B, Hq, T, d]; k, v [B, Hkv, Tkv, d]."""
     B, Hq, T, d = q.shape
     Hkv, Tkv = k.shape[1], k.shape[2]
-    a = plx_prefill_args()
-    a.q, a.k, a.v, a.o = q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr()
-    a.r = r.data_ptr() if r is not None else None
-    a.B, a.Hq, a.Hkv, a.T, a.d = B, Hq, Hkv, T, d
-    for name, t in (("q_stride", q), ("r_stride", r if r is not None else q), ("k_stride", k),
-                    ("v_stride", v), ("o_stride", out)):
-        setattr(a, name, (ctypes.c_int64 * 3)(t.stride(0), t.stride(1), t.stride(2)))
-    a.scale = float(scale)
-    a.causal = 1 if causal else 0
-    a.use_r = 1 if use_r else 0
-    a.dtype = _dtype_code(q)
-    a.Tkv = Tkv
-    a.window = int(window)
-    return a
+    q_stride = q.stride()[:3]
+    return _filled(plx_prefill_args, q.data_ptr(), _ptr(r), k.data_ptr(), v.data_ptr(), out.data_ptr(), B, Hq, Hkv, T, d,
+                   *q_stride, *(r.stride()[:3] if r is not None else q_stride), *k.stride()[:3], *v.stride()[:3],
+                   *out.stride()[:3], _f32(scale), 1 if causal else 0, 1 if use_r else 0, _dtype_code(q), Tkv, _i32(window),
+                   0, 0, 0, 0, 0, 0, *_NO_PREP)
 
 
 BLOCK_ROWS, BLOCK_KEYS = 128, 64  # the block-sparse granularity: the prefill kernel's tiles
@@ -572,21 +589,10 @@ def prefill_bwd_args(q, r, k, v, o, vbar, row_stats, d_o, dq, dr, dk, dv, scale,
     if not row_stats.is_contiguous() or not workspace.is_contiguous():
         raise ValueError("row_stats and the workspace must be contiguous")
     B, Hq, T, d = q.shape
-    a = plx_prefill_bwd_args()
-    a.q, a.r, a.k, a.v = q.data_ptr(), r.data_ptr(), k.data_ptr(), v.data_ptr()
-    a.o, a.vbar, a.row_stats, a.d_o = o.data_ptr(), vbar.data_ptr(), row_stats.data_ptr(), d_o.data_ptr()
-    a.dq, a.dr, a.dk, a.dv = dq.data_ptr(), dr.data_ptr(), dk.data_ptr(), dv.data_ptr()
-    a.B, a.Hq, a.Hkv, a.T, a.Tkv, a.d = B, Hq, k.shape[1], T, k.shape[2], d
-    a.scale = float(scale)
-    a.causal = 1 if causal else 0
-    a.window = int(window)
-    a.dtype = _dtype_code(q)
-    a.workspace = workspace.data_ptr()
-    a.workspace_bytes = workspace.numel() * workspace.element_size()
-    for name, t in (("q", q), ("r", r), ("k", k), ("v", v), ("o", o), ("vbar", vbar), ("d_o", d_o),
-                    ("dq", dq), ("dr", dr), ("dk", dk), ("dv", dv)):
-        setattr(a, name + "_stride", (ctypes.c_int64 * 3)(*t.stride()[:3]))
-    return a
+    ptrs = [t.data_ptr() for t in (q, r, k, v, o, vbar, row_stats, d_o, dq, dr, dk, dv)]
+    strides = [x for t in (q, r, k, v, o, vbar, d_o, dq, dr, dk, dv) for x in t.stride()[:3]]
+    return _filled(plx_prefill_bwd_args, *ptrs, B, Hq, k.shape[1], T, k.shape[2], d, _f32(scale), 1 if causal else 0,
+                   _dtype_code(q), _i32(window), workspace.data_ptr(), _bytes(workspace), *strides, 0, 0, 0, 0, 0, 0)
 
 
 def parallax_prefill_backward(q, r, k, v, o, vbar, row_stats, d_o, scale, causal=True, stream=None,
@@ -613,25 +619,24 @@ def parallax_prefill_backward(q, r, k, v, o, vbar, row_stats, d_o, scale, causal
 def norm_rope_args(tensors, pos0=None, eps=1e-6, theta=1.0e6, rope_table=None):
     """Fill a plx_norm_rope_args. tensors: up to three (x, gamma, rope, out) with x, out
     [B, H, T, d] contiguous (out may be x) and gamma [d] fp32."""
-    a = plx_norm_rope_args()
-    a.n_tensors = len(tensors)
     B, _, T, d = tensors[0][0].shape
-    for i, (x, gamma, use_rope, out) in enumerate(tensors):
+    flat = []
+    for x, gamma, use_rope, out in tensors:
         if not (x.is_cuda and x.is_contiguous() and out.is_contiguous() and gamma.dtype == torch.float32):
             raise ValueError("parallax_norm_rope needs contiguous device tensors and fp32 weights")
         if x.shape[0] != B or x.shape[2] != T or x.shape[3] != d or out.shape != x.shape:
             raise ValueError("the tensors of one call share B, T and d")
-        a.tensors[i].x, a.tensors[i].y, a.tensors[i].gamma = x.data_ptr(), out.data_ptr(), gamma.data_ptr()
-        a.tensors[i].H, a.tensors[i].rope = x.shape[1], 1 if use_rope else 0
-    a.B, a.T, a.d = B, T, d
-    a.pos0 = pos0.data_ptr() if pos0 is not None else None
-    a.eps, a.theta = float(eps), float(theta)
-    a.dtype = _dtype_code(tensors[0][0])
+        flat += (x.data_ptr(), out.data_ptr(), gamma.data_ptr(), x.shape[1], 1 if use_rope else 0)
+    if len(tensors) > 3:
+        raise IndexError("at most three tensors per call")
+    flat += (0,) * (15 - len(flat))
+    table, n_pos = 0, 0
     if rope_table is not None:  # [n_pos, d / 2, 2] fp32 from parallax_rope_table (same d, theta)
         if rope_table.dtype != torch.float32 or not rope_table.is_contiguous() or rope_table.shape[1] != d // 2:
             raise ValueError("rope_table must be the contiguous fp32 [n_pos, d/2, 2] table of this d")
-        a.rope_table, a.table_positions = rope_table.data_ptr(), rope_table.shape[0]
-    return a
+        table, n_pos = rope_table.data_ptr(), rope_table.shape[0]
+    return _filled(plx_norm_rope_args, *flat, len(tensors), B, T, d, _ptr(pos0), _f32(eps), _f32(theta),
+                   _dtype_code(tensors[0][0]), table, n_pos)
 
 
 def parallax_norm_rope(tensors, pos0=None, eps=1e-6, theta=1.0e6, stream=None, inplace=False, rope_table=None):
@@ -667,27 +672,16 @@ def decode_mla_args(q, r, ckv, out, scale, seq_lens=None, num_splits=0, workspac
             raise ValueError("parallax_decode_mla needs contiguous device tensors for q, r and out")
     if not ckv.is_cuda or ckv.stride(-1) != 1:
         raise ValueError("the last dimension of the cache must be contiguous")
-    a = plx_decode_mla_args()
-    a.q, a.r, a.ckv, a.o = q.data_ptr(), r.data_ptr(), ckv.data_ptr(), out.data_ptr()
-    a.seq_lens = seq_lens.data_ptr() if seq_lens is not None else None
-    a.B, a.Hq, a.Lmax = q.shape[0], q.shape[1], ckv.shape[1]
+    paged, Lmax = (0, 0, 0, 0), ckv.shape[1]
     if block_table is not None:
         if block_table.dtype != torch.int32 or not block_table.is_cuda or block_table.stride(-1) != 1:
             raise ValueError("block_table must be a device int32 tensor with a contiguous last dimension")
-        a.block_table = block_table.data_ptr()
-        a.page_size, a.num_pages, a.block_table_stride = ckv.shape[1], ckv.shape[0], block_table.stride(0)
-        a.Lmax = int(max_len) if max_len is not None else block_table.shape[1] * ckv.shape[1]
-    a.d_latent, a.d_rope = d_latent, q.shape[-1] - d_latent
-    a.Tq = q.shape[2] if q.dim() == 4 else 1
-    a.window = int(window)
-    a.num_splits = int(num_splits)
-    a.ckv_stride_b, a.ckv_stride_l = ckv.stride(0), ckv.stride(1)
-    a.scale = float(scale)
-    a.dtype = _dtype_code(q)
-    if workspace is not None:
-        a.workspace = workspace.data_ptr()
-        a.workspace_bytes = workspace.numel() * workspace.element_size()
-    return a
+        paged = (block_table.data_ptr(), ckv.shape[1], ckv.shape[0], block_table.stride(0))
+        Lmax = _i32(max_len if max_len is not None else block_table.shape[1] * ckv.shape[1])
+    return _filled(plx_decode_mla_args, q.data_ptr(), r.data_ptr(), ckv.data_ptr(), out.data_ptr(), _ptr(seq_lens),
+                   q.shape[0], q.shape[1], Lmax, d_latent, q.shape[-1] - d_latent, _i32(num_splits), ckv.stride(0),
+                   ckv.stride(1), _f32(scale), _dtype_code(q), _ptr(workspace), 0 if workspace is None else _bytes(workspace), *paged,
+                   q.shape[2] if q.dim() == 4 else 1, _i32(window))
 
 
 def parallax_decode_mla(q, r, ckv, scale, seq_lens=None, num_splits=0, out=None, workspace=None,

@@ -442,3 +442,24 @@ def test_block_mask_lists_by_rows_and_by_columns(binding):
                             want.append(4 * rb + f)
                     assert col_idx[col_ptr[e]:col_ptr[e + 1]].tolist() == want
                     e += 1
+
+
+def test_packed_arguments_land_in_their_fields(binding):
+    """The struct.pack layouts of the binding against the ctypes structures: values 1, 2, 3 ... come back
+    in field order."""
+    import ctypes
+
+    def leaves(obj):
+        for name, kind in obj._fields_:
+            value = getattr(obj, name)
+            if isinstance(value, ctypes.Structure):
+                yield from leaves(value)
+            elif isinstance(value, ctypes.Array):
+                for x in value:
+                    yield from (leaves(x) if isinstance(x, ctypes.Structure) else (x,))
+            else:
+                yield 0 if value is None else value
+
+    for args, layout in binding._PACK.items():
+        n = len(list(leaves(args())))
+        assert list(leaves(args.from_buffer_copy(layout.pack(*range(1, n + 1))))) == list(range(1, n + 1)), args
