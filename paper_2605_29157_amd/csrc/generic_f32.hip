@@ -22,8 +22,12 @@
 // a 16-key block costs 4 * DP matrix instructions of 32 clocks against 2 * 16 * DP * 4 bytes of
 // loads, 16 bytes per clock and compute unit. One row, one key at a time on the vector ALU (one
 // workgroup per row, the kernels these replaced), the step of 8 sequences x 8 heads x 512 rows,
-// d = 64, forward and backward, took 7800 us, 6286 of them in dK / dV; these take 206 us = 78 TFLOP/s.
-// A decode step over 4 sequences x 2048 keys, 8 key heads, d = 64: 320 -> 17 us (half of that by
+// d = 64, forward and backward, took 7800 us, 6286 of them in dK / dV; these take 190 us = 85
+// TFLOP/s (206 with the row pointers formed per lane, padding tests where d = 64 needs none, and the
+// two sums merged one after the other). At 4 x 8 heads x 2048 rows the forward reaches 95 TFLOP/s.
+// Tried and slower: a wave alone with its columns (no merge; 8 x 8 x 512: 64 -> 82 us forward), four
+// waves per SIMD for d = 64 (spills; 62 -> 67, dK / dV 82 -> 109).
+// A decode step over 4 sequences x 2048 keys, 8 key heads, d = 64: 320 -> 16 us (half of that by
 // splitting the keys over workgroups).
 #include "plx_device.h"
 #include "plx_kernels.h"
@@ -151,20 +155,24 @@ __device__ __forceinline__ void f32_turn(const f32x4 (&in)[DP / 16], F32Rows<DP>
         for (int m = 0; m < DP / 64; ++m) out[r][m] = *(const f32x4 *)&tile.x[4 * g + r][64 * m + 4 * c];
 }
 
-// Adds up N accumulators per lane over the four waves (already on one scale): waves 2, 3 hand
-// theirs to waves 0, 1, then wave 1 to wave 0, which holds the result. buf: [2][N * 64] f32x4.
+// Adds up two sets of N accumulators per lane over the four waves (already on one scale): waves 2, 3
+// hand theirs to waves 0, 1, then wave 1 to wave 0, which holds the result. buf: [2][2 N * 64] f32x4.
 template <int N>
-__device__ __forceinline__ void f32_sum_waves(f32x4 (&acc)[N], f32x4 *buf, int w, int lane) {
+__device__ __forceinline__ void f32_sum_waves(f32x4 (&a)[N], f32x4 (&b)[N], f32x4 *buf, int w, int lane) {
 #pragma unroll
     for (int step = 2; step > 0; step >>= 1) {
         __syncthreads();
-        if (w >= step && w < 2 * step)
+        if (w >= step && w < 2 * step) {
+            f32x4 *to = buf + (w - step) * 2 * N * 64 + lane;
 #pragma unroll
-            for (int n = 0; n < N; ++n) buf[((w - step) * N + n) * 64 + lane] = acc[n];
+            for (int n = 0; n < N; ++n) to[n * 64] = a[n], to[(N + n) * 64] = b[n];
+        }
         __syncthreads();
-        if (w < step)
+        if (w < step) {
+            const f32x4 *from = buf + w * 2 * N * 64 + lane;
 #pragma unroll
-            for (int n = 0; n < N; ++n) acc[n] += buf[(w * N + n) * 64 + lane];
+            for (int n = 0; n < N; ++n) a[n] += from[n * 64], b[n] += from[(N + n) * 64];
+        }
     }
 }
 
@@ -180,17 +188,18 @@ __device__ __forceinline__ int64_t f32_block_id() { return (int64_t)blockIdx.y *
 template <int DP>
 union F32ForwardLds {
     F32Rows<DP> rows[2];                  // q, rho of the 16 columns
-    f32x4 merge[2 * (DP / 16) * 64];      // half of the accumulators of two waves
+    f32x4 merge[2 * 2 * (DP / 16) * 64];  // the accumulators of two waves
 };
 
-template <int DP, bool PAGED, bool USE_R>
+// FULL: d == DP, nothing to pad
+template <int DP, bool PAGED, bool USE_R, bool FULL>
 __global__ __launch_bounds__(kF32Threads, DP <= 128 ? 2 : 1) void f32_forward_kernel(F32Forward p) {
     __shared__ F32ForwardLds<DP> lds;
     __shared__ float sm[3][kF32Waves][16];
     constexpr int NA = DP / 16;
 
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-    const int c = lane & 15, g = lane >> 4, d = p.d;
+    const int c = lane & 15, g = lane >> 4, d = FULL ? DP : p.d;
     int64_t id = f32_block_id();
     if (id >= (int64_t)p.n_blocks * p.B * p.heads * p.S) return;
     const int split = (int)(id % p.S);
@@ -244,12 +253,19 @@ __global__ __launch_bounds__(kF32Threads, DP <= 128 ? 2 : 1) void f32_forward_ke
             return base + (int64_t)key * st[2];
         }
     };
+    // (the rows of a whole block of a contiguous cache: a uniform base plus this lane's own offset)
+    const int64_t k_lane = (int64_t)c * p.ks[2], v_lane = (int64_t)(4 * g) * p.vs[2];
     f32x4 kf[NA], vf[4][DP / 64];
-    auto load_k = [&](int kblk) { f32_load_row<DP>(kf, row_of(kb, p.ks, 16 * kblk + c), d, g); };
+    auto load_k = [&](int kblk) {
+        const bool plain = !PAGED && 16 * kblk + 15 <= last_key;  // uniform
+        const float *row = plain ? kb + (int64_t)(16 * kblk) * p.ks[2] + k_lane : row_of(kb, p.ks, 16 * kblk + c);
+        f32_load_row<DP>(kf, row, d, g);
+    };
     auto load_v = [&](int kblk) {
+        const bool plain = !PAGED && 16 * kblk + 15 <= last_key;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const float *row = row_of(vb, p.vs, 16 * kblk + 4 * g + r);
+            const float *row = plain ? vb + (int64_t)(16 * kblk + r) * p.vs[2] + v_lane : row_of(vb, p.vs, 16 * kblk + 4 * g + r);
 #pragma unroll
             for (int m = 0; m < DP / 64; ++m) {
                 const int dim = 64 * m + 4 * c;
@@ -334,8 +350,7 @@ __global__ __launch_bounds__(kF32Threads, DP <= 128 ? 2 : 1) void f32_forward_ke
     const float wt = m_run == kNegInf ? 0.f : fast_exp2(m_run - m_all);
 #pragma unroll
     for (int n = 0; n < NA; ++n) o1[n] *= wt, o2[n] *= wt;
-    f32_sum_waves<NA>(o1, lds.merge, w, lane);
-    f32_sum_waves<NA>(o2, lds.merge, w, lane);
+    f32_sum_waves<NA>(o1, o2, lds.merge, w, lane);
     if (w != 0 || 16 * blk + c >= p.n_cols) return;
 
     // lane (c, g): dimensions 64 m + 16 g + 4 rr .. + 3 of column c, float4 by float4
@@ -439,12 +454,16 @@ static hipError_t launch_forward(F32Forward &g, hipStream_t stream) {
     const dim3 grid = f32_grid((int64_t)g.n_blocks * g.B * g.heads * g.S), block(kF32Threads);
     auto pick = [&](auto paged, auto use_r) {
         constexpr bool P = decltype(paged)::value, R = decltype(use_r)::value;
-        if (g.d <= 64)
-            hipLaunchKernelGGL((f32_forward_kernel<64, P, R>), grid, block, 0, stream, g);
-        else if (g.d <= 128)
-            hipLaunchKernelGGL((f32_forward_kernel<128, P, R>), grid, block, 0, stream, g);
+        if (g.d == 64)
+            hipLaunchKernelGGL((f32_forward_kernel<64, P, R, true>), grid, block, 0, stream, g);
+        else if (g.d < 64)
+            hipLaunchKernelGGL((f32_forward_kernel<64, P, R, false>), grid, block, 0, stream, g);
+        else if (g.d == 128)
+            hipLaunchKernelGGL((f32_forward_kernel<128, P, R, true>), grid, block, 0, stream, g);
+        else if (g.d < 128)
+            hipLaunchKernelGGL((f32_forward_kernel<128, P, R, false>), grid, block, 0, stream, g);
         else
-            hipLaunchKernelGGL((f32_forward_kernel<256, P, R>), grid, block, 0, stream, g);
+            hipLaunchKernelGGL((f32_forward_kernel<256, P, R, false>), grid, block, 0, stream, g);
     };
     const std::true_type yes;
     const std::false_type no;
@@ -501,17 +520,17 @@ struct F32RowsLds {
     F32Rows<DP> rows[3];             // q, rho, dO
     union {
         F32Rows<DP> tile[kF32Waves];     // K blocks on their way into the other operand order
-        f32x4 merge[2 * (DP / 16) * 64];
+        f32x4 merge[2 * 2 * (DP / 16) * 64];
     };
 };
 
-template <int DP>
+template <int DP, bool FULL>
 __global__ __launch_bounds__(kF32Threads, DP <= 128 ? 2 : 1) void f32_bwd_rows_kernel(PrefillBwdParams p) {
     __shared__ F32RowsLds<DP> lds;
     __shared__ f32x4 scalars[16];
     constexpr int NA = DP / 16;
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-    const int c = lane & 15, g = lane >> 4, d = p.d, off = p.Tk - p.T;
+    const int c = lane & 15, g = lane >> 4, d = FULL ? DP : p.d, off = p.Tk - p.T;
     const int n_blocks = (p.T + 15) / 16;
     int64_t id = f32_block_id();
     if (id >= (int64_t)n_blocks * p.B * p.Hq) return;
@@ -599,8 +618,7 @@ __global__ __launch_bounds__(kF32Threads, DP <= 128 ? 2 : 1) void f32_bwd_rows_k
             f32_outputs<DP>(kt, g2, dr);
         }
     }
-    f32_sum_waves<NA>(dq, lds.merge, w, lane);
-    f32_sum_waves<NA>(dr, lds.merge, w, lane);
+    f32_sum_waves<NA>(dq, dr, lds.merge, w, lane);
     if (w != 0 || i0 + c >= p.T) return;
     const int64_t e0 = (head + i0 + c) * d;
 #pragma unroll
@@ -623,16 +641,16 @@ struct F32ColsLds {
     F32Rows<DP> rows[2];  // k, v
     union {
         F32Rows<DP> tile[kF32Waves];
-        f32x4 merge[2 * (DP / 16) * 64];
+        f32x4 merge[2 * 2 * (DP / 16) * 64];
     };
 };
 
-template <int DP>
-__global__ __launch_bounds__(kF32Threads, DP <= 64 ? 2 : 1) void f32_bwd_cols_kernel(PrefillBwdParams p) {
+template <int DP, bool FULL>
+__global__ __launch_bounds__(kF32Threads, DP <= 128 ? 2 : 1) void f32_bwd_cols_kernel(PrefillBwdParams p) {
     __shared__ F32ColsLds<DP> lds;
     constexpr int NA = DP / 16;
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-    const int c = lane & 15, g = lane >> 4, d = p.d, off = p.Tk - p.T;
+    const int c = lane & 15, g = lane >> 4, d = FULL ? DP : p.d, off = p.Tk - p.T;
     const int n_blocks = (p.Tk + 15) / 16;
     int64_t id = f32_block_id();
     if (id >= (int64_t)n_blocks * p.B * p.Hkv) return;
@@ -711,8 +729,7 @@ __global__ __launch_bounds__(kF32Threads, DP <= 64 ? 2 : 1) void f32_bwd_cols_ke
         add(xr, p.r, g2, dk);
         add(xg, p.d_o, wt, dv);
     }
-    f32_sum_waves<NA>(dk, lds.merge, w, lane);
-    f32_sum_waves<NA>(dv, lds.merge, w, lane);
+    f32_sum_waves<NA>(dk, dv, lds.merge, w, lane);
     if (w != 0 || j0 + c >= p.Tk) return;
     const int64_t e0 = (khead + j0 + c) * d;
 #pragma unroll
@@ -726,19 +743,21 @@ __global__ __launch_bounds__(kF32Threads, DP <= 64 ? 2 : 1) void f32_bwd_cols_ke
         }
 }
 
-template <int DP>
+template <int DP, bool FULL>
 static hipError_t launch_backward(const PrefillBwdParams &p, hipStream_t stream) {
     const int64_t row_blocks = (p.T + 15) / 16, key_blocks = (p.Tk + 15) / 16;
-    hipLaunchKernelGGL((f32_bwd_rows_kernel<DP>), f32_grid(row_blocks * p.B * p.Hq), dim3(kF32Threads), 0, stream, p);
+    hipLaunchKernelGGL((f32_bwd_rows_kernel<DP, FULL>), f32_grid(row_blocks * p.B * p.Hq), dim3(kF32Threads), 0, stream, p);
     if (hipError_t err = hipGetLastError()) return err;
-    hipLaunchKernelGGL((f32_bwd_cols_kernel<DP>), f32_grid(key_blocks * p.B * p.Hkv), dim3(kF32Threads), 0, stream, p);
+    hipLaunchKernelGGL((f32_bwd_cols_kernel<DP, FULL>), f32_grid(key_blocks * p.B * p.Hkv), dim3(kF32Threads), 0, stream, p);
     return hipGetLastError();
 }
 
 hipError_t launch_prefill_bwd_f32(const PrefillBwdParams &p, hipStream_t stream) {
-    return p.d <= 64    ? launch_backward<64>(p, stream)
-           : p.d <= 128 ? launch_backward<128>(p, stream)
-                        : launch_backward<256>(p, stream);
+    return p.d == 64    ? launch_backward<64, true>(p, stream)
+           : p.d < 64   ? launch_backward<64, false>(p, stream)
+           : p.d == 128 ? launch_backward<128, true>(p, stream)
+           : p.d < 128  ? launch_backward<128, false>(p, stream)
+                        : launch_backward<256, false>(p, stream);
 }
 
 }  // namespace plx
