@@ -490,7 +490,10 @@ int32_t parallax_decode_mla_num_splits(int32_t B, int32_t Hq, int32_t Lmax, int3
     // tile's chain of phases) when W < num_cus workgroups share the memory; merging splits costs
     // one more launch (about 6 us). The split count is the one with the smallest
     //     (rounds - 1) * (tiles * 3.2 + 10) + (tiles * max(2.4, 3.2 * W_last / num_cus) + 10) + (S > 1 ? 6 : 0)
-    // with at least 256 keys per split. Against sweeps of S on MI355X (model / measured us):
+    // with at least 256 keys per split, or 128 as long as there are few splits to merge (32; 12 of the
+    // 32-column kernel, whose records are eight times the bytes at 128 heads). 16 heads, 1 x 4096 tokens: 16 splits
+    // 22.9 us, 32 19.9; 1 x 2000: 7 22.3, 15 17.8; 16 x 1500: 5 25.9, 11 21.2; 128 heads, 1 x 1000: 4 24.6,
+    // 8 21.8, but 1 x 4000: 15 25.0, 16 26.7, 31 28.1. Against sweeps of S on MI355X (model / measured us):
     // 64 pairs of (sequence, column group) x L = 16384: S = 4 221 / 226 (8: 242); 96 pairs: S = 2
     // 323 / 344 (3, a round and an eighth: 501 / 505); 160 pairs x L = 8192: S = 3 284 / 289 (2:
     // 384 / 392, 1: 317 / 334); 256 pairs: unsplit 829 / 813 (2: 836, 4: 864); 40 pairs x
@@ -501,7 +504,9 @@ int32_t parallax_decode_mla_num_splits(int32_t B, int32_t Hq, int32_t Lmax, int3
     const double t_full = wide ? 2.6 : 3.2, t_least = wide ? 2.3 : 2.4;
     const int64_t pairs = (int64_t)B * (wide ? (Hq + 31) / 32 : 1);
     const int64_t n_tiles = ((int64_t)Lmax + 63) / 64;
+    const int64_t few = wide ? 12 : 32;
     int64_t cap = n_tiles >= 8 ? n_tiles / 4 : 1;
+    if (n_tiles >= 8 && cap < few) cap = n_tiles / 2 < few ? n_tiles / 2 : few;
     if (cap > PLX_MAX_SPLITS) cap = PLX_MAX_SPLITS;
     auto cost_of = [&](int64_t s) {
         const int64_t rounds = (pairs * s + num_cus - 1) / num_cus;
