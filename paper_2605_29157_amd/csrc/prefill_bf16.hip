@@ -1351,15 +1351,16 @@ __global__ __launch_bounds__(256) void prefill_combine_kernel(PrefillParams p) {
 }
 
 // Key ranges of a launch that leaves compute units idle: the tiles per range with the smallest
-// estimate, in units of one 64-key tile of a workgroup (1.6 us at d = 128; twice as many rows with
-// twice the work per key weigh the same at d = 64): 4 to start and finish a workgroup, one workgroup
-// per compute unit at a time; what a launch with more items than units loses at its end is taken as half
-// an item. Merging costs a launch (3) and twice the records' bytes at about 4.5 TB/s (7.2 MB per unit).
+// estimate, in units of one 64-key tile of a workgroup (1.2 us at d = 128, 1.5 at d = 64, where it
+// serves twice as many rows): 4 to start and finish a workgroup, one workgroup per compute unit at a
+// time; what a launch with more items than units loses at its end is taken as half an item. Merging
+// costs a launch (4) and the records' bytes there and back (4.2 MB per unit, what the sweeps below show).
 // 0 = leave the launch whole (also when the gain would be under a tenth). Measured us against the number
 // of ranges of the longest row block, 16 heads, d = 128: 512 rows over 16384 keys whole 267, 2 160, 3 128,
-// 4 (the rule) 121, 5 160, 8 135; 1024 over 16384 whole 302, 2 (the rule) 218, 3 250, 4 226; square
-// prompts of 400 ... 3000 rows whole (the rule) 17 ... 75, 2 25 ... 108; 17 over 5000 whole 88, 8 33, 16
-// (the rule) 38; d = 64, 8 heads, 3000 square whole 69, 2 54, 4 (the rule) 45, 8 58.
+// 4 (the rule) 114, 5 160, 8 135; 1024 over 16384 whole 302, 2 (the rule) 207, 3 250, 4 226; 256 over 2000
+// whole 41, 2 34, 3 31, 4 33; 17 over 5000 whole 86, 8 30, 16 34; square prompts of 300 ... 3000 rows whole
+// (the rule) 13 ... 75, 2 18 ... 108; 8 heads, 1000 square whole (the rule) 24, 2 25, 4 29; d = 64, 8 heads,
+// 2000 square whole 50, 2 39, 3 37, 6 36, 8 47.
 static int choose_split_tiles(const PrefillParams &p, int num_cus, int *items_per_head) {
     const int rows = p.d == 64 ? 256 : 128, nrb = (p.T + rows - 1) / rows;
     const int64_t heads = (int64_t)p.B * p.Hq;
@@ -1379,7 +1380,7 @@ static int choose_split_tiles(const PrefillParams &p, int num_cus, int *items_pe
         }
         *items = (int)n;
         double t = std::max(widest, (double)heads * work / num_cus + (heads * n > num_cus ? 0.5 * widest : 0.0));
-        if (records > 0) t += 3.0 + (double)(heads * records) * (2.0 * 32 * (2 * p.d + 5) * 4.0 / 7.2e6);
+        if (records > 0) t += 4.0 + (double)(heads * records) * (2.0 * 32 * (2 * p.d + 5) * 4.0 / 4.2e6);
         return t;
     };
     int items = 0, best = 0;
