@@ -1308,11 +1308,22 @@ __global__ __launch_bounds__(256) void prefill_combine_kernel(PrefillParams p) {
     auto record = [&](int i) {
         return p.ws + ((bh * p.items_per_head + item0 + i) * (4 * RW) + sub) * prefill_record_floats(D);
     };
-    float m = kNegInf;
+    // The reference of a record is that of its range's first 32 keys unless its sums overflowed, so a
+    // range may weigh up to 2^128 times its reference: the records are merged at the size of their
+    // sums, m + exponent of d1, and each is scaled by 2^-exponent on the way (exact, in two factors so
+    // that neither leaves the range of fp32). Every scaled d1 is in [0.5, 1), so no total overflows
+    // and no record that counts is weighted down to nothing.
+    float m = 0.f;
+    int e = 0;
+    bool any = false;
 #pragma unroll 8
-    for (int i = 0; i < n_ranges; ++i) m = fmaxf(m, record(i)[64 * D + col]);
-    const float m_use = m == kNegInf ? 0.f : m;
-    float d1 = 0.f, d2 = 0.f, f1 = 0.f, f2 = 0.f;
+    for (int i = 0; i < n_ranges; ++i) {
+        const float *sc = record(i) + 64 * D + col;
+        const float mi = sc[0];
+        const int ei = __builtin_amdgcn_frexp_expf(sc[32]);
+        if (mi != kNegInf && (!any || (mi - m) + (float)(ei - e) > 0.f)) m = mi, e = ei, any = true;
+    }
+    float d1 = 0.f, d2 = 0.f, f1 = 0.f, f2 = 0.f;  // all times 2^-e, relative to reference m
     f32x4 o1[4], o2[4];
 #pragma unroll
     for (int q4 = 0; q4 < 4; ++q4) o1[q4] = o2[q4] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -1320,13 +1331,16 @@ __global__ __launch_bounds__(256) void prefill_combine_kernel(PrefillParams p) {
     for (int i = 0; i < n_ranges; ++i) {
         const float *rec = record(i), *sc = rec + 64 * D + col;
         const f32x4 *ob = (const f32x4 *)rec + 32 * h + col;
-        const float wt = fast_exp2(sc[0] - m_use);  // 0 where the range shows the row nothing
-        d1 += wt * sc[32], d2 += wt * sc[64];
-        if constexpr (STATS) f1 += wt * sc[96], f2 += wt * sc[128];
+        const int ei = __builtin_amdgcn_frexp_expf(sc[32]);
+        const float down = __builtin_amdgcn_ldexpf(1.f, -(ei >> 1));
+        // (0 where the range shows the row nothing)
+        const float wt = fast_exp2((sc[0] - m) + (float)(ei - e)) * __builtin_amdgcn_ldexpf(1.f, -(ei - (ei >> 1)));
+        d1 += wt * (down * sc[32]), d2 += wt * (down * sc[64]);
+        if constexpr (STATS) f1 += wt * (down * sc[96]), f2 += wt * (down * sc[128]);
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4) {
-            o1[q4] += wt * ob[64 * (4 * n + q4)];
-            if constexpr (USE_R) o2[q4] += wt * ob[64 * (4 * (NDB + n) + q4)];
+            o1[q4] += wt * (down * ob[64 * (4 * n + q4)]);
+            if constexpr (USE_R) o2[q4] += wt * (down * ob[64 * (4 * (NDB + n) + q4)]);
         }
     }
     if (row >= p.T) return;
@@ -1345,7 +1359,7 @@ __global__ __launch_bounds__(256) void prefill_combine_kernel(PrefillParams p) {
     if constexpr (STATS)
         if (n == 0 && h == 0) {
             float *st = p.row_stats + (bh * p.T + row) * 2;
-            st[0] = f1 > 0.f ? m_use + log2f(f1) : -kNegInf;
+            st[0] = f1 > 0.f ? m + ((float)e + log2f(f1)) : -kNegInf;
             st[1] = f1 > 0.f ? f2 / f1 : 0.f;
         }
 }

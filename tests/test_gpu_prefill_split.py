@@ -97,6 +97,34 @@ def test_logits_that_grow_along_the_sequence(plx, synth, oracle):
     assert rel_l2(host(got), oracle_prefill(oracle, y)) <= BF16_REL_L2
 
 
+@pytest.mark.parametrize("d,high", [(128, 7.75), (64, 10.9375)])  # 126.5 and 126.2 binades above the other keys
+@pytest.mark.parametrize("where", ["late_then_first", "late_everywhere"])
+def test_ranges_whose_sums_come_close_to_the_end_of_fp32(plx, synth, oracle, d, high, where):
+    """A range keeps the reference of its first 32 keys as long as its sums are finite. Late in the first
+    range and first in the second: the ranges weigh the same, at references 126 binades apart. Late in
+    every range: each sum is finite, their total at one reference is not."""
+    T, Tkv = 32, 4096
+    y = _inputs(synth, 1, 2, 2, T, Tkv, d, 4500)
+    _, need = _whole(plx, y)
+    ranges = need // (2 * (128 if d == 128 else 256) // 32 * (64 * d + 160) * 4)
+    tiles = -(-(Tkv // 64) // ranges)
+    assert ranges >= 4 and tiles >= 2
+    first = [64 * tiles * i for i in range(ranges)]
+    at = [40, first[1]] if where == "late_then_first" else [x + 40 for x in first]
+    y["q"] = torch.ones_like(y["q"])
+    y["k"] = torch.zeros_like(y["k"])
+    y["k"][:, :, at] = high
+    y["r"], y["v"] = (0.002 * y["r"]).to(torch.bfloat16), (0.2 * y["v"]).to(torch.bfloat16)
+    (whole, vbar, st), _ = _whole(plx, y, stats=True)
+    got, gv, gs = plx.parallax_prefill(y["q"], y["r"], y["k"], y["v"], y["scale"], save_for_backward=True)
+    plain = plx.parallax_prefill(y["q"], y["r"], y["k"], y["v"], y["scale"])
+    ref = oracle_prefill(oracle, y)
+    assert rel_l2(host(whole), ref) <= BF16_REL_L2
+    assert rel_l2(host(got), ref) <= BF16_REL_L2 and rel_l2(host(plain), ref) <= BF16_REL_L2
+    assert rel_l2(host(gv), host(vbar).astype(np.float64)) <= BF16_REL_L2
+    np.testing.assert_allclose(host(gs), host(st), rtol=1e-5, atol=2e-3)
+
+
 def test_small_workspace_and_full_chip_run_whole(plx, synth):
     y = _inputs(synth, 1, 2, 2, 130, 5000, 128, 4400)
     whole, need = _whole(plx, y)
