@@ -1187,6 +1187,10 @@ __global__ __launch_bounds__(256, 1) void prefill_bf16_kernel(PrefillParams p) {
     // ---- SPLIT, more than one key range: the record of every row ----------------------------
     // Laid out by accumulator: [float4 block (O1, O2; dimension block n, q4)][half-wave][row], so that
     // every store of a wave is one contiguous KB, then the row scalars.
+    // A range keeps the reference of its first 32 keys as long as its sums are finite, so it may weigh up
+    // to 2^128 times its reference. Its record is therefore scaled by 2^-exponent of d1 (exact) with
+    // the exponent added to the reference: every d1 is in [0.5, 1), the references compare what the
+    // ranges weigh, and the merge neither overflows nor flushes the weight of a range that counts.
     if constexpr (SPLIT)
         if (n_ranges > 1) {
             const int64_t slot = ((int64_t)b * p.Hq + hq) * p.items_per_head + item;
@@ -1195,13 +1199,17 @@ __global__ __launch_bounds__(256, 1) void prefill_bf16_kernel(PrefillParams p) {
                 if (row0 + 32 * a >= T) continue;  // (wave-uniform) no such rows
                 float *rec = p.ws + ((slot * 4 + w) * RW + a) * prefill_record_floats(D);
                 f32x4 *ob = (f32x4 *)rec + 32 * h + col;
+                const int e = __builtin_amdgcn_frexp_expf(dsum1[a]);  // (0 for 0, inf and NaN)
+                auto scaled = [&](float x) __attribute__((always_inline)) { return __builtin_amdgcn_ldexpf(x, -e); };
+                auto scaled4 = [&](const f32x16 &x, int q4) __attribute__((always_inline)) {
+                    return f32x4{scaled(x[4 * q4]), scaled(x[4 * q4 + 1]), scaled(x[4 * q4 + 2]), scaled(x[4 * q4 + 3])};
+                };
 #pragma unroll
                 for (int n = 0; n < NDB; ++n)
 #pragma unroll
                     for (int q4 = 0; q4 < 4; ++q4) {
-                        ob[64 * (4 * n + q4)] = f32x4{o1[a][n][4 * q4], o1[a][n][4 * q4 + 1], o1[a][n][4 * q4 + 2], o1[a][n][4 * q4 + 3]};
-                        if constexpr (USE_R)
-                            ob[64 * (4 * (NDB + n) + q4)] = f32x4{o2[a][n][4 * q4], o2[a][n][4 * q4 + 1], o2[a][n][4 * q4 + 2], o2[a][n][4 * q4 + 3]};
+                        ob[64 * (4 * n + q4)] = scaled4(o1[a][n], q4);
+                        if constexpr (USE_R) ob[64 * (4 * (NDB + n) + q4)] = scaled4(o2[a][n], q4);
                     }
                 float fsum1 = 0.f, fsum2 = 0.f;  // row cache: sums of the unrounded P1, P2 (see msum1)
                 if constexpr (STATS) {
@@ -1210,10 +1218,10 @@ __global__ __launch_bounds__(256, 1) void prefill_bf16_kernel(PrefillParams p) {
                 }
                 if (h == 0) {
                     float *row = rec + 64 * D + col;  // [m | d1 | d2 | sums of the unrounded P1 | P2][32 rows]
-                    row[0] = dsum1[a] > 0.f ? m_ref[a] : kNegInf;
-                    row[32] = dsum1[a];
-                    row[64] = dsum2s[a];
-                    if constexpr (STATS) row[96] = fsum1, row[128] = fsum2;
+                    row[0] = dsum1[a] > 0.f ? m_ref[a] + (float)e : kNegInf;
+                    row[32] = scaled(dsum1[a]);
+                    row[64] = scaled(dsum2s[a]);
+                    if constexpr (STATS) row[96] = scaled(fsum1), row[128] = scaled(fsum2);
                 }
             }
             return;
@@ -1308,22 +1316,11 @@ __global__ __launch_bounds__(256) void prefill_combine_kernel(PrefillParams p) {
     auto record = [&](int i) {
         return p.ws + ((bh * p.items_per_head + item0 + i) * (4 * RW) + sub) * prefill_record_floats(D);
     };
-    // The reference of a record is that of its range's first 32 keys unless its sums overflowed, so a
-    // range may weigh up to 2^128 times its reference: the records are merged at the size of their
-    // sums, m + exponent of d1, and each is scaled by 2^-exponent on the way (exact, in two factors so
-    // that neither leaves the range of fp32). Every scaled d1 is in [0.5, 1), so no total overflows
-    // and no record that counts is weighted down to nothing.
-    float m = 0.f;
-    int e = 0;
-    bool any = false;
+    float m = kNegInf;
 #pragma unroll 8
-    for (int i = 0; i < n_ranges; ++i) {
-        const float *sc = record(i) + 64 * D + col;
-        const float mi = sc[0];
-        const int ei = __builtin_amdgcn_frexp_expf(sc[32]);
-        if (mi != kNegInf && (!any || (mi - m) + (float)(ei - e) > 0.f)) m = mi, e = ei, any = true;
-    }
-    float d1 = 0.f, d2 = 0.f, f1 = 0.f, f2 = 0.f;  // all times 2^-e, relative to reference m
+    for (int i = 0; i < n_ranges; ++i) m = fmaxf(m, record(i)[64 * D + col]);
+    const float m_use = m == kNegInf ? 0.f : m;
+    float d1 = 0.f, d2 = 0.f, f1 = 0.f, f2 = 0.f;
     f32x4 o1[4], o2[4];
 #pragma unroll
     for (int q4 = 0; q4 < 4; ++q4) o1[q4] = o2[q4] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -1331,16 +1328,13 @@ __global__ __launch_bounds__(256) void prefill_combine_kernel(PrefillParams p) {
     for (int i = 0; i < n_ranges; ++i) {
         const float *rec = record(i), *sc = rec + 64 * D + col;
         const f32x4 *ob = (const f32x4 *)rec + 32 * h + col;
-        const int ei = __builtin_amdgcn_frexp_expf(sc[32]);
-        const float down = __builtin_amdgcn_ldexpf(1.f, -(ei >> 1));
-        // (0 where the range shows the row nothing)
-        const float wt = fast_exp2((sc[0] - m) + (float)(ei - e)) * __builtin_amdgcn_ldexpf(1.f, -(ei - (ei >> 1)));
-        d1 += wt * (down * sc[32]), d2 += wt * (down * sc[64]);
-        if constexpr (STATS) f1 += wt * (down * sc[96]), f2 += wt * (down * sc[128]);
+        const float wt = fast_exp2(sc[0] - m_use);  // 0 where the range shows the row nothing
+        d1 += wt * sc[32], d2 += wt * sc[64];
+        if constexpr (STATS) f1 += wt * sc[96], f2 += wt * sc[128];
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4) {
-            o1[q4] += wt * (down * ob[64 * (4 * n + q4)]);
-            if constexpr (USE_R) o2[q4] += wt * (down * ob[64 * (4 * (NDB + n) + q4)]);
+            o1[q4] += wt * ob[64 * (4 * n + q4)];
+            if constexpr (USE_R) o2[q4] += wt * ob[64 * (4 * (NDB + n) + q4)];
         }
     }
     if (row >= p.T) return;
@@ -1359,7 +1353,7 @@ __global__ __launch_bounds__(256) void prefill_combine_kernel(PrefillParams p) {
     if constexpr (STATS)
         if (n == 0 && h == 0) {
             float *st = p.row_stats + (bh * p.T + row) * 2;
-            st[0] = f1 > 0.f ? m + ((float)e + log2f(f1)) : -kNegInf;
+            st[0] = f1 > 0.f ? m_use + log2f(f1) : -kNegInf;
             st[1] = f1 > 0.f ? f2 / f1 : 0.f;
         }
 }
