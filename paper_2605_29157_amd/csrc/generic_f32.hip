@@ -417,9 +417,11 @@ __global__ __launch_bounds__(256) void f32_combine_kernel(F32Forward p) {
         }
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-            if (h[u][0] == kNegInf) continue;  // (uniform per split lane) nothing there, or no key seen
-            const float m_new = fmaxf(m, h[u][0]);
-            const float w_old = fast_exp2(m - m_new), w_new = fast_exp2(h[u][0] - m_new);
+            // (uniform per split lane) nothing there, or no key seen; a reference of -inf with a sum that is
+            // not zero is a record of NaN scores only, which must reach the result
+            if (h[u][0] == kNegInf && h[u][1] == 0.f) continue;
+            const float m_new = fmaxf(m, h[u][0]), m_use = m_new == kNegInf ? 0.f : m_new;
+            const float w_old = fast_exp2(m - m_use), w_new = fast_exp2(h[u][0] - m_use);
             m = m_new;
             d1 = w_old * d1 + w_new * h[u][1], d2 = w_old * d2 + w_new * h[u][2];
             a1 = w_old * a1 + w_new * x1[u], a2 = w_old * a2 + w_new * x2[u];
@@ -435,7 +437,7 @@ __global__ __launch_bounds__(256) void f32_combine_kernel(F32Forward p) {
     d1 = d2 = 0.f, a1 = a2 = zero;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const float wt = hdr[i][0] == kNegInf ? 0.f : fast_exp2(hdr[i][0] - m_all);
+        const float wt = hdr[i][0] == kNegInf ? 0.f : fast_exp2(hdr[i][0] - m_all);  // (0 * NaN stays NaN)
         d1 += wt * hdr[i][1], d2 += wt * hdr[i][2];
         a1 += wt * acc[i][0][dl], a2 += wt * acc[i][1][dl];
     }

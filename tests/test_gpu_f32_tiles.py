@@ -64,6 +64,16 @@ def test_decode_edges_split_and_unsplit(plx, synth, oracle, L, d, Hq, Hkv, Tq, S
     assert torch.equal(few, outs[1])
 
 
+def test_a_split_of_nan_keys_is_not_dropped(plx, synth):
+    """The last of four splits (keys 1536 on) holds NaN keys only: the row has no result (zeros, as unsplit), not the
+    result of the other splits."""
+    x = synth.decode_inputs(2, 4, 2, 2000, 64, seed=31, dtype=torch.float32, device=DEV)
+    x["k"][1, :, 1536:] = math.nan
+    outs = [plx.parallax_decode(x["q"], x["r"], x["k"], x["v"], x["scale"], num_splits=s) for s in (1, 4)]
+    for out in outs:
+        assert float(out[0].abs().max()) > 0.0 and float(out[1].abs().max()) == 0.0
+
+
 @pytest.mark.parametrize("bad", [math.nan, math.inf])
 @pytest.mark.parametrize("T,d,window", [(50, 64, 0), (40, 128, 9), (37, 256, 0)])
 def test_a_row_ignores_what_it_does_not_see(plx, synth, T, d, window, bad):
