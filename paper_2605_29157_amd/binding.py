@@ -283,19 +283,42 @@ def _ptr(t) -> int:
     return 0 if t is None else t.data_ptr()
 
 
-def _used_on(buf, stream_ptr):
-    """Tell the allocator that `buf`, allocated on the current stream, is used on another one (then
-    returned), so that its memory is not handed out again before that stream is through with it."""
-    if stream_ptr == _stream_ptr(None):
+def _other_stream(stream, device):
+    """The stream that a launch goes to if it is not the current one, else None."""
+    if stream is None or _stream_ptr(stream) == _stream_ptr(None):
         return None
-    other = torch.cuda.ExternalStream(stream_ptr, device=buf.device)
-    buf.record_stream(other)
-    return other
+    if isinstance(stream, torch.cuda.Stream):
+        return stream
+    return torch.cuda.ExternalStream(int(stream.cuda_stream), device=device)
+
+
+def _scratch(stream, n_floats, device):
+    """fp32 scratch of a launch on `stream`, from that stream's own memory: a block of the current stream's
+    may still be in use by work queued there, and may be handed out again there as soon as
+    the call returns."""
+    other = _other_stream(stream, device)
+    if other is None:
+        return torch.empty(n_floats, dtype=torch.float32, device=device)
+    with torch.cuda.stream(other):
+        return torch.empty(n_floats, dtype=torch.float32, device=device)
+
+
+def _result(stream, make, *args, **kw):
+    """make(*args, **kw) (torch.empty or empty_like), a tensor that a launch on `stream` writes and the caller gets: from the launch
+    stream's memory as well, and not reused there before the current stream, where the caller
+    goes on, is through with it."""
+    other = _other_stream(stream, kw["device"] if "device" in kw else args[0].device)
+    if other is None:
+        return make(*args, **kw)
+    with torch.cuda.stream(other):
+        t = make(*args, **kw)
+    t.record_stream(torch.cuda.current_stream(t.device))
+    return t
 
 
 def parallax_rope_table(n_pos, d, theta=1.0e6, device="cuda:0", stream=None):
     """(cos, sin) of pos * theta^(-2i/d): fp32 tensor [n_pos, d/2, 2] for qr_prep()."""
-    table = torch.empty(n_pos, d // 2, 2, dtype=torch.float32, device=device)
+    table = _result(stream, torch.empty, n_pos, d // 2, 2, dtype=torch.float32, device=device)
     st = load_library().parallax_rope_table(table.data_ptr(), int(n_pos), int(d), float(theta), _stream_ptr(stream))
     if st != PLX_OK:
         raise ParallaxError(st, "parallax_rope_table")
@@ -375,15 +398,14 @@ def parallax_decode(q, r, k, v, scale, seq_lens=None, use_r=True, num_splits=0, 
             raise ValueError("block_table needs one row per sequence; k and v pools of one shape")
         Lmax = int(max_len) if max_len is not None else block_table.shape[1] * k.shape[2]
     if out is None:
-        out = torch.empty_like(q)
+        out = _result(stream, torch.empty_like, q)
     if workspace is None and num_splits != 1:
         # (with a window the library may pick fewer splits than for Lmax, never more)
         # (fp32: one record per 128 keys is the most that the library asks for)
         S = num_splits or (parallax_decode_num_splits(B, Hq, Hkv, Lmax, d) if q.dtype == torch.bfloat16
                            else min(PLX_MAX_SPLITS, Lmax // 128))
         if S > 1:
-            workspace = torch.empty(B * Hq * Tq * S * (2 * d + 4), dtype=torch.float32,
-                                    device=q.device)
+            workspace = _scratch(stream, B * Hq * Tq * S * (2 * d + 4), q.device)
     a = decode_args(q, r, k, v, out, scale, seq_lens, use_r, num_splits, workspace, block_table,
                     max_len, window)
     if prep is not None:
@@ -531,8 +553,9 @@ def attach_block_lists(a, block_mask, device, stream=None, columns=False):
     st = load_library().parallax_block_lists(ctypes.byref(la), current.cuda_stream)
     if st != PLX_OK:
         raise ParallaxError(st, "parallax_block_lists")
-    other = _used_on(buf, _stream_ptr(stream))
-    if other is not None:
+    other = _other_stream(stream, device)
+    if other is not None:  # read there: after the lists are built, and not reused here before
+        buf.record_stream(other)
         other.wait_stream(current)
     return buf
 
@@ -550,7 +573,7 @@ def parallax_prefill(q, r, k, v, scale, causal=True, use_r=True, out=None, strea
     if v.shape[2] != k.shape[2]:
         raise ValueError("k and v must hold the same number of keys")
     if out is None:
-        out = torch.empty_like(q)
+        out = _result(stream, torch.empty_like, q)
     a = prefill_args(q, r, k, v, out, scale, causal, use_r, window)
     if block_mask is not None:
         nrb, nkt = -(-q.shape[2] // BLOCK_ROWS), -(-k.shape[2] // BLOCK_KEYS)
@@ -560,14 +583,13 @@ def parallax_prefill(q, r, k, v, scale, causal=True, use_r=True, out=None, strea
     if prep is not None:
         a.prep = prep
     if save_for_backward:
-        vbar = torch.empty_like(out)
-        row_stats = torch.empty(q.shape[:3] + (2,), dtype=torch.float32, device=q.device)
+        vbar = _result(stream, torch.empty_like, out)
+        row_stats = _result(stream, torch.empty, q.shape[:3] + (2,), dtype=torch.float32, device=q.device)
         a.vbar, a.row_stats = vbar.data_ptr(), row_stats.data_ptr()
     lib, where = load_library(), _stream_ptr(stream)
     split_bytes = lib.parallax_prefill_workspace_bytes(ctypes.byref(a))
     if split_bytes:  # few row blocks, many keys: split over key ranges
-        workspace = torch.empty(split_bytes // 4, dtype=torch.float32, device=q.device)
-        _used_on(workspace, where)
+        workspace = _scratch(stream, split_bytes // 4, q.device)
         st = lib.parallax_prefill_split(ctypes.byref(a), workspace.data_ptr(), split_bytes, where)
     else:
         st = lib.parallax_prefill(ctypes.byref(a), where)
@@ -599,11 +621,9 @@ def parallax_prefill_backward(q, r, k, v, o, vbar, row_stats, d_o, scale, causal
                               workspace=None, window=0, block_mask=None):
     """Gradients (dq, dr, dk, dv) of parallax_prefill for the upstream gradient d_o, from the
     forward's output and row cache (save_for_backward=True, same causal / window / block_mask)."""
-    dq, dr = torch.empty_like(q), torch.empty_like(q)
-    dk, dv = torch.empty_like(k), torch.empty_like(k)
+    dq, dr, dk, dv = (_result(stream, torch.empty_like, t) for t in (q, q, k, k))
     if workspace is None:
-        workspace = torch.empty(q.shape[0] * q.shape[1] * q.shape[2] * 4, dtype=torch.float32,
-                                device=q.device)
+        workspace = _scratch(stream, q.shape[0] * q.shape[1] * q.shape[2] * 4, q.device)
     a = prefill_bwd_args(q, r, k, v, o, vbar, row_stats, d_o, dq, dr, dk, dv, scale, causal, workspace, window)
     if block_mask is not None:
         nrb, nkt = -(-q.shape[2] // BLOCK_ROWS), -(-k.shape[2] // BLOCK_KEYS)
@@ -644,7 +664,7 @@ def parallax_norm_rope(tensors, pos0=None, eps=1e-6, theta=1.0e6, stream=None, i
     returns the list of results (the inputs themselves with inplace=True)."""
     if pos0 is not None and pos0.dtype != torch.int32:
         raise TypeError("pos0 must be int32")
-    full = [(x, g, rp, x if inplace else torch.empty_like(x)) for (x, g, rp) in tensors]
+    full = [(x, g, rp, x if inplace else _result(stream, torch.empty_like, x)) for (x, g, rp) in tensors]
     a = norm_rope_args(full, pos0, eps, theta, rope_table)
     st = load_library().parallax_norm_rope(ctypes.byref(a), _stream_ptr(stream))
     if st != PLX_OK:
@@ -691,15 +711,14 @@ def parallax_decode_mla(q, r, ckv, scale, seq_lens=None, num_splits=0, out=None,
     [B, Hq, Tq, dk] (rows at the last Tq positions, causal among themselves: a chunked decode
     step, or the prefill over the latent cache with Tq = prompt length); window > 0 = sliding."""
     if out is None:
-        out = torch.empty(q.shape[:-1] + (d_latent,), dtype=q.dtype, device=q.device)
+        out = _result(stream, torch.empty, q.shape[:-1] + (d_latent,), dtype=q.dtype, device=q.device)
     n_cols = q.shape[1] * (q.shape[2] if q.dim() == 4 else 1)
     if workspace is None and num_splits != 1:
         lmax = ckv.shape[1] if block_table is None else (
             int(max_len) if max_len is not None else block_table.shape[1] * ckv.shape[1])
         S = num_splits or parallax_decode_mla_num_splits(q.shape[0], n_cols, lmax)
         if S > 1:
-            workspace = torch.empty(q.shape[0] * n_cols * S * (2 * d_latent + 4), dtype=torch.float32,
-                                    device=q.device)
+            workspace = _scratch(stream, q.shape[0] * n_cols * S * (2 * d_latent + 4), q.device)
     a = decode_mla_args(q, r, ckv, out, scale, seq_lens, num_splits, workspace, d_latent, block_table, max_len,
                         window)
     st = load_library().parallax_decode_mla(ctypes.byref(a), _stream_ptr(stream))

@@ -1,0 +1,114 @@
+"""Whose memory a call on another stream uses. The entry points are run with the launches and the streams
+replaced by records, on host tensors that pass for device tensors: whatever a call allocates for
+a launch stream has to come from that stream's memory (or be told to the allocator, with the launch
+waiting for the stream that it came from)."""
+import contextlib
+import types
+
+import pytest
+import torch
+
+
+class Dev(torch.Tensor):
+    """A host tensor that says it is on the device."""
+
+    is_cuda = property(lambda self: True)
+
+    def record_stream(self, stream):
+        self.told = getattr(self, "told", ()) + (stream.cuda_stream,)
+
+
+def dev(*shape, dtype=torch.bfloat16):
+    return torch.zeros(*shape, dtype=dtype).as_subclass(Dev)
+
+
+class Stream(types.SimpleNamespace):
+    def wait_stream(self, other):
+        self.waited.append(other.cuda_stream)
+
+
+@pytest.fixture()
+def world(monkeypatch):
+    """binding with stream 1 as the current one, launches on stream 2, and the list of allocations."""
+    from paper_2605_29157_amd import binding
+
+    lib = binding.load_library()
+    streams = {i: Stream(cuda_stream=i, waited=[]) for i in (1, 2)}
+    now, made, launches = [1], [], []
+
+    @contextlib.contextmanager
+    def use(stream):
+        now.append(stream.cuda_stream)
+        yield
+        now.pop()
+
+    def recorded(make):
+        def wrapped(*args, **kw):
+            kw.pop("device", None)
+            t = make(*args, **kw).as_subclass(Dev)
+            made.append((now[-1], t))
+            return t
+        return wrapped
+
+    class Lib:
+        def __getattr__(self, name):
+            if name.endswith(("bytes", "splits")):
+                return getattr(lib, name)
+            return lambda *args: launches.append((name, args[-1])) or 0
+
+    monkeypatch.setattr(binding, "load_library", lambda: Lib())
+    monkeypatch.setattr(binding, "_stream_ptr", lambda s: now[-1] if s is None else s.cuda_stream)
+    monkeypatch.setattr(torch.cuda, "stream", use)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: streams[now[-1]])
+    monkeypatch.setattr(torch.cuda, "ExternalStream", lambda ptr, device=None: streams[ptr])
+    monkeypatch.setattr(torch, "empty", recorded(torch.empty))
+    monkeypatch.setattr(torch, "empty_like", recorded(torch.empty_like))
+    return types.SimpleNamespace(plx=binding, streams=streams, made=made, launches=launches)
+
+
+def _prefill(w, T, Tkv, **kw):
+    q, r, k, v = dev(1, 2, T, 128), dev(1, 2, T, 128), dev(1, 2, Tkv, 128), dev(1, 2, Tkv, 128)
+    return w.plx.parallax_prefill(q, r, k, v, 0.1, stream=w.streams[2], **kw)
+
+
+def _decode(w, dtype, **kw):
+    q, r, k, v = dev(1, 4, 64, dtype=dtype), dev(1, 4, 64, dtype=dtype), *(dev(1, 2, 4096, 64, dtype=dtype) for _ in "kv")
+    return w.plx.parallax_decode(q, r, k, v, 0.1, stream=w.streams[2], **kw)
+
+
+def _backward(w, **kw):
+    x = [dev(1, 2, 256, 128) for _ in range(7)]
+    return w.plx.parallax_prefill_backward(*x[:6], dev(1, 2, 256, 2, dtype=torch.float32), x[6], 0.1, stream=w.streams[2], **kw)
+
+
+MASK = torch.ones(2, 4, dtype=torch.bool).as_subclass(Dev)
+CALLS = {
+    "decode_bf16": lambda w: _decode(w, torch.bfloat16),
+    "decode_f32": lambda w: _decode(w, torch.float32),
+    "decode_own_output": lambda w: _decode(w, torch.float32, out=dev(1, 4, 64, dtype=torch.float32)),
+    "mla": lambda w: w.plx.parallax_decode_mla(dev(1, 16, 576), dev(1, 16, 576), dev(1, 4096, 576), 0.1, stream=w.streams[2]),
+    "prefill_split": lambda w: _prefill(w, 64, 8192),
+    "prefill_cache": lambda w: _prefill(w, 64, 64, save_for_backward=True),
+    "prefill_mask": lambda w: _prefill(w, 256, 256, block_mask=MASK),
+    "backward": lambda w: _backward(w),
+    "backward_mask": lambda w: _backward(w, block_mask=MASK),
+    "norm_rope": lambda w: w.plx.parallax_norm_rope([(dev(1, 2, 3, 64), dev(64, dtype=torch.float32), True)], stream=w.streams[2]),
+    "rope_table": lambda w: w.plx.parallax_rope_table(4, 64, stream=w.streams[2]),
+}
+
+
+@pytest.mark.parametrize("name", CALLS)
+def test_memory_of_a_call_on_another_stream(world, name):
+    result = CALLS[name](world)
+    assert world.made and world.launches[-1][1] == 2
+    returned = [t for t in (result if isinstance(result, (tuple, list)) else [result])]
+    for stream, t in world.made:
+        told = getattr(t, "told", ())
+        if stream == 2:  # its own memory; what the caller gets is used on the caller's stream too
+            assert any(t is x for x in returned) == (1 in told)
+        else:  # the lists of a block mask: built on the current stream, where the mask is
+            assert "mask" in name and t.dtype == torch.int32
+            assert told == (2,) and world.streams[2].waited == [1]
+            assert world.launches[0] == ("parallax_block_lists", 1)
+    assert any(t.dtype == torch.float32 and not any(t is x for x in returned) for _, t in world.made) == (
+        name in ("decode_bf16", "decode_f32", "decode_own_output", "mla", "prefill_split", "backward", "backward_mask"))
