@@ -158,6 +158,11 @@ size_t parallax_decode_workspace_bytes(int32_t B, int32_t Hq, int32_t Hkv, int32
 int32_t parallax_decode_num_splits(int32_t B, int32_t Hq, int32_t Hkv, int32_t Lmax, int32_t d,
                                    int32_t num_cus);
 
+/* Key-range splits that a call with these arguments uses given workspace for them: num_splits, or the
+ * heuristic's pick for its dtype, shape, window and rows; 0 if the arguments are not valid (o and the
+ * workspace are not looked at). More than one takes B * Hq * Tq * S * (2d + 4) * 4 bytes. */
+int32_t parallax_decode_call_splits(const plx_decode_args *args);
+
 plx_status parallax_decode(const plx_decode_args *args, void *hip_stream);
 
 /*
@@ -166,7 +171,8 @@ plx_status parallax_decode(const plx_decode_args *args, void *hip_stream);
  * fixed array inside the library's code object instead (one copy per GPU, held until the
  * process ends; parallax_decode_static_scratch_bytes() = 17 039 360 bytes, i.e.
  * PLX_STATIC_SCRATCH_RECORDS records at d = 128). Same arguments, kernels and results as
- * parallax_decode (bit-identical for the same num_splits); args->workspace and
+ * parallax_decode (bit-identical for the same num_splits; fp32 calls run as with
+ * num_splits = 1); args->workspace and
  * args->workspace_bytes are ignored. The call allocates nothing and calls no allocating
  * routine; the first call on a device looks the array's address up once.
  *   Limit: B * Hq * Tq * S * (2d + 4) * 4 bytes must fit the scratch (S = num_splits, or the

@@ -22,7 +22,7 @@ PLX_MAX_SPLITS = 128
 PLX_STATIC_SCRATCH_RECORDS = 16384
 
 EXPORTED_SYMBOLS = (
-    "parallax_decode_workspace_bytes", "parallax_decode_num_splits", "parallax_decode",
+    "parallax_decode_workspace_bytes", "parallax_decode_num_splits", "parallax_decode_call_splits", "parallax_decode",
     "parallax_decode_partials", "parallax_decode_combine", "parallax_decode_fused",
     "parallax_decode_static", "parallax_decode_static_scratch_bytes",
     "parallax_decode_mla", "parallax_decode_mla_workspace_bytes", "parallax_decode_mla_num_splits",
@@ -193,6 +193,8 @@ def load_library() -> ctypes.CDLL:
         lib.parallax_decode_workspace_bytes.restype = ctypes.c_size_t
         lib.parallax_decode_num_splits.argtypes = [ctypes.c_int32] * 6
         lib.parallax_decode_num_splits.restype = ctypes.c_int32
+        lib.parallax_decode_call_splits.argtypes = [ctypes.POINTER(plx_decode_args)]
+        lib.parallax_decode_call_splits.restype = ctypes.c_int32
         lib.parallax_decode.argtypes = [ctypes.POINTER(plx_decode_args), ctypes.c_void_p]
         lib.parallax_decode.restype = ctypes.c_int
         lib.parallax_decode_static_scratch_bytes.argtypes = []
@@ -390,24 +392,22 @@ def parallax_decode(q, r, k, v, scale, seq_lens=None, use_r=True, num_splits=0, 
         raise TypeError("seq_lens must be int32")
     B, Hq, d = q.shape[0], q.shape[1], q.shape[-1]
     Tq = q.shape[2] if q.dim() == 4 else 1
-    _, Hkv, Lmax, _ = k.shape
+    _, Hkv, _, _ = k.shape
     if block_table is not None:
         if block_table.dtype != torch.int32 or not block_table.is_cuda or block_table.stride(1) != 1:
             raise TypeError("block_table must be an int32 device tensor [B, pages per sequence]")
         if block_table.shape[0] != B or v.shape != k.shape:
             raise ValueError("block_table needs one row per sequence; k and v pools of one shape")
-        Lmax = int(max_len) if max_len is not None else block_table.shape[1] * k.shape[2]
     if out is None:
         out = _result(stream, torch.empty_like, q)
-    if workspace is None and num_splits != 1:
-        # (with a window the library may pick fewer splits than for Lmax, never more)
-        # (fp32: one record per 128 keys is the most that the library asks for)
-        S = num_splits or (parallax_decode_num_splits(B, Hq, Hkv, Lmax, d) if q.dtype == torch.bfloat16
-                           else min(PLX_MAX_SPLITS, Lmax // 128))
-        if S > 1:
-            workspace = _scratch(stream, B * Hq * Tq * S * (2 * d + 4), q.device)
     a = decode_args(q, r, k, v, out, scale, seq_lens, use_r, num_splits, workspace, block_table,
                     max_len, window)
+    lib = load_library()
+    if workspace is None and num_splits != 1:
+        S = lib.parallax_decode_call_splits(ctypes.byref(a))  # (0: refused below)
+        if S > 1:
+            workspace = _scratch(stream, B * Hq * Tq * S * (2 * d + 4), q.device)
+            a.workspace, a.workspace_bytes = workspace.data_ptr(), _bytes(workspace)
     if prep is not None:
         a.prep = prep
     entry = "parallax_decode"
@@ -417,7 +417,7 @@ def parallax_decode(q, r, k, v, scale, seq_lens=None, use_r=True, num_splits=0, 
             raise TypeError("split_counters must be a contiguous int32 device tensor, >= B * Hkv")
         a.split_counters = split_counters.data_ptr()
         entry = "parallax_decode_fused"
-    st = getattr(load_library(), entry)(ctypes.byref(a), _stream_ptr(stream))
+    st = getattr(lib, entry)(ctypes.byref(a), _stream_ptr(stream))
     if st != PLX_OK:
         raise ParallaxError(st, entry)
     return out

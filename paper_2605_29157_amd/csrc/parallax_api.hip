@@ -236,26 +236,29 @@ int32_t pick_splits(const plx_decode_args *a, int32_t Tq) {
     return parallax_decode_num_splits(a->B, a->Hq, a->Hkv, (int32_t)keys_read(a, Tq), a->d, 0);
 }
 
-// Split count of an fp32 call: as many workgroups as the compute units hold at a time (two each, one
-// above d = 128: 2 sequences x 3000 keys, 16 pairs, d = 256, S = 16 55 us, S = 23 90), at least 128 keys (two rounds of a
-// workgroup's four waves) per split, and no more than the caller's workspace has room for. Measured us
+// Split count of an fp32 call with scratch for any: as many workgroups as the compute units hold at a time
+// (two each, one above d = 128: 2 sequences x 3000 keys, 16 pairs, d = 256, S = 16 55 us, S = 23 90), at least 128 keys (two rounds of a
+// workgroup's four waves) per split. Measured us
 // at S = 1, 2, 4, 8, 16, 32, 64: 16 sequences x 1024 keys (128 pairs, d = 128; the rule: 4) 61, 41, 38,
 // 44, 56; 8 x 4096 (32 pairs; 16) 220, 120, 67, 43, 40, 47, 58; 1 x 16384 (8 pairs; 64) 849, 432, 222,
 // 118, 66, 42, 42; 64 x 512 (512 pairs; 1) 58, 67, 80, 104.
 int32_t pick_splits_f32(const plx_decode_args *a, int32_t Tq) {
+    if (a->num_splits > 0) return a->num_splits;
     const int64_t groups = (int64_t)a->B * a->Hkv * (((int64_t)(a->Hq / a->Hkv) * Tq + 15) / 16);
-    int64_t s = a->num_splits;
-    if (s == 0) {
-        const int64_t resident = (int64_t)query_num_cus() * (a->d <= 128 ? 2 : 1);
-        s = (resident + groups - 1) / groups;
-        const int64_t cap = keys_read(a, Tq) / 128;
-        if (s > cap) s = cap;
-        if (s > PLX_MAX_SPLITS) s = PLX_MAX_SPLITS;
-    }
+    const int64_t resident = (int64_t)query_num_cus() * (a->d <= 128 ? 2 : 1);
+    int64_t s = (resident + groups - 1) / groups;
+    const int64_t cap = keys_read(a, Tq) / 128;
+    if (s > cap) s = cap;
+    if (s > PLX_MAX_SPLITS) s = PLX_MAX_SPLITS;
+    return s < 1 ? 1 : (int32_t)s;
+}
+
+// ... and no more than the caller's workspace has room for.
+int32_t splits_with_room_f32(const plx_decode_args *a, int32_t Tq) {
     const int64_t room =
         a->workspace && aligned16(a->workspace) ? (int64_t)(a->workspace_bytes / ws_bytes(a->B, (int64_t)a->Hq * Tq, 1, a->d)) : 0;
-    if (s > room) s = room;
-    return s < 1 ? 1 : (int32_t)s;
+    const int64_t s = pick_splits_f32(a, Tq);
+    return s > room ? (room < 1 ? 1 : (int32_t)room) : (int32_t)s;
 }
 
 plx_status attach_workspace(const plx_decode_args *a, int32_t S, plx::DecodeParams *p) {
@@ -301,7 +304,7 @@ plx_status decode_two_kernels(const plx_decode_args *a, bool static_scratch, voi
 
     if (a->dtype == PLX_F32) {
         // (fp32 calls need no workspace and leave the static scratch alone, so that they may overlap)
-        p.S = static_scratch ? 1 : pick_splits_f32(a, p.Tq);
+        p.S = static_scratch ? 1 : splits_with_room_f32(a, p.Tq);
         p.ws = static_cast<float *>(a->workspace);
         p.r = a->r;
         return plx::launch_decode_f32(p, stream) == hipSuccess ? PLX_OK : PLX_ERR_LAUNCH;
@@ -321,6 +324,13 @@ plx_status decode_two_kernels(const plx_decode_args *a, bool static_scratch, voi
 }
 
 }  // namespace
+
+int32_t parallax_decode_call_splits(const plx_decode_args *a) {
+    plx::DecodeParams p{};
+    if (prepare_decode(a, true, false, &p) != PLX_OK) return 0;
+    if (a->num_splits > 0) return a->num_splits;
+    return a->dtype == PLX_F32 ? pick_splits_f32(a, p.Tq) : pick_splits(a, p.Tq);
+}
 
 plx_status parallax_decode(const plx_decode_args *a, void *hip_stream) {
     return decode_two_kernels(a, false, hip_stream);

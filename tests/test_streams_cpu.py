@@ -1,4 +1,4 @@
-"""Whose memory a call on another stream uses. The entry points are run with the launches and the streams
+"""What a call allocates, and from whose memory where it goes to another stream. The entry points are run with the launches and the streams
 replaced by records, on host tensors that pass for device tensors: whatever a call allocates for
 a launch stream has to come from that stream's memory (or be told to the allocator, with the launch
 waiting for the stream that it came from)."""
@@ -112,3 +112,29 @@ def test_memory_of_a_call_on_another_stream(world, name):
             assert world.launches[0] == ("parallax_block_lists", 1)
     assert any(t.dtype == torch.float32 and not any(t is x for x in returned) for _, t in world.made) == (
         name in ("decode_bf16", "decode_f32", "decode_own_output", "mla", "prefill_split", "backward", "backward_mask"))
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,Tq,L,window,records", [
+    (64, 32, 8, 1, 16384, 0, 0),         # workgroups for every compute unit twice: unsplit
+    (1, 16, 8, 4096, 16384, 0, 0),       # so have many query rows
+    (1, 16, 8, 1, 16384, 256, 16 * 2),   # two splits of 128 keys inside the window
+    (1, 16, 8, 1, 16384, 0, 16 * 64),    # 512 workgroups for 256 compute units
+    (2, 4, 4, 1, 200, 0, 0)])
+def test_fp32_decode_allocates_the_records_that_it_uses(world, B, Hq, Hkv, Tq, L, window, records):
+    q = dev(B, Hq, Tq, 64, dtype=torch.float32) if Tq > 1 else dev(B, Hq, 64, dtype=torch.float32)
+    k = dev(1, 1, L, 64, dtype=torch.float32).expand(B, Hkv, L, 64)
+    world.plx.parallax_decode(q, q, k, k, 0.1, window=window, out=q)
+    assert sum(t.numel() for _, t in world.made) == records * (2 * 64 + 4)
+
+
+def test_split_count_of_a_call(world):
+    """bf16: the pick of the shape query; explicit counts; 0 for arguments that the call would refuse."""
+    import ctypes
+
+    lib = world.plx.load_library()
+    q, k = dev(1, 16, 128), dev(1, 8, 16384, 128)
+    for kw, want in ((dict(), lib.parallax_decode_num_splits(1, 16, 8, 16384, 128, 0)), (dict(num_splits=3), 3),
+                     (dict(window=2000), lib.parallax_decode_num_splits(1, 16, 8, 2000, 128, 0)), (dict(num_splits=129), 0)):
+        a = world.plx.decode_args(q, q, k, k, q, 0.1, **kw)
+        a.o = None
+        assert lib.parallax_decode_call_splits(ctypes.byref(a)) == want
