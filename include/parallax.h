@@ -404,7 +404,10 @@ plx_status parallax_prefill_backward(const plx_prefill_bwd_args *args, void *hip
  *   col_ptr   [lists * ceil(n_tiles / 2) + 1], col_idx [lists * ceil(n_tiles / 2) * n_row_blocks]:
  *             written, or both NULL
  *   counts    scratch, lists * (n_row_blocks + ceil(n_tiles / 2)) int32
- * Entries behind the last one listed are left as they are. Two kernels, no synchronisation.
+ * Entries behind the last one listed are left as they are. Two kernels (three from 8192 row or key
+ * lines on), no synchronisation. The host never learns the number of entries, so the index arrays are
+ * sized for a full mask: 4 bytes per cell, 6 with the key lists. At most 2^31 - 1 cells and 2^25
+ * lines (lists * (n_row_blocks + ceil(n_tiles / 2))), else PLX_ERR_SHAPE.
  */
 typedef struct {
     const uint8_t *mask;

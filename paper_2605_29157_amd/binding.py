@@ -526,38 +526,52 @@ def block_mask_column_lists(block_mask):
     return col_ptr, col_idx
 
 
+# What parallax_block_lists takes: entries in 32 bits, lines (row blocks + key blocks of all lists)
+_MAX_LIST_CELLS, _MAX_LIST_LINES = 0x7fffffff, 1 << 25
+
+
 def attach_block_lists(a, block_mask, device, stream=None, columns=False):
     """Build the lists of a block mask on the device (current stream) and point the prefill (columns:
-    backward) arguments `a` at them, for a launch on `stream`. Returns the buffer that holds them:
-    keep it until the call has been enqueued."""
+    backward) arguments `a` at them, for a launch on `stream`. Returns the buffer that holds them
+    (several tensors for a mask beyond what parallax_block_lists takes): keep it until the call has
+    been enqueued."""
     m = block_mask.to(device=device, dtype=torch.bool)
     while m.dim() < 4:
         m = m.unsqueeze(0)
     Bs, Hs, nrb, nkt = m.shape
-    m = m.contiguous()
-    rows, cols, ncb = Bs * Hs * nrb, 0, (nkt + 1) // 2
-    if columns:
-        cols = Bs * Hs * ncb
-    # [row_ptr | col_ptr | counts | tile_idx | col_idx]
-    sizes = [rows + 1, cols + 1 if columns else 0, rows + cols, rows * nkt, cols * nrb]
-    buf = torch.empty(sum(sizes), dtype=torch.int32, device=device)
-    at = [buf.data_ptr() + 4 * sum(sizes[:i]) for i in range(5)]
-    la = plx_block_list_args()
-    la.mask, la.lists, la.n_row_blocks, la.n_tiles = m.data_ptr(), Bs * Hs, nrb, nkt
-    la.row_ptr, la.counts, la.tile_idx = at[0], at[2], at[3]
-    a.sparse_row_ptr, a.sparse_tile_idx, a.sparse_batch, a.sparse_heads = at[0], at[3], Bs, Hs
-    if columns:
-        la.col_ptr, la.col_idx = at[1], at[4]
-        a.sparse_col_ptr, a.sparse_col_idx = at[1], at[4]
+    rows, cols = Bs * Hs * nrb, Bs * Hs * ((nkt + 1) // 2)
     current = torch.cuda.current_stream()
-    st = load_library().parallax_block_lists(ctypes.byref(la), current.cuda_stream)
-    if st != PLX_OK:
-        raise ParallaxError(st, "parallax_block_lists")
+    col_ptr = col_idx = 0
+    if rows * nkt > _MAX_LIST_CELLS or rows + cols > _MAX_LIST_LINES:
+        held = list(block_mask_lists(m)[:2])
+        if columns:
+            held += block_mask_column_lists(m)
+        row_ptr, tile_idx, col_ptr, col_idx = ([t.data_ptr() for t in held] + [0, 0])[:4]
+    else:
+        m = m.contiguous()
+        if not columns:
+            cols = 0
+        # [row_ptr | col_ptr | counts | tile_idx | col_idx]
+        sizes = [rows + 1, cols + 1 if columns else 0, rows + cols, rows * nkt, cols * nrb]
+        held = [torch.empty(sum(sizes), dtype=torch.int32, device=device)]
+        row_ptr, col_ptr, counts, tile_idx, col_idx = (held[0].data_ptr() + 4 * sum(sizes[:i]) for i in range(5))
+        la = plx_block_list_args()
+        la.mask, la.lists, la.n_row_blocks, la.n_tiles = m.data_ptr(), Bs * Hs, nrb, nkt
+        la.row_ptr, la.counts, la.tile_idx = row_ptr, counts, tile_idx
+        if columns:
+            la.col_ptr, la.col_idx = col_ptr, col_idx
+        st = load_library().parallax_block_lists(ctypes.byref(la), current.cuda_stream)
+        if st != PLX_OK:
+            raise ParallaxError(st, "parallax_block_lists")
+    a.sparse_row_ptr, a.sparse_tile_idx, a.sparse_batch, a.sparse_heads = row_ptr, tile_idx, Bs, Hs
+    if columns:
+        a.sparse_col_ptr, a.sparse_col_idx = col_ptr, col_idx
     other = _other_stream(stream, device)
     if other is not None:  # read there: after the lists are built, and not reused here before
-        buf.record_stream(other)
+        for t in held:
+            t.record_stream(other)
         other.wait_stream(current)
-    return buf
+    return held[0] if len(held) == 1 else held
 
 
 def parallax_prefill(q, r, k, v, scale, causal=True, use_r=True, out=None, stream=None, window=0,

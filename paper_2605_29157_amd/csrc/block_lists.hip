@@ -4,8 +4,9 @@
 // A line is a row block (entries: its listed key tiles) or a key block of two key tiles (entries:
 // 4 * row block + flags); lines are independent but for where their entries go, so one launch
 // counts and a second places: every workgroup adds up the counts in front of its lines itself
-// (reads that the L2 holds) instead of a third launch scanning them. What bounds it is the two
-// launches; the host never learns the number of entries, so nothing waits for the GPU. Built from
+// (reads that the L2 holds) instead of a third launch scanning them. With many lines (kScanLines) those
+// reads, quadratic in the number of lines, would cost more than the launch, and the scan is made. What
+// bounds it otherwise is the two launches; the host never learns the number of entries, so nothing waits for the GPU. Built from
 // tensor operations instead (a scan, a compaction whose size the host reads back, casts: 40 launches
 // and three waits per training step), the lists took 310 us of a 537 us step over 2 sequences x
 // 2048 rows, 16 heads, a quarter of the cells; the whole step now takes 220 us.
@@ -16,6 +17,11 @@ namespace plx {
 
 namespace {
 constexpr int kLinesPerGroup = 4;  // one wave each
+constexpr int kScanThreads = 1024, kScanPerThread = 4;
+// Lines of one kind from which the counts are scanned in a launch of their own. Row and key lists, us
+// for two launches / three: 4096 lines in all 13.9 / -, 8192 + 8192 lines 19.1 / 16.6 (32 row blocks a
+// list) and 23.6 / 20.8 (128), 32768 + 32768 130 / 71 (128) and 284 / 241 (512).
+constexpr int64_t kScanLines = 8192;
 
 // Entry n of a line: 0 = not listed, else 1 + the value that goes into the list.
 struct LineReader {
@@ -58,35 +64,81 @@ __global__ __launch_bounds__(64 * kLinesPerGroup) void block_list_count_kernel(B
     if (lane == 0) p.counts[line] = count;
 }
 
+// Many lines: workgroup 0 turns the counts of the row lines into row_ptr, workgroup 1 those of the key
+// lines into col_ptr.
+__global__ __launch_bounds__(kScanThreads) void block_list_scan_kernel(BlockListParams p) {
+    __shared__ int wave_sum[kScanThreads / 64];
+    const int64_t rows = (int64_t)p.lists * p.n_row_blocks;
+    const int64_t n = blockIdx.x == 0 ? rows : line_total(p) - rows;
+    const int32_t *counts = p.counts + (blockIdx.x == 0 ? 0 : rows);
+    int32_t *ptr = blockIdx.x == 0 ? p.row_ptr : p.col_ptr;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    int before = 0;  // entries in front of this round's lines
+    for (int64_t first = 0; first < n; first += kScanThreads * kScanPerThread) {
+        const int64_t at = first + threadIdx.x * kScanPerThread;
+        int c[kScanPerThread], mine = 0;
+#pragma unroll
+        for (int i = 0; i < kScanPerThread; ++i) c[i] = at + i < n ? counts[at + i] : 0, mine += c[i];
+        int upto = mine;  // inclusive over the wave
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int x = __shfl_up(upto, off, 64);
+            if (lane >= off) upto += x;
+        }
+        __syncthreads();  // (the last round's sums have been read)
+        if (lane == 63) wave_sum[w] = upto;
+        __syncthreads();
+        int start = before + upto - mine, all = 0;
+#pragma unroll
+        for (int i = 0; i < kScanThreads / 64; ++i) {
+            if (i < w) start += wave_sum[i];
+            all += wave_sum[i];
+        }
+#pragma unroll
+        for (int i = 0; i < kScanPerThread; ++i) {
+            if (at + i < n) ptr[at + i] = start;
+            start += c[i];
+        }
+        before += all;
+    }
+    if (threadIdx.x == 0) ptr[n] = before;
+}
+
+template <bool SCANNED>
 __global__ __launch_bounds__(64 * kLinesPerGroup) void block_list_place_kernel(BlockListParams p) {
     __shared__ int part[kLinesPerGroup];
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int64_t total = line_total(p), rows = (int64_t)p.lists * p.n_row_blocks;
     const int64_t line0 = (int64_t)blockIdx.x * kLinesPerGroup, line = line0 + w;
-    // entries in front of the workgroup's first line, of its kind (row lines and key lines are separate
-    // lists; a workgroup may hold the last of one and the first of the other)
-    const int64_t kind0 = line0 < rows ? 0 : rows;
-    int before = 0;
-    for (int64_t i = kind0 + threadIdx.x; i < line0; i += 64 * kLinesPerGroup) before += p.counts[i];
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) before += __shfl_xor(before, off, 64);
-    if (lane == 0) part[w] = before;
-    __syncthreads();
-    if (line >= total) return;
     const bool row_line = line < rows;
-    int at = 0;
-    if (row_line == (line0 < rows))
-        for (int i = 0; i < kLinesPerGroup; ++i) at += part[i];
-    for (int64_t i = row_line ? line0 : (line0 > rows ? line0 : rows); i < line; ++i) at += p.counts[i];
-
     int32_t *ptr = row_line ? p.row_ptr : p.col_ptr;
     int32_t *idx = row_line ? p.tile_idx : p.col_idx;
     const int64_t e = row_line ? line : line - rows;
-    const LineReader in(p, line);
-    if (lane == 0) {
-        ptr[e] = at;
-        if (line + 1 == (row_line ? rows : total)) ptr[e + 1] = at + p.counts[line];
+    int at = 0;
+    if constexpr (SCANNED) {
+        if (line >= total) return;
+        at = ptr[e];
+    } else {
+        // entries in front of the workgroup's first line, of its kind (row lines and key lines are separate
+        // lists; a workgroup may hold the last of one and the first of the other)
+        const int64_t kind0 = line0 < rows ? 0 : rows;
+        int before = 0;
+        for (int64_t i = kind0 + threadIdx.x; i < line0; i += 64 * kLinesPerGroup) before += p.counts[i];
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) before += __shfl_xor(before, off, 64);
+        if (lane == 0) part[w] = before;
+        __syncthreads();
+        if (line >= total) return;
+        if (row_line == (line0 < rows))
+            for (int i = 0; i < kLinesPerGroup; ++i) at += part[i];
+        for (int64_t i = row_line ? line0 : (line0 > rows ? line0 : rows); i < line; ++i) at += p.counts[i];
+        if (lane == 0) {
+            ptr[e] = at;
+            if (line + 1 == (row_line ? rows : total)) ptr[e + 1] = at + p.counts[line];
+        }
     }
+
+    const LineReader in(p, line);
     for (int i = lane; i - lane < in.n; i += 64) {
         const int x = in.entry(i);
         const unsigned long long hits = __ballot(x != 0);
@@ -103,7 +155,14 @@ hipError_t launch_block_lists(const BlockListParams &p, hipStream_t stream) {
     const dim3 grid((unsigned)groups), block(64 * kLinesPerGroup);
     hipLaunchKernelGGL(block_list_count_kernel, grid, block, 0, stream, p);
     if (hipError_t err = hipGetLastError()) return err;
-    hipLaunchKernelGGL(block_list_place_kernel, grid, block, 0, stream, p);
+    const int64_t row_lines = (int64_t)p.lists * p.n_row_blocks;
+    if (row_lines < kScanLines && lines - row_lines < kScanLines) {
+        hipLaunchKernelGGL(block_list_place_kernel<false>, grid, block, 0, stream, p);
+        return hipGetLastError();
+    }
+    hipLaunchKernelGGL(block_list_scan_kernel, dim3(p.col_ptr ? 2 : 1), dim3(kScanThreads), 0, stream, p);
+    if (hipError_t err = hipGetLastError()) return err;
+    hipLaunchKernelGGL(block_list_place_kernel<true>, grid, block, 0, stream, p);
     return hipGetLastError();
 }
 

@@ -294,6 +294,13 @@ def test_lists_built_on_the_device(plx, lists, nrb, nkt, density):
     assert torch.equal(buf[:len(want[0])], want[0]) and torch.equal(buf[first:first + int(want[0][-1])], want[1][:int(want[0][-1])])
 
 
+# (from 8192 lines of a kind on the counts are scanned, 4096 to a round)
+@pytest.mark.parametrize("lists,nrb,nkt", [((8191, 1), 1, 1), ((8192, 1), 1, 1), ((2, 4097), 1, 3), ((300, 1), 30, 3),
+                                           ((1000, 3), 2, 6), ((9, 1000), 1, 40)])
+def test_lists_of_many_lines(plx, lists, nrb, nkt):
+    test_lists_built_on_the_device(plx, lists, nrb, nkt, 0.4)
+
+
 def test_masked_call_on_another_stream(plx, synth):
     """The lists are built on the current stream and walked on the caller's."""
     y = synth.prefill_inputs(1, 4, 2, 700, 128, seed=6611, device=DEV)

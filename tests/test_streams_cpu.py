@@ -138,3 +138,21 @@ def test_split_count_of_a_call(world):
         a = world.plx.decode_args(q, q, k, k, q, 0.1, **kw)
         a.o = None
         assert lib.parallax_decode_call_splits(ctypes.byref(a)) == want
+
+
+@pytest.mark.parametrize("columns", [False, True])
+def test_masks_that_the_list_kernels_do_not_take(world, monkeypatch, columns):
+    """Beyond the lines that parallax_block_lists accepts, the lists come from tensor operations."""
+    monkeypatch.setattr(world.plx, "_MAX_LIST_LINES", 27)  # (7 lines per list)
+    mask = (torch.arange(2 * 4 * 5) % 3 == 0).reshape(2, 1, 4, 5)
+    a = (world.plx.plx_prefill_bwd_args if columns else world.plx.plx_prefill_args)()
+    world.plx.attach_block_lists(a, mask[:1], "cpu", columns=columns)
+    assert [name for name, _ in world.launches] == ["parallax_block_lists"]
+    held = world.plx.attach_block_lists(a, mask.repeat(2, 1, 1, 1), "cpu", world.streams[1], columns)
+    assert len(world.launches) == 1 and (a.sparse_batch, a.sparse_heads) == (4, 1)
+    want = world.plx.block_mask_lists(mask.repeat(2, 1, 1, 1))[:2]
+    want += world.plx.block_mask_column_lists(mask.repeat(2, 1, 1, 1)) if columns else ()
+    assert len(held) == len(want) and all(torch.equal(x, y) for x, y in zip(held, want))
+    assert [t.data_ptr() for t in held[:2]] == [a.sparse_row_ptr, a.sparse_tile_idx]
+    if columns:
+        assert [t.data_ptr() for t in held[2:]] == [a.sparse_col_ptr, a.sparse_col_idx]
