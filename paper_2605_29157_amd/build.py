@@ -65,25 +65,42 @@ def _check_pipelined_assembly(src: str, full: bool) -> None:
         raise RuntimeError("hazard in %s:\n  %s" % (asm, "\n  ".join(bad[:20])))
 
 
-def _check_decode_assembly() -> None:
-    """The bf16 decode kernel sits at the 256-register limit of two workgroups per compute
-    unit; one spilled register costs it 10 %. Fail the build if any decode kernel spills."""
+def _spills(src: str, kernel: str) -> dict[str, int]:
+    """Spilled vector registers of the kernels of a file whose name holds `kernel`."""
     import re
-    with open(_device_asm_path("decode_bf16.hip")) as f:
+    with open(_device_asm_path(src)) as f:
         text = f.read()
     spills = {}
     for block in text.split("  - .agpr_count")[1:]:
         name = re.search(r"\.name:\s+(\S+)", block).group(1)
-        if "decode_bf16_kernel" in name:
+        if kernel in name:
             spills[name] = int(re.search(r"\.vgpr_spill_count:\s+(\d+)", block).group(1))
+    if not spills:
+        raise RuntimeError("%s: no %s kernel found" % (src, kernel))
+    return spills
+
+
+def _check_decode_assembly() -> None:
+    """The bf16 decode kernel sits at the 256-register limit of two workgroups per compute
+    unit; one spilled register costs it 10 %. Fail the build if any decode kernel spills."""
     # (the instantiations that normalise and rotate q, rho first -- last template flag set -- may
     # park a few registers around that prologue: the row-by-row one does, 5 of them; with 50 and more
     # spilled, as a first form of that prologue had, the reloads queue up behind the tile loads and the
     # step takes half as long again)
     prep = "Lb1EEEvNS_12DecodeParamsE"
-    bad = {n: c for n, c in spills.items() if c > (16 if n.endswith(prep) else 0)}
-    if not spills or bad:
+    bad = {n: c for n, c in _spills("decode_bf16.hip", "decode_bf16_kernel").items() if c > (16 if n.endswith(prep) else 0)}
+    if bad:
         raise RuntimeError("decode_bf16.hip: register spills in a decode kernel (%s)" % bad)
+
+
+def _check_f32_assembly() -> None:
+    """The fp32 kernels hold their accumulators in registers at every head dimension; with 150 - 290
+    spilled, calls at d = 256 took twice as long. Fail the build if one spills, but for the dK / dV
+    pass at d = 256: three row blocks, one of them turned round, and two accumulators are 450
+    registers, and it parks 46 (ten stores in a loop of 448 matrix instructions)."""
+    bad = {n: c for n, c in _spills("generic_f32.hip", "f32_").items() if c > (48 if "cols_kernelILi256" in n else 0)}
+    if bad:
+        raise RuntimeError("generic_f32.hip: register spills in an fp32 kernel (%s)" % bad)
 
 
 def build_library(extra_flags: list[str] | None = None, verbose: bool = True) -> str:
@@ -97,6 +114,7 @@ def build_library(extra_flags: list[str] | None = None, verbose: bool = True) ->
     _check_pipelined_assembly("decode_mla_bf16.hip", False)
     _check_pipelined_assembly("decode_mla_wide_bf16.hip", False)
     _check_decode_assembly()
+    _check_f32_assembly()
     tmp = LIB_PATH + ".tmp%d" % os.getpid()
     cmd = [_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs]
     res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)

@@ -19,14 +19,20 @@
 //   Where a tensor is needed in both orders (K in the dQ / dR pass; Q, R, dO in the dK / dV pass)
 //   the wave turns it round in a 16-row LDS tile of its own.
 // What bounds it: the matrix pipe, at 64 flop per clock and SIMD (157 TFLOP/s nominal on the chip):
-// a 16-key block costs 4 * DP matrix instructions of 32 clocks against 2 * 16 * DP * 4 bytes of
-// loads, 16 bytes per clock and compute unit. One row, one key at a time on the vector ALU (one
-// workgroup per row, the kernels these replaced), the step of 8 sequences x 8 heads x 512 rows,
-// d = 64, forward and backward, took 7800 us, 6286 of them in dK / dV; these take 190 us = 85
-// TFLOP/s (206 with the row pointers formed per lane, padding tests where d = 64 needs none, and the
-// two sums merged one after the other). At 4 x 8 heads x 2048 rows the forward reaches 95 TFLOP/s.
+// a 16-key block costs DP matrix instructions of 32 clocks (two score products of DP / 4, two output
+// products of DP / 4) against 2 * 16 * DP * 4 bytes of loads, 16 bytes per clock and compute unit. One row, one
+// key at a time on the vector ALU (one workgroup per row, the kernels these replaced), the step of 8
+// sequences x 8 heads x 512 rows, d = 64, forward and backward, took 7800 us, 6286 of them in
+// dK / dV; these take 187 us = 86 TFLOP/s (206 with the row pointers formed per lane, padding tests
+// where d = 64 needs none, and the two sums merged one after the other; 191 with the rare path of
+// f32_take_out_not_finite as a loop). At 4 x 8 heads x 2048 rows the forward reaches 95 TFLOP/s.
+// 2 x 8 heads x 500 rows, forward / backward: d = 128 38 / 95 us (273 / 3440 before), d = 256 68 / 194
+// (394 / 7100), d = 132 62 / 159 (304 / 3690). Tiles padded beyond d skip the matrix instructions of the
+// padding. The one call that one workgroup per row served better: d > 128 over 65 to about 130 keys in a
+// single split, two rounds of a wave where a column holds two heads (d = 256, 100 keys: 17.4 -> 19.3 us).
 // Tried and slower: a wave alone with its columns (no merge; 8 x 8 x 512: 64 -> 82 us forward), four
-// waves per SIMD for d = 64 (spills; 62 -> 67, dK / dV 82 -> 109).
+// waves per SIMD for d = 64 (spills; 62 -> 67, dK / dV 82 -> 109); no gain: all four waves adding up and
+// finishing a quarter of the dimensions each at d = 256.
 // A decode step over 4 sequences x 2048 keys, 8 key heads, d = 64: 320 -> 16 us (half of that by
 // splitting the keys over workgroups).
 #include "plx_device.h"
@@ -65,16 +71,17 @@ struct F32Rows {
     float x[16][DP + 4];
 };
 
-// One 16 x 16 score block: acc += A (lane (c, g): chunks 4 j + g of row c) x rows. (The offset of the
-// lane is made opaque: seeing that the operand never changes, the compiler would otherwise keep all
-// of it in registers around the loop, and the registers decide how many waves a SIMD holds.)
+// One 16 x 16 score block: acc += A (lane (c, g): chunks 4 j + g of row c) x rows, up to dimension d. (The
+// offset of the lane is made opaque: seeing that the operand never changes, the compiler would otherwise
+// keep all of it in registers around the loop, and the registers decide how many waves a SIMD holds.)
 template <int DP>
-__device__ __forceinline__ f32x4 f32_scores(const f32x4 (&a)[DP / 16], const F32Rows<DP> &rows, int c, int g) {
+__device__ __forceinline__ f32x4 f32_scores(const f32x4 (&a)[DP / 16], const F32Rows<DP> &rows, int d, int c, int g) {
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     int at = c * (DP + 4) + 4 * g;
     asm volatile("" : "+v"(at));
 #pragma unroll
     for (int j = 0; j < DP / 16; ++j) {
+        if (16 * j >= d) break;
         const f32x4 b = *(const f32x4 *)(&rows.x[0][0] + at + 16 * j);
 #pragma unroll
         for (int i = 0; i < 4; ++i) acc = mfma_f32(a[j][i], b[i], acc);
@@ -86,13 +93,15 @@ __device__ __forceinline__ f32x4 f32_scores(const f32x4 (&a)[DP / 16], const F32
 // weight of key 4 g + r for column c. In accumulator register rr of acc[4 m + i] lane (c, g) then
 // holds dimension 64 m + 4 (4 g + rr) + i of column c.
 template <int DP>
-__device__ __forceinline__ void f32_outputs(const f32x4 (&a)[4][DP / 64], const f32x4 &p, f32x4 (&acc)[DP / 16]) {
+__device__ __forceinline__ void f32_outputs(const f32x4 (&a)[4][DP / 64], const f32x4 &p, int d, f32x4 (&acc)[DP / 16]) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
+    for (int m = 0; m < DP / 64; ++m) {
+        if (64 * m >= d) break;
 #pragma unroll
-        for (int m = 0; m < DP / 64; ++m)
+        for (int r = 0; r < 4; ++r)
 #pragma unroll
             for (int i = 0; i < 4; ++i) acc[4 * m + i] = mfma_f32(a[r][m][i], p[r], acc[4 * m + i]);
+    }
 }
 
 // A key a column does not see must not reach it, also where the key's row holds infinities or NaN
@@ -108,24 +117,39 @@ __device__ __forceinline__ bool f32_not_finite(const f32x4 (&a)[4][DP / 64]) {
             for (int i = 0; i < 4; ++i) chk = fmaf(a[r][m][i], 0.f, chk);
     return __any(chk != 0.f);
 }
-// ... and where a value is not finite the keys go in one by one, each to the columns that see it
-// (bit r of `seen`: key 4 g + r).
-template <int DP>
-__device__ __forceinline__ void f32_outputs_one_by_one(const f32x4 (&a)[4][DP / 64], const f32x4 &p, unsigned seen,
-                                                       int c, int g, f32x4 (&acc)[DP / 16]) {
-#pragma unroll 1
-    for (int kg = 0; kg < 4; ++kg) {
-        const unsigned seen_g = __shfl((int)seen, 16 * kg + c, 64);
+// ... and where a value is not finite it is taken out of the operand (a zero), after what it does to the
+// columns that see its key (bit r of `seen`: key 4 g + r) has been added: sums of products of finite
+// numbers that overflow where +inf (up) or -inf (down) reaches a column, and both where a NaN does or a
+// zero weight meets an infinity. (The common path pays for this one in registers: with the keys added one
+// by one in a loop it spilled 150 to 290 of them at d = 256 and up to 35 at d = 128.)
+template <int DP, int SETS>
+__device__ __forceinline__ void f32_take_out_not_finite(f32x4 (&a)[4][DP / 64], const f32x4 *const (&p)[SETS],
+                                                        unsigned seen, f32x4 (*const (&acc)[SETS])[DP / 16]) {
+    constexpr float kBig = 3.0e38f, kInf = -kNegInf;
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
+    for (int n = 0; n < DP / 16; ++n) {
 #pragma unroll
-            for (int n = 0; n < DP / 16; ++n) {
-                const f32x4 one = mfma_f32(g == kg ? a[r][n >> 2][n & 3] : 0.f, g == kg ? p[r] : 0.f,
-                                           f32x4{0.f, 0.f, 0.f, 0.f});
+        for (int i = 0; i < SETS; ++i)
 #pragma unroll
-                for (int rr = 0; rr < 4; ++rr) acc[n][rr] += (seen_g >> r) & 1 ? one[rr] : 0.f;
-                __builtin_amdgcn_sched_barrier(0);  // (rare path: keep its registers few)
+            for (int sign = 1; sign >= -1; sign -= 2) {  // what goes up, then what goes down
+                f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+                asm volatile("" : "+v"(seen));  // (few registers rather than few instructions)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float x = a[r][n >> 2][n & 3], w = (float)sign * (*p[i])[r];
+                    const bool sees = (seen >> r) & 1;
+                    sum = mfma_f32(!(x < kInf) ? kBig : 0.f, sees && !(w < 0.f) ? kBig : 0.f, sum);
+                    sum = mfma_f32(!(x > kNegInf) ? kBig : 0.f, sees && !(w > 0.f) ? kBig : 0.f, sum);
+                }
+                (*acc[i])[n] += (float)sign * sum;
+                __builtin_amdgcn_sched_barrier(0);
             }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float x = a[r][n >> 2][n & 3];
+            a[r][n >> 2][n & 3] = fabsf(x) < kInf ? x : 0.f;
+        }
+        __builtin_amdgcn_sched_barrier(0);
     }
 }
 
@@ -155,20 +179,22 @@ __device__ __forceinline__ void f32_turn(const f32x4 (&in)[DP / 16], F32Rows<DP>
         for (int m = 0; m < DP / 64; ++m) out[r][m] = *(const f32x4 *)&tile.x[4 * g + r][64 * m + 4 * c];
 }
 
-// Adds up two sets of N accumulators per lane over the four waves (already on one scale): waves 2, 3
-// hand theirs to waves 0, 1, then wave 1 to wave 0, which holds the result. buf: [2][2 N * 64] f32x4.
+// Adds up two sets of N accumulators per lane over the first `live` waves (already on one scale; the
+// others hold zeros): waves 2, 3 hand theirs to waves 0, 1, then wave 1 to wave 0, which holds the
+// result. buf: [2][2 N * 64] f32x4.
 template <int N>
-__device__ __forceinline__ void f32_sum_waves(f32x4 (&a)[N], f32x4 (&b)[N], f32x4 *buf, int w, int lane) {
+__device__ __forceinline__ void f32_sum_waves(f32x4 (&a)[N], f32x4 (&b)[N], f32x4 *buf, int w, int lane, int live) {
 #pragma unroll
     for (int step = 2; step > 0; step >>= 1) {
+        if (live <= step) continue;  // (uniform over the workgroup)
         __syncthreads();
-        if (w >= step && w < 2 * step) {
+        if (w >= step && w < min(2 * step, live)) {
             f32x4 *to = buf + (w - step) * 2 * N * 64 + lane;
 #pragma unroll
             for (int n = 0; n < N; ++n) to[n * 64] = a[n], to[(N + n) * 64] = b[n];
         }
         __syncthreads();
-        if (w < step) {
+        if (w < step && w + step < live) {
             const f32x4 *from = buf + w * 2 * N * 64 + lane;
 #pragma unroll
             for (int n = 0; n < N; ++n) a[n] += from[n * 64], b[n] += from[(N + n) * 64];
@@ -285,9 +311,9 @@ __global__ __launch_bounds__(kF32Threads, DP <= 128 ? 2 : 1) void f32_forward_ke
     __syncthreads();
     for (; kblk < hi; kblk += kF32Waves) {
         const int key0 = 16 * kblk, next = kblk + kF32Waves;
-        f32x4 s1 = f32_scores<DP>(kf, lds.rows[0], c, g);
+        f32x4 s1 = f32_scores<DP>(kf, lds.rows[0], d, c, g);
         f32x4 s2 = {0.f, 0.f, 0.f, 0.f};
-        if constexpr (USE_R) s2 = f32_scores<DP>(kf, lds.rows[1], c, g);
+        if constexpr (USE_R) s2 = f32_scores<DP>(kf, lds.rows[1], d, c, g);
         // the next block's K rows travel under the exponentials and the V product, its V rows (below)
         // under its scores: each register set is refilled as soon as it has been used
         if (next < hi) load_k(next);
@@ -324,13 +350,14 @@ __global__ __launch_bounds__(kF32Threads, DP <= 128 ? 2 : 1) void f32_forward_ke
 #pragma unroll
             for (int n = 0; n < NA; ++n) o1[n] *= alpha, o2[n] *= alpha;
         }
-        if (!whole && f32_not_finite<DP>(vf)) {
-            f32_outputs_one_by_one<DP>(vf, p1, seen, c, g, o1);
-            if constexpr (USE_R) f32_outputs_one_by_one<DP>(vf, p2, seen, c, g, o2);
-        } else {
-            f32_outputs<DP>(vf, p1, o1);
-            if constexpr (USE_R) f32_outputs<DP>(vf, p2, o2);
+        if (__builtin_expect(!whole && f32_not_finite<DP>(vf), 0)) {
+            if constexpr (USE_R)
+                f32_take_out_not_finite<DP, 2>(vf, {&p1, &p2}, seen, {&o1, &o2});
+            else
+                f32_take_out_not_finite<DP, 1>(vf, {&p1}, seen, {&o1});
         }
+        f32_outputs<DP>(vf, p1, d, o1);
+        if constexpr (USE_R) f32_outputs<DP>(vf, p2, d, o2);
         if (next < hi) load_v(next);
     }
 
@@ -350,7 +377,7 @@ __global__ __launch_bounds__(kF32Threads, DP <= 128 ? 2 : 1) void f32_forward_ke
     const float wt = m_run == kNegInf ? 0.f : fast_exp2(m_run - m_all);
 #pragma unroll
     for (int n = 0; n < NA; ++n) o1[n] *= wt, o2[n] *= wt;
-    f32_sum_waves<NA>(o1, o2, lds.merge, w, lane);
+    f32_sum_waves<NA>(o1, o2, lds.merge, w, lane, hi - lo);
     if (w != 0 || 16 * blk + c >= p.n_cols) return;
 
     // lane (c, g): dimensions 64 m + 16 g + 4 rr .. + 3 of column c, float4 by float4
@@ -464,6 +491,8 @@ static hipError_t launch_forward(F32Forward &g, hipStream_t stream) {
             hipLaunchKernelGGL((f32_forward_kernel<128, P, R, true>), grid, block, 0, stream, g);
         else if (g.d < 128)
             hipLaunchKernelGGL((f32_forward_kernel<128, P, R, false>), grid, block, 0, stream, g);
+        else if (g.d == 256)
+            hipLaunchKernelGGL((f32_forward_kernel<256, P, R, true>), grid, block, 0, stream, g);
         else
             hipLaunchKernelGGL((f32_forward_kernel<256, P, R, false>), grid, block, 0, stream, g);
     };
@@ -591,10 +620,10 @@ __global__ __launch_bounds__(kF32Threads, DP <= 128 ? 2 : 1) void f32_bwd_rows_k
     const f32x4 sc = scalars[c];
     for (; kblk < hi; kblk += kF32Waves) {
         const int key0 = 16 * kblk, next = kblk + kF32Waves;
-        const f32x4 a = f32_scores<DP>(vf, lds.rows[2], c, g);
+        const f32x4 a = f32_scores<DP>(vf, lds.rows[2], d, c, g);
         if (next < hi) load(vf, v, next);
-        const f32x4 s1 = f32_scores<DP>(kf, lds.rows[0], c, g);
-        const f32x4 s2 = f32_scores<DP>(kf, lds.rows[1], c, g);
+        const f32x4 s1 = f32_scores<DP>(kf, lds.rows[0], d, c, g);
+        const f32x4 s2 = f32_scores<DP>(kf, lds.rows[1], d, c, g);
         f32x4 kt[4][DP / 64];
         f32_turn<DP>(kf, lds.tile[w], kt, c, g);
         if (next < hi) load(kf, k, next);
@@ -612,15 +641,11 @@ __global__ __launch_bounds__(kF32Threads, DP <= 128 ? 2 : 1) void f32_bwd_rows_k
                 if (!(key >= my_lo && key < my_end)) g1[r] = g2[r] = 0.f, seen &= ~(1u << r);
             }
         }
-        if (!whole && f32_not_finite<DP>(kt)) {
-            f32_outputs_one_by_one<DP>(kt, g1, seen, c, g, dq);
-            f32_outputs_one_by_one<DP>(kt, g2, seen, c, g, dr);
-        } else {
-            f32_outputs<DP>(kt, g1, dq);
-            f32_outputs<DP>(kt, g2, dr);
-        }
+        if (__builtin_expect(!whole && f32_not_finite<DP>(kt), 0)) f32_take_out_not_finite<DP, 2>(kt, {&g1, &g2}, seen, {&dq, &dr});
+        f32_outputs<DP>(kt, g1, d, dq);
+        f32_outputs<DP>(kt, g2, d, dr);
     }
-    f32_sum_waves<NA>(dq, dr, lds.merge, w, lane);
+    f32_sum_waves<NA>(dq, dr, lds.merge, w, lane, hi - lo);
     if (w != 0 || i0 + c >= p.T) return;
     const int64_t e0 = (head + i0 + c) * d;
 #pragma unroll
@@ -700,9 +725,9 @@ __global__ __launch_bounds__(kF32Threads, DP <= 128 ? 2 : 1) void f32_bwd_cols_k
         f32x4 sc[4];  // (lse, ubar, tau, beta) of rows i0 + 4 g + r
 #pragma unroll
         for (int r = 0; r < 4; ++r) sc[r] = ((const f32x4 *)p.row_cache)[head + min(i0 + 4 * g + r, end - 1)];
-        const f32x4 s1 = f32_scores<DP>(xq, lds.rows[0], c, g);
-        const f32x4 s2 = f32_scores<DP>(xr, lds.rows[0], c, g);
-        const f32x4 a = f32_scores<DP>(xg, lds.rows[1], c, g);
+        const f32x4 s1 = f32_scores<DP>(xq, lds.rows[0], d, c, g);
+        const f32x4 s2 = f32_scores<DP>(xr, lds.rows[0], d, c, g);
+        const f32x4 a = f32_scores<DP>(xg, lds.rows[1], d, c, g);
         const bool whole = i0 >= all_lo && i0 + 16 <= all_end;
         unsigned seen = 15u;
         f32x4 wt, g1, g2;
@@ -722,16 +747,14 @@ __global__ __launch_bounds__(kF32Threads, DP <= 128 ? 2 : 1) void f32_bwd_cols_k
             f32x4 xt[4][DP / 64];
             f32_turn<DP>(x, lds.tile[w], xt, c, g);
             if (next < n_items) load(x, base, next);
-            if (!whole && f32_not_finite<DP>(xt))
-                f32_outputs_one_by_one<DP>(xt, weights, seen, c, g, acc);
-            else
-                f32_outputs<DP>(xt, weights, acc);
+            if (__builtin_expect(!whole && f32_not_finite<DP>(xt), 0)) f32_take_out_not_finite<DP, 1>(xt, {&weights}, seen, {&acc});
+            f32_outputs<DP>(xt, weights, d, acc);
         };
         add(xq, p.q, g1, dk);
         add(xr, p.r, g2, dk);
         add(xg, p.d_o, wt, dv);
     }
-    f32_sum_waves<NA>(dk, dv, lds.merge, w, lane);
+    f32_sum_waves<NA>(dk, dv, lds.merge, w, lane, n_items);
     if (w != 0 || j0 + c >= p.Tk) return;
     const int64_t e0 = (khead + j0 + c) * d;
 #pragma unroll
@@ -759,6 +782,7 @@ hipError_t launch_prefill_bwd_f32(const PrefillBwdParams &p, hipStream_t stream)
            : p.d < 64   ? launch_backward<64, false>(p, stream)
            : p.d == 128 ? launch_backward<128, true>(p, stream)
            : p.d < 128  ? launch_backward<128, false>(p, stream)
+           : p.d == 256 ? launch_backward<256, true>(p, stream)
                         : launch_backward<256, false>(p, stream);
 }
 

@@ -101,3 +101,32 @@ def test_a_row_ignores_what_it_does_not_see(plx, synth, T, d, window, bad):
     blind = [j for j in range(T) if j > at or (window and j <= at - window)]
     for a, b in zip(got[3:], clean[3:]):  # dk, dv
         np.testing.assert_allclose(host(a)[:, :, blind], host(b)[:, :, blind], rtol=1e-5, atol=1e-5)
+
+
+@pytest.mark.parametrize("bad", [math.nan, math.inf, -math.inf])
+@pytest.mark.parametrize("T,d", [(50, 64), (37, 100), (37, 128), (40, 200), (37, 256)])
+@pytest.mark.parametrize("use_r", [True, False])
+@pytest.mark.parametrize("low", [False, True])
+def test_a_row_takes_what_it_sees(plx, synth, T, d, use_r, bad, low):
+    """A value that is not finite, in a block of keys that some rows see only in part: it is in the
+    outputs of the rows that see the key, in its own dimension and no other, also where the weight of
+    the key is zero (low: its score lies hundreds of binades down), and in no other row."""
+    y = synth.prefill_inputs(1, 2, 1, T, d, seed=79, dtype=torch.float32, device=DEV)
+    at, dim = T // 2 + 1, 3
+    if low:
+        y["q"] = y["q"].abs() + 1.0
+        y["k"][:, :, at] = -100.0
+        y["r"] = 0.0 * y["r"]  # (keeps the key's finite dimensions comparable)
+    args = (y["q"], y["r"] if use_r else None, y["k"])
+    clean = plx.parallax_prefill(*args, y["v"], y["scale"], use_r=use_r)
+    v = y["v"].clone()
+    v[:, :, at, dim] = bad
+    got = plx.parallax_prefill(*args, v, y["scale"], use_r=use_r)
+    assert not torch.isfinite(got[:, :, at:, dim]).any()
+    if math.isnan(bad) or low:
+        assert torch.isnan(got[:, :, at:, dim]).all()
+    elif not use_r:
+        assert (got[:, :, at:, dim] == bad).all()
+    rest = torch.ones_like(got, dtype=torch.bool)
+    rest[:, :, at:, dim] = False
+    assert torch.equal(got[rest], clean[rest])
