@@ -463,3 +463,56 @@ def test_packed_arguments_land_in_their_fields(binding):
     for args, layout in binding._PACK.items():
         n = len(list(leaves(args())))
         assert list(leaves(args.from_buffer_copy(layout.pack(*range(1, n + 1))))) == list(range(1, n + 1)), args
+
+
+def _prefill_split_by_search(B, Hq, T, Tk, d, causal, cus=256):
+    """Workspace of the split with the smallest estimate over all range counts, every row block of every
+    count estimated: units of one 64-key tile of a workgroup."""
+    rows = 64 * (4 if d == 64 else 2)
+    nrb, heads = -(-T // rows), B * Hq
+    if heads * nrb >= 2 * cus or nrb > 64:
+        return 0
+    blocks = []  # (key tiles seen, records of 32 rows)
+    for i in range(nrb):
+        keys = min(Tk, (i + 1) * rows + Tk - T) if causal else Tk
+        blocks.append((-(-keys // 64), -(-min(rows, T - i * rows) // 32)))
+    longest = max(t for t, _ in blocks)
+
+    def estimate(tiles):
+        n = records = work = widest = 0
+        for t, subs in blocks:
+            per = -(-t // -(-t // tiles))
+            count = -(-t // per)
+            n, work, widest = n + count, work + count * (4 + per), max(widest, 4 + per)
+            records += count * subs if count > 1 else 0
+        cost = max(widest, heads * work / cus + (0.5 * widest if heads * n > cus else 0))
+        return cost + (4 + heads * records * (2 * 32 * (2 * d + 5) * 4 / 4.2e6) if records else 0), n
+
+    best, items = 0.9 * estimate(longest)[0], 0
+    for ranges in range(2, 33):
+        tiles = -(-longest // ranges)
+        if tiles >= 2 and estimate(tiles)[0] < best:
+            best, items = estimate(tiles)
+    return heads * items * (rows // 32) * (64 * d + 160) * 4
+
+
+def test_prefill_split_is_the_cheapest_of_all_range_counts(binding):
+    """The plan leaves out what cannot win; it has to find what the whole search finds."""
+    import ctypes
+    import random
+
+    rng, lib, n_split = random.Random(5), binding.load_library(), 0
+    for _ in range(400):
+        B, Hq, d, causal = rng.randint(1, 3), rng.choice([1, 2, 7, 8, 16, 40]), rng.choice([64, 128]), rng.random() < 0.6
+        T = rng.randint(1, rng.choice([600, 8000]))
+        Tk = T + rng.choice([0, rng.randint(0, 20000)])
+        a = binding.plx_prefill_args()
+        a.q = a.r = a.k = a.v = a.o = 1 << 20
+        a.B, a.Hq, a.Hkv, a.T, a.Tkv, a.d = B, Hq, Hq, T, Tk, d
+        a.scale, a.causal, a.use_r, a.dtype = 0.1, int(causal), 1, binding.PLX_BF16
+        for name, L in (("q", T), ("r", T), ("k", Tk), ("v", Tk), ("o", T)):
+            setattr(a, name + "_stride", (ctypes.c_int64 * 3)(Hq * L * d, L * d, d))
+        want = _prefill_split_by_search(B, Hq, T, Tk, d, causal)
+        assert lib.parallax_prefill_workspace_bytes(ctypes.byref(a)) == want, (B, Hq, T, Tk, d, causal)
+        n_split += want > 0
+    assert 100 < n_split < 300
