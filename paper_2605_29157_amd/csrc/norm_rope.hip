@@ -9,6 +9,7 @@
 // formed and reduced modulo 2 pi in double precision (pos * frequency reaches 1e5 and more, where
 // fp32 would lose the fraction), sine and cosine are taken in single precision -- once per
 // (position, pair), for all heads of all tensors.
+#include <algorithm>
 #include <cmath>
 
 #include "plx_device.h"
@@ -38,9 +39,9 @@ struct Chunk<float> {
 // A wave owns 64 / (lanes per row) consecutive positions of one sequence and walks over some of the
 // trips there, a trip being four heads of one tensor, all four in flight (the first trip's loads are
 // issued before the trigonometry).
-// With many positions a wave takes all trips: sine and cosine of a (position, pair) are then computed
-// once. With few (a decode step has one row per sequence) the trips are dealt over more waves,
-// because a wave that walks 40 heads alone is a chain of 10 dependent memory round trips.
+// A wave that walked all 40 heads of a layer alone would compute sine and cosine of a (position, pair)
+// once, but is a chain of 10 dependent memory round trips: two trips a wave are faster at every size
+// (many positions are bound by memory, 4.9 - 5.4 TB/s), one where there are few positions.
 // q, rho [1,16,777,128] and k [1,8,777,128]: 11.2 -> 7.0 us; one row each, 10.3 -> 5.2 us; [4,..,4096,128] 66.
 template <typename T>
 __global__ __launch_bounds__(256) void norm_rope_kernel(NormRopeParams p) {
@@ -139,8 +140,9 @@ __global__ __launch_bounds__(256) void norm_rope_kernel(NormRopeParams p) {
 }
 
 // (cos, sin) of pos * theta^(-2i/d), one thread per (position, pair): the same double-precision
-// angle reduction as above, so that the attention kernels that apply the rotation themselves
-// (from this table) see the values this file's kernel would have used.
+// angle reduction as above for the attention kernels that apply the rotation themselves. (The power is
+// taken for every pair here, where the kernel above multiplies on from a lane's first: the angles agree to
+// four roundings of double precision, before they are taken to single.)
 __global__ __launch_bounds__(256) void rope_table_kernel(float *table, int n_pos, int d, float theta) {
     const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int half = d / 2;
@@ -166,13 +168,13 @@ hipError_t launch_norm_rope(const NormRopeParams &p_in, bool f32, hipStream_t st
     const int elems = f32 ? 4 : 8;
     const int rows_per_wave = 64 / (p.d / elems);
     const int64_t groups = (int64_t)p.B * ((p.T + rows_per_wave - 1) / rows_per_wave);
-    // trips per wave: all of them when there are position groups enough for four waves per SIMD, else
-    // as many as leave eight waves per SIMD, down to one. Measured us, 16 / 16 / 8 heads, d = 128, for
-    // 2048, 4096, 8192, 16384 waves aimed at: 4096 positions 21.4, 20.0, 17.8, 19.4; 4444 24.8, 21.3,
-    // 19.0, 21.6; 16384 (4096 groups: one wave each 66.6, two 68.8).
+    // trips per wave: one, or two from where that leaves eight waves per SIMD. Measured us, 16 / 16 / 8 heads
+    // (10 trips), for all trips in a wave, two, one: d = 128, 16384 positions 65, 64 - 69, 69; 32768 positions
+    // 141, 125 - 128, 131 - 143; d = 64, 65536 positions 154, 126, 129; d = 128, 4096 positions 29, 16.6,
+    // 18.4; d = 64, 4096 positions 26, 13.4, 13.3. 40 / 40 / 5 heads (22 trips), 32768 positions 300, 269, 278.
     int trips = 0;
     for (int i = 0; i < p.n_tensors; ++i) trips += (p.t[i].H + kNormRopeTripHeads - 1) / kNormRopeTripHeads;
-    int64_t chunks = groups >= 4096 ? 1 : (8192 + groups - 1) / groups;
+    int64_t chunks = std::max<int64_t>((8192 + groups - 1) / groups, (trips + 1) / 2);
     if (chunks > trips) chunks = trips;
     p.trips_per_wave = (trips + (int)chunks - 1) / (int)chunks;
     p.trip_chunks = (trips + p.trips_per_wave - 1) / p.trips_per_wave;
