@@ -1363,6 +1363,11 @@ __global__ __launch_bounds__(256) void prefill_combine_kernel(PrefillParams p) {
 // serves twice as many rows): 4 to start and finish a workgroup, one workgroup per compute unit at a
 // time; what a launch with more items than units loses at its end is taken as half an item. Merging
 // costs a launch (4) and the records' bytes there and back (4.2 MB per unit, what the sweeps below show).
+// With fewer than 16 tiles to cut, the records are few and dearer than that: the split has to win with 9
+// units and 0.3 of the bytes' share (d = 64: 5 and 0.7) as well. (Over 488 splits that the first form alone
+// makes, 1 - 1000 rows over 0 - 3000 keys before them, 2 - 64 heads, 52 were slower than the whole launch, by
+// up to 18 % -- 16 rows over 616 keys, 32 heads: whole 18.3, split 21.6. With the second one
+// 8 of 432 are, by up to 4 %, and a dozen gains of up to 10 % are not taken.)
 // 0 = leave the launch whole (also when the gain would be under a tenth). Measured us against the number
 // of ranges of the longest row block, 16 heads, d = 128: 512 rows over 16384 keys whole 267, 2 160, 3 128,
 // 4 (the rule) 114, 5 160, 8 135; 1024 over 16384 whole 302, 2 (the rule) 207, 3 250, 4 226; 256 over 2000
@@ -1384,11 +1389,11 @@ static int choose_split_tiles(const PrefillParams &p, int num_cus, int *items_pe
     // records of 32 rows of a range, all row blocks of the kind together
     auto subs_of = [&](int i) { return p.causal ? (std::min(rows, p.T - (nrb - 1 - i) * rows) + 31) / 32 : (p.T + 31) / 32; };
     const int longest = tiles_of(0);
-    auto cost = [&](double widest, double n, double work, double records) {
+    auto cost = [&](double widest, double n, double work, double records, double start, double part) {
         const double t = std::max(widest, (double)heads * work / num_cus + (heads * n > num_cus ? 0.5 * widest : 0.0));
-        return records > 0 ? t + 4.0 + heads * records * (2.0 * 32 * (2 * p.d + 5) * 4.0 / 4.2e6) : t;
+        return records > 0 ? t + start + part * heads * records * (2.0 * 32 * (2 * p.d + 5) * 4.0 / 4.2e6) : t;
     };
-    auto estimate = [&](int tiles, int *items) {
+    auto estimate = [&](int tiles, int *items, double start, double part) {
         double work = 0, widest = 0;
         int64_t n = 0, records = 0;
         for (int i = 0; i < kinds; ++i) {
@@ -1398,10 +1403,11 @@ static int choose_split_tiles(const PrefillParams &p, int num_cus, int *items_pe
             n += alike * r.count, records += r.count > 1 ? r.count * subs_of(i) : 0;
         }
         *items = (int)n;
-        return cost(widest, (double)n, work, (double)records);
+        return cost(widest, (double)n, work, (double)records, start, part);
     };
     int items = 0, best = 0, last = longest, cut = 0;
-    double best_cost = 0.9 * estimate(longest, &items);
+    const double limit = 0.9 * estimate(longest, &items, 4.0, 1.0);
+    double best_cost = limit;
     int64_t all = 0, cut_tiles = 0, cut_subs = 0;  // tiles; of the row blocks with more than one range: tiles, tiles x records
     for (int i = 0; i < kinds; ++i) all += alike * tiles_of(i);
     for (int ranges = 2; ranges <= 32; ++ranges) {
@@ -1412,11 +1418,14 @@ static int choose_split_tiles(const PrefillParams &p, int num_cus, int *items_pe
         for (; cut < kinds && tiles_of(cut) > tiles; ++cut)  // (ever fewer tiles from row block to row block)
             cut_tiles += alike * tiles_of(cut), cut_subs += (int64_t)tiles_of(cut) * subs_of(cut);
         const double n = (double)cut_tiles / tiles + alike * (kinds - cut);
-        const double least = cost(4.0 + PrefillRanges(keys(0), tiles).tiles, n, all + 4.0 * n, (double)cut_subs / tiles);
+        const double least = cost(4.0 + PrefillRanges(keys(0), tiles).tiles, n, all + 4.0 * n, (double)cut_subs / tiles, 4.0, 1.0);
         if (least * (1.0 - 1e-9) >= best_cost) continue;
-        const double t = estimate(tiles, &items);
+        const double t = estimate(tiles, &items, 4.0, 1.0);
         if (t < best_cost) best_cost = t, best = tiles, *items_per_head = items;
     }
+    // Short chains: the merge of their few records is bound by its start instead of its bytes
+    if (best > 0 && longest < 16 && (p.d == 64 ? estimate(best, &items, 5.0, 0.7) : estimate(best, &items, 9.0, 0.3)) >= limit)
+        best = 0, *items_per_head = nrb;
     return best;
 }
 

@@ -478,7 +478,7 @@ def _prefill_split_by_search(B, Hq, T, Tk, d, causal, cus=256):
         blocks.append((-(-keys // 64), -(-min(rows, T - i * rows) // 32)))
     longest = max(t for t, _ in blocks)
 
-    def estimate(tiles):
+    def estimate(tiles, start=4.0, part=1.0):
         n = records = work = widest = 0
         for t, subs in blocks:
             per = -(-t // -(-t // tiles))
@@ -486,13 +486,17 @@ def _prefill_split_by_search(B, Hq, T, Tk, d, causal, cus=256):
             n, work, widest = n + count, work + count * (4 + per), max(widest, 4 + per)
             records += count * subs if count > 1 else 0
         cost = max(widest, heads * work / cus + (0.5 * widest if heads * n > cus else 0))
-        return cost + (4 + heads * records * (2 * 32 * (2 * d + 5) * 4 / 4.2e6) if records else 0), n
+        return cost + (start + part * heads * records * (2 * 32 * (2 * d + 5) * 4 / 4.2e6) if records else 0), n
 
-    best, items = 0.9 * estimate(longest)[0], 0
+    limit = 0.9 * estimate(longest)[0]
+    best, items, few = limit, 0, 0
     for ranges in range(2, 33):
         tiles = -(-longest // ranges)
         if tiles >= 2 and estimate(tiles)[0] < best:
             best, items = estimate(tiles)
+            few = estimate(tiles, *((5.0, 0.7) if d == 64 else (9.0, 0.3)))[0]  # short chains: the merge's start
+    if longest < 16 and few >= limit:
+        return 0
     return heads * items * (rows // 32) * (64 * d + 160) * 4
 
 
