@@ -84,7 +84,7 @@ def _check_decode_assembly() -> None:
     """The bf16 decode kernel sits at the 256-register limit of two workgroups per compute
     unit; one spilled register costs it 10 %. Fail the build if any decode kernel spills."""
     # (the instantiations that normalise and rotate q, rho first -- last template flag set -- may
-    # park a few registers around that prologue: the row-by-row one does, 5 of them; with 50 and more
+    # park a few registers around that prologue: the row-by-row one does, 9 of them; with 50 and more
     # spilled, as a first form of that prologue had, the reloads queue up behind the tile loads and the
     # step takes half as long again)
     prep = "Lb1EEEvNS_12DecodeParamsE"

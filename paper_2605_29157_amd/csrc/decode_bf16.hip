@@ -226,15 +226,17 @@ __global__ __launch_bounds__(256, 2) void decode_bf16_kernel(DecodeParams p) {
 
     const int ld_row = lane / CPR, ld_chunk = lane % CPR;  // this lane's place in a load
     u32x4 kst[NLD], vst[NLD];
-    const int32_t *table = p.block_table + (int64_t)b * p.table_stride;  // (paged forms only)
     // kRows: page numbers of this lane's rows, looked up one tile before the rows themselves are
-    // fetched so that the table read is off the critical path
+    // fetched so that the table read is off the critical path. A contiguous cache is a
+    // single page of unbounded size here (the launcher says so): what is read in place of a table, the first
+    // bytes of q, is clamped to page 0. (A branch over the two kinds of cache inside the tile loop, and the
+    // pages looked up apart from the rows, cost pages of 8 or 24 keys 3 - 9 % of a small step.)
+    const int32_t *table = CACHE == kRows && batch_rows ? (const int32_t *)p.q : p.block_table + (int64_t)b * p.table_stride;
     int32_t pg[NLD];
     auto lookup_pages = [&](int tk0) {
         if constexpr (CACHE == kRows)
-            if (p.block_table != nullptr)
 #pragma unroll
-                for (int i = 0; i < NLD; ++i) pg[i] = table[min(tk0 + i * KPI + ld_row, Lb - 1) / p.page_size];
+            for (int i = 0; i < NLD; ++i) pg[i] = table[min(tk0 + i * KPI + ld_row, Lb - 1) / p.page_size];
     };
     // kPagedRuns: element offsets of the first rows of this wave's next 32 tiles' halves, lane 2 * j + half
     const int last16 = (Lb - 1) & ~15;  // first key of the last half tile that exists
@@ -280,13 +282,9 @@ __global__ __launch_bounds__(256, 2) void decode_bf16_kernel(DecodeParams p) {
 #pragma unroll
             for (int i = 0; i < NLD; ++i) {
                 const int key = min(tk0 + i * KPI + ld_row, Lb - 1);
-                int64_t koff = (int64_t)key * p.ksl, voff = (int64_t)key * p.vsl;
-                if (p.block_table != nullptr) {
-                    const int64_t page = min(max(pg[i], 0), p.num_pages - 1);
-                    const int row = key % p.page_size;
-                    koff = page * p.ksb + (int64_t)row * p.ksl;
-                    voff = page * p.vsb + (int64_t)row * p.vsl;
-                }
+                const int64_t page = min(max(pg[i], 0), p.num_pages - 1);
+                const int row = key % p.page_size;
+                const int64_t koff = page * p.ksb + (int64_t)row * p.ksl, voff = page * p.vsb + (int64_t)row * p.vsl;
                 kst[i] = *(const u32x4 *)(kbase + koff + ld_chunk * 8);
                 vst[i] = *(const u32x4 *)(vbase + voff + ld_chunk * 8);
             }
@@ -295,7 +293,7 @@ __global__ __launch_bounds__(256, 2) void decode_bf16_kernel(DecodeParams p) {
     {  // (the first tiles' pages travel with the query rows, in front of everything else)
         const int tk_first = key_lo + w * kTileKeys;
         if (tk_first < key_hi) {
-            if constexpr (CACHE == kRows) lookup_pages(tk_first);
+            if constexpr (CACHE == kRows && PREP) lookup_pages(tk_first);
             if constexpr (CACHE == kPagedRuns) lookup_runs(tk_first);
         }
     }
@@ -386,6 +384,7 @@ __global__ __launch_bounds__(256, 2) void decode_bf16_kernel(DecodeParams p) {
         asm volatile("" : "+v"(tk) : "v"(qf[KSTEPS - 1][3]), "v"(rf[KSTEPS - 1][3]));
     }
     if (tk < key_hi) {
+        if constexpr (CACHE == kRows && !PREP) lookup_pages(tk);  // (here the rows below share its divisions)
         issue_loads(tk);
         if (tk + kWaves * kTileKeys < key_hi) lookup_pages(tk + kWaves * kTileKeys);
     }
@@ -647,8 +646,11 @@ static void launch_decode_variant(const DecodeParams &p, dim3 grid, hipStream_t 
         launch_decode_form<D, USE_R, kContiguous>(p, grid, stream);
     else if (short_rows && p.page_size % 16 == 0)
         launch_decode_form<D, USE_R, kPagedRuns>(p, grid, stream);
-    else
-        launch_decode_form<D, USE_R, kRows>(p, grid, stream);
+    else {
+        DecodeParams rows = p;
+        if (p.block_table == nullptr) rows.page_size = 0x7fffffff, rows.num_pages = 1;
+        launch_decode_form<D, USE_R, kRows>(rows, grid, stream);
+    }
 }
 
 hipError_t launch_decode_bf16(const DecodeParams &p, hipStream_t stream) {
