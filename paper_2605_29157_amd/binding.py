@@ -7,6 +7,7 @@ no CPU or PyTorch fallback: if the library is missing, loading fails loudly.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 import struct
 
@@ -298,7 +299,7 @@ def _scratch(stream, n_floats, device):
     """fp32 scratch of a launch on `stream`, from that stream's own memory: a block of the current stream's
     may still be in use by work queued there, and may be handed out again there as soon as
     the call returns."""
-    other = _other_stream(stream, device)
+    other = None if stream is None else _other_stream(stream, device)
     if other is None:
         return torch.empty(n_floats, dtype=torch.float32, device=device)
     with torch.cuda.stream(other):
@@ -318,9 +319,15 @@ def _result(stream, make, *args, **kw):
     return t
 
 
+def _result_maker(stream, make):
+    """`make` for the results of a launch on `stream` (itself without one: a training step of small
+    shapes makes nine tensors, and is bound by the host)."""
+    return make if stream is None else functools.partial(_result, stream, make)
+
+
 def parallax_rope_table(n_pos, d, theta=1.0e6, device="cuda:0", stream=None):
     """(cos, sin) of pos * theta^(-2i/d): fp32 tensor [n_pos, d/2, 2] for qr_prep()."""
-    table = _result(stream, torch.empty, n_pos, d // 2, 2, dtype=torch.float32, device=device)
+    table = _result_maker(stream, torch.empty)(n_pos, d // 2, 2, dtype=torch.float32, device=device)
     st = load_library().parallax_rope_table(table.data_ptr(), int(n_pos), int(d), float(theta), _stream_ptr(stream))
     if st != PLX_OK:
         raise ParallaxError(st, "parallax_rope_table")
@@ -399,7 +406,7 @@ def parallax_decode(q, r, k, v, scale, seq_lens=None, use_r=True, num_splits=0, 
         if block_table.shape[0] != B or v.shape != k.shape:
             raise ValueError("block_table needs one row per sequence; k and v pools of one shape")
     if out is None:
-        out = _result(stream, torch.empty_like, q)
+        out = _result_maker(stream, torch.empty_like)(q)
     a = decode_args(q, r, k, v, out, scale, seq_lens, use_r, num_splits, workspace, block_table,
                     max_len, window)
     lib = load_library()
@@ -587,7 +594,7 @@ def parallax_prefill(q, r, k, v, scale, causal=True, use_r=True, out=None, strea
     if v.shape[2] != k.shape[2]:
         raise ValueError("k and v must hold the same number of keys")
     if out is None:
-        out = _result(stream, torch.empty_like, q)
+        out = _result_maker(stream, torch.empty_like)(q)
     a = prefill_args(q, r, k, v, out, scale, causal, use_r, window)
     if block_mask is not None:
         nrb, nkt = -(-q.shape[2] // BLOCK_ROWS), -(-k.shape[2] // BLOCK_KEYS)
@@ -597,8 +604,8 @@ def parallax_prefill(q, r, k, v, scale, causal=True, use_r=True, out=None, strea
     if prep is not None:
         a.prep = prep
     if save_for_backward:
-        vbar = _result(stream, torch.empty_like, out)
-        row_stats = _result(stream, torch.empty, q.shape[:3] + (2,), dtype=torch.float32, device=q.device)
+        vbar = _result_maker(stream, torch.empty_like)(out)
+        row_stats = _result_maker(stream, torch.empty)(q.shape[:3] + (2,), dtype=torch.float32, device=q.device)
         a.vbar, a.row_stats = vbar.data_ptr(), row_stats.data_ptr()
     lib, where = load_library(), _stream_ptr(stream)
     split_bytes = lib.parallax_prefill_workspace_bytes(ctypes.byref(a))
@@ -635,7 +642,8 @@ def parallax_prefill_backward(q, r, k, v, o, vbar, row_stats, d_o, scale, causal
                               workspace=None, window=0, block_mask=None):
     """Gradients (dq, dr, dk, dv) of parallax_prefill for the upstream gradient d_o, from the
     forward's output and row cache (save_for_backward=True, same causal / window / block_mask)."""
-    dq, dr, dk, dv = (_result(stream, torch.empty_like, t) for t in (q, q, k, k))
+    like = _result_maker(stream, torch.empty_like)
+    dq, dr, dk, dv = like(q), like(q), like(k), like(k)
     if workspace is None:
         workspace = _scratch(stream, q.shape[0] * q.shape[1] * q.shape[2] * 4, q.device)
     a = prefill_bwd_args(q, r, k, v, o, vbar, row_stats, d_o, dq, dr, dk, dv, scale, causal, workspace, window)
@@ -678,7 +686,8 @@ def parallax_norm_rope(tensors, pos0=None, eps=1e-6, theta=1.0e6, stream=None, i
     returns the list of results (the inputs themselves with inplace=True)."""
     if pos0 is not None and pos0.dtype != torch.int32:
         raise TypeError("pos0 must be int32")
-    full = [(x, g, rp, x if inplace else _result(stream, torch.empty_like, x)) for (x, g, rp) in tensors]
+    like = _result_maker(stream, torch.empty_like)
+    full = [(x, g, rp, x if inplace else like(x)) for (x, g, rp) in tensors]
     a = norm_rope_args(full, pos0, eps, theta, rope_table)
     st = load_library().parallax_norm_rope(ctypes.byref(a), _stream_ptr(stream))
     if st != PLX_OK:
@@ -725,7 +734,7 @@ def parallax_decode_mla(q, r, ckv, scale, seq_lens=None, num_splits=0, out=None,
     [B, Hq, Tq, dk] (rows at the last Tq positions, causal among themselves: a chunked decode
     step, or the prefill over the latent cache with Tq = prompt length); window > 0 = sliding."""
     if out is None:
-        out = _result(stream, torch.empty, q.shape[:-1] + (d_latent,), dtype=q.dtype, device=q.device)
+        out = _result_maker(stream, torch.empty)(q.shape[:-1] + (d_latent,), dtype=q.dtype, device=q.device)
     n_cols = q.shape[1] * (q.shape[2] if q.dim() == 4 else 1)
     if workspace is None and num_splits != 1:
         lmax = ckv.shape[1] if block_table is None else (
