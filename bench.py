@@ -189,7 +189,7 @@ def main():
     roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBPS,
                 "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBPS, 4),
                 "traffic": measured_traffic("decode_bf16_config2") if is_config2 else None,
-                "kernel": "decode_bf16_kernel<128,true,false,false>", "kernel_us": round(kern_us, 2),
+                "kernel": "decode_bf16_kernel<128,true,0,false,false>", "kernel_us": round(kern_us, 2),
                 "algorithmic_bytes_per_launch": step_bytes}
 
     # per-launch spread: one event pair per step (whole step) and per split-KV kernel launch

@@ -483,3 +483,16 @@ def test_rows_too_far_apart_for_lane_offsets(plx, synth):
     v.copy_(x["v"])
     want = plx.parallax_decode(x["q"], x["r"], x["k"], x["v"], x["scale"])
     assert torch.equal(plx.parallax_decode(x["q"], x["r"], k, v, x["scale"]), want)
+
+
+def test_several_sequences_of_rows_too_far_apart(plx, synth):
+    """The same with a batch and ragged lengths: the one page that such a cache is taken for starts at its
+    sequence."""
+    x = synth.decode_inputs(3, 4, 2, 9, 64, seed=611, device=DEV)
+    x["seq_lens"] = torch.tensor([9, 4, 7], dtype=torch.int32, device=DEV)
+    wide = torch.empty(3, 2, 9, 1 << 23, dtype=torch.bfloat16, device=DEV)
+    k, v = wide[..., :64], wide[..., 64:128]
+    k.copy_(x["k"])
+    v.copy_(x["v"])
+    want = plx.parallax_decode(x["q"], x["r"], x["k"], x["v"], x["scale"], seq_lens=x["seq_lens"])
+    assert torch.equal(plx.parallax_decode(x["q"], x["r"], k, v, x["scale"], seq_lens=x["seq_lens"]), want)
