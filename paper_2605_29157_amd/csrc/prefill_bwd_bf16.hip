@@ -958,6 +958,10 @@ __device__ __forceinline__ void bwd_dk_dv(const PrefillBwdParams &p, const int i
 // end, and from the start where there are fewer key blocks than units. Two launches in a row
 // against one, us for the whole backward, 16 query / 8 key heads, d = 128, causal: 1 x 300 rows 54 -> 38,
 // 1 x 1000 117 -> 87, 1 x 2048 212 -> 162, 4 x 1000 152 -> 133, 4 x 4096 1419 -> 1401; same bits.
+// d = 64 with full attention and block lists pays for it when nearly every tile is listed: its row pass alone
+// fitted twice into a compute unit (256 registers; together 275, and held to 256 109 of them spill). 2 x 2048
+// rows, every tile 225 -> 234, a quarter 133 -> 124; 2 x 4096, a quarter 433 -> 386; 1 x 700 60 -> 48. What
+// share is listed the host does not know.
 template <int D, bool CAUSAL, bool WINDOW, bool SPARSE>
 __global__ __launch_bounds__(256, 1) void bwd_passes_kernel(PrefillBwdParams p, int n_columns) {
     __shared__ u32x4 lds[kBwdLdsChunks<D>];
