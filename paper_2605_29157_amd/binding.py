@@ -605,6 +605,8 @@ def parallax_prefill(q, r, k, v, scale, causal=True, use_r=True, out=None, strea
         a.prep = prep
     if save_for_backward:
         vbar = _result_maker(stream, torch.empty_like)(out)
+        if vbar.stride() != out.stride():  # (out has gaps: the kernel writes vbar with out's strides)
+            vbar = _result_maker(stream, torch.empty_strided)(out.shape, out.stride(), dtype=out.dtype, device=out.device)
         row_stats = _result_maker(stream, torch.empty)(q.shape[:3] + (2,), dtype=torch.float32, device=q.device)
         a.vbar, a.row_stats = vbar.data_ptr(), row_stats.data_ptr()
     lib, where = load_library(), _stream_ptr(stream)

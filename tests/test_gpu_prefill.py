@@ -276,3 +276,18 @@ def test_register_only_mfma_loop_runs_and_counts_its_flops(plx):
     assert np.isfinite(s).all() and np.abs(s).max() > 1.0 and len(np.unique(s)) > 1000
     rate = flops / (e0.elapsed_time(e1) * 1e-3) / 1e12
     assert 250.0 < rate < 2600.0, rate
+
+
+@pytest.mark.parametrize("B,Hq,T,Tkv,d,dtype", [(1, 2, 200, 200, 128, torch.bfloat16), (1, 2, 64, 4000, 128, torch.bfloat16),
+                                                (1, 2, 300, 2049, 64, torch.bfloat16), (1, 2, 40, 40, 64, torch.float32)])
+def test_row_cache_beside_an_output_with_gaps(plx, synth, B, Hq, T, Tkv, d, dtype):
+    """out = every second row of a larger tensor (whole launches and key ranges): what a dense output
+    gives, and nothing between the rows."""
+    y = synth.prefill_inputs(B, Hq, Hq, Tkv, d, seed=77, dtype=dtype, device=DEV)
+    y["q"], y["r"] = y["q"][:, :, Tkv - T:].contiguous(), y["r"][:, :, Tkv - T:].contiguous()
+    want = plx.parallax_prefill(y["q"], y["r"], y["k"], y["v"], y["scale"], save_for_backward=True)
+    room = torch.full((B, Hq, 2 * T, d), 7.0, dtype=dtype, device=DEV)
+    got = plx.parallax_prefill(y["q"], y["r"], y["k"], y["v"], y["scale"], save_for_backward=True, out=room[:, :, ::2])
+    for a, b in zip(got, want):
+        assert torch.equal(a, b)
+    assert bool((room[:, :, 1::2] == 7.0).all())

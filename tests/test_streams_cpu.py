@@ -63,6 +63,7 @@ def world(monkeypatch):
     monkeypatch.setattr(torch.cuda, "ExternalStream", lambda ptr, device=None: streams[ptr])
     monkeypatch.setattr(torch, "empty", recorded(torch.empty))
     monkeypatch.setattr(torch, "empty_like", recorded(torch.empty_like))
+    monkeypatch.setattr(torch, "empty_strided", recorded(torch.empty_strided))
     return types.SimpleNamespace(plx=binding, streams=streams, made=made, launches=launches)
 
 
@@ -156,3 +157,12 @@ def test_masks_that_the_list_kernels_do_not_take(world, monkeypatch, columns):
     assert [t.data_ptr() for t in held[:2]] == [a.sparse_row_ptr, a.sparse_tile_idx]
     if columns:
         assert [t.data_ptr() for t in held[2:]] == [a.sparse_col_ptr, a.sparse_col_idx]
+
+
+def test_the_row_cache_is_laid_out_like_an_output_with_gaps(world):
+    """The kernel writes vbar with the strides of out: so it has to have them, where out is every second row
+    of a larger tensor (bytes behind a dense vbar's end would be written otherwise)."""
+    q, out = dev(1, 2, 8, 64), dev(1, 2, 16, 64)[:, :, ::2]
+    for stream in (None, world.streams[2]):
+        got, vbar, _ = world.plx.parallax_prefill(q, q, q, q, 0.1, out=out, save_for_backward=True, stream=stream)
+        assert got is out and vbar.stride() == out.stride() and vbar.shape == out.shape
