@@ -103,7 +103,7 @@ typedef struct {
  *   num_splits 0 = library heuristic, else the number of key-range splits to use
  *   workspace fp32 scratch for split partials, >= parallax_decode_workspace_bytes(...);
  *             may be NULL only when num_splits == 1 (bf16). fp32 calls use as many splits as it
- *             has room for, one without it
+ *             has room for, one without it; parallax_decode_call_splits says how many pay
  *
  * Several query rows (Tq > 1; speculative rows or a short chunk, the causal set of Sec. 2.1 at
  * absolute positions): q, r, o are [B, Hq, Tq, d] and the rows are the LAST Tq positions of the
