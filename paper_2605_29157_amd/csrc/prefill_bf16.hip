@@ -229,6 +229,14 @@ __global__ __launch_bounds__(256, 1) void prefill_bf16_kernel(PrefillParams p) {
         }
     }
     u32x4 qf[RW][KSTEPS], rf[RW][KSTEPS];
+    // SPLIT: the first 32 keys of the sequence as MFMA operands (row col, chunk 2 * ks + h), for the
+    // reference; they travel with the wave's own rows.
+    u32x4 k_ref[SPLIT ? KSTEPS : 1];
+    if constexpr (SPLIT) {
+        const __bf16 *krow = (const __bf16 *)p.k + b * p.ks[0] + hk * p.ks[1] + (int64_t)min(col, p.Tk - 1) * p.ks[2];
+#pragma unroll
+        for (int ks = 0; ks < KSTEPS; ++ks) k_ref[ks] = *(const u32x4 *)(krow + (2 * ks + h) * 8);
+    }
 
     const __bf16 *kbase = (const __bf16 *)p.k + b * p.ks[0] + hk * p.ks[1] + (int64_t)kt_skip * kBC * p.ks[2];
     const __bf16 *vbase = (const __bf16 *)p.v + b * p.vs[0] + hk * p.vs[1] + (int64_t)kt_skip * kBC * p.vs[2];
@@ -982,10 +990,27 @@ __global__ __launch_bounds__(256, 1) void prefill_bf16_kernel(PrefillParams p) {
 #pragma unroll
         for (int a = 0; a < RW; ++a) {
             float tmax = kNegInf;
+            if constexpr (SPLIT) {
+                // Every range takes the reference of the whole launch, so that it forms and rounds the very
+                // same P. (A range of its own block's maximum would be as safe, but rounds P
+                // against another scale: outputs apart by the bf16 bound, and by 2^-9 from exact where one key
+                // has all the weight.) A range far below the reference adds what it would add there.
+                f32x16 s0;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) tmax = fmaxf(tmax, key_ok(kb0, r, a) ? sa1[a][r] : kNegInf);
+                for (int r = 0; r < 16; ++r) s0[r] = 0.f;
+#pragma unroll
+                for (int ks = 0; ks < KSTEPS; ++ks) s0 = mfma32(k_ref[ks], qf[a][ks], s0);
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int key = 8 * (r >> 2) + 4 * h + (r & 3);
+                    tmax = fmaxf(tmax, key < p.Tk && (!CAUSAL || key <= my_row(a) + (p.Tk - T)) ? s0[r] : kNegInf);
+                }
+            } else {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) tmax = fmaxf(tmax, key_ok(kb0, r, a) ? sa1[a][r] : kNegInf);
+            }
             tmax = halves_max(tmax);
-            if constexpr (WINDOW || SPARSE || SPLIT) {
+            if constexpr (WINDOW || SPARSE) {
                 // a row whose window starts behind this block takes the block's plain maximum: any
                 // finite reference will do (the check after the loops catches one that was too far off)
                 float tall = sa1[a][0];
@@ -1115,16 +1140,14 @@ __global__ __launch_bounds__(256, 1) void prefill_bf16_kernel(PrefillParams p) {
         return chk;
     };
     float chk = stage_outputs();
-    if constexpr (WINDOW || SPARSE || SPLIT) {
+    if constexpr (WINDOW || SPARSE) {
         // the reference of a row may come from keys outside its window; if it was so far above
         // the row's own scores that the sum underflowed, take the exact path as well
         // (block-sparse: only for rows that do see a listed key -- the list is ascending, so that
         // is decided by its first tile)
 #pragma unroll
         for (int a = 0; a < RW; ++a)
-            if (my_row(a) < T && (!SPARSE || tile_at(0) * kBC <= row_lim[a]) && (!SPLIT || row_lim[a] >= 0) &&
-                !(dsum1[a] > 1e-30f))
-                chk = 1.f;
+            if (my_row(a) < T && (!SPARSE || tile_at(0) * kBC <= row_lim[a]) && !(dsum1[a] > 1e-30f)) chk = 1.f;
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // tile loads past the end have landed
     const bool overflow = __syncthreads_or(chk != 0.f);  // NaN != 0 is true; all waves agree
@@ -1187,8 +1210,9 @@ __global__ __launch_bounds__(256, 1) void prefill_bf16_kernel(PrefillParams p) {
     // ---- SPLIT, more than one key range: the record of every row ----------------------------
     // Laid out by accumulator: [float4 block (O1, O2; dimension block n, q4)][half-wave][row], so that
     // every store of a wave is one contiguous KB, then the row scalars.
-    // A range keeps the reference of its first 32 keys as long as its sums are finite, so it may weigh up
-    // to 2^128 times its reference. Its record is therefore scaled by 2^-exponent of d1 (exact) with
+    // A range keeps its reference (the maximum of the first 32 keys of all) as long as its sums are finite,
+    // so it may weigh up to 2^128 times that, beside ranges that took the online update and have
+    // another. Its record is therefore scaled by 2^-exponent of d1 (exact) with
     // the exponent added to the reference: every d1 is in [0.5, 1), the references compare what the
     // ranges weigh, and the merge neither overflows nor flushes the weight of a range that counts.
     if constexpr (SPLIT)
@@ -1367,7 +1391,7 @@ __global__ __launch_bounds__(256) void prefill_combine_kernel(PrefillParams p) {
 // units and 0.3 of the bytes' share (d = 64: 5 and 0.7) as well. (Over 488 splits that the first form alone
 // makes, 1 - 1000 rows over 0 - 3000 keys before them, 2 - 64 heads, 52 were slower than the whole launch, by
 // up to 18 % -- 16 rows over 616 keys, 32 heads: whole 18.3, split 21.6. With the second one
-// 8 of 432 are, by up to 4 %, and a dozen gains of up to 10 % are not taken.)
+// 13 of 432 are, by up to 5 %, and a dozen gains of up to 10 % are not taken.)
 // 0 = leave the launch whole (also when the gain would be under a tenth). Measured us against the number
 // of ranges of the longest row block, 16 heads, d = 128: 512 rows over 16384 keys whole 267, 2 160, 3 128,
 // 4 (the rule) 114, 5 160, 8 135; 1024 over 16384 whole 302, 2 (the rule) 207, 3 250, 4 226; 256 over 2000

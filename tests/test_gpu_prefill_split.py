@@ -62,11 +62,26 @@ def test_split_prefill(plx, synth, oracle, B, Hq, Hkv, T, Tkv, d, causal, use_r)
     torch.cuda.synchronize()
     ref = oracle_prefill(oracle, y, causal=causal, use_r=use_r)
     assert rel_l2(host(got), ref) <= BF16_REL_L2
-    # the two forms round P against other references and merge in fp32: both within the bf16 bound of the
-    # oracle, and of each other
+    # (both within the bf16 bound of the oracle, and of each other)
     assert rel_l2(host(got), host(whole).astype(np.float64)) <= BF16_REL_L2
     if causal and T == Tkv:
         assert torch.equal(got[:, :, 0], y["v"][:, :, 0].repeat_interleave(Hq // Hkv, 1))  # one key: v_0 exactly
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,T,Tkv,d", SHAPES)
+@pytest.mark.parametrize("causal", [True, False])
+def test_split_prefill_rounds_like_the_whole_launch(plx, synth, B, Hq, Hkv, T, Tkv, d, causal):
+    """All ranges share the reference of the whole launch, so P is rounded to the same bf16 values and what
+    is left is the order of fp32 sums (and, in a range's last step, whether a sum takes P before or after
+    its rounding): outputs a rounding step of bf16 apart here and there. Ranges with references of
+    their own differ by 2.9e-3."""
+    y = _inputs(synth, B, Hq, Hkv, T, Tkv, d, 4250 + T)
+    whole, need = _whole(plx, y, causal)
+    assert need > 0
+    got = plx.parallax_prefill(y["q"], y["r"], y["k"], y["v"], y["scale"], causal=causal)
+    e = rel_l2(host(got), host(whole).astype(np.float64))
+    print("rel", e)
+    assert e <= 1e-3
 
 
 @pytest.mark.parametrize("B,Hq,Hkv,T,Tkv,d", SHAPES)
@@ -100,9 +115,10 @@ def test_logits_that_grow_along_the_sequence(plx, synth, oracle):
 @pytest.mark.parametrize("d,high", [(128, 7.75), (64, 10.9375)])  # 126.5 and 126.2 binades above the other keys
 @pytest.mark.parametrize("where", ["late_then_first", "late_everywhere"])
 def test_ranges_whose_sums_come_close_to_the_end_of_fp32(plx, synth, oracle, d, high, where):
-    """A range keeps the reference of its first 32 keys as long as its sums are finite. Late in the first
-    range and first in the second: the ranges weigh the same, at references 126 binades apart. Late in
-    every range: each sum is finite, their total at one reference is not."""
+    """A range keeps its reference, the first 32 keys, as long as its sums are finite. Late in the first range
+    and first in the second: two sums close to the end of fp32 (with references of their own: the
+    ranges weigh the same, at references 126 binades apart). Late in every range: each sum is finite,
+    their total is not."""
     T, Tkv = 32, 4096
     y = _inputs(synth, 1, 2, 2, T, Tkv, d, 4500)
     _, need = _whole(plx, y)
