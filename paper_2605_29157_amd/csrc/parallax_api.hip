@@ -678,7 +678,7 @@ plx_status parallax_prefill_backward(const plx_prefill_bwd_args *a, void *hip_st
     }
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     const hipError_t err = a->dtype == PLX_F32 ? plx::launch_prefill_bwd_f32(p, stream)
-                                               : plx::launch_prefill_bwd_bf16(p, stream);
+                                               : plx::launch_prefill_bwd_bf16(p, query_num_cus(), stream);
     return err == hipSuccess ? PLX_OK : PLX_ERR_LAUNCH;
 }
 

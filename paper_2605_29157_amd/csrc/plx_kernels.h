@@ -137,7 +137,7 @@ hipError_t launch_decode_combine(const DecodeParams &p, hipStream_t stream);
 hipError_t launch_prefill_bf16(const PrefillParams &p, hipStream_t stream);
 // Plans the split of a call over key ranges: 0 = not split, else the bytes of p.ws that its launch takes
 size_t plan_prefill_split_bf16(PrefillParams &p, int num_cus);
-hipError_t launch_prefill_bwd_bf16(const PrefillBwdParams &p, hipStream_t stream);
+hipError_t launch_prefill_bwd_bf16(const PrefillBwdParams &p, int num_cus, hipStream_t stream);
 hipError_t launch_prefill_bwd_f32(const PrefillBwdParams &p, hipStream_t stream);
 hipError_t launch_decode_f32(const DecodeParams &p, hipStream_t stream);
 hipError_t launch_prefill_f32(const PrefillParams &p, hipStream_t stream);

@@ -20,19 +20,27 @@ namespace plx {
 // GUARD = true brings two wait states along. GUARD = false is for the steady-state loop, where
 // the generated code has no such copy -- the build verifies that on the assembly it produced
 // (asm_check.py) and fails otherwise.
-// acc = A * B (first k-step) and acc += A * B, 32x32x16 bf16, all operands in vector registers.
-template <bool GUARD>
+// acc = A * B (first k-step) and acc += A * B, 32x32x16 bf16, destination and A in vector registers.
+// ACC_B: B (a resident fragment) in accumulation registers, for kernels with one wave per SIMD, whose 512
+// registers are half of that kind. A kernel held to 256 registers (two waves per SIMD) has to take it in
+// vector registers: a single operand constrained to the accumulation registers makes the compiler
+// split the 256 evenly between the two kinds, and the d = 64 backward then spills 200 of them.
+template <bool GUARD, bool ACC_B = true>
 __device__ __forceinline__ void mfma32_scores_first(f32x16 &acc, u32x4 a, u32x4 b) {
     // early clobber: the destination block must not share registers with A or B
-    if constexpr (GUARD)
+    if constexpr (GUARD && ACC_B)
         asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(acc) : "v"(a), "a"(b));
+    else if constexpr (GUARD)
+        asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(acc) : "v"(a), "v"(b));
     else
         asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0 ; unguarded" : "=&v"(acc) : "v"(a), "a"(b));
 }
-template <bool GUARD>
+template <bool GUARD, bool ACC_B = true>
 __device__ __forceinline__ void mfma32_scores(f32x16 &acc, u32x4 a, u32x4 b) {
-    if constexpr (GUARD)
+    if constexpr (GUARD && ACC_B)
         asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "a"(b));
+    else if constexpr (GUARD)
+        asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
     else
         asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0 ; unguarded" : "+v"(acc) : "v"(a), "a"(b));
 }

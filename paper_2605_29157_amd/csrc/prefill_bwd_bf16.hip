@@ -34,6 +34,8 @@
 // passes then run the masked form of their pipeline throughout.
 #include "plx_device.h"
 #include "plx_kernels.h"
+#include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "plx_lds_dma.h"
@@ -45,6 +47,10 @@ namespace {
 
 constexpr int kTileRows = 64;  // rows (keys or query rows) per LDS tile
 constexpr int kBlk = 32;       // rows per MFMA block
+
+// d = 64: two workgroups per compute unit, 256 registers a wave (see bwd_passes_kernel)
+template <int D>
+constexpr bool kAccB = D == 128;
 
 // Every tile is read both ways -- whole chunks of 32 consecutive rows (A / B operand of a score
 // MFMA) and transposed, 4 consecutive rows x 4 chunks (A operand of an output MFMA) -- so rows are
@@ -156,6 +162,79 @@ __global__ __launch_bounds__(256) void bwd_rows_prepare_kernel(PrefillBwdParams 
 template <int D>
 constexpr int kBwdLdsChunks = 3 * (3 * BwdTile<D>::CHUNKS + kTileRows);
 
+// ---- end of a pass -----------------------------------------------------------------------------
+// Each wave's two accumulators hold 32 output rows, transposed (register r of block n = dimension
+// 32n + 8*(r/4) + 4h + r%4 of row `col`).
+// PAIR: the two waves (w, w ^ 2) that took the halves of every tile hold the sums over theirs. Each hands
+// one accumulator over through the LDS, the lower half's the second and the upper's the first, and adds
+// what it receives to the other.
+template <int D>
+__device__ __forceinline__ void swap_halves(f32x16 (&first)[D / 32], f32x16 (&second)[D / 32], int w, int half, int lane,
+                                            u32x4 *lds) {
+    constexpr int NDB = D / 32;
+    static_assert(4 * NDB * 4 * 64 <= kBwdLdsChunks<D>, "the workgroup's LDS");
+    f32x4 *mine = (f32x4 *)lds + w * NDB * 4 * 64 + lane, *theirs = (f32x4 *)lds + (w ^ 2) * NDB * 4 * 64 + lane;
+    auto quad = [](const f32x16 &x, int q4) __attribute__((always_inline)) {
+        return f32x4{x[4 * q4], x[4 * q4 + 1], x[4 * q4 + 2], x[4 * q4 + 3]};
+    };
+    auto give = [&](const f32x16 (&acc)[NDB]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int n = 0; n < NDB; ++n)
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4) mine[(n * 4 + q4) * 64] = quad(acc[n], q4);
+    };
+    auto take = [&](f32x16 (&acc)[NDB]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int n = 0; n < NDB; ++n)
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4) {
+                const f32x4 x = theirs[(n * 4 + q4) * 64];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc[n][4 * q4 + i] += x[i];
+            }
+    };
+    if (half == 0)  // (wave-uniform)
+        give(second);
+    else
+        give(first);
+    __syncthreads();
+    if (half == 0)
+        take(first);
+    else
+        take(second);
+    __syncthreads();
+}
+// 32 rows, times `scale`, to base + row * stride (rows < n_rows only). A lane owns one ROW: stored from the
+// registers, an instruction would touch 32 rows, 16 bytes each; the wave turns its block through its own
+// piece of the LDS and writes whole rows. (4 x 4096 rows, d = 128: 5.1 -> 2.5 us at the end of a workgroup.)
+template <int D>
+__device__ __forceinline__ void store_rows(const f32x16 (&acc)[D / 32], float scale, __bf16 *base, int64_t stride,
+                                           int n_rows, int w, int lane, u32x4 *lds) {
+    constexpr int CPR = D / 8, ROW = CPR + 1;  // padded row, in 16-byte chunks
+    static_assert(4 * 32 * ROW <= kBwdLdsChunks<D>, "the workgroup's LDS");
+    u32x4 *zone = lds + w * 32 * ROW;
+    unsigned short *zone16 = (unsigned short *)zone;
+    const int col = lane & 31, h = lane >> 5;
+#pragma unroll
+    for (int n = 0; n < D / 32; ++n)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4)
+            *(u32x2 *)(zone16 + col * (ROW * 8) + 32 * n + 8 * q4 + 4 * h) =
+                u32x2{pack_bf16(acc[n][4 * q4] * scale, acc[n][4 * q4 + 1] * scale),
+                      pack_bf16(acc[n][4 * q4 + 2] * scale, acc[n][4 * q4 + 3] * scale)};
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    constexpr int RPI = 64 / CPR;  // rows of one wave-wide store
+#pragma unroll
+    for (int i = 0; i < 32 / RPI; ++i) {
+        const int rr = i * RPI + lane / CPR, chunk = lane % CPR;
+        if (rr < n_rows) *(u32x4 *)(base + rr * stride + chunk * 8) = zone[rr * ROW + chunk];
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // ---- row pass: dQ, dR -------------------------------------------------------------------------
 // Software pipeline over 32-key blocks, written as slots of ONE MFMA plus its share of vector
 // work (the single wave of a SIMD issues in order, so vector instructions only run in the shadow
@@ -169,7 +248,8 @@ constexpr int kBwdLdsChunks = 3 * (3 * BwdTile<D>::CHUNKS + kTileRows);
 // WINDOW (sliding window, causal only): the key tiles before the window of the block's first row
 // are skipped by moving the key origin; the leading tiles that some row sees only in part take
 // the masked form of the pipeline, like the diagonal ones.
-template <int D, bool CAUSAL, bool WINDOW = false, bool SPARSE = false>
+// PAIR: see bwd_passes_kernel.
+template <int D, bool CAUSAL, bool WINDOW, bool SPARSE, bool PAIR>
 __device__ __forceinline__ void bwd_dq_dr(const PrefillBwdParams &p, const int id, u32x4 *lds) {
     static_assert(CAUSAL || !WINDOW, "a sliding window is causal");
     static_assert(!(SPARSE && WINDOW), "block lists and a sliding window do not combine");
@@ -177,12 +257,14 @@ __device__ __forceinline__ void bwd_dq_dr(const PrefillBwdParams &p, const int i
     constexpr int CPR = TL::CPR, KSTEPS = D / 16, NDB = D / 32;
     constexpr int STAGES = 3, STAGE_CHUNKS = 2 * TL::CHUNKS;  // ring of [K tile | V tile]
     static_assert(STAGES * STAGE_CHUNKS <= kBwdLdsChunks<D>, "the workgroup's LDS");
+    constexpr int ROWS = PAIR ? 64 : 128;  // query rows of a workgroup
 
     const int tid = threadIdx.x;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int col = lane & 31, h = lane >> 5;
+    const int wr = PAIR ? w & 1 : w, half = PAIR ? w >> 1 : 0;  // this wave's 32 rows; PAIR: its half of every tile
     const int T = p.T;
-    const int nrb = (T + 127) / 128;
+    const int nrb = (T + ROWS - 1) / ROWS;
     // Work item: the row block is the slowest index, so that under a causal mask ALL heavy row
     // blocks are dispatched before any light one (with the row block as the fastest index every
     // head ends on its own light blocks while the last head's heavy ones have just started: the
@@ -210,10 +292,10 @@ __device__ __forceinline__ void bwd_dq_dr(const PrefillBwdParams &p, const int i
     }
     const int rb = CAUSAL ? nrb - 1 - rbi : rbi;  // heavy row blocks first
     // key tiles no row of this block sees (all keys before the window of its first row)
-    const int kt_skip = WINDOW ? max(rb * 128 + (p.Tk - T) - p.window + 1, 0) / kTileRows : 0;
+    const int kt_skip = WINDOW ? max(rb * ROWS + (p.Tk - T) - p.window + 1, 0) / kTileRows : 0;
     const int Tk = p.Tk - kt_skip * kTileRows, off = Tk - T;  // keys from the first tile read on
     const int hk = hq / p.G;
-    const int row0 = rb * 128 + w * 32, my_row = row0 + col;
+    const int row0 = rb * ROWS + wr * 32, my_row = row0 + col;
     const int ld_row = min(my_row, T - 1);
 
     // B operands of the score MFMAs: column = query row, k-elements = the 8 dims of chunk 2*ks + h
@@ -237,11 +319,6 @@ __device__ __forceinline__ void bwd_dq_dr(const PrefillBwdParams &p, const int i
     const __bf16 *kbase = (const __bf16 *)p.k + b * p.ks[0] + hk * p.ks[1] + (int64_t)kt_skip * kTileRows * p.ks[2];
     const __bf16 *vbase = (const __bf16 *)p.v + b * p.vs[0] + hk * p.vs[1] + (int64_t)kt_skip * kTileRows * p.vs[2];
     const uint32_t lds_base = lds_byte_address(lds);
-    auto issue_tile = [&](int tile, int stage) __attribute__((always_inline)) {  // key tile -> ring stage
-        load_tile64<D>(kbase, p.ks[2], tile * kTileRows, Tk, lds_base + (uint32_t)(stage * STAGE_CHUNKS) * 16u, w, lane);
-        load_tile64<D>(vbase, p.vs[2], tile * kTileRows, Tk,
-                       lds_base + (uint32_t)(stage * STAGE_CHUNKS + TL::CHUNKS) * 16u, w, lane);
-    };
     // The steady-state loop spreads the loads of tile t + 2 over the MFMA slots of a step (as a
     // block at the top of an iteration they cost about a tenth of it): per-lane byte offsets
     // inside a complete tile, a wave-uniform tile base.
@@ -261,11 +338,33 @@ __device__ __forceinline__ void bwd_dq_dr(const PrefillBwdParams &p, const int i
             tile_load16_uniform<false>(toffk[i], dma_k, dma_lds + 1024u * i);
         else
             tile_load16_uniform<false>(toffv[i - TL::NDMA], dma_v,
-                                       dma_lds + (uint32_t)TL::CHUNKS * 16u + 1024u * (i - TL::NDMA));
+                            dma_lds + (uint32_t)TL::CHUNKS * 16u + 1024u * (i - TL::NDMA));
+    };
+    const int64_t k_tile_bytes = (int64_t)kTileRows * 2 * p.ks[2], v_tile_bytes = (int64_t)kTileRows * 2 * p.vs[2];
+    auto stage_addr = [&](int stage) __attribute__((always_inline)) {
+        return lds_base + (uint32_t)(stage * STAGE_CHUNKS + w * TL::NDMA * 64) * 16u;
+    };
+    // key tile -> ring stage, all loads at once. Only a tile that ends behind the last key needs an address
+    // per row (64-bit products for every load: 3 x 1111 rows, d = 128, 112 -> 107 us without them). With
+    // block lists at d = 128 every tile takes that way: the scalars of the other one no longer fit the scalar
+    // registers and come back lane by lane (2 x 2048, a quarter of the tiles: 115 us, with both ways 118).
+    constexpr bool kPlainTiles = !(SPARSE && D == 128);
+    auto issue_tile = [&](int tile, int stage) __attribute__((always_inline)) {
+        if (kPlainTiles && (tile + 1) * kTileRows <= Tk) {  // (workgroup-uniform)
+            dma_k = (const char *)kbase + tile * k_tile_bytes;
+            dma_v = (const char *)vbase + tile * v_tile_bytes;
+            dma_lds = stage_addr(stage);
+#pragma unroll
+            for (int i = 0; i < 2 * TL::NDMA; ++i) dma_slot(i);
+        } else {
+            load_tile64<D>(kbase, p.ks[2], tile * kTileRows, Tk, lds_base + (uint32_t)(stage * STAGE_CHUNKS) * 16u, w, lane);
+            load_tile64<D>(vbase, p.vs[2], tile * kTileRows, Tk,
+                           lds_base + (uint32_t)(stage * STAGE_CHUNKS + TL::CHUNKS) * 16u, w, lane);
+        }
     };
     auto k_block = [&](int stage, int kb) __attribute__((always_inline)) { return (const u32x4 *)(lds + stage * STAGE_CHUNKS + kb * kBlk * CPR); };
 
-    const int key_end = CAUSAL ? min(Tk, (rb + 1) * 128 + off) : Tk;
+    const int key_end = CAUSAL ? min(Tk, (rb + 1) * ROWS + off) : Tk;
     // Block-sparse: ring position t holds key tile tile_at(t) of the row block's list (ascending,
     // caller's arrays, read as scalar loads; entries clamped to existing tiles; listed tiles past
     // the causal limit dropped) -- the list the forward walked.
@@ -274,7 +373,7 @@ __device__ __forceinline__ void bwd_dq_dr(const PrefillBwdParams &p, const int i
     int n_list = 0;
     if constexpr (SPARSE) {
         const int sb = p.sparse_batch > 1 ? b : 0, sh = p.sparse_heads > 1 ? hq : 0;
-        const int64_t e = ((int64_t)sb * p.sparse_heads + sh) * nrb + rb;
+        const int64_t e = ((int64_t)sb * p.sparse_heads + sh) * ((T + 127) / 128) + rb * ROWS / 128;
         const_i32 *row_ptr = (const_i32 *)(uintptr_t)p.sparse_row_ptr;
         const int first = row_ptr[e];
         tile_list = (const_i32 *)(uintptr_t)p.sparse_tile_idx + first;
@@ -298,7 +397,7 @@ __device__ __forceinline__ void bwd_dq_dr(const PrefillBwdParams &p, const int i
     const int lim_row = CAUSAL ? min(my_row + off, Tk - 1) : Tk - 1;  // last key this lane's row sees
     if constexpr (SPARSE) {
         if (n_tiles == 0) {  // (workgroup-uniform) a row block that lists nothing: zero gradients
-            if (my_row < T) {
+            if (my_row < T && half == 0) {
                 __bf16 *dq_row = (__bf16 *)p.dq + b * p.dqs[0] + hq * p.dqs[1] + my_row * p.dqs[2];
                 __bf16 *dr_row = (__bf16 *)p.dr + b * p.drs[0] + hq * p.drs[1] + my_row * p.drs[2];
 #pragma unroll
@@ -330,7 +429,7 @@ __device__ __forceinline__ void bwd_dq_dr(const PrefillBwdParams &p, const int i
             load_f1(next_blk, g);
         else if (g < NF1 + NF2)
             load_f2(cur_blk, g - NF1);
-        else
+        else if constexpr (!PAIR)  // (PAIR: the block after is in the tile that is still on its way)
             load_f1(after_blk, g - NF1 - NF2);
     };
 
@@ -387,15 +486,15 @@ __device__ __forceinline__ void bwd_dq_dr(const PrefillBwdParams &p, const int i
             if constexpr (DMA)
                 if (sl < 2 * TL::NDMA) dma_slot(sl);
             if (which == 0) {
-                if (ks == 0) mfma32_scores_first<true>(n1, f1[2 * ks], qf[ks]);
-                else mfma32_scores<true>(n1, f1[2 * ks], qf[ks]);
+                if (ks == 0) mfma32_scores_first<true, kAccB<D>>(n1, f1[2 * ks], qf[ks]);
+                else mfma32_scores<true, kAccB<D>>(n1, f1[2 * ks], qf[ks]);
                 prefetch(2 * ks, next_blk, cur_blk, after_blk);
             } else if (which == 1) {
-                if (ks == 0) mfma32_scores_first<true>(n2, f1[2 * ks], rf[ks]);
-                else mfma32_scores<true>(n2, f1[2 * ks], rf[ks]);
+                if (ks == 0) mfma32_scores_first<true, kAccB<D>>(n2, f1[2 * ks], rf[ks]);
+                else mfma32_scores<true, kAccB<D>>(n2, f1[2 * ks], rf[ks]);
             } else {
-                if (ks == 0) mfma32_scores_first<true>(na, f1[2 * ks + 1], gf[ks]);
-                else mfma32_scores<true>(na, f1[2 * ks + 1], gf[ks]);
+                if (ks == 0) mfma32_scores_first<true, kAccB<D>>(na, f1[2 * ks + 1], gf[ks]);
+                else mfma32_scores<true, kAccB<D>>(na, f1[2 * ks + 1], gf[ks]);
                 prefetch(2 * ks + 1, next_blk, cur_blk, after_blk);
             }
             elem_stages(masked_tag, c1, c2, ca, 8, sl, 0, SLOTS1, lim_cur);
@@ -433,8 +532,8 @@ __device__ __forceinline__ void bwd_dq_dr(const PrefillBwdParams &p, const int i
         tile_barrier<0>();
     f32x16 a1, a2, a3, b1, b2, b3;
     {
-        // prologue: scores of block (0, 0); its lower 16 keys -> g1 / g2; first fragments of (0, 1)
-        const u32x4 *blk = k_block(0, 0);
+        // prologue: scores of block (0, half); its lower 16 keys -> g1 / g2; first fragments of (0, 1)
+        const u32x4 *blk = k_block(0, half);
         a1 = a2 = a3 = zero16();
 #pragma unroll
         for (int ks = 0; ks < KSTEPS; ++ks) {
@@ -445,24 +544,36 @@ __device__ __forceinline__ void bwd_dq_dr(const PrefillBwdParams &p, const int i
         }
 #pragma unroll
         for (int sl = 0; sl < 12; ++sl)
-            elem_stages(std::true_type{}, a1, a2, a3, 0, sl, 0, 12, lim_row - tile_at(0) * kTileRows - 4 * h);
+            elem_stages(std::true_type{}, a1, a2, a3, 0, sl, 0, 12,
+                        lim_row - tile_at(0) * kTileRows - half * kBlk - 4 * h);
         pg1[0] = pack_group(a3, 0);
         pg2[0] = pack_group(a2, 0);
+        if constexpr (!PAIR)
 #pragma unroll
-        for (int f = 0; f < LA; ++f) load_f1(k_block(0, 1), f);
+            for (int f = 0; f < LA; ++f) load_f1(k_block(0, 1), f);
     }
     int stage = 0;
-    auto tile_steps = [&](auto masked_tag, auto dma_tag, int t) __attribute__((always_inline)) {
-        constexpr bool DMA = decltype(dma_tag)::value;
+    auto tile_steps = [&](auto masked_tag, auto dma_tag, int t, f32x16 &a1, f32x16 &a2, f32x16 &a3, f32x16 &b1,
+                          f32x16 &b2, f32x16 &b3) __attribute__((always_inline)) {
         const int next_stage = stage == STAGES - 1 ? 0 : stage + 1;
         const int free_stage = stage == 0 ? STAGES - 1 : stage - 1;
         tile_barrier<0>();  // tile t + 1 has landed; tile t - 1 is free
-        if constexpr (DMA) {  // tile t + 2 is complete: fetched by the first step, slot by slot
-            dma_lds = lds_base + (uint32_t)(free_stage * STAGE_CHUNKS + w * TL::NDMA * 64) * 16u;
+        if constexpr (decltype(dma_tag)::value) {  // tile t + 2 is complete: fetched by the first step, slot by slot
+            dma_lds = stage_addr(free_stage);
         } else {
             if (t + 2 < n_tiles) issue_tile(tile_at(t + 2), free_stage);
         }
         const int key_base = tile_at(t) * kTileRows, key_base_after = tile_at(t + 1) * kTileRows;
+        if constexpr (PAIR) {
+            // block (t, half) -> g, dQ / dR; scores of (t + 1, half), whose first fragments are read now
+            const u32x4 *next_blk = k_block(next_stage, half);
+#pragma unroll
+            for (int f = 0; f < LA; ++f) load_f1(next_blk, f);
+            pipeline_step(masked_tag, dma_tag, key_base + half * kBlk, key_base_after + half * kBlk, next_blk,
+                          k_block(stage, half), nullptr, a1, a2, a3, b1, b2, b3);
+            stage = next_stage;
+            return;
+        }
         // block (t, 0) -> g, dQ / dR; scores of (t, 1); fragments of (t + 1, 0)
         pipeline_step(masked_tag, dma_tag, key_base, key_base + kBlk, k_block(stage, 1), k_block(stage, 0),
                       k_block(next_stage, 0), a1, a2, a3, b1, b2, b3);
@@ -471,46 +582,85 @@ __device__ __forceinline__ void bwd_dq_dr(const PrefillBwdParams &p, const int i
                       k_block(stage, 1), k_block(next_stage, 1), b1, b2, b3, a1, a2, a3);
         stage = next_stage;
     };
+    // Tiles [t, end) -- PAIR: an even number of them, as a step hands its score registers over to the
+    // next one in the other set (the odd last tile is a step of its own: left by a break, the loop spills)
+    auto run_tiles = [&](auto masked_tag, auto dma_tag, int &t, int end, auto after) __attribute__((always_inline)) {
+        while (t < end) {
+            tile_steps(masked_tag, dma_tag, t, a1, a2, a3, b1, b2, b3);
+            ++t;
+            after();
+            if constexpr (PAIR) {
+                tile_steps(masked_tag, dma_tag, t, b1, b2, b3, a1, a2, a3);
+                ++t;
+                after();
+            }
+        }
+    };
     // tiles whose keys -- and those of the tile after (a step also prepares the lower half of the
     // next block) -- every row of the workgroup sees: no masks; then the diagonal / tail tiles.
     // The unmasked loop also stops two short of the last complete tile, so that the tile it
     // fetches exists completely.
-    const int n_full = SPARSE ? 0 : min(CAUSAL ? (rb * 128 + off + 1) / kTileRows : Tk / kTileRows, Tk / kTileRows - 1);
+    const int n_full = SPARSE ? 0 : min(CAUSAL ? (rb * ROWS + off + 1) / kTileRows : Tk / kTileRows, Tk / kTileRows - 1);
     int t = 0;
     if constexpr (WINDOW) {
         // leading tiles that hold a key before the window of the block's last row
-        const int n_left = min(n_tiles, max(rb * 128 + 128 + off - p.window + kTileRows - 1, 0) / kTileRows);
-        for (; t < n_left; ++t) tile_steps(std::true_type{}, std::false_type{}, t);
+        const int n_left = min(n_tiles, max(rb * ROWS + ROWS + off - p.window + kTileRows - 1, 0) / kTileRows);
+        run_tiles(std::true_type{}, std::false_type{}, t, PAIR ? min((n_left + 1) & ~1, n_tiles & ~1) : n_left, [] {});
     }
-    const int64_t k_tile_bytes = (int64_t)kTileRows * 2 * p.ks[2], v_tile_bytes = (int64_t)kTileRows * 2 * p.vs[2];
     dma_k = (const char *)kbase + (t + 2) * k_tile_bytes;
     dma_v = (const char *)vbase + (t + 2) * v_tile_bytes;
-    for (; t < n_full - 1; ++t) {
-        tile_steps(std::false_type{}, std::true_type{}, t);
+    // (PAIR: in pairs of tiles, an odd one is left to the masked form)
+    run_tiles(std::false_type{}, std::true_type{}, t, PAIR ? t + (max(n_full - 1 - t, 0) & ~1) : n_full - 1, [&] {
         dma_k += k_tile_bytes;
         dma_v += v_tile_bytes;
+    });
+    run_tiles(std::true_type{}, std::false_type{}, t, PAIR ? n_tiles & ~1 : n_tiles, [] {});
+    if (PAIR && t < n_tiles) {
+        tile_steps(std::true_type{}, std::false_type{}, t, a1, a2, a3, b1, b2, b3);
+        asm volatile("" ::"v"(b1), "v"(b2), "v"(b3));  // (unused, but nothing else may move in before they are written)
     }
-    for (; t < n_tiles; ++t) tile_steps(std::true_type{}, std::false_type{}, t);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no tile load may land after the workgroup ends
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no tile load may land behind this
+    __syncthreads();                                  // the ring is free
 
+    if constexpr (PAIR) swap_halves<D>(dq, dr, w, half, lane, lds);
     // dQ^T / dR^T register r of block n <-> dim 32n + 8*(r/4) + 4h + r%4 of row my_row
-    if (my_row < T) {
-        __bf16 *dq_row = (__bf16 *)p.dq + b * p.dqs[0] + hq * p.dqs[1] + my_row * p.dqs[2];
-        __bf16 *dr_row = (__bf16 *)p.dr + b * p.drs[0] + hq * p.drs[1] + my_row * p.drs[2];
-#pragma unroll
-        for (int n = 0; n < NDB; ++n)
-#pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) {
-                const int dim = 32 * n + 8 * q4 + 4 * h;
-                const u32x2 a = {pack_bf16(dq[n][4 * q4] * p.scale, dq[n][4 * q4 + 1] * p.scale),
-                                 pack_bf16(dq[n][4 * q4 + 2] * p.scale, dq[n][4 * q4 + 3] * p.scale)};
-                const u32x2 c = {pack_bf16(dr[n][4 * q4], dr[n][4 * q4 + 1]),
-                                 pack_bf16(dr[n][4 * q4 + 2], dr[n][4 * q4 + 3])};
-                *(u32x2 *)(dq_row + dim) = a;
-                *(u32x2 *)(dr_row + dim) = c;
-            }
-    }
+    __bf16 *dq_base = (__bf16 *)p.dq + b * p.dqs[0] + hq * p.dqs[1] + row0 * p.dqs[2];
+    __bf16 *dr_base = (__bf16 *)p.dr + b * p.drs[0] + hq * p.drs[1] + row0 * p.drs[2];
+    if (!PAIR || half == 0) store_rows<D>(dq, p.scale, dq_base, p.dqs[2], T - row0, w, lane, lds);
+    if (!PAIR || half == 1) store_rows<D>(dr, 1.f, dr_base, p.drs[2], T - row0, w, lane, lds);
 }
+
+// Work item of the column pass: the key block is the slowest index (causal: low key blocks see the
+// most rows; all of them come first, over every batch entry and head -- with the key block as the
+// fastest index the tail of the pass cost a quarter of it); (batch, kv head) pairs by
+// workgroup id modulo 8 onto the XCDs.
+__device__ __forceinline__ void column_item(const PrefillBwdParams &p, int id, int &cb, int &hk, int &b) {
+    const int pairs = p.B * p.Hkv;
+    int pair;
+    if (pairs % 8 == 0) {
+        const int x = id & 7, j = id >> 3, per = pairs / 8;
+        cb = j / per;
+        pair = (j - cb * per) * 8 + x;
+    } else {
+        cb = id / pairs;
+        pair = id - cb * pairs;
+    }
+    b = pair / p.Hkv;
+    hk = pair - b * p.Hkv;
+}
+// Block lists: the row blocks that list one of the two key tiles 2 * cb, 2 * cb + 1 of key block cb are the entries
+// [first, end) of query head hq's column list.
+struct ColumnList {
+    int first, end;
+    __device__ __forceinline__ ColumnList(const PrefillBwdParams &p, int b, int hq, int cb) {
+        using const_i32 = const __attribute__((address_space(4))) int32_t;
+        const int sb = p.sparse_batch > 1 ? b : 0, sh = p.sparse_heads > 1 ? hq : 0;
+        const int64_t e = ((int64_t)sb * p.sparse_heads + sh) * ((p.Tk + 127) / 128) + cb;
+        const_i32 *col_ptr = (const_i32 *)(uintptr_t)p.sparse_col_ptr;
+        first = col_ptr[e];
+        end = max(col_ptr[e + 1], first);
+    }
+};
 
 // ---- column pass: dK, dV ----------------------------------------------------------------------
 // The same software pipeline over 32-row blocks of the streamed (Q, R, dO) tiles:
@@ -523,8 +673,9 @@ __device__ __forceinline__ void bwd_dq_dr(const PrefillBwdParams &p, const int i
 // one float4 per register, read one slot ahead of their use.
 // WINDOW: key j is seen by the rows [j - off, j - off + window) only; the row tiles past the
 // last of them are not visited, those cut by the upper edge take the masked form.
-template <int D, bool CAUSAL, bool WINDOW = false, bool SPARSE = false>
-__device__ __forceinline__ void bwd_dk_dv(const PrefillBwdParams &p, const int id, u32x4 *lds) {
+// PAIR: see bwd_passes_kernel.
+template <int D, bool CAUSAL, bool WINDOW, bool SPARSE, bool PAIR>
+__device__ __forceinline__ void bwd_dk_dv(const PrefillBwdParams &p, const int cb, const int hk, const int b, u32x4 *lds) {
     static_assert(CAUSAL || !WINDOW, "a sliding window is causal");
     static_assert(!(SPARSE && WINDOW), "block lists and a sliding window do not combine");
     using TL = BwdTile<D>;
@@ -536,27 +687,10 @@ __device__ __forceinline__ void bwd_dk_dv(const PrefillBwdParams &p, const int i
     const int tid = threadIdx.x;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int col = lane & 31, h = lane >> 5;
+    constexpr int KEYS = PAIR ? 64 : 128;  // keys of a workgroup
+    const int wk = PAIR ? w & 1 : w, half = PAIR ? w >> 1 : 0;  // this wave's 32 keys; PAIR: its half of every tile
     const int T = p.T, Tk = p.Tk, off = Tk - T, G = p.G;
-    // Work item: the key block is the slowest index (causal: low key blocks see the most rows;
-    // all of them come first, over every batch entry and head -- with the key block as the
-    // fastest index the tail of the pass cost a quarter of it); (batch, kv head) pairs by
-    // workgroup id modulo 8 onto the XCDs.
-    int cb, hk, b;
-    {
-        const int pairs = p.B * p.Hkv;
-        int pair;
-        if (pairs % 8 == 0) {
-            const int x = id & 7, j = id >> 3, per = pairs / 8;
-            cb = j / per;
-            pair = (j - cb * per) * 8 + x;
-        } else {
-            cb = id / pairs;
-            pair = id - cb * pairs;
-        }
-        b = pair / p.Hkv;
-        hk = pair - b * p.Hkv;
-    }
-    const int key0 = cb * 128 + w * 32, my_key = key0 + col;
+    const int key0 = cb * KEYS + wk * 32, my_key = key0 + col;
     const int ld_key = min(my_key, Tk - 1);
 
     // B operands of the score MFMAs: column = key, k-elements = the 8 dims of chunk 2*ks + h
@@ -574,50 +708,62 @@ __device__ __forceinline__ void bwd_dk_dv(const PrefillBwdParams &p, const int i
     const BwdLaneOffsets<D> lo(lane);
 
     // row tiles that hold a row which sees a key of this block: rows i >= key - off
-    const int rt_lo = CAUSAL ? max(cb * 128 - off, 0) / kTileRows : 0;
+    const int rt_lo = CAUSAL ? max(cb * KEYS - off, 0) / kTileRows : 0;
     const int n_rt = (T + kTileRows - 1) / kTileRows;
     // window: rows up to (last key of the block) - off + window - 1. A block no row sees at all
     // (keys before every window) still visits one tile, with every pair masked: zeros.
     const int rt_hi =
-        WINDOW ? max(min(n_rt, (min(cb * 128 + 127, Tk - 1) - off + p.window + kTileRows - 1) / kTileRows), rt_lo + 1)
+        WINDOW ? max(min(n_rt, (min(cb * KEYS + KEYS - 1, Tk - 1) - off + p.window + kTileRows - 1) / kTileRows), rt_lo + 1)
                : n_rt;
     const int per_head = rt_hi - rt_lo;
     int n_items = per_head * G;  // (head of the group, row tile)
     // Row tiles in which every (row, key) pair counts -- all rows exist and see every key of the
     // block, and the key block is complete -- need no masks. The items are taken in an order that
     // puts those of all heads first, so that the two forms of the pipeline are two loops.
-    const int rt_full_lo = max(CAUSAL ? max(cb * 128 + 127 - off + kTileRows - 1, 0) / kTileRows : 0, rt_lo);
+    const int rt_full_lo = max(CAUSAL ? max(cb * KEYS + KEYS - 1 - off + kTileRows - 1, 0) / kTileRows : 0, rt_lo);
     // (window: the first key of the block is the first to drop out of a row's window)
     const int rt_full_hi =
-        (cb + 1) * 128 <= Tk ? (WINDOW ? min(T, max(cb * 128 - off + p.window, 0)) : T) / kTileRows : 0;
+        (cb + 1) * KEYS <= Tk ? (WINDOW ? min(T, max(cb * KEYS - off + p.window, 0)) : T) / kTileRows : 0;
     const int full_per_head = max(rt_full_hi - rt_full_lo, 0);
     const int n_full_items = full_per_head * G;
-    const int rest_per_head = per_head - full_per_head;
     // Block-sparse: the items are, head after head of the group, the two row tiles of every row
     // block in the head's column list (entry = 4 * row block + flags; flag bit t: the row block
     // lists key tile 2 * cb + t). A cursor walks the lists; items are decoded in order, once each.
     using const_i32 = const __attribute__((address_space(4))) int32_t;
-    const int n_cb = (Tk + 127) / 128, n_rb = (T + 127) / 128;
+    const int n_rb = (T + 127) / 128;
     auto col_list = [&](int g, int &first, int &end) __attribute__((always_inline)) {
-        const int hq = hk * G + g;
-        const int sb = p.sparse_batch > 1 ? b : 0, sh = p.sparse_heads > 1 ? hq : 0;
-        const int64_t e = ((int64_t)sb * p.sparse_heads + sh) * n_cb + cb;
-        const_i32 *col_ptr = (const_i32 *)(uintptr_t)p.sparse_col_ptr;
-        first = col_ptr[e];
-        end = max(col_ptr[e + 1], first);
+        const ColumnList list(p, b, hk * G + g, cb * KEYS / 128);
+        first = list.first, end = list.end;
     };
+    // (PAIR: a workgroup's keys are one key tile, and it takes only the entries that list it)
     int cur_g = 0, cur_pos = 0, cur_end = 0, cur_half = 0;  // the cursor: next item to decode
+    auto entry_at = [&](int pos) __attribute__((always_inline)) { return ((const_i32 *)(uintptr_t)p.sparse_col_idx)[pos]; };
+    auto settle = [&]() __attribute__((always_inline)) {  // the cursor onto the next entry to take
+        for (;;) {
+            while (cur_pos == cur_end && ++cur_g < G) col_list(cur_g, cur_pos, cur_end);
+            if (!PAIR || cur_g >= G || ((entry_at(cur_pos) >> (cb & 1)) & 1) != 0) break;
+            ++cur_pos;
+        }
+    };
     if constexpr (SPARSE) {
         n_items = 0;
         for (int g = 0; g < G; ++g) {
             int first, end;
             col_list(g, first, end);
-            n_items += 2 * (end - first);
+            if constexpr (PAIR) {
+                for (int pos = first; pos < end; pos += 64) {
+                    const int entry = pos + lane < end ? p.sparse_col_idx[pos + lane] : 0;
+                    n_items += 2 * __popcll(__ballot((entry >> (cb & 1)) & 1));
+                }
+            } else {
+                n_items += 2 * (end - first);
+            }
         }
+        n_items = __builtin_amdgcn_readfirstlane(n_items);
         cur_g = -1;
-        while (cur_pos == cur_end && ++cur_g < G) col_list(cur_g, cur_pos, cur_end);  // first non-empty list
+        settle();
         if (n_items == 0) {  // (workgroup-uniform) nobody lists these keys: zero gradients
-            if (my_key < Tk) {
+            if (my_key < Tk && half == 0) {
                 __bf16 *dk_row = (__bf16 *)p.dk + b * p.dks[0] + hk * p.dks[1] + my_key * p.dks[2];
                 __bf16 *dv_row = (__bf16 *)p.dv + b * p.dvs[0] + hk * p.dvs[1] + my_key * p.dvs[2];
 #pragma unroll
@@ -631,55 +777,45 @@ __device__ __forceinline__ void bwd_dk_dv(const PrefillBwdParams &p, const int i
     }
     // decodes the item under the cursor into (head of the group, row tile, flags) and moves on
     auto next_sparse_item = [&](int &g, int &rt, int &flags) __attribute__((always_inline)) {
-        const int entry = ((const_i32 *)(uintptr_t)p.sparse_col_idx)[cur_pos];
+        const int entry = entry_at(cur_pos);
         g = cur_g;
         rt = 2 * min(max(entry >> 2, 0), n_rb - 1) + cur_half;
         flags = entry & 3;
         cur_half ^= 1;
         if (cur_half == 0) {
             ++cur_pos;
-            while (cur_pos == cur_end && ++cur_g < G) col_list(cur_g, cur_pos, cur_end);
+            settle();
         }
     };
-    auto item_of = [&](int it, int &g, int &rt) __attribute__((always_inline)) {
-        if (it < n_full_items) {
-            g = it / full_per_head;
-            rt = rt_full_lo + it % full_per_head;
+    // The items in order: (head, row tile) of the next one to fetch. Kept by steps, not worked out from the
+    // number of the item: two divisions by a runtime value stand in front of a step's first matrix
+    // instruction.
+    int nx_g = 0, nx_rt = n_full_items > 0 ? rt_full_lo : rt_lo;
+    bool nx_full = n_full_items > 0;
+    auto rest_from = [&](int rt) __attribute__((always_inline)) {  // a head's tiles before, then after, its full ones
+        return rt == rt_full_lo ? rt + full_per_head : rt;
+    };
+    if (!nx_full) nx_rt = rest_from(nx_rt);
+    auto next_item = [&](int &g, int &rt) __attribute__((always_inline)) {
+        g = nx_g, rt = nx_rt++;
+        if (nx_full) {  // (workgroup-uniform)
+            if (nx_rt == rt_full_hi) {
+                nx_full = ++nx_g < G;
+                nx_rt = nx_full ? rt_full_lo : rest_from(rt_lo);
+                if (!nx_full) nx_g = 0;
+            }
         } else {
-            const int j = it - n_full_items;
-            g = j / rest_per_head;
-            const int k = j % rest_per_head;  // the head's tiles before, then after, its full ones
-            rt = rt_lo + k + (k >= rt_full_lo - rt_lo ? full_per_head : 0);
+            nx_rt = rest_from(nx_rt);
+            if (nx_rt >= rt_hi) ++nx_g, nx_rt = rest_from(rt_lo);
         }
     };
 
     const uint32_t lds_base = lds_byte_address(lds);
-    auto issue_item_at = [&](int g, int rt, int stage) __attribute__((always_inline)) {
-        const int hq = hk * G + g;
-        const int64_t head = ((int64_t)b * p.Hq + hq) * T;
-        const uint32_t s0 = lds_base + (uint32_t)(stage * STAGE_CHUNKS) * 16u;
-        load_tile64<D>((const __bf16 *)p.q + b * p.qs[0] + hq * p.qs[1], p.qs[2], rt * kTileRows, T, s0, w, lane);
-        load_tile64<D>((const __bf16 *)p.r + b * p.rs[0] + hq * p.rs[1], p.rs[2], rt * kTileRows, T,
-                       s0 + (uint32_t)TL::CHUNKS * 16u, w, lane);
-        load_tile64<D>((const __bf16 *)p.d_o + b * p.gs[0] + hq * p.gs[1], p.gs[2], rt * kTileRows, T,
-                       s0 + (uint32_t)(2 * TL::CHUNKS) * 16u, w, lane);
-        if (w == 0) {  // the rows' scalars, one float4 per lane
-            const f32x4 *src = (const f32x4 *)p.row_cache + head + min(rt * kTileRows + lane, T - 1);
-            tile_load16<64>(src, s0 + (uint32_t)(3 * TL::CHUNKS) * 16u);
-        }
-    };
     // The three items in flight: (head, row tile, flags) of item it, it + 1 and it + 2.
     int it_g[3] = {0, 0, 0}, it_rt[3] = {0, 0, 0}, it_flags[3] = {3, 3, 3};
-    auto issue_item = [&](int it, int stage, int slot) __attribute__((always_inline)) {
-        if constexpr (SPARSE)
-            next_sparse_item(it_g[slot], it_rt[slot], it_flags[slot]);
-        else
-            item_of(it, it_g[slot], it_rt[slot]);
-        issue_item_at(it_g[slot], it_rt[slot], stage);
-    };
-    constexpr int kItemLoads = 3 * TL::NDMA;  // per wave (wave 0 issues one more, last)
+    constexpr int kItemLoads = 3 * TL::NDMA + 1;  // per wave
     // The unmasked loop spreads the loads of item it + 2 over the MFMA slots of a step: per-lane
-    // byte offsets inside a complete tile, wave-uniform tile bases. (There every wave fetches the
+    // byte offsets inside a complete tile, wave-uniform tile bases. (Every wave fetches the
     // 64 row scalars -- the same bytes to the same place -- so that the slots hold no branch.)
     uint32_t toffq[TL::NDMA], toffr[TL::NDMA], toffg[TL::NDMA];
 #pragma unroll
@@ -708,12 +844,39 @@ __device__ __forceinline__ void bwd_dk_dv(const PrefillBwdParams &p, const int i
             tile_load16_uniform<false>(toffq[i], dma_q, dma_lds + 1024u * i);
         else if (i < 2 * TL::NDMA)
             tile_load16_uniform<false>(toffr[i - TL::NDMA], dma_r,
-                                       dma_lds + (uint32_t)TL::CHUNKS * 16u + 1024u * (i - TL::NDMA));
+                            dma_lds + (uint32_t)TL::CHUNKS * 16u + 1024u * (i - TL::NDMA));
         else if (i < 3 * TL::NDMA)
             tile_load16_uniform<false>(toffg[i - 2 * TL::NDMA], dma_g,
-                                       dma_lds + (uint32_t)(2 * TL::CHUNKS) * 16u + 1024u * (i - 2 * TL::NDMA));
+                            dma_lds + (uint32_t)(2 * TL::CHUNKS) * 16u + 1024u * (i - 2 * TL::NDMA));
         else
             tile_load16_uniform<false>((uint32_t)lane * 16u, dma_rc, dma_lds_rc);
+    };
+    constexpr bool kPlainTiles = !(SPARSE && D == 128);  // see issue_tile of the row pass
+    auto issue_item_at = [&](int g, int rt, int stage) __attribute__((always_inline)) {
+        if (kPlainTiles && (rt + 1) * kTileRows <= T) {  // (workgroup-uniform)
+            set_dma_item(g, rt, stage);
+#pragma unroll
+            for (int i = 0; i < 3 * TL::NDMA + 1; ++i) dma_slot(i);
+            return;
+        }
+        const int hq = hk * G + g;
+        const int64_t head = ((int64_t)b * p.Hq + hq) * T;
+        const uint32_t s0 = lds_base + (uint32_t)(stage * STAGE_CHUNKS) * 16u;
+        load_tile64<D>((const __bf16 *)p.q + b * p.qs[0] + hq * p.qs[1], p.qs[2], rt * kTileRows, T, s0, w, lane);
+        load_tile64<D>((const __bf16 *)p.r + b * p.rs[0] + hq * p.rs[1], p.rs[2], rt * kTileRows, T,
+                       s0 + (uint32_t)TL::CHUNKS * 16u, w, lane);
+        load_tile64<D>((const __bf16 *)p.d_o + b * p.gs[0] + hq * p.gs[1], p.gs[2], rt * kTileRows, T,
+                       s0 + (uint32_t)(2 * TL::CHUNKS) * 16u, w, lane);
+        // the rows' scalars, one float4 per lane (every wave: as many loads in flight in each)
+        const f32x4 *src = (const f32x4 *)p.row_cache + head + min(rt * kTileRows + lane, T - 1);
+        tile_load16<64>(src, s0 + (uint32_t)(3 * TL::CHUNKS) * 16u);
+    };
+    auto issue_item = [&](int stage, int slot) __attribute__((always_inline)) {  // the next item
+        if constexpr (SPARSE)
+            next_sparse_item(it_g[slot], it_rt[slot], it_flags[slot]);
+        else
+            next_item(it_g[slot], it_rt[slot]);
+        issue_item_at(it_g[slot], it_rt[slot], stage);
     };
     // Q-tile pointer of row block rbk of a stage; the R and dO tiles follow at + CHUNKS each
     auto q_block = [&](int stage, int rbk) __attribute__((always_inline)) {
@@ -728,7 +891,8 @@ __device__ __forceinline__ void bwd_dk_dv(const PrefillBwdParams &p, const int i
     for (int n = 0; n < NDB; ++n) dk[n] = dv[n] = zero16();
 
     // fragments in flight
-    constexpr int NF1 = 3 * KSTEPS, NF2 = 6 * NDB, LA = 5;  // (5 against 3: 1 % on the config-4 pass)
+    constexpr int NF1 = 3 * KSTEPS, NF2 = 6 * NDB;
+    constexpr int LA = D == 128 ? 5 : 3;  // (d = 128: 5 against 3, 1 % of the pass at 4 x 4096; d = 64: 5 would spill)
     u32x4 f1[NF1], f2[NF2];
     auto load_f1 = [&](const u32x4 *qblk, int f) __attribute__((always_inline)) {  // (k-step, Q / R / dO chunk)
         f1[f] = qblk[(f % 3) * TL::CHUNKS + lo.nt[f / 3]];
@@ -745,7 +909,7 @@ __device__ __forceinline__ void bwd_dk_dv(const PrefillBwdParams &p, const int i
             load_f1(next_blk, g);
         else if (g < NF1 + NF2)
             load_f2(cur_blk, g - NF1);
-        else
+        else if constexpr (!PAIR)  // (PAIR: the block after is in the item that is still on its way)
             load_f1(after_blk, g - NF1 - NF2);
     };
 
@@ -797,7 +961,7 @@ __device__ __forceinline__ void bwd_dk_dv(const PrefillBwdParams &p, const int i
     // offsets [lo, hi) relative to row_base + 4h
     auto row_window = [&](int row_base, int flags, int &neg_lo, unsigned &span) __attribute__((always_inline)) {
         // (block-sparse: a row block that does not list this wave's key tile -- none of its rows)
-        const bool listed = !SPARSE || ((flags >> (w >> 1)) & 1) != 0;
+        const bool listed = !SPARSE || PAIR || ((flags >> (w >> 1)) & 1) != 0;
         const int first_row = (my_key < Tk && listed) ? (CAUSAL ? max(my_key - off, 0) : 0) : T;  // no row at all
         const int end_row = WINDOW ? min(T, max(my_key - off + p.window, 0)) : T;
         const int lo_off = max(first_row - row_base - 4 * h, 0);
@@ -824,9 +988,9 @@ __device__ __forceinline__ void bwd_dk_dv(const PrefillBwdParams &p, const int i
                 if (sl < 3 * TL::NDMA + 1) dma_slot(sl);
             f32x16 &dst = which == 0 ? n1 : which == 1 ? n2 : na;
             if (ks == 0)
-                mfma32_scores_first<true>(dst, f1[sl], which == 2 ? vf[ks] : kf[ks]);
+                mfma32_scores_first<true, kAccB<D>>(dst, f1[sl], which == 2 ? vf[ks] : kf[ks]);
             else
-                mfma32_scores<true>(dst, f1[sl], which == 2 ? vf[ks] : kf[ks]);
+                mfma32_scores<true, kAccB<D>>(dst, f1[sl], which == 2 ? vf[ks] : kf[ks]);
             prefetch(sl, next_blk, cur_blk, after_blk);
             elem_stages(masked_tag, c1, c2, ca, rows_cur, 8, sl, 0, SLOTS1, nlo_c, span_c);
             if (sl == SLOTS1 - 2) {
@@ -863,22 +1027,16 @@ __device__ __forceinline__ void bwd_dk_dv(const PrefillBwdParams &p, const int i
     // Ring invariant at the top of iteration it: items it and (after the barrier) it + 1 are in
     // stages it % 3 and (it + 1) % 3; the barrier also proves that nobody reads item it - 1 any
     // more, whose stage then receives item it + 2.
-    issue_item(0, 0, 0);
-    if (n_items > 1) issue_item(1, 1, 1);
-    // item 0 has landed (loads complete in order; wave 0 has one more in flight per item)
-    if (n_items > 1) {
-        if (w == 0)
-            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kItemLoads + 1) : "memory");
-        else
-            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kItemLoads) : "memory");
-    } else {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    }
-    __syncthreads();
+    issue_item(0, 0);
+    if (n_items > 1) issue_item(1, 1);
+    if (n_items > 1)
+        tile_barrier<kItemLoads>();  // item 0 has landed (loads complete in order)
+    else
+        tile_barrier<0>();
     f32x16 a1, a2, a3, b1, b2, b3;
     {
-        // prologue: scores of row block 0 of item 0; its lower 16 rows -> w, g1, g2
-        const u32x4 *blk = q_block(0, 0);
+        // prologue: scores of row block 0 (PAIR: half) of item 0; its lower 16 rows -> w, g1, g2
+        const u32x4 *blk = q_block(0, half);
         a1 = a2 = a3 = zero16();
 #pragma unroll
         for (int ks = 0; ks < KSTEPS; ++ks) {
@@ -888,69 +1046,82 @@ __device__ __forceinline__ void bwd_dk_dv(const PrefillBwdParams &p, const int i
         }
         int nlo;
         unsigned span;
-        row_window(it_rt[0] * kTileRows, it_flags[0], nlo, span);
+        row_window(it_rt[0] * kTileRows + half * kBlk, it_flags[0], nlo, span);
 #pragma unroll
         for (int sl = 0; sl < 16; ++sl)
-            elem_stages(std::true_type{}, a1, a2, a3, row_scalars(0, 0), 0, sl, 0, 16, nlo, span);
+            elem_stages(std::true_type{}, a1, a2, a3, row_scalars(0, half), 0, sl, 0, 16, nlo, span);
         pw[0] = pack_w();
         pg1[0] = pack_group(a3, 0);
         pg2[0] = pack_group(a2, 0);
+        if constexpr (!PAIR)
 #pragma unroll
-        for (int f = 0; f < LA; ++f) load_f1(q_block(0, 1), f);
+            for (int f = 0; f < LA; ++f) load_f1(q_block(0, 1), f);
     }
     int stage = 0;
-    auto item_steps = [&](auto masked_tag, auto dma_tag, int it) __attribute__((always_inline)) {
-        constexpr bool DMA = decltype(dma_tag)::value;
+    auto item_steps = [&](auto masked_tag, auto dma_tag, int it, f32x16 &a1, f32x16 &a2, f32x16 &a3, f32x16 &b1,
+                          f32x16 &b2, f32x16 &b3) __attribute__((always_inline)) {
         const int next_stage = stage == STAGES - 1 ? 0 : stage + 1;
         const int free_stage = stage == 0 ? STAGES - 1 : stage - 1;
         tile_barrier<0>();  // item it + 1 has landed; item it - 1 is free
         // (items it, it + 1, it + 2 sit in slots 0, 1, 2 of the item record)
-        if constexpr (DMA) {  // item it + 2 is a complete tile: fetched by the first step, slot by slot
-            item_of(it + 2, it_g[2], it_rt[2]);
+        if constexpr (decltype(dma_tag)::value) {  // item it + 2 is a complete tile
+            next_item(it_g[2], it_rt[2]);
             set_dma_item(it_g[2], it_rt[2], free_stage);
         } else {
-            if (it + 2 < n_items) issue_item(it + 2, free_stage, 2);
+            if (it + 2 < n_items) issue_item(free_stage, 2);
         }
         const int row_base = it_rt[0] * kTileRows, row_base_after = it_rt[1] * kTileRows;  // (past the end: never used)
         const int flags = it_flags[0], flags_after = it_flags[1];
-        // row block 0 -> w, g; dV / dK; scores of row block 1; fragments of the next item
-        pipeline_step(masked_tag, dma_tag, row_base, flags, row_base + kBlk, flags, q_block(stage, 1), q_block(stage, 0),
-                      q_block(next_stage, 0), row_scalars(stage, 0), row_scalars(stage, 1), a1, a2, a3, b1, b2,
-                      b3);
-        // row block 1 -> w, g; dV / dK; scores of row block 0 of the next item
-        pipeline_step(masked_tag, std::false_type{}, row_base + kBlk, flags, row_base_after, flags_after,
-                      q_block(next_stage, 0), q_block(stage, 1),
-                      q_block(next_stage, 1), row_scalars(stage, 1), row_scalars(next_stage, 0), b1, b2, b3, a1,
-                      a2, a3);
+        if constexpr (PAIR) {
+            // row block `half` -> w, g; dV / dK; scores of that of the next item, whose first fragments are read now
+            const u32x4 *next_blk = q_block(next_stage, half);
+#pragma unroll
+            for (int f = 0; f < LA; ++f) load_f1(next_blk, f);
+            pipeline_step(masked_tag, dma_tag, row_base + half * kBlk, flags, row_base_after + half * kBlk, flags_after,
+                          next_blk, q_block(stage, half), nullptr, row_scalars(stage, half),
+                          row_scalars(next_stage, half), a1, a2, a3, b1, b2, b3);
+        } else {
+            // row block 0 -> w, g; dV / dK; scores of row block 1; fragments of the next item
+            pipeline_step(masked_tag, dma_tag, row_base, flags, row_base + kBlk, flags, q_block(stage, 1),
+                          q_block(stage, 0), q_block(next_stage, 0), row_scalars(stage, 0), row_scalars(stage, 1), a1,
+                          a2, a3, b1, b2, b3);
+            // row block 1 -> w, g; dV / dK; scores of row block 0 of the next item
+            pipeline_step(masked_tag, std::false_type{}, row_base + kBlk, flags, row_base_after, flags_after,
+                          q_block(next_stage, 0), q_block(stage, 1), q_block(next_stage, 1), row_scalars(stage, 1),
+                          row_scalars(next_stage, 0), b1, b2, b3, a1, a2, a3);
+        }
         stage = next_stage;
 #pragma unroll
         for (int j = 0; j < 2; ++j) it_g[j] = it_g[j + 1], it_rt[j] = it_rt[j + 1], it_flags[j] = it_flags[j + 1];
     };
     // a step also prepares the lower half of the next item's first block, and the unmasked loop
     // fetches item it + 2 as a complete tile: it stops two short of the last unmasked item
-    int it = 0;
-    if constexpr (!SPARSE)
-        for (; it < n_full_items - 2; ++it) item_steps(std::false_type{}, std::true_type{}, it);
-    for (; it < n_items; ++it) item_steps(std::true_type{}, std::false_type{}, it);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no tile load may land after the workgroup ends
-
-    // dK^T / dV^T register r of block n <-> dim 32n + 8*(r/4) + 4h + r%4 of key my_key
-    if (my_key < Tk) {
-        __bf16 *dk_row = (__bf16 *)p.dk + b * p.dks[0] + hk * p.dks[1] + my_key * p.dks[2];
-        __bf16 *dv_row = (__bf16 *)p.dv + b * p.dvs[0] + hk * p.dvs[1] + my_key * p.dvs[2];
-#pragma unroll
-        for (int n = 0; n < NDB; ++n)
-#pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) {
-                const int dim = 32 * n + 8 * q4 + 4 * h;
-                const u32x2 a = {pack_bf16(dk[n][4 * q4], dk[n][4 * q4 + 1]),
-                                 pack_bf16(dk[n][4 * q4 + 2], dk[n][4 * q4 + 3])};
-                const u32x2 c = {pack_bf16(dv[n][4 * q4], dv[n][4 * q4 + 1]),
-                                 pack_bf16(dv[n][4 * q4 + 2], dv[n][4 * q4 + 3])};
-                *(u32x2 *)(dk_row + dim) = a;
-                *(u32x2 *)(dv_row + dim) = c;
+    // (PAIR: an even number of items a loop, the odd last one by itself, as in the row pass)
+    auto run_items = [&](auto masked_tag, auto dma_tag, int &it, int end) __attribute__((always_inline)) {
+        while (it < end) {
+            item_steps(masked_tag, dma_tag, it, a1, a2, a3, b1, b2, b3);
+            ++it;
+            if constexpr (PAIR) {
+                item_steps(masked_tag, dma_tag, it, b1, b2, b3, a1, a2, a3);
+                ++it;
             }
+        }
+    };
+    int it = 0;
+    if constexpr (!SPARSE) run_items(std::false_type{}, std::true_type{}, it, PAIR ? max(n_full_items - 2, 0) & ~1 : n_full_items - 2);
+    run_items(std::true_type{}, std::false_type{}, it, PAIR ? n_items & ~1 : n_items);
+    if (PAIR && it < n_items) {
+        item_steps(std::true_type{}, std::false_type{}, it, a1, a2, a3, b1, b2, b3);
+        asm volatile("" ::"v"(b1), "v"(b2), "v"(b3));  // (unused, but nothing else may move in before they are written)
     }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no tile load may land behind this
+    __syncthreads();                                  // the ring is free
+
+    if constexpr (PAIR) swap_halves<D>(dk, dv, w, half, lane, lds);
+    __bf16 *dk_base = (__bf16 *)p.dk + b * p.dks[0] + hk * p.dks[1] + key0 * p.dks[2];
+    __bf16 *dv_base = (__bf16 *)p.dv + b * p.dvs[0] + hk * p.dvs[1] + key0 * p.dvs[2];
+    if (!PAIR || half == 0) store_rows<D>(dk, 1.f, dk_base, p.dks[2], Tk - key0, w, lane, lds);
+    if (!PAIR || half == 1) store_rows<D>(dv, 1.f, dv_base, p.dvs[2], Tk - key0, w, lane, lds);
 }
 
 // Both passes in one launch, the column pass's workgroups (the longer ones) first: they need nothing from
@@ -958,48 +1129,107 @@ __device__ __forceinline__ void bwd_dk_dv(const PrefillBwdParams &p, const int i
 // end, and from the start where there are fewer key blocks than units. Two launches in a row
 // against one, us for the whole backward, 16 query / 8 key heads, d = 128, causal: 1 x 300 rows 54 -> 38,
 // 1 x 1000 117 -> 87, 1 x 2048 212 -> 162, 4 x 1000 152 -> 133, 4 x 4096 1419 -> 1401; same bits.
-// d = 64 with full attention and block lists pays for it when nearly every tile is listed: its row pass alone
-// fitted twice into a compute unit (256 registers; together 275, and held to 256 109 of them spill). 2 x 2048
-// rows, every tile 225 -> 234, a quarter 133 -> 124; 2 x 4096, a quarter 433 -> 386; 1 x 700 60 -> 48. What
-// share is listed the host does not know.
-template <int D, bool CAUSAL, bool WINDOW, bool SPARSE>
-__global__ __launch_bounds__(256, 1) void bwd_passes_kernel(PrefillBwdParams p, int n_columns) {
+// d = 64: two workgroups per compute unit (77 KB of LDS, 256 registers a wave), so that the vector work of one,
+// which takes as long as its matrix work there, runs under the matrix instructions of the other: 32 / 16
+// heads, 4 x 4096 1677 -> 1430 us, 3 x 1111 137 -> 111, 2 x 2048 with a quarter of the tiles listed 146 -> 104.
+// PAIR: a workgroup owns 64 keys (column pass) or 64 rows (row pass) instead of 128, two waves share 32 of them,
+// and each takes one 32-row half of every tile it streams; their sums are added at the end. The
+// chain of a workgroup is half as long for twice as many workgroups, and with block lists a column
+// workgroup's keys are one key tile, so that nobody walks a tile that only its neighbour lists. Against that a
+// tile serves half the work per load, and the first operands of a step are read only behind its barrier.
+// Which form: backward_plan.
+template <int D, bool CAUSAL, bool WINDOW, bool SPARSE, bool PAIR_C, bool PAIR_R>
+__global__ __launch_bounds__(256, D == 64 ? 2 : 1) void bwd_passes_kernel(PrefillBwdParams p, int n_columns) {
     __shared__ u32x4 lds[kBwdLdsChunks<D>];
     const int id = blockIdx.x;
-    if (id < n_columns)
-        bwd_dk_dv<D, CAUSAL, WINDOW, SPARSE>(p, id, lds);
+    if (id >= n_columns) {
+        bwd_dq_dr<D, CAUSAL, WINDOW, SPARSE, PAIR_R>(p, id - n_columns, lds);
+        return;
+    }
+    if constexpr (D == 64) __builtin_amdgcn_s_setprio(2);  // the longer ones first, where two share a unit
+    int cb, hk, b;
+    column_item(p, id, cb, hk, b);
+    bwd_dk_dv<D, CAUSAL, WINDOW, SPARSE, PAIR_C>(p, cb, hk, b, lds);
+}
+
+// The form of a launch, from estimates in us: `chain`, the longest column workgroup (2.4 us per 64 rows x 128
+// keys at d = 128 and 9 to start and end; 1.3 and 5 at d = 64), against `load`, all workgroups dealt evenly over the
+// chip (row pass: 1.75 and 1.0 per tile). Halved chains pay where the longest one is what the launch waits for. us
+// in the whole form / with PAIR columns, chain / load in brackets; 16 / 8 heads, d = 128: 4 x 4096 (0.26) 1337 /
+// 1430, 2 x 2048 full attention (0.56) 324 / 348, 3 x 1111 (1.03) 107 / 118, 4 x 600 (1.19) 63 / 66; 1 x 3000 (1.36)
+// 237 / 217, 1 x 2000 (1.93) 154 / 109, 4 x 300 (1.62) 37 / 30, 1 x 1000 (3.4) 79 / 55; 32 / 16, d = 64: 3 x 1111 (0.50)
+// 111 / 114; 1 x 3000 (0.67) 229 / 224, 4 x 500 (0.68) 48 / 43, 1 x 1000 (1.65) 65 / 46.
+// One query head per key head: the row workgroups' chains are then as long, and are halved too (8 / 8 heads,
+// whole / columns / both: d = 64, 2 x 2000 73 / 67 / 61, 1 x 3000 92 / 78 / 68; d = 128, 1 x 2000 81 / 73 / 66),
+// but for a sliding window (d = 64, 1 x 2500, 500 keys: 31 / 28 / 32).
+// Block lists: what share is listed the host does not know. With full lists PAIR costs up to a tenth (d = 128, 2 x
+// 2048: 218 -> 231, 4 x 4096 1508 -> 1655), at half of the tiles and below it gains (2 x 2048: a half 176 -> 153, a
+// quarter 141 -> 115, 0.15 101 -> 99): taken from a chain of half the load on (as if all were listed), and
+// always at d = 64 (3 x 2048 a quarter 162 -> 154, all 326 -> 348; the one-per-unit form 223 and 406).
+// From 4096 rows on every launch takes the whole form: the two add a gradient's terms in different orders, and
+// there a sequence's gradients are to have the same bits whatever else is in the launch.
+struct BackwardPlan {
+    bool pair_c, pair_r;
+};
+static BackwardPlan backward_plan(const PrefillBwdParams &p, int num_cus) {
+    const bool sparse = p.sparse_row_ptr != nullptr, windowed = p.causal && p.window > 0 && p.window < p.Tk;
+    const double per_item = p.d == 128 ? 2.4 : 1.3, per_tile = p.d == 128 ? 1.75 : 1.0, fixed = p.d == 128 ? 9.0 : 5.0;
+    const double T = p.T, Tk = p.Tk, heads = (double)p.B * p.Hq, kv_heads = (double)p.B * p.Hkv, G = p.G;
+    const double row_blocks = std::ceil(T / 128), key_blocks = std::ceil(Tk / 128);
+    // tiles that the longest column (row) workgroup walks, per head, and cells of 64 x 128 in all
+    const double span = windowed ? (p.window + 127.0) / 64 : 1e30;
+    const double col_tiles = std::min(std::ceil(T / 64), span), row_tiles = std::min(std::ceil(Tk / 64), span);
+    const double pairs = windowed ? T * p.window : p.causal ? T * (Tk - T) + T * T / 2 : T * Tk;
+    const double cells = pairs / (64 * 128);
+    const double chain = G * col_tiles * per_item + fixed, row_chain = row_tiles * per_tile + fixed;
+    const double load = (heads * ((cells + (p.causal ? key_blocks : 0)) * per_item + (cells + (p.causal ? row_blocks : 0)) * per_tile) +
+                         fixed * (heads * row_blocks + kv_heads * key_blocks)) / num_cus;
+    BackwardPlan plan{};
+    if (p.T >= 4096) return plan;
+    if (sparse)
+        plan.pair_c = p.d == 64 || chain > 0.5 * load;
     else
-        bwd_dq_dr<D, CAUSAL, WINDOW, SPARSE>(p, id - n_columns, lds);
+        plan.pair_c = chain > (p.d == 128 ? 1.3 : 0.6) * load && chain >= row_chain;
+    plan.pair_r = plan.pair_c && !sparse && p.window <= 0 && 3 * row_tiles > 2 * G * col_tiles;
+    return plan;
 }
 
 template <int D>
-static hipError_t launch_bwd_d(const PrefillBwdParams &p, hipStream_t stream) {
+static hipError_t launch_bwd_d(const PrefillBwdParams &p, int num_cus, hipStream_t stream) {
+    const BackwardPlan plan = backward_plan(p, num_cus);
+    const int keys = plan.pair_c ? 64 : 128, rows = plan.pair_r ? 64 : 128;
     const long long n_rows = (long long)p.B * p.Hq * p.T;
     constexpr int kPrepRows = 2048 / D;  // rows per workgroup of the rows-prepare kernel
     const long long g0 = (n_rows + kPrepRows - 1) / kPrepRows;
-    const long long g1 = (long long)((p.T + 127) / 128) * p.Hq * p.B;
-    const long long g2 = (long long)((p.Tk + 127) / 128) * p.Hkv * p.B;
+    const long long g1 = (long long)((p.T + rows - 1) / rows) * p.Hq * p.B;
+    const long long g2 = (long long)((p.Tk + keys - 1) / keys) * p.Hkv * p.B;
     if (g0 > 0x7fffffffLL || g1 + g2 > 0x7fffffffLL) return hipErrorInvalidValue;
     hipLaunchKernelGGL((bwd_rows_prepare_kernel<D>), dim3((unsigned)g0), dim3(256), 0, stream, p);
     const dim3 grid((unsigned)(g1 + g2)), block(256);
     const int cols = (int)g2;
-    if (p.sparse_row_ptr != nullptr) {  // block lists (no window; checked by the caller)
-        if (p.causal)
-            hipLaunchKernelGGL((bwd_passes_kernel<D, true, false, true>), grid, block, 0, stream, p, cols);
-        else
-            hipLaunchKernelGGL((bwd_passes_kernel<D, false, false, true>), grid, block, 0, stream, p, cols);
-    } else if (p.causal && p.window > 0) {
-        hipLaunchKernelGGL((bwd_passes_kernel<D, true, true, false>), grid, block, 0, stream, p, cols);
-    } else if (p.causal) {
-        hipLaunchKernelGGL((bwd_passes_kernel<D, true, false, false>), grid, block, 0, stream, p, cols);
-    } else {
-        hipLaunchKernelGGL((bwd_passes_kernel<D, false, false, false>), grid, block, 0, stream, p, cols);
-    }
-    return hipGetLastError();
+    const std::true_type yes;
+    const std::false_type no;
+    auto run = [&](auto causal, auto window, auto sparse, auto pair_c, auto pair_r) {
+        hipLaunchKernelGGL((bwd_passes_kernel<D, decltype(causal)::value, decltype(window)::value, decltype(sparse)::value,
+                                              decltype(pair_c)::value, decltype(pair_r)::value>),
+                           grid, block, 0, stream, p, cols);
+        return hipGetLastError();
+    };
+    auto dense = [&](auto causal) {
+        if (plan.pair_r) return run(causal, no, no, yes, yes);
+        return plan.pair_c ? run(causal, no, no, yes, no) : run(causal, no, no, no, no);
+    };
+    auto lists = [&](auto causal) {
+        return plan.pair_c ? run(causal, no, yes, yes, no) : run(causal, no, yes, no, no);
+    };
+    if (p.sparse_row_ptr != nullptr) return p.causal ? lists(yes) : lists(no);  // (no window; checked by the caller)
+    if (p.causal && p.window > 0)
+        return plan.pair_c ? run(yes, yes, no, yes, no) : run(yes, yes, no, no, no);
+    return p.causal ? dense(yes) : dense(no);
 }
 
-hipError_t launch_prefill_bwd_bf16(const PrefillBwdParams &p, hipStream_t stream) {
-    return p.d == 128 ? launch_bwd_d<128>(p, stream) : launch_bwd_d<64>(p, stream);
+hipError_t launch_prefill_bwd_bf16(const PrefillBwdParams &p, int num_cus, hipStream_t stream) {
+    return p.d == 128 ? launch_bwd_d<128>(p, num_cus, stream) : launch_bwd_d<64>(p, num_cus, stream);
 }
 
 }  // namespace plx

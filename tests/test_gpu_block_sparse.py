@@ -178,6 +178,33 @@ def test_backward_random_block_masks_shared_by_all_heads(plx, synth, masked, T, 
     _check_backward(plx, synth, masked, y, bm, causal, seed=3600 + T)
 
 
+@pytest.mark.parametrize("B,T,Tkv,d,causal", [(96, 300, 300, 128, True), (96, 130, 200, 128, False), (2, 300, 300, 64, True),
+                                              (2, 129, 385, 64, False), (2, 385, 385, 128, True)])
+def test_backward_forms_of_a_launch_with_lists(plx, synth, masked, B, T, Tkv, d, causal):
+    """Launches that fill the chip (a workgroup takes two key tiles and the entries that list either) and
+    small ones (one key tile, the entries that list it), lists per head, entries for one tile, both, none."""
+    Hq, Hkv = 4, 2
+    y = synth.prefill_inputs(2, Hq, Hkv, Tkv, d, seed=3300 + T, device=DEV)
+    if Tkv > T:
+        y["q"], y["r"] = y["q"][:, :, Tkv - T:].contiguous(), y["r"][:, :, Tkv - T:].contiguous()
+    nrb, nkt = -(-T // 128), -(-Tkv // 64)
+    bm = np.random.default_rng(3301 + T).random((1, Hq, nrb, nkt)) < 0.5
+    bm[0, 1, :, 1] = False
+    bm[0, 0, 0], bm[0, 0, :, 0] = True, True
+    small = _check_backward(plx, synth, masked, y, bm, causal, seed=3620)
+    if B > 2:  # the same two sequences, repeated: every copy like the small launch up to the order of the sums
+        g = synth.prefill_inputs(2, Hq, Hkv, T, d, seed=3620, device=DEV)["q"].contiguous()
+        t = {n: y[n].repeat(B // 2, 1, 1, 1) for n in "qrkv"}
+        m = torch.as_tensor(bm, device=DEV)
+        o, vbar, stats = plx.parallax_prefill(t["q"], t["r"], t["k"], t["v"], y["scale"], causal=causal, block_mask=m,
+                                              save_for_backward=True)
+        big = plx.parallax_prefill_backward(t["q"], t["r"], t["k"], t["v"], o, vbar, stats, g.repeat(B // 2, 1, 1, 1),
+                                            y["scale"], causal=causal, block_mask=m)
+        for name, got, ref in zip(("dq", "dr", "dk", "dv"), big, small):
+            for i in (0, B // 2 - 1):
+                assert_gradient_close(name, host(got[2 * i:2 * i + 2]), host(ref).astype(np.float64), 2.0 ** -8, (i,))
+
+
 def test_backward_per_batch_and_per_head_masks_with_empty_blocks(plx, synth, masked):
     B, Hq, T = 2, 4, 700
     y = synth.prefill_inputs(B, Hq, 2, T, 128, seed=3100, device=DEV)
