@@ -134,9 +134,10 @@ struct NormRopeParams {
 // Each returns hipSuccess or the launch error. No allocation, no synchronisation.
 hipError_t launch_decode_bf16(const DecodeParams &p, hipStream_t stream);
 hipError_t launch_decode_combine(const DecodeParams &p, hipStream_t stream);
-hipError_t launch_prefill_bf16(const PrefillParams &p, hipStream_t stream);
-// Plans the split of a call over key ranges: 0 = not split, else the bytes of p.ws that its launch takes
-size_t plan_prefill_split_bf16(PrefillParams &p, int num_cus);
+hipError_t launch_prefill_bf16(const PrefillParams &p, int num_cus, hipStream_t stream);
+// Plans the split of a call over key ranges: 0 = none pays against the whole launch, else the bytes of p.ws that its
+// launch takes; best_form: nor is another form without a workspace quicker
+size_t plan_prefill_split_bf16(PrefillParams &p, int num_cus, bool *best_form);
 hipError_t launch_prefill_bwd_bf16(const PrefillBwdParams &p, int num_cus, hipStream_t stream);
 hipError_t launch_prefill_bwd_f32(const PrefillBwdParams &p, hipStream_t stream);
 hipError_t launch_decode_f32(const DecodeParams &p, hipStream_t stream);

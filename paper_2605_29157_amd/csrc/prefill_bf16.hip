@@ -7,13 +7,13 @@
 // keys than query rows the rows are the last positions of the sequence, j <= i + (Tk - T).
 //
 // Layout for CDNA4:
-//   * one workgroup = 4 waves, one wave per SIMD, so a wave may use the whole 512-register
+//   * one workgroup = 4 waves of 32 query rows. d = 128: one wave per SIMD, so a wave may use the whole 512-register
 //     budget: O1^T, O2^T and the Q, R fragments live in the accumulation registers for the whole
 //     pass -- an MFMA can take its B operand from there -- and the vector registers hold scores,
-//     P and LDS fragments. A wave owns RW sub-blocks of 32 query rows: one at d = 128 (128 rows
-//     per workgroup); two at d = 64 (256 rows per workgroup), where the accumulators of 64 rows
-//     fit and every K / V^T fragment read from LDS then feeds four MFMAs instead of two, with
-//     half as many tile barriers and workgroups per MFMA;
+//     P and LDS fragments. d = 64: 256 registers and half of the LDS, two workgroups per compute unit, as the
+//     element-wise work takes as long as the matrix work there and one wave's runs under the other's
+//     matrix instructions (64 rows per wave, one workgroup per unit, before: 32 heads, 4 x 4096 rows 512 -> 492 us,
+//     3 x 1111 52 -> 40, 1 x 777 25 -> 16, 4 x 2048 with a window of 512 125 -> 84);
 //   * every global read is a direct global -> LDS load of whole rows (global_load_lds_dwordx4:
 //     no staging registers, no LDS write instructions): the wave's own Q and R rows once, then
 //     K/V tiles of 64 keys into a three-stage ring, fetched two tiles ahead, one load per MFMA
@@ -69,7 +69,9 @@ __host__ __device__ constexpr int64_t prefill_record_floats(int d) { return 64 *
 
 
 
-// RW: sub-blocks of 32 query rows per wave (the workgroup covers 128 * RW rows).
+// Keeps two score blocks where they are up to this point.
+__device__ __forceinline__ void keep_blocks(const f32x16 &a, const f32x16 &b) { asm volatile("" ::"v"(a), "v"(b)); }
+
 // SPLIT: a row block with many key tiles is cut into key ranges of at most p.split_tiles tiles, each a
 // workgroup of its own that writes unnormalised records instead of output rows (the split-KV form of
 // App. C, merged by prefill_combine_kernel) -- for launches with fewer row blocks than compute units.
@@ -77,15 +79,16 @@ __host__ __device__ constexpr int64_t prefill_record_floats(int d) { return 64 *
 // fragments are read (the operations the paper's language-model runs put in front of the attention
 // call: Sec. 5 experiment setup and the backbone appendix; same formulas and order of operations as
 // norm_rope.hip, the rotation taken from a table of (cos, sin) per position and pair).
-template <int D, bool USE_R, bool CAUSAL, bool WINDOW, bool STATS = false, bool SPARSE = false, int RW = 1,
-          bool PREP = false, bool SPLIT = false>
-__global__ __launch_bounds__(256, 1) void prefill_bf16_kernel(PrefillParams p) {
+// PAIR: 64 rows per workgroup. Waves w and w ^ 2 share 32 rows, each takes one 32-key half of every tile, and they add
+// their sums up at the end: half the chain for twice the workgroups, for launches that wait for their longest one.
+template <int D, bool USE_R, bool CAUSAL, bool WINDOW, bool STATS = false, bool SPARSE = false, bool PREP = false,
+          bool SPLIT = false, bool PAIR = false>
+__global__ __launch_bounds__(256, D == 64 ? 2 : 1) void prefill_bf16_kernel(PrefillParams p) {
     static_assert(!PREP || (USE_R && !WINDOW && !STATS && !SPARSE), "q / rho preparation: dense forward only");
-    static_assert(RW == 1 || (RW == 2 && D == 64), "two row sub-blocks per wave fit the registers at d = 64 only");
-    static_assert(!SPARSE || RW == 1, "block-sparse lists are per 128 query rows");
     static_assert(!SPLIT || (!WINDOW && !SPARSE && !PREP), "key ranges: dense forward only");
-    constexpr int WROWS = 32 * RW;  // query rows per wave
-    constexpr int kBR = 4 * WROWS;  // query rows per workgroup
+    constexpr int WROWS = 32;  // query rows per wave
+    constexpr int kBR = PAIR ? 2 * WROWS : 4 * WROWS;  // query rows per workgroup
+    static_assert(!PAIR || (CAUSAL && !SPARSE && !SPLIT), "two waves to 32 rows: dense causal forward");
     static_assert(CAUSAL || !WINDOW, "a sliding window needs the rows' positions");
     static_assert(!STATS || USE_R, "the row cache is written for the backward pass only");
     static_assert(!SPARSE || !WINDOW, "block-sparse: its own tile iterator, no window");
@@ -111,15 +114,17 @@ __global__ __launch_bounds__(256, 1) void prefill_bf16_kernel(PrefillParams p) {
     constexpr int STAGE_CHUNKS = K_CHUNKS + V_CHUNKS;
 
     // Behind the ring: one padded WROWS x D tile per wave. It receives the wave's Q rows at the
-    // start and stages its output rows at the end. The R rows land in ring stage 2 where they
-    // fit (RW = 1), else in a zone of their own behind the Q zone.
+    // start and stages its output rows at the end. The R rows land in ring stage 2.
     constexpr int WAVE_TILE_CHUNKS = WROWS * KROW;
-    constexpr int QZONE = STAGES * STAGE_CHUNKS;
-    constexpr bool R_IN_RING = 4 * WAVE_TILE_CHUNKS <= STAGE_CHUNKS;
-    static_assert(STAGES >= 3 && (R_IN_RING || RW > 1), "R rows land in ring stage 2");
-    constexpr int RZONE = R_IN_RING ? 2 * STAGE_CHUNKS : QZONE + 4 * WAVE_TILE_CHUNKS;
-    constexpr int LDS_CHUNKS = QZONE + (R_IN_RING ? 4 : 8) * WAVE_TILE_CHUNKS;
-    static_assert(LDS_CHUNKS * 16 <= 160 * 1024, "LDS of one compute unit");
+    // TWO (d = 64): two workgroups per compute unit. For its half of the LDS the Q zone starts in
+    // the end of stage 2 that the R rows leave free: the tile loads do not reach it before the
+    // fragments are in registers, and outputs are staged behind a barrier.
+    constexpr bool TWO = D == 64;
+    constexpr int QZONE = STAGES * STAGE_CHUNKS - (TWO ? STAGE_CHUNKS - 4 * WAVE_TILE_CHUNKS : 0);
+    static_assert(STAGES >= 3 && 4 * WAVE_TILE_CHUNKS <= STAGE_CHUNKS, "R rows land in ring stage 2");
+    constexpr int RZONE = 2 * STAGE_CHUNKS;
+    constexpr int LDS_CHUNKS = QZONE + 4 * WAVE_TILE_CHUNKS;
+    static_assert(LDS_CHUNKS * 16 <= (TWO ? 80 : 160) * 1024, "LDS of one compute unit");
     __shared__ u32x4 lds[LDS_CHUNKS];  // [stage][K tile | V tile], Q (, R)
 
     const int tid = threadIdx.x;
@@ -174,9 +179,10 @@ __global__ __launch_bounds__(256, 1) void prefill_bf16_kernel(PrefillParams p) {
     const int b = pair / p.Hkv, hk = pair - b * p.Hkv;
     const int hq = hk * G + hg;
 
-    const int row0 = rb * kBR + w * WROWS;  // first query row of this wave
-    // this lane's query row in sub-block a (may be >= T)
-    auto my_row = [&](int a) __attribute__((always_inline)) { return row0 + 32 * a + col; };
+    const int half = PAIR ? w >> 1 : 0;  // PAIR: this wave's half of every tile
+    const int row0 = rb * kBR + (PAIR ? w & 1 : w) * WROWS;  // first query row of this wave
+    // this lane's query row (may be >= T)
+    const int my_row = row0 + col;
 
     // ---- Q / R rows of this wave: global -> LDS, whole rows (a lane fetching its own MFMA
     // fragments straight from global memory would touch 64 different rows per instruction).
@@ -228,7 +234,7 @@ __global__ __launch_bounds__(256, 1) void prefill_bf16_kernel(PrefillParams p) {
             }
         }
     }
-    u32x4 qf[RW][KSTEPS], rf[RW][KSTEPS];
+    u32x4 qf[KSTEPS], rf[KSTEPS];
     // SPLIT: the first 32 keys of the sequence as MFMA operands (row col, chunk 2 * ks + h), for the
     // reference; they travel with the wave's own rows.
     u32x4 k_ref[SPLIT ? KSTEPS : 1];
@@ -296,9 +302,8 @@ __global__ __launch_bounds__(256, 1) void prefill_bf16_kernel(PrefillParams p) {
                               : max(0, min(CAUSAL ? min((rb * kBR + off + 1) / kBC, Tv / kBC) : Tv / kBC, Tk / kBC - kDist));
     // sliding window: first key this lane's row sees, and the leading tiles that hold a key
     // some row of the workgroup does not see (its last row starts latest)
-    int row_lo[RW];
-#pragma unroll
-    for (int a = 0; a < RW; ++a) row_lo[a] = WINDOW ? my_row(a) + off - p.window + 1 : 0;
+    int row_lo;
+    row_lo = WINDOW ? my_row + off - p.window + 1 : 0;
     const int n_left = WINDOW ? min(n_tiles, max(rb * kBR + kBR + off - p.window + kBC - 1, 0) / kBC) : 0;
 
     // ---- global -> LDS tile loads (no staging registers, no LDS write instructions) --------
@@ -381,31 +386,26 @@ __global__ __launch_bounds__(256, 1) void prefill_bf16_kernel(PrefillParams p) {
         }
     };
 
-    // S1^T, S2^T (32 keys x 32 rows per row sub-block) of key block kb of the tile in `stage`
-    auto scores = [&](int stage, int kb, f32x16(&s1)[RW], f32x16(&s2)[RW]) __attribute__((always_inline)) {
+    // S1^T, S2^T (32 keys x 32 rows) of key block kb of the tile in `stage`
+    auto scores = [&](int stage, int kb, f32x16 &s1, f32x16 &s2) __attribute__((always_inline)) {
         const u32x4 *tk = lds + stage * STAGE_CHUNKS + col * KROW + h;
 #pragma unroll
-        for (int a = 0; a < RW; ++a)
-#pragma unroll
             for (int r = 0; r < 16; ++r) {
-                s1[a][r] = 0.f;
-                s2[a][r] = 0.f;
+                s1[r] = 0.f;
+                s2[r] = 0.f;
             }
 #pragma unroll
         for (int ks = 0; ks < KSTEPS; ++ks) {
             const u32x4 kf = tk[kb * kKB * KROW + 2 * ks];
-#pragma unroll
-            for (int a = 0; a < RW; ++a) {
-                s1[a] = mfma32(kf, qf[a][ks], s1[a]);
-                if constexpr (USE_R) s2[a] = mfma32(kf, rf[a][ks], s2[a]);
-            }
+            s1 = mfma32(kf, qf[ks], s1);
+            if constexpr (USE_R) s2 = mfma32(kf, rf[ks], s2);
         }
     };
 
     // accumulator register r of an S^T block <-> key key_base + 8*(r/4) + 4*h + r%4
-    auto key_ok = [&](int key_base, int r, int a) __attribute__((always_inline)) {
+    auto key_ok = [&](int key_base, int r) __attribute__((always_inline)) {
         const int key = key_base + 8 * (r >> 2) + 4 * h + (r & 3);
-        return key < Tv && (!CAUSAL || key <= my_row(a) + off) && (!WINDOW || key >= row_lo[a]) && !no_tiles;
+        return key < Tv && (!CAUSAL || key <= my_row + off) && (!WINDOW || key >= row_lo) && !no_tiles;
     };
 
     // d1 / d2 are accumulated by MFMAs as well: Ones(32 x 16 keys) x P^T gives a block whose
@@ -413,37 +413,31 @@ __global__ __launch_bounds__(256, 1) void prefill_bf16_kernel(PrefillParams p) {
     // Algorithm 1 taken over exactly the numbers that enter O1 / O2 -- the effective attention
     // weights then sum to one exactly, and no vector-ALU work is spent on the sums (a dot-product
     // instruction would share the matrix pipeline and stall it; measured). One accumulator block
-    // per row sub-block serves both sums: the A operand of the P1 sum is one in rows 0..15 and
+    // serves both sums: the A operand of the P1 sum is one in rows 0..15 and
     // zero below, that of the P2 sum the other way round, so rows 0..15 of the block hold d1
     // (register 0 of every lane) and rows 16..31 hold d2 (register 8).
     // Only the masked tiles take these MFMAs; the tiles every row sees completely add the
-    // unrounded fp32 values on the vector ALU. (Measured at d = 64 with two row sub-blocks, where
-    // the vector ALU has twice the work per MFMA: the MFMA sums in every tile -- a quarter more
-    // matrix instructions -- cost what the removed adds saved and more, 537 against 514 us.)
-    // With two row sub-blocks per wave the accumulation registers are taken (O1^T, O2^T, Q, R fill
-    // three quarters of them and the rest backs the vector registers): the masked tiles then add
-    // the rounded operands with dot-product instructions against (1, 1) instead, per lane like
-    // vsum below (rsum).
-    constexpr bool MFMA_SUMS = RW == 1;
-    float m_ref[RW];
-    f32x16 o1[RW][NDB], o2[RW][NDB], dacc[MFMA_SUMS ? RW : 1];
-    float rsum1[RW] = {}, rsum2[RW] = {};                // !MFMA_SUMS: sums of rounded operands, this lane's keys
-    float vsum1[RW][2] = {}, vsum2[RW][2] = {};          // per-lane partial row sums (this lane's keys)
+    // unrounded fp32 values on the vector ALU.
+    // TWO: no registers for that block and its constants; the masked tiles add the rounded operands with
+    // dot-product instructions against (1, 1) instead, per lane like vsum below (rsum).
+    constexpr bool MFMA_SUMS = !TWO;
+    float m_ref;
+    f32x16 o1[NDB], o2[NDB], dacc;
+    float rsum1 = {}, rsum2 = {};                // !MFMA_SUMS: sums of rounded operands, this lane's keys
+    float vsum1[2] = {}, vsum2[2] = {};          // per-lane partial row sums (this lane's keys)
     // Row cache only: fp32 sums of the UNROUNDED P1, P2 over the masked tiles as well. The backward
     // pass recomputes p and u in fp32 and forms 1 + ubar - u, which is 1 for a row with one key only
     // if ubar carries no bf16 rounding of P2; the output keeps the sums of the rounded operands.
-    float msum1[RW][2] = {}, msum2[RW][2] = {};
-#pragma unroll
-    for (int a = 0; a < RW; ++a) m_ref[a] = kNegInf;
+    float msum1[2] = {}, msum2[2] = {};
+    m_ref = kNegInf;
     const uint32_t one_top = col < 16 ? 0x3f803f80u : 0u, one_bot = col < 16 ? 0u : 0x3f803f80u;
     const u32x4 ones_top = {one_top, one_top, one_top, one_top}, ones_bot = {one_bot, one_bot, one_bot, one_bot};
     const float scale_log2 = p.scale * kLog2e;  // >= 0 (checked by the host)
-    // What multiplies S1 in front of the exponential, per row sub-block. PREP: the 1 / rms of
+    // What multiplies S1 in front of the exponential. PREP: the 1 / rms of
     // the row's RMSNorm is a per-row scalar, so it is not applied to the q elements but rides on
     // this factor (and that of rho on the final O2, d2, which are linear in S2): r_gain.
-    float row_scale[RW], r_gain[RW];
-#pragma unroll
-    for (int a = 0; a < RW; ++a) row_scale[a] = scale_log2, r_gain[a] = 1.f;
+    float row_scale, r_gain;
+    row_scale = scale_log2, r_gain = 1.f;
 
     // adds the bf16 values of a packed MFMA operand (this lane's 8 keys) to acc: one dot product
     // against (1, 1) per packed pair. Written as assembly: through the builtin, viewing a dword of
@@ -456,33 +450,30 @@ __global__ __launch_bounds__(256, 1) void prefill_bf16_kernel(PrefillParams p) {
 
     // P1 = exp2(S1*scale - m_ref), P2 = P1*S2 for one key block, left as packed bf16 MFMA
     // operands (two groups of 16 keys).
-    auto probs = [&](auto masked_tag, int key_base, f32x16(&s1)[RW], f32x16(&s2)[RW], u32x4(&pb1)[RW][2],
-                     u32x4(&pb2)[RW][2]) __attribute__((always_inline)) {
+    auto probs = [&](auto masked_tag, int key_base, f32x16 &s1, f32x16 &s2, u32x4(&pb1)[2],
+                     u32x4(&pb2)[2]) __attribute__((always_inline)) {
         constexpr bool MASKED = decltype(masked_tag)::value;
+        const float neg_m = m_ref == kNegInf ? 0.f : -m_ref;
 #pragma unroll
-        for (int a = 0; a < RW; ++a) {
-            const float neg_m = m_ref[a] == kNegInf ? 0.f : -m_ref[a];
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                float p1 = fast_exp2(fmaf(s1[a][r], row_scale[a], neg_m));
-                if constexpr (MASKED) p1 = key_ok(key_base, r, a) ? p1 : 0.f;
-                s1[a][r] = p1;
-                // s2 is finite (rows past the last key re-read it) and P1 = 0 where masked
-                if constexpr (USE_R) s2[a][r] = p1 * s2[a][r];
-                if constexpr (STATS) {
-                    msum1[a][r & 1] += s1[a][r];
-                    msum2[a][r & 1] += s2[a][r];
-                }
+        for (int r = 0; r < 16; ++r) {
+            float p1 = fast_exp2(fmaf(s1[r], row_scale, neg_m));
+            if constexpr (MASKED) p1 = key_ok(key_base, r) ? p1 : 0.f;
+            s1[r] = p1;
+            // s2 is finite (rows past the last key re-read it) and P1 = 0 where masked
+            if constexpr (USE_R) s2[r] = p1 * s2[r];
+            if constexpr (STATS) {
+                msum1[r & 1] += s1[r];
+                msum2[r & 1] += s2[r];
             }
+        }
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                // B operand k-element e <-> register 8j+e <-> key 16j + 8*(e/4) + 4h + e%4
-                pb1[a][j] = u32x4{pack_bf16(s1[a][8 * j + 0], s1[a][8 * j + 1]), pack_bf16(s1[a][8 * j + 2], s1[a][8 * j + 3]),
-                                  pack_bf16(s1[a][8 * j + 4], s1[a][8 * j + 5]), pack_bf16(s1[a][8 * j + 6], s1[a][8 * j + 7])};
-                if constexpr (USE_R)
-                    pb2[a][j] = u32x4{pack_bf16(s2[a][8 * j + 0], s2[a][8 * j + 1]), pack_bf16(s2[a][8 * j + 2], s2[a][8 * j + 3]),
-                                      pack_bf16(s2[a][8 * j + 4], s2[a][8 * j + 5]), pack_bf16(s2[a][8 * j + 6], s2[a][8 * j + 7])};
-            }
+        for (int j = 0; j < 2; ++j) {
+            // B operand k-element e <-> register 8j+e <-> key 16j + 8*(e/4) + 4h + e%4
+            pb1[j] = u32x4{pack_bf16(s1[8 * j + 0], s1[8 * j + 1]), pack_bf16(s1[8 * j + 2], s1[8 * j + 3]),
+                              pack_bf16(s1[8 * j + 4], s1[8 * j + 5]), pack_bf16(s1[8 * j + 6], s1[8 * j + 7])};
+            if constexpr (USE_R)
+                pb2[j] = u32x4{pack_bf16(s2[8 * j + 0], s2[8 * j + 1]), pack_bf16(s2[8 * j + 2], s2[8 * j + 3]),
+                                  pack_bf16(s2[8 * j + 4], s2[8 * j + 5]), pack_bf16(s2[8 * j + 6], s2[8 * j + 7])};
         }
     };
 
@@ -493,7 +484,7 @@ __global__ __launch_bounds__(256, 1) void prefill_bf16_kernel(PrefillParams p) {
     const int tr_half = (lane & 1) * 4;
     const int tr_chunk = 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
     const int tr_lane_off = (tr_row * VROW + tr_chunk) * 8 + tr_half;  // in bf16 elements
-    auto accumulate = [&](int stage, int kb, const u32x4(&pb1)[RW][2], const u32x4(&pb2)[RW][2]) __attribute__((always_inline)) {
+    auto accumulate = [&](int stage, int kb, const u32x4(&pb1)[2], const u32x4(&pb2)[2]) __attribute__((always_inline)) {
         const unsigned short *tv16 =
             (const unsigned short *)(lds + stage * STAGE_CHUNKS + K_CHUNKS) + tr_lane_off;
 #pragma unroll
@@ -504,41 +495,31 @@ __global__ __launch_bounds__(256, 1) void prefill_bf16_kernel(PrefillParams p) {
                 const u32x2 lo = lds_read_tr16(tv16 + off);
                 const u32x2 hi = lds_read_tr16(tv16 + off + 8 * VROW * 8);
                 const u32x4 vt = {lo[0], lo[1], hi[0], hi[1]};
-#pragma unroll
-                for (int a = 0; a < RW; ++a) {
-                    o1[a][n] = mfma32(vt, pb1[a][j], o1[a][n]);
-                    if constexpr (USE_R) o2[a][n] = mfma32(vt, pb2[a][j], o2[a][n]);
-                }
+                o1[n] = mfma32(vt, pb1[j], o1[n]);
+                if constexpr (USE_R) o2[n] = mfma32(vt, pb2[j], o2[n]);
             }
 #pragma unroll
         for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int a = 0; a < RW; ++a) {
-                if constexpr (MFMA_SUMS) {
-                    dacc[a] = mfma32(ones_top, pb1[a][j], dacc[a]);
-                    if constexpr (USE_R) dacc[a] = mfma32(ones_bot, pb2[a][j], dacc[a]);
-                } else {
-                    add_rounded(pb1[a][j], rsum1[a]);
-                    if constexpr (USE_R) add_rounded(pb2[a][j], rsum2[a]);
-                }
+            if constexpr (MFMA_SUMS) {
+                dacc = mfma32(ones_top, pb1[j], dacc);
+                if constexpr (USE_R) dacc = mfma32(ones_bot, pb2[j], dacc);
+            } else {
+                add_rounded(pb1[j], rsum1);
+                if constexpr (USE_R) add_rounded(pb2[j], rsum2);
             }
     };
 
     auto zero_state = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
+            if constexpr (MFMA_SUMS) dacc[r] = 0.f;
 #pragma unroll
-            for (int a = 0; a < RW; ++a) {
-                if constexpr (MFMA_SUMS) dacc[a][r] = 0.f;
-#pragma unroll
-                for (int n = 0; n < NDB; ++n) {
-                    o1[a][n][r] = 0.f;
-                    o2[a][n][r] = 0.f;
-                }
+            for (int n = 0; n < NDB; ++n) {
+                o1[n][r] = 0.f;
+                o2[n][r] = 0.f;
             }
         }
-#pragma unroll
-        for (int a = 0; a < RW; ++a) rsum1[a] = rsum2[a] = 0.f;
+        rsum1 = rsum2 = 0.f;
     };
 
     // does this wave see any key of the block starting at key_base?
@@ -547,9 +528,8 @@ __global__ __launch_bounds__(256, 1) void prefill_bf16_kernel(PrefillParams p) {
                (!WINDOW || key_base + kKB > row0 + off - p.window + 1);
     };
 
-    u32x4 pb1[RW][2], pb2[RW][2];
-#pragma unroll
-    for (int a = 0; a < RW; ++a) pb2[a][0] = pb2[a][1] = u32x4{0u, 0u, 0u, 0u};
+    u32x4 pb1[2], pb2[2];
+    pb2[0] = pb2[1] = u32x4{0u, 0u, 0u, 0u};
 
     // One step of the software pipeline over fully visible key blocks, written as slots of ONE
     // MFMA each followed by its share of vector-ALU work (measured on this chip: a wave can
@@ -588,7 +568,7 @@ __global__ __launch_bounds__(256, 1) void prefill_bf16_kernel(PrefillParams p) {
             load_kfrag(tk_next, f);
         else if (f < 2 * KSTEPS)
             load_vfrag(tv_cur, f - KSTEPS);
-        else
+        else if constexpr (!PAIR)  // (PAIR: the block after is in a tile that has not landed yet)
             load_kfrag(tk_after, f - 2 * KSTEPS);
     };
     // exp / P2 of the 8 score registers [r0, r0+8) of a block, spread over the MFMA slots of a
@@ -599,186 +579,95 @@ __global__ __launch_bounds__(256, 1) void prefill_bf16_kernel(PrefillParams p) {
     // already subtracted) and, with a sliding window, `lo` its smallest: register r holds key
     // offset 8*(r/4) + r%4.
     // last key this lane's row may see
-    int row_lim[RW];
-#pragma unroll
-    for (int a = 0; a < RW; ++a) row_lim[a] = no_tiles ? -1 : (CAUSAL ? min(my_row(a) + off, Tv - 1) : Tv - 1);
-    // The 8 * RW chains (row sub-block a, register r0 + u) of a phase, one after the other.
-    auto exp_stages = [&](auto masked_tag, auto sums_tag, f32x16(&s1)[RW], f32x16(&s2)[RW], int r0, int slot,
-                          int slot0, int n_slots, const float(&neg_m)[RW], const int(&lim)[RW], const int(&lo)[RW],
-                          float(&acc1)[RW][2], float(&acc2)[RW][2]) __attribute__((always_inline)) {
+    int row_lim;
+    row_lim = no_tiles ? -1 : (CAUSAL ? min(my_row + off, Tv - 1) : Tv - 1);
+    // The 8 chains (register r0 + u) of a phase, one after the other.
+    auto exp_stages = [&](auto masked_tag, auto sums_tag, f32x16 &s1, f32x16 &s2, int r0, int slot,
+                          int slot0, int n_slots, const float &neg_m, const int &lim, const int &lo,
+                          float(&acc1)[2], float(&acc2)[2]) __attribute__((always_inline)) {
         constexpr bool MASKED = decltype(masked_tag)::value;
         constexpr bool SUMS = decltype(sums_tag)::value;  // a fourth stage adds P1, P2 to acc1, acc2
 #pragma unroll
-        for (int c = 0; c < 8 * RW; ++c) {
-            const int a = c / 8, u = c % 8;
+        for (int u = 0; u < 8; ++u) {
             const int r = r0 + u;
             // stages in slots first, first+1, first+2 (, first+3); none before slot0, none in
             // the last two
-            const int first = slot0 + c * (n_slots - (SUMS ? 5 : 4) - slot0) / (8 * RW);
+            const int first = slot0 + u * (n_slots - (SUMS ? 5 : 4) - slot0) / 8;
             if constexpr (SUMS)
                 if (slot == first + 3) {
-                    acc1[a][u & 1] += s1[a][r];
-                    if constexpr (USE_R) acc2[a][u & 1] += s2[a][r];
+                    acc1[u & 1] += s1[r];
+                    if constexpr (USE_R) acc2[u & 1] += s2[r];
                 }
-            if (slot == first) s1[a][r] = fmaf(s1[a][r], row_scale[a], neg_m[a]);
+            if (slot == first) s1[r] = fmaf(s1[r], row_scale, neg_m);
             if (slot == first + 1) {
-                const float p1 = fast_exp2(s1[a][r]);
+                const float p1 = fast_exp2(s1[r]);
                 const int key_off = 8 * (r >> 2) + (r & 3);
-                const bool seen = !MASKED || (key_off <= lim[a] && (!WINDOW || key_off >= lo[a]));
-                s1[a][r] = seen ? p1 : 0.f;
+                const bool seen = !MASKED || (key_off <= lim && (!WINDOW || key_off >= lo));
+                s1[r] = seen ? p1 : 0.f;
             }
             // P2: S2 is finite (rows past the last key re-read it) and P1 = 0 where masked
             if constexpr (USE_R)
-                if (slot == first + 2) s2[a][r] = s1[a][r] * s2[a][r];
+                if (slot == first + 2) s2[r] = s1[r] * s2[r];
         }
     };
     auto pack_group = [&](const f32x16 &s, int j) __attribute__((always_inline)) {
         return u32x4{pack_bf16(s[8 * j + 0], s[8 * j + 1]), pack_bf16(s[8 * j + 2], s[8 * j + 3]),
                      pack_bf16(s[8 * j + 4], s[8 * j + 5]), pack_bf16(s[8 * j + 6], s[8 * j + 7])};
     };
-    // Two row sub-blocks per wave: a step has twice the element-wise work per MFMA and the vector
-    // ALU, not the matrix pipe, is what fills a slot. So the work is laid over ALL slots of the
-    // step by absolute slot number g (phase 1 = [0, n1), phase 2 = [n1, n_slots)) instead of
-    // phase by phase, one chain (scale-and-shift, exp2, times S2[, row-sum add]) starting per slot:
-    //   U chains, upper key group of the CURRENT block (registers 8..15 of sc): chain c starts in
-    //     slot c; they run over into phase 2, whose MFMAs need their operands from slot
-    //     n1 + n2 / 2 on;
-    //   L chains, lower key group of the NEXT block (registers 0..7 of sn): from the last slot of
-    //     phase 1 (the scores of sub-block 0 are complete two slots earlier, those of sub-block 1
-    //     when its chains start) to the end of the step;
-    //   operands are packed pair by pair as soon as both chains of a pair are through, not as
-    //     blocks of four at the end of a phase;
-    //   the row-sum adds of the current block's lower key group (finished by the previous step)
-    //     fill the slots at both ends of the step, where chains are still starting or already done.
-    auto step_valu = [&](auto masked_tag, auto sums_tag, int g, int n1, int n_slots, f32x16(&sc1)[RW],
-                         f32x16(&sc2)[RW], f32x16(&sn1)[RW], f32x16(&sn2)[RW], const float(&neg_m)[RW],
-                         const int(&lim_cur)[RW], const int(&lo_cur)[RW], const int(&lim_next)[RW],
-                         const int(&lo_next)[RW], float(&acc1)[RW][2], float(&acc2)[RW][2], u32x4(&nb1)[RW],
-                         u32x4(&nb2)[RW]) __attribute__((always_inline)) {
-        constexpr bool MASKED = decltype(masked_tag)::value;
-        constexpr bool ADDS = decltype(sums_tag)::value;
-        constexpr int NCH = 8 * RW;
-        const int l0 = n1 - 1, l_span = n_slots - 4 - l0;  // L chains start in [l0, l0 + l_span]
-        // (the result of every stage passes through an empty volatile statement in the stage's
-        // slot: such data dependences are what keeps a vector instruction from sinking over the
-        // scheduling fences to the slot of its first use)
-        auto pin = [](float x) __attribute__((always_inline)) {
-            asm volatile("" : "+v"(x));
-            return x;
-        };
-
-        // register r of a score block pair (b1, b2); r holds key offset 8*(r/4) + r%4
-        auto chain = [&](f32x16 &b1, f32x16 &b2, int r, int start, float nm, float sc, int lim, int lo)
-                         __attribute__((always_inline)) {
-            if (g == start) b1[r] = pin(fmaf(b1[r], sc, nm));
-            if (g == start + 1) {
-                const float p1 = fast_exp2(b1[r]);
-                const int key_off = 8 * (r >> 2) + (r & 3);
-                const bool seen = !MASKED || (key_off <= lim && (!WINDOW || key_off >= lo));
-                b1[r] = pin(seen ? p1 : 0.f);
-            }
-            // P2: S2 is finite (rows past the last key re-read it) and P1 = 0 where masked
-            if constexpr (USE_R)
-                if (g == start + 2) b2[r] = pin(b1[r] * b2[r]);
-        };
-#pragma unroll
-        for (int c = 0; c < NCH; ++c) {
-            const int a = c / 8, u = c % 8;
-            const int us = c, ls = l0 + c * l_span / (NCH - 1);
-            chain(sc1[a], sc2[a], 8 + u, us, neg_m[a], row_scale[a], lim_cur[a], lo_cur[a]);
-            if constexpr (ADDS)
-                if (g == us + 3) {
-                    acc1[a][u & 1] = pin(acc1[a][u & 1] + sc1[a][8 + u]);
-                    if constexpr (USE_R) acc2[a][u & 1] = pin(acc2[a][u & 1] + sc2[a][8 + u]);
-                }
-            chain(sn1[a], sn2[a], u, ls, neg_m[a], row_scale[a], lim_next[a], lo_next[a]);
-            if (u & 1) {  // both chains of the pair (u - 1, u) are through: B operand dword u / 2
-                if (g == us + 2) pb1[a][1][u / 2] = pack_bf16(sc1[a][8 + u - 1], sc1[a][8 + u]);
-                if (g == ls + 2) nb1[a][u / 2] = pack_bf16(sn1[a][u - 1], sn1[a][u]);
-                if constexpr (USE_R) {
-                    if (g == us + 3) pb2[a][1][u / 2] = pack_bf16(sc2[a][8 + u - 1], sc2[a][8 + u]);
-                    if (g == ls + 3) nb2[a][u / 2] = pack_bf16(sn2[a][u - 1], sn2[a][u]);
-                }
-            }
-        }
-        if constexpr (ADDS) {
-            // 3, 2, 1 adds in the first three slots, the rest towards the end of the step
-#pragma unroll
-            for (int q = 0; q < NCH; ++q) {
-                static_assert(NCH == 16, "slot table of the 16 lower-group adds");
-                const int early[6] = {0, 0, 0, 1, 1, 2}, late[10] = {6, 5, 4, 3, 2, 2, 2, 1, 1, 1};
-                const int at = q < 6 ? early[q] : n_slots - late[q - 6];
-                if (g == at) {
-                    const int a = q / 8, r = q % 8;
-                    acc1[a][r & 1] = pin(acc1[a][r & 1] + sc1[a][r]);
-                    if constexpr (USE_R) acc2[a][r & 1] = pin(acc2[a][r & 1] + sc2[a][r]);
-                }
-            }
-        }
-    };
     auto pipeline_step = [&](auto masked_tag, auto dma_tag, int key_base_cur, int key_base_next, const u32x4 *tk_next,
-                             const unsigned short *tv_cur, const u32x4 *tk_after, f32x16(&sc1)[RW],
-                             f32x16(&sc2)[RW], f32x16(&sn1)[RW], f32x16(&sn2)[RW]) __attribute__((always_inline)) {
-        int lim_cur[RW], lim_next[RW], lo_cur[RW], lo_next[RW];  // current block, next block
-        float neg_m[RW];
-#pragma unroll
-        for (int a = 0; a < RW; ++a) {
-            lim_cur[a] = row_lim[a] - key_base_cur - 4 * h;
-            lim_next[a] = row_lim[a] - key_base_next - 4 * h;
-            lo_cur[a] = row_lo[a] - key_base_cur - 4 * h;
-            lo_next[a] = row_lo[a] - key_base_next - 4 * h;
-            neg_m[a] = -m_ref[a];
-        }
-        constexpr int SLOTS1 = 2 * KSTEPS * RW;      // phase 1: one slot per score MFMA
+                             const unsigned short *tv_cur, const u32x4 *tk_after, f32x16 &sc1,
+                             f32x16 &sc2, f32x16 &sn1, f32x16 &sn2) __attribute__((always_inline)) {
+        int lim_cur, lim_next, lo_cur, lo_next;  // current block, next block
+        float neg_m;
+        lim_cur = row_lim - key_base_cur - 4 * h;
+        lim_next = row_lim - key_base_next - 4 * h;
+        lo_cur = row_lo - key_base_cur - 4 * h;
+        lo_next = row_lo - key_base_next - 4 * h;
+        neg_m = -m_ref;
+        constexpr int SLOTS1 = 2 * KSTEPS;               // phase 1: one slot per score MFMA
         constexpr bool DMA = decltype(dma_tag)::value;  // this step also fetches tile (dma_tk, dma_tv)
         constexpr bool MASKED = decltype(masked_tag)::value;
         // Row sums of the CURRENT block belong to this step. Masked steps (a row may see only a
         // few keys, so the sums must be those of the rounded operands exactly): two MFMAs against
-        // ones per key group and row sub-block. Unmasked steps: vector adds of the fp32 values,
+        // ones per key group. Unmasked steps: vector adds of the fp32 values,
         // which stay in the score registers until the next step -- upper key group behind its
         // exp stages in phase 1, lower key group (finished by the previous step) during phase 2.
         constexpr bool SUMS = !MASKED;
-        constexpr int PV = 2 * NDB * RW;                 // PV MFMAs per key group
-        constexpr int GROUP2 = PV + (!SUMS && MFMA_SUMS ? 2 * RW : 0);  // phase 2, per key group: PV (+ row sums)
+        constexpr int PV = 2 * NDB;                      // PV MFMAs per key group
+        constexpr int GROUP2 = PV + (!SUMS && MFMA_SUMS ? 2 : 0);  // phase 2, per key group: PV (+ row sums)
         constexpr int SLOTS2 = 2 * GROUP2;
         // (row cache: masked steps add the fp32 values as well, to sums of their own)
         constexpr bool ADDS = SUMS || STATS;
         const std::integral_constant<bool, ADDS> sums_tag{};
-        float(&acc1)[RW][2] = SUMS ? vsum1 : msum1;
-        float(&acc2)[RW][2] = SUMS ? vsum2 : msum2;
-        static_assert(NDMA_K <= KSTEPS * RW && NDMA_V <= GROUP2, "one tile load per odd slot");
-        u32x4 nb1[RW], nb2[RW];  // lower key group of the next block as operands
-#pragma unroll
-        for (int a = 0; a < RW; ++a) nb1[a] = nb2[a] = u32x4{0u, 0u, 0u, 0u};
+        float(&acc1)[2] = SUMS ? vsum1 : msum1;
+        float(&acc2)[2] = SUMS ? vsum2 : msum2;
+        static_assert(NDMA_K <= KSTEPS && NDMA_V <= GROUP2, "one tile load per odd slot");
+        u32x4 nb1, nb2;  // lower key group of the next block as operands
+        nb1 = nb2 = u32x4{0u, 0u, 0u, 0u};
         // ---- phase 1: scores of the next block | upper key group of the current block ------
-        // slot = ((k-step, row sub-block), S1 | S2): a K fragment serves 2 * RW MFMAs in a row
+        // slot = (k-step, S1 | S2): a K fragment serves two MFMAs in a row
 #pragma unroll
         for (int sl = 0; sl < SLOTS1; ++sl) {
-            const int ks = (sl / 2) / RW, a = (sl / 2) % RW;
+            const int ks = sl / 2;
             if (sl % 2 == 0) {
                 if (ks == 0)
-                    mfma32_scores_first<MASKED>(sn1[a], kf[ks], qf[a][ks]);
+                    mfma32_scores_first<MASKED, !TWO>(sn1, kf[ks], qf[ks]);
                 else
-                    mfma32_scores<MASKED>(sn1[a], kf[ks], qf[a][ks]);
-                if (a == 0) prefetch(ks, tk_next, tv_cur, tk_after);
+                    mfma32_scores<MASKED, !TWO>(sn1, kf[ks], qf[ks]);
+                prefetch(ks, tk_next, tv_cur, tk_after);
             } else if constexpr (USE_R) {
                 if (ks == 0)
-                    mfma32_scores_first<MASKED>(sn2[a], kf[ks], rf[a][ks]);
+                    mfma32_scores_first<MASKED, !TWO>(sn2, kf[ks], rf[ks]);
                 else
-                    mfma32_scores<MASKED>(sn2[a], kf[ks], rf[a][ks]);
+                    mfma32_scores<MASKED, !TWO>(sn2, kf[ks], rf[ks]);
             }
             if constexpr (DMA)
                 if (sl % 2 == 1 && sl / 2 < NDMA_K) k_load(sl / 2, dma_tk, dma_dk);
-            if constexpr (RW == 1) {
-                exp_stages(masked_tag, sums_tag, sc1, sc2, 8, sl, 0, SLOTS1, neg_m, lim_cur, lo_cur, acc1, acc2);
-                // upper key group -> operands, in the last two slots
-                if (sl == SLOTS1 - 2) pb1[0][1] = pack_group(sc1[0], 1);
-                if (sl == SLOTS1 - 1) {
-                    if constexpr (USE_R) pb2[0][1] = pack_group(sc2[0], 1);
-                }
-            } else {
-                step_valu(masked_tag, sums_tag, sl, SLOTS1, SLOTS1 + SLOTS2, sc1, sc2, sn1, sn2, neg_m, lim_cur, lo_cur,
-                          lim_next, lo_next, acc1, acc2, nb1, nb2);
+            exp_stages(masked_tag, sums_tag, sc1, sc2, 8, sl, 0, SLOTS1, neg_m, lim_cur, lo_cur, acc1, acc2);
+            // upper key group -> operands, in the last two slots
+            if (sl == SLOTS1 - 2) pb1[1] = pack_group(sc1, 1);
+            if (sl == SLOTS1 - 1) {
+                if constexpr (USE_R) pb2[1] = pack_group(sc2, 1);
             }
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -790,56 +679,47 @@ __global__ __launch_bounds__(256, 1) void prefill_bf16_kernel(PrefillParams p) {
         for (int sl = 0; sl < SLOTS2; ++sl) {
             const int j = sl / GROUP2, t = sl % GROUP2;
             if (t < PV) {
-                const int n = (t / 2) / RW, a = (t / 2) % RW, f = j * NDB + n;
+                const int n = t / 2, f = j * NDB + n;
                 if (t % 2 == 0) {
-                    o1[a][n] = mfma32(vt[f], pb1[a][j], o1[a][n]);
-                    if (a == 0) prefetch(KSTEPS + f, tk_next, tv_cur, tk_after);
+                    o1[n] = mfma32(vt[f], pb1[j], o1[n]);
+                    prefetch(KSTEPS + f, tk_next, tv_cur, tk_after);
                 } else if constexpr (USE_R) {
-                    o2[a][n] = mfma32(vt[f], pb2[a][j], o2[a][n]);
+                    o2[n] = mfma32(vt[f], pb2[j], o2[n]);
                 }
             } else if constexpr (MFMA_SUMS) {
-                const int a = (t - PV) / 2;
                 if ((t - PV) % 2 == 0)
-                    dacc[a] = mfma32(ones_top, pb1[a][j], dacc[a]);
+                    dacc = mfma32(ones_top, pb1[j], dacc);
                 else if constexpr (USE_R)
-                    dacc[a] = mfma32(ones_bot, pb2[a][j], dacc[a]);
+                    dacc = mfma32(ones_bot, pb2[j], dacc);
             }
             if constexpr (!SUMS && !MFMA_SUMS) {  // rounded operands of key group j, one operand per slot
-                if (t < 2 * RW) {
+                if (t < 2) {
                     if (t % 2 == 0)
-                        add_rounded(pb1[t / 2][j], rsum1[t / 2]);
+                        add_rounded(pb1[j], rsum1);
                     else if constexpr (USE_R)
-                        add_rounded(pb2[t / 2][j], rsum2[t / 2]);
+                        add_rounded(pb2[j], rsum2);
                 }
             }
             if constexpr (DMA)
                 if (sl % 2 == 1 && sl / 2 < NDMA_V) v_load(sl / 2, dma_tv, dma_dv);
-            if constexpr (RW == 1) {
-                exp_stages(masked_tag, std::false_type{}, sn1, sn2, 0, sl, 1, SLOTS2, neg_m, lim_next, lo_next, acc1,
-                           acc2);
-                if constexpr (ADDS) {
-                    constexpr int PER = SLOTS2 / 8;  // lower key group of the current block
-                    if (sl % PER == 0 && sl / PER < 8) {
-                        const int r = sl / PER;
-                        acc1[0][r & 1] += sc1[0][r];
-                        if constexpr (USE_R) acc2[0][r & 1] += sc2[0][r];
-                    }
+            exp_stages(masked_tag, std::false_type{}, sn1, sn2, 0, sl, 1, SLOTS2, neg_m, lim_next, lo_next, acc1,
+                       acc2);
+            if constexpr (ADDS) {
+                constexpr int PER = SLOTS2 / 8;  // lower key group of the current block
+                if (sl % PER == 0 && sl / PER < 8) {
+                    const int r = sl / PER;
+                    acc1[r & 1] += sc1[r];
+                    if constexpr (USE_R) acc2[r & 1] += sc2[r];
                 }
-                if (sl == SLOTS2 - 2) nb1[0] = pack_group(sn1[0], 0);
-                if (sl == SLOTS2 - 1) {
-                    if constexpr (USE_R) nb2[0] = pack_group(sn2[0], 0);
-                }
-            } else {
-                step_valu(masked_tag, sums_tag, SLOTS1 + sl, SLOTS1, SLOTS1 + SLOTS2, sc1, sc2, sn1, sn2, neg_m, lim_cur,
-                          lo_cur, lim_next, lo_next, acc1, acc2, nb1, nb2);
+            }
+            if (sl == SLOTS2 - 2) nb1 = pack_group(sn1, 0);
+            if (sl == SLOTS2 - 1) {
+                if constexpr (USE_R) nb2 = pack_group(sn2, 0);
             }
             __builtin_amdgcn_sched_barrier(0);
         }
-#pragma unroll
-        for (int a = 0; a < RW; ++a) {
-            pb1[a][0] = nb1[a];
-            pb2[a][0] = nb2[a];
-        }
+        pb1[0] = nb1;
+        pb2[0] = nb2;
     };
 
     // =========================== fast pass: fixed reference ================================
@@ -953,11 +833,8 @@ __global__ __launch_bounds__(256, 1) void prefill_bf16_kernel(PrefillParams p) {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-        for (int a = 0; a < RW; ++a) {
-            row_scale[a] = scale_log2 * *(const float *)&zq[(32 * a + col) * KROW + CPR];
-            r_gain[a] = *(const float *)&zr[(32 * a + col) * KROW + CPR];
-        }
+        row_scale = scale_log2 * *(const float *)&zq[col * KROW + CPR];
+        r_gain = *(const float *)&zr[col * KROW + CPR];
     }
     tile_barrier<kTileLoads>();  // Q, R and tile 0 have landed
     {
@@ -965,76 +842,93 @@ __global__ __launch_bounds__(256, 1) void prefill_bf16_kernel(PrefillParams p) {
         const u32x4 *zq = lds + QZONE + w * WAVE_TILE_CHUNKS + col * KROW + h;
         const u32x4 *zr = lds + RZONE + w * WAVE_TILE_CHUNKS + col * KROW + h;
 #pragma unroll
-        for (int a = 0; a < RW; ++a)
-#pragma unroll
             for (int ks = 0; ks < KSTEPS; ++ks) {
-                qf[a][ks] = zq[32 * a * KROW + 2 * ks];
-                if constexpr (USE_R) rf[a][ks] = zr[32 * a * KROW + 2 * ks];
+                qf[ks] = zq[2 * ks];
+                if constexpr (USE_R) rf[ks] = zr[2 * ks];
             }
     }
     int stage = 0;
-    f32x16 sa1[RW], sa2[RW], sb1[RW], sb2[RW];
+    f32x16 sa1, sa2, sb1, sb2;
     {
         // Pipeline prologue: scores of block (0, 0); reference = its row maximum (key 0 is
         // visible to every row); lower key group -> P. (Everything the loops read from registers
         // loaded out of global memory -- the Q, R fragments -- is consumed here first, so the
         // loops contain no wait on the vector-memory counter, which the tile loads in flight
         // would turn into a full memory round trip.)
-        scores(0, 0, sa1, sa2);
+        scores(0, half, sa1, sa2);
+        if constexpr (!PAIR)
 #pragma unroll
-        for (int f = 0; f < kLookAhead; ++f) load_kfrag(k_block_ptr(0, 1), f);
+            for (int f = 0; f < kLookAhead; ++f) load_kfrag(k_block_ptr(0, 1), f);
         int kb0 = tile_at(0) * kBC;  // 0 unless block-sparse
         if constexpr (SPARSE) asm volatile("" : "+s"(kb0));  // (opaque, for the same reason as n_tiles)
-        float neg_m[RW];
-        int lim0[RW], lo0[RW];
+        float neg_m;
+        int lim0, lo0;
+        float tmax = kNegInf, tall = kNegInf;
+        if constexpr (PAIR) {
+            // both waves of a pair take the maximum of block (0, 0): P as a whole row block forms it
+            f32x16 s0;
 #pragma unroll
-        for (int a = 0; a < RW; ++a) {
-            float tmax = kNegInf;
-            if constexpr (SPLIT) {
-                // Every range takes the reference of the whole launch, so that it forms and rounds the very
-                // same P. (A range of its own block's maximum would be as safe, but rounds P
-                // against another scale: outputs apart by the bf16 bound, and by 2^-9 from exact where one key
-                // has all the weight.) A range far below the reference adds what it would add there.
-                f32x16 s0;
+            for (int r = 0; r < 16; ++r) s0[r] = 0.f;
 #pragma unroll
-                for (int r = 0; r < 16; ++r) s0[r] = 0.f;
+            for (int ks = 0; ks < KSTEPS; ++ks) s0 = mfma32(k_block_ptr(0, 0)[2 * ks], qf[ks], s0);
 #pragma unroll
-                for (int ks = 0; ks < KSTEPS; ++ks) s0 = mfma32(k_ref[ks], qf[a][ks], s0);
+            for (int r = 0; r < 16; ++r) tmax = fmaxf(tmax, key_ok(0, r) ? s0[r] : kNegInf);
+            if constexpr (WINDOW) {
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int key = 8 * (r >> 2) + 4 * h + (r & 3);
-                    tmax = fmaxf(tmax, key < p.Tk && (!CAUSAL || key <= my_row(a) + (p.Tk - T)) ? s0[r] : kNegInf);
-                }
-            } else {
-#pragma unroll
-                for (int r = 0; r < 16; ++r) tmax = fmaxf(tmax, key_ok(kb0, r, a) ? sa1[a][r] : kNegInf);
+                for (int r = 0; r < 16; ++r) tall = fmaxf(tall, s0[r]);
             }
-            tmax = halves_max(tmax);
-            if constexpr (WINDOW || SPARSE) {
-                // a row whose window starts behind this block takes the block's plain maximum: any
-                // finite reference will do (the check after the loops catches one that was too far off)
-                float tall = sa1[a][0];
+        } else if constexpr (SPLIT) {
+            // Every range takes the reference of the whole launch, so that it forms and rounds the very
+            // same P. (A range of its own block's maximum would be as safe, but rounds P
+            // against another scale: outputs apart by the bf16 bound, and by 2^-9 from exact where one key
+            // has all the weight.) A range far below the reference adds what it would add there.
+            f32x16 s0;
 #pragma unroll
-                for (int r = 1; r < 16; ++r) tall = fmaxf(tall, sa1[a][r]);
-                tall = halves_max(tall);
-                tmax = tmax == kNegInf ? tall : tmax;
+            for (int r = 0; r < 16; ++r) s0[r] = 0.f;
+#pragma unroll
+            for (int ks = 0; ks < KSTEPS; ++ks) s0 = mfma32(k_ref[ks], qf[ks], s0);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int key = 8 * (r >> 2) + 4 * h + (r & 3);
+                tmax = fmaxf(tmax, key < p.Tk && (!CAUSAL || key <= my_row + (p.Tk - T)) ? s0[r] : kNegInf);
             }
-            m_ref[a] = tmax * row_scale[a];
-            neg_m[a] = -m_ref[a];
-            lim0[a] = row_lim[a] - kb0 - 4 * h;
-            lo0[a] = row_lo[a] - kb0 - 4 * h;
+        } else {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) tmax = fmaxf(tmax, key_ok(kb0, r) ? sa1[r] : kNegInf);
         }
+        tmax = halves_max(tmax);
+        if constexpr (WINDOW || SPARSE) {
+            // a row whose window starts behind this block takes the block's plain maximum: any
+            // finite reference will do (the check after the loops catches one that was too far off)
+            if constexpr (!PAIR) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) tall = fmaxf(tall, sa1[r]);
+            }
+            tall = halves_max(tall);
+            tmax = tmax == kNegInf ? tall : tmax;
+        }
+        m_ref = tmax * row_scale;
+        neg_m = -m_ref;
+        lim0 = row_lim - kb0 - half * kKB - 4 * h;
+        lo0 = row_lo - kb0 - half * kKB - 4 * h;
 #pragma unroll
         for (int sl = 0; sl < 12; ++sl)
             exp_stages(std::true_type{}, std::false_type{}, sa1, sa2, 0, sl, 0, 12, neg_m, lim0, lo0, msum1, msum2);
-#pragma unroll
-        for (int a = 0; a < RW; ++a) {
-            pb1[a][0] = pack_group(sa1[a], 0);
-            if constexpr (USE_R) pb2[a][0] = pack_group(sa2[a], 0);
-        }
+        pb1[0] = pack_group(sa1, 0);
+        if constexpr (USE_R) pb2[0] = pack_group(sa2, 0);
     }
     // kt: key tile in `stage`, kt_next: key tile in `next_stage` (kt + 1 unless block-sparse)
-    auto tile_steps = [&](auto masked_tag, auto dma_tag, int kt, int kt_next, int stage, int next_stage) __attribute__((always_inline)) {
+    auto tile_steps = [&](auto masked_tag, auto dma_tag, int kt, int kt_next, int stage, int next_stage, f32x16 &sa1,
+                          f32x16 &sa2, f32x16 &sb1, f32x16 &sb2) __attribute__((always_inline)) {
+        if constexpr (PAIR) {
+            // block (kt, half) -> P, PV; scores of (kt_next, half), whose first fragments are read now
+            const u32x4 *tk_next = k_block_ptr(next_stage, half);
+#pragma unroll
+            for (int f = 0; f < kLookAhead; ++f) load_kfrag(tk_next, f);
+            pipeline_step(masked_tag, dma_tag, kt * kBC + half * kKB, kt_next * kBC + half * kKB, tk_next,
+                          v_block_ptr(stage, half), nullptr, sa1, sa2, sb1, sb2);
+            return;
+        }
         // block (kt,0) -> P, PV; scores of (kt,1); K fragments of (kt_next,0); loads of the tile after
         pipeline_step(masked_tag, dma_tag, kt * kBC, kt * kBC + kKB, k_block_ptr(stage, 1),
                       v_block_ptr(stage, 0), k_block_ptr(next_stage, 0), sa1, sa2, sb1, sb2);
@@ -1044,7 +938,8 @@ __global__ __launch_bounds__(256, 1) void prefill_bf16_kernel(PrefillParams p) {
     };
     // One tile of the pipeline with per-lane key masks. Blocks a wave cannot see at all
     // contribute exact zeros.
-    auto masked_tile = [&](int kt) __attribute__((always_inline)) {
+    auto masked_tile = [&](int kt, f32x16 &sa1, f32x16 &sa2, f32x16 &sb1, f32x16 &sb2)
+                           __attribute__((always_inline)) {
         const int next_stage = stage == STAGES - 1 ? 0 : stage + 1;
         const int free_stage = stage == 0 ? STAGES - 1 : stage - 1;
         tile_barrier();
@@ -1055,18 +950,30 @@ __global__ __launch_bounds__(256, 1) void prefill_bf16_kernel(PrefillParams p) {
             else
                 dma_tile(k2, free_stage);
         }
-        tile_steps(std::true_type{}, std::false_type{}, tile_at(kt), tile_at(kt + 1), stage, next_stage);
+        tile_steps(std::true_type{}, std::false_type{}, tile_at(kt), tile_at(kt + 1), stage, next_stage, sa1, sa2, sb1, sb2);
         stage = next_stage;
+    };
+    // PAIR: tiles go by twos, as a step hands its score registers over to the next one in the other set; the
+    // odd last tile is a step of its own (left by a break, the loop spills)
+    auto masked_tiles = [&](int &kt, int end) __attribute__((always_inline)) {
+        while (kt < end) {
+            masked_tile(kt, sa1, sa2, sb1, sb2);
+            ++kt;
+            if constexpr (PAIR) {
+                masked_tile(kt, sb1, sb2, sa1, sa2);
+                ++kt;
+            }
+        }
     };
     int kt = 0;
     // Sliding window: the leading tiles are cut by the left edge of some row's window.
-    if constexpr (WINDOW)
-        for (; kt < n_left; ++kt) masked_tile(kt);
+    if constexpr (WINDOW) masked_tiles(kt, PAIR ? min((n_left + 1) & ~1, n_tiles & ~1) : n_left);
     // Tiles whose keys -- and those of the tile after -- are visible to every row: no masks, a
     // branch-free body. (A step also prepares the lower half of the NEXT block, hence the -1.)
     dma_tk = (const char *)kbase + (kt + kDist) * k_tile_bytes;
     dma_tv = (const char *)vbase + (kt + kDist) * v_tile_bytes;
-    for (; kt < n_full - 1; ++kt) {
+    auto full_tile = [&](int kt, f32x16 &sa1, f32x16 &sa2, f32x16 &sb1, f32x16 &sb2)
+                         __attribute__((always_inline)) {
         const int next_stage = stage == STAGES - 1 ? 0 : stage + 1;
         const int free_stage = stage == 0 ? STAGES - 1 : stage - 1;  // held tile kt - 1
         // tile kt + 1 has landed; the kDist - 2 tiles after it may still be in flight
@@ -1079,15 +986,24 @@ __global__ __launch_bounds__(256, 1) void prefill_bf16_kernel(PrefillParams p) {
             dma_tk = (const char *)kbase + k2 * k_tile_bytes;
             dma_tv = (const char *)vbase + k2 * v_tile_bytes;
         }
-        tile_steps(std::false_type{}, std::true_type{}, tile_at(kt), tile_at(kt + 1), stage, next_stage);
+        tile_steps(std::false_type{}, std::true_type{}, tile_at(kt), tile_at(kt + 1), stage, next_stage, sa1, sa2, sb1, sb2);
         if constexpr (!SPARSE) {
             dma_tk += k_tile_bytes;
             dma_tv += v_tile_bytes;
         }
         stage = next_stage;
+    };
+    const int full_end = PAIR ? kt + (max(n_full - 1 - kt, 0) & ~1) : n_full - 1;
+    for (; kt < full_end; ++kt) {
+        full_tile(kt, sa1, sa2, sb1, sb2);
+        if constexpr (PAIR) full_tile(++kt, sb1, sb2, sa1, sa2);
     }
     // Remaining tiles (diagonal / tail): the same pipeline with per-lane key masks.
-    for (; kt < n_tiles; ++kt) masked_tile(kt);
+    masked_tiles(kt, PAIR ? n_tiles & ~1 : n_tiles);
+    if (PAIR && kt < n_tiles) {
+        masked_tile(kt, sa1, sa2, sb1, sb2);
+        keep_blocks(sb1, sb2);  // (unused, but nothing else may move in before they are written)
+    }
     // ---- closing formula into the wave's staging tile, and the check of the fast pass -------
     // O^T register r of block n <-> dim 32n + 8*(r/4) + 4h + r%4 of row my_row. A lane owns one
     // output ROW, so direct stores would scatter 8 bytes over 32 rows per instruction; the wave
@@ -1099,55 +1015,133 @@ __global__ __launch_bounds__(256, 1) void prefill_bf16_kernel(PrefillParams p) {
     // and comes back here once more.
     constexpr int OROW = CPR + 1;  // padded row of the staging tile, in 16-byte chunks
     static_assert(OROW == KROW, "the staging tile is the wave's Q tile");
-    u32x4 *otile = lds + QZONE + w * WAVE_TILE_CHUNKS;
+    u32x4 *otile = lds + QZONE + (PAIR ? w & 1 : w) * WAVE_TILE_CHUNKS;  // (PAIR: of both waves, each its dimensions)
     unsigned short *otile16 = (unsigned short *)otile;
-    float inv[RW], dsum1[RW], dsum2s[RW];
-    auto stage_outputs = [&]() __attribute__((always_inline)) {
-        float chk = 0.f;
+    float inv, dsum1, dsum2s;
+    // PAIR: the sums of the two waves of a pair, each exact on its keys under its own reference (the same one
+    // unless they took the online update). Through the ring, which nobody reads any more: a wave hands over
+    // the other's half of the dimensions and the row scalars, and ends up with everything of its own half.
+    constexpr int NOWN = PAIR ? NDB / 2 : NDB;
+    auto owned = [&](int n) __attribute__((always_inline)) { return !PAIR || n / NOWN == half; };  // (wave-uniform)
+    float psum1 = 0.f, psum2 = 0.f, pfsum1 = 0.f, pfsum2 = 0.f;  // PAIR: row sums of both waves
+    auto merge_halves = [&]() __attribute__((always_inline)) {
+        constexpr int ACC = 2 * NOWN * 4 * 64, ROWSC = 5 * 64 / 4;  // chunks per wave: accumulators, row scalars
+        static_assert(!PAIR || 4 * (ACC + ROWSC) <= QZONE, "the ring");
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // tile loads past the end have landed
+        __syncthreads();
+        f32x4 *mine = (f32x4 *)lds + w * (ACC + ROWSC), *theirs = (f32x4 *)lds + (w ^ 2) * (ACC + ROWSC);
+        float *sc = (float *)(mine + ACC) + lane, *osc = (float *)(theirs + ACC) + lane;
+        float d1, d2;  // (as in stage_outputs)
+        if constexpr (MFMA_SUMS) {
+            d1 = dacc[0] + halves_sum(vsum1[0] + vsum1[1]);
+            d2 = dacc[8] + halves_sum(vsum2[0] + vsum2[1]);
+        } else {
+            d1 = halves_sum(rsum1 + vsum1[0] + vsum1[1]);
+            d2 = halves_sum(rsum2 + vsum2[0] + vsum2[1]);
+        }
+        const float f1 = halves_sum(vsum1[0] + vsum1[1] + msum1[0] + msum1[1]);
+        const float f2 = halves_sum(vsum2[0] + vsum2[1] + msum2[0] + msum2[1]);
+        sc[0] = m_ref, sc[64] = d1, sc[128] = d2;
+        if constexpr (STATS) sc[192] = f1, sc[256] = f2;
+        auto give = [&](auto first) __attribute__((always_inline)) {
 #pragma unroll
-        for (int a = 0; a < RW; ++a) {
-            // Every row of the MFMA row-sum accumulators holds the sum over this lane's query row;
-            // the per-lane partial sums cover this lane's keys only: add the other half-wave's.
-            float dsum2;
-            if constexpr (MFMA_SUMS) {
-                dsum1[a] = dacc[a][0] + halves_sum(vsum1[a][0] + vsum1[a][1]);
-                dsum2 = dacc[a][8] + halves_sum(vsum2[a][0] + vsum2[a][1]);
-            } else {
-                dsum1[a] = halves_sum(rsum1[a] + vsum1[a][0] + vsum1[a][1]);
-                dsum2 = halves_sum(rsum2[a] + vsum2[a][0] + vsum2[a][1]);
-            }
-            if constexpr (PREP) dsum2 *= r_gain[a];
-            if constexpr (SPLIT) dsum2s[a] = dsum2;
-            inv[a] = dsum1[a] > 0.f ? 1.f / dsum1[a] : 0.f;  // empty key set: zeros
-            const float gain = inv[a] * (1.f + dsum2 * inv[a]);
-            const float inv2 = PREP ? inv[a] * r_gain[a] : inv[a];
-            chk = fmaf(dsum1[a] + dsum2, 0.f, chk);  // inf or NaN -> NaN
-#pragma unroll
-            for (int n = 0; n < NDB; ++n)
+            for (int n = 0; n < NOWN; ++n)
 #pragma unroll
                 for (int q4 = 0; q4 < 4; ++q4) {
-                    float y[4];
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const int r = 4 * q4 + i;
-                        y[i] = o1[a][n][r] * gain - (USE_R ? o2[a][n][r] * inv2 : 0.f);
-                        chk = fmaf(y[i], 0.f, chk);
-                    }
-                    const u32x2 packed = {pack_bf16(y[0], y[1]), pack_bf16(y[2], y[3])};
-                    *(u32x2 *)(otile16 + (32 * a + col) * (OROW * 8) + 32 * n + 8 * q4 + 4 * h) = packed;
+                    const f32x16 &x = o1[decltype(first)::value + n], &y = o2[decltype(first)::value + n];
+                    mine[lane + 64 * (4 * n + q4)] = f32x4{x[4 * q4], x[4 * q4 + 1], x[4 * q4 + 2], x[4 * q4 + 3]};
+                    if constexpr (USE_R)
+                        mine[lane + 64 * (4 * (NOWN + n) + q4)] = f32x4{y[4 * q4], y[4 * q4 + 1], y[4 * q4 + 2], y[4 * q4 + 3]};
                 }
+        };
+        const std::integral_constant<int, 0> lower{};
+        const std::integral_constant<int, PAIR ? NOWN : 0> upper{};
+        // (the empty statements keep the two branches apart: merged, they would pick their accumulators
+        // through a pointer, and those would live in scratch memory)
+        if (half == 0) {  // (wave-uniform)
+            give(upper);
+            asm volatile("; upper dimensions handed over");
+        } else {
+            give(lower);
         }
+        __syncthreads();
+        const float m = fmaxf(m_ref, osc[0]), m_use = m == kNegInf ? 0.f : m;
+        const float fm = fast_exp2(m_ref - m_use), ft = fast_exp2(osc[0] - m_use);  // (1 under one reference)
+        psum1 = d1 * fm + osc[64] * ft, psum2 = d2 * fm + osc[128] * ft;
+        if constexpr (STATS) pfsum1 = f1 * fm + osc[192] * ft, pfsum2 = f2 * fm + osc[256] * ft;
+        m_ref = m;
+        auto take = [&](auto first) __attribute__((always_inline)) {
+#pragma unroll
+            for (int n = 0; n < NOWN; ++n)
+#pragma unroll
+                for (int q4 = 0; q4 < 4; ++q4) {
+                    f32x16 &x = o1[decltype(first)::value + n], &y = o2[decltype(first)::value + n];
+                    const f32x4 u = theirs[lane + 64 * (4 * n + q4)];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) x[4 * q4 + i] = x[4 * q4 + i] * fm + u[i] * ft;
+                    if constexpr (USE_R) {
+                        const f32x4 v = theirs[lane + 64 * (4 * (NOWN + n) + q4)];
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) y[4 * q4 + i] = y[4 * q4 + i] * fm + v[i] * ft;
+                    }
+                }
+        };
+        if (half == 0) {
+            take(lower);
+            asm volatile("; lower dimensions complete");
+        } else {
+            take(upper);
+        }
+    };
+    if constexpr (PAIR) merge_halves();
+    auto stage_outputs = [&]() __attribute__((always_inline)) {
+        float chk = 0.f;
+        // Every row of the MFMA row-sum accumulators holds the sum over this lane's query row;
+        // the per-lane partial sums cover this lane's keys only: add the other half-wave's.
+        float dsum2;
+        if constexpr (PAIR) {
+            dsum1 = psum1, dsum2 = psum2;
+        } else if constexpr (MFMA_SUMS) {
+            dsum1 = dacc[0] + halves_sum(vsum1[0] + vsum1[1]);
+            dsum2 = dacc[8] + halves_sum(vsum2[0] + vsum2[1]);
+        } else {
+            dsum1 = halves_sum(rsum1 + vsum1[0] + vsum1[1]);
+            dsum2 = halves_sum(rsum2 + vsum2[0] + vsum2[1]);
+        }
+        if constexpr (PREP) dsum2 *= r_gain;
+        if constexpr (SPLIT) dsum2s = dsum2;
+        inv = dsum1 > 0.f ? 1.f / dsum1 : 0.f;  // empty key set: zeros
+        const float gain = inv * (1.f + dsum2 * inv);
+        const float inv2 = PREP ? inv * r_gain : inv;
+        chk = fmaf(dsum1 + dsum2, 0.f, chk);  // inf or NaN -> NaN
+#pragma unroll
+        for (int n = 0; n < NDB; ++n)
+            if (owned(n))
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4) {
+                float y[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int r = 4 * q4 + i;
+                    y[i] = o1[n][r] * gain - (USE_R ? o2[n][r] * inv2 : 0.f);
+                    chk = fmaf(y[i], 0.f, chk);
+                }
+                const u32x2 packed = {pack_bf16(y[0], y[1]), pack_bf16(y[2], y[3])};
+                *(u32x2 *)(otile16 + col * (OROW * 8) + 32 * n + 8 * q4 + 4 * h) = packed;
+            }
         return chk;
     };
+    if constexpr (TWO && !PAIR) {  // (the staging tiles reach into ring stage 2)
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+    }
     float chk = stage_outputs();
     if constexpr (WINDOW || SPARSE) {
         // the reference of a row may come from keys outside its window; if it was so far above
         // the row's own scores that the sum underflowed, take the exact path as well
         // (block-sparse: only for rows that do see a listed key -- the list is ascending, so that
         // is decided by its first tile)
-#pragma unroll
-        for (int a = 0; a < RW; ++a)
-            if (my_row(a) < T && (!SPARSE || tile_at(0) * kBC <= row_lim[a]) && !(dsum1[a] > 1e-30f)) chk = 1.f;
+            if (my_row < T && (!SPARSE || tile_at(0) * kBC <= row_lim) && !(dsum1 > 1e-30f)) chk = 1.f;
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // tile loads past the end have landed
     const bool overflow = __syncthreads_or(chk != 0.f);  // NaN != 0 is true; all waves agree
@@ -1155,12 +1149,9 @@ __global__ __launch_bounds__(256, 1) void prefill_bf16_kernel(PrefillParams p) {
     // =========================== fallback: online max / rescale ============================
     if (overflow) {
         zero_state();
-#pragma unroll
-        for (int a = 0; a < RW; ++a) {
-            vsum1[a][0] = vsum1[a][1] = vsum2[a][0] = vsum2[a][1] = 0.f;
-            msum1[a][0] = msum1[a][1] = msum2[a][0] = msum2[a][1] = 0.f;
-            m_ref[a] = kNegInf;
-        }
+        vsum1[0] = vsum1[1] = vsum2[0] = vsum2[1] = 0.f;
+        msum1[0] = msum1[1] = msum2[0] = msum2[1] = 0.f;
+        m_ref = kNegInf;
         dma_tile(tile_at(0), 0);
         stage = 0;
         for (int t = 0; t < n_tiles; ++t) {
@@ -1169,33 +1160,31 @@ __global__ __launch_bounds__(256, 1) void prefill_bf16_kernel(PrefillParams p) {
             dma_tile(tile_at(t + 1), next_stage);
 #pragma unroll 1
             for (int kb = 0; kb < kBC / kKB; ++kb) {
+                if (PAIR && kb != half) continue;
                 const int key_base = tile_at(t) * kBC + kb * kKB;
                 if (!block_visible(key_base)) continue;
                 scores(stage, kb, sa1, sa2);
+                float tmax = kNegInf;
 #pragma unroll
-                for (int a = 0; a < RW; ++a) {
-                    float tmax = kNegInf;
+                for (int r = 0; r < 16; ++r)
+                    tmax = fmaxf(tmax, key_ok(key_base, r) ? sa1[r] * row_scale : kNegInf);
+                tmax = halves_max(tmax);
+                const float m_new = fmaxf(m_ref, tmax);
+                const float m_use = m_new == kNegInf ? 0.f : m_new;
+                const float alpha = fast_exp2(m_ref - m_use);  // 0 while m_ref = -inf
+                m_ref = m_new;
+                if constexpr (STATS) {
+                    msum1[0] *= alpha, msum1[1] *= alpha;
+                    msum2[0] *= alpha, msum2[1] *= alpha;
+                }
+                if constexpr (!MFMA_SUMS) rsum1 *= alpha, rsum2 *= alpha;
 #pragma unroll
-                    for (int r = 0; r < 16; ++r)
-                        tmax = fmaxf(tmax, key_ok(key_base, r, a) ? sa1[a][r] * row_scale[a] : kNegInf);
-                    tmax = halves_max(tmax);
-                    const float m_new = fmaxf(m_ref[a], tmax);
-                    const float m_use = m_new == kNegInf ? 0.f : m_new;
-                    const float alpha = fast_exp2(m_ref[a] - m_use);  // 0 while m_ref = -inf
-                    m_ref[a] = m_new;
-                    if constexpr (STATS) {
-                        msum1[a][0] *= alpha, msum1[a][1] *= alpha;
-                        msum2[a][0] *= alpha, msum2[a][1] *= alpha;
-                    }
-                    if constexpr (!MFMA_SUMS) rsum1[a] *= alpha, rsum2[a] *= alpha;
+                for (int r = 0; r < 16; ++r) {
+                    if constexpr (MFMA_SUMS) dacc[r] *= alpha;
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        if constexpr (MFMA_SUMS) dacc[a][r] *= alpha;
-#pragma unroll
-                        for (int n = 0; n < NDB; ++n) {
-                            o1[a][n][r] *= alpha;
-                            if constexpr (USE_R) o2[a][n][r] *= alpha;
-                        }
+                    for (int n = 0; n < NDB; ++n) {
+                        o1[n][r] *= alpha;
+                        if constexpr (USE_R) o2[n][r] *= alpha;
                     }
                 }
                 probs(std::true_type{}, key_base, sa1, sa2, pb1, pb2);
@@ -1204,7 +1193,9 @@ __global__ __launch_bounds__(256, 1) void prefill_bf16_kernel(PrefillParams p) {
             stage = next_stage;
         }
         tile_barrier();  // outstanding tile loads land before the workgroup may exit
+        if constexpr (PAIR) merge_halves();
         (void)stage_outputs();
+        if constexpr (PAIR) __syncthreads();
     }
 
     // ---- SPLIT, more than one key range: the record of every row ----------------------------
@@ -1218,35 +1209,32 @@ __global__ __launch_bounds__(256, 1) void prefill_bf16_kernel(PrefillParams p) {
     if constexpr (SPLIT)
         if (n_ranges > 1) {
             const int64_t slot = ((int64_t)b * p.Hq + hq) * p.items_per_head + item;
+            if (row0 >= T) return;  // (wave-uniform) no such rows
+            float *rec = p.ws + (slot * 4 + w) * prefill_record_floats(D);
+            f32x4 *ob = (f32x4 *)rec + 32 * h + col;
+            const int e = __builtin_amdgcn_frexp_expf(dsum1);  // (0 for 0, inf and NaN)
+            auto scaled = [&](float x) __attribute__((always_inline)) { return __builtin_amdgcn_ldexpf(x, -e); };
+            auto scaled4 = [&](const f32x16 &x, int q4) __attribute__((always_inline)) {
+                return f32x4{scaled(x[4 * q4]), scaled(x[4 * q4 + 1]), scaled(x[4 * q4 + 2]), scaled(x[4 * q4 + 3])};
+            };
 #pragma unroll
-            for (int a = 0; a < RW; ++a) {
-                if (row0 + 32 * a >= T) continue;  // (wave-uniform) no such rows
-                float *rec = p.ws + ((slot * 4 + w) * RW + a) * prefill_record_floats(D);
-                f32x4 *ob = (f32x4 *)rec + 32 * h + col;
-                const int e = __builtin_amdgcn_frexp_expf(dsum1[a]);  // (0 for 0, inf and NaN)
-                auto scaled = [&](float x) __attribute__((always_inline)) { return __builtin_amdgcn_ldexpf(x, -e); };
-                auto scaled4 = [&](const f32x16 &x, int q4) __attribute__((always_inline)) {
-                    return f32x4{scaled(x[4 * q4]), scaled(x[4 * q4 + 1]), scaled(x[4 * q4 + 2]), scaled(x[4 * q4 + 3])};
-                };
+            for (int n = 0; n < NDB; ++n)
 #pragma unroll
-                for (int n = 0; n < NDB; ++n)
-#pragma unroll
-                    for (int q4 = 0; q4 < 4; ++q4) {
-                        ob[64 * (4 * n + q4)] = scaled4(o1[a][n], q4);
-                        if constexpr (USE_R) ob[64 * (4 * (NDB + n) + q4)] = scaled4(o2[a][n], q4);
-                    }
-                float fsum1 = 0.f, fsum2 = 0.f;  // row cache: sums of the unrounded P1, P2 (see msum1)
-                if constexpr (STATS) {
-                    fsum1 = halves_sum(vsum1[a][0] + vsum1[a][1] + msum1[a][0] + msum1[a][1]);
-                    fsum2 = halves_sum(vsum2[a][0] + vsum2[a][1] + msum2[a][0] + msum2[a][1]);
+                for (int q4 = 0; q4 < 4; ++q4) {
+                    ob[64 * (4 * n + q4)] = scaled4(o1[n], q4);
+                    if constexpr (USE_R) ob[64 * (4 * (NDB + n) + q4)] = scaled4(o2[n], q4);
                 }
-                if (h == 0) {
-                    float *row = rec + 64 * D + col;  // [m | d1 | d2 | sums of the unrounded P1 | P2][32 rows]
-                    row[0] = dsum1[a] > 0.f ? m_ref[a] + (float)e : kNegInf;
-                    row[32] = scaled(dsum1[a]);
-                    row[64] = scaled(dsum2s[a]);
-                    if constexpr (STATS) row[96] = scaled(fsum1), row[128] = scaled(fsum2);
-                }
+            float fsum1 = 0.f, fsum2 = 0.f;  // row cache: sums of the unrounded P1, P2 (see msum1)
+            if constexpr (STATS) {
+                fsum1 = halves_sum(vsum1[0] + vsum1[1] + msum1[0] + msum1[1]);
+                fsum2 = halves_sum(vsum2[0] + vsum2[1] + msum2[0] + msum2[1]);
+            }
+            if (h == 0) {
+                float *row = rec + 64 * D + col;  // [m | d1 | d2 | sums of the unrounded P1 | P2][32 rows]
+                row[0] = dsum1 > 0.f ? m_ref + (float)e : kNegInf;
+                row[32] = scaled(dsum1);
+                row[64] = scaled(dsum2s);
+                if constexpr (STATS) row[96] = scaled(fsum1), row[128] = scaled(fsum2);
             }
             return;
         }
@@ -1258,9 +1246,11 @@ __global__ __launch_bounds__(256, 1) void prefill_bf16_kernel(PrefillParams p) {
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         __bf16 *obase = (__bf16 *)p.o + b * p.os[0] + hq * p.os[1];
         constexpr int RPI = 64 / CPR;  // rows covered by one wave-wide 16-byte store
+        constexpr int NIT = (PAIR ? WROWS / 2 : WROWS) / RPI;  // PAIR: each wave stores half of the rows
+        const int rr0 = PAIR ? half * (WROWS / 2) : 0;
 #pragma unroll
-        for (int i = 0; i < WROWS / RPI; ++i) {
-            const int rr = i * RPI + lane / CPR, chunk = lane % CPR;
+        for (int i = 0; i < NIT; ++i) {
+            const int rr = rr0 + i * RPI + lane / CPR, chunk = lane % CPR;
             const int row = row0 + rr;
             if (row < T) *(u32x4 *)(obase + (int64_t)row * p.os[2] + chunk * 8) = otile[rr * OROW + chunk];
         }
@@ -1269,37 +1259,35 @@ __global__ __launch_bounds__(256, 1) void prefill_bf16_kernel(PrefillParams p) {
             // staging tile, and per row the log-sum-exp of the scaled scores in the exp2 domain
             // (P1 = exp2(S1 * scale * log2 e - lse) needs no further division) and ubar = d2 / d1.
             // (from the fp32 sums of the unrounded P1, P2 -- see msum1 above)
-#pragma unroll
-            for (int a = 0; a < RW; ++a) {
-                const float fsum1 = halves_sum(vsum1[a][0] + vsum1[a][1] + msum1[a][0] + msum1[a][1]);
-                const float fsum2 = halves_sum(vsum2[a][0] + vsum2[a][1] + msum2[a][0] + msum2[a][1]);
-                if (h == 0 && my_row(a) < T) {
-                    float *st = p.row_stats + (((int64_t)b * p.Hq + hq) * T + my_row(a)) * 2;
-                    // (a row with no visible key stores +inf: the backward's exp2(S1 - lse) is then
-                    // zero for every pair of the row, whatever the mask arithmetic does)
-                    st[0] = fsum1 > 0.f ? m_ref[a] + log2f(fsum1) : -kNegInf;
-                    st[1] = fsum1 > 0.f ? fsum2 / fsum1 : 0.f;
-                }
+            const float fsum1 = PAIR ? pfsum1 : halves_sum(vsum1[0] + vsum1[1] + msum1[0] + msum1[1]);
+            const float fsum2 = PAIR ? pfsum2 : halves_sum(vsum2[0] + vsum2[1] + msum2[0] + msum2[1]);
+            if (h == 0 && half == 0 && my_row < T) {
+                float *st = p.row_stats + (((int64_t)b * p.Hq + hq) * T + my_row) * 2;
+                // (a row with no visible key stores +inf: the backward's exp2(S1 - lse) is then
+                // zero for every pair of the row, whatever the mask arithmetic does)
+                st[0] = fsum1 > 0.f ? m_ref + log2f(fsum1) : -kNegInf;
+                st[1] = fsum1 > 0.f ? fsum2 / fsum1 : 0.f;
             }
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
-#pragma unroll
-            for (int a = 0; a < RW; ++a)
+            if constexpr (PAIR) __syncthreads();  // (the other wave has read its rows)
 #pragma unroll
                 for (int n = 0; n < NDB; ++n)
+                    if (owned(n))
 #pragma unroll
                     for (int q4 = 0; q4 < 4; ++q4) {
-                        const u32x2 packed = {pack_bf16(o1[a][n][4 * q4] * inv[a], o1[a][n][4 * q4 + 1] * inv[a]),
-                                              pack_bf16(o1[a][n][4 * q4 + 2] * inv[a], o1[a][n][4 * q4 + 3] * inv[a])};
-                        *(u32x2 *)(otile16 + (32 * a + col) * (OROW * 8) + 32 * n + 8 * q4 + 4 * h) = packed;
+                        const u32x2 packed = {pack_bf16(o1[n][4 * q4] * inv, o1[n][4 * q4 + 1] * inv),
+                                              pack_bf16(o1[n][4 * q4 + 2] * inv, o1[n][4 * q4 + 3] * inv)};
+                        *(u32x2 *)(otile16 + col * (OROW * 8) + 32 * n + 8 * q4 + 4 * h) = packed;
                     }
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            if constexpr (PAIR) __syncthreads();
             __bf16 *vbase_out = (__bf16 *)p.vbar + b * p.os[0] + hq * p.os[1];
 #pragma unroll
-            for (int i = 0; i < WROWS / RPI; ++i) {
-                const int rr = i * RPI + lane / CPR, chunk = lane % CPR;
+            for (int i = 0; i < NIT; ++i) {
+                const int rr = rr0 + i * RPI + lane / CPR, chunk = lane % CPR;
                 const int row = row0 + rr;
                 if (row < T)
                     *(u32x4 *)(vbase_out + (int64_t)row * p.os[2] + chunk * 8) = otile[rr * OROW + chunk];
@@ -1314,16 +1302,16 @@ __global__ __launch_bounds__(256, 1) void prefill_bf16_kernel(PrefillParams p) {
 // records do, so every load is one contiguous KB. Row blocks with one range were written by the
 // prefill kernel itself. Memory bound: the records travel twice, 2 x 1 KB per row and range at d = 128
 // (512 rows over 16384 keys, 16 heads: 8192 rows x 4 ranges, 34 MB each way).
-template <int D, bool USE_R, bool STATS, int RW>
+template <int D, bool USE_R, bool STATS>
 __global__ __launch_bounds__(256) void prefill_combine_kernel(PrefillParams p) {
-    constexpr int NDB = D / 32, ROWS = 128 * RW;
+    constexpr int NDB = D / 32, ROWS = 128;
     const int lane = threadIdx.x & 63, col = lane & 31, h = lane >> 5;
     const int nrb = (p.T + ROWS - 1) / ROWS;
     int64_t id = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);  // (batch, head, row block, 32 rows, n)
     const int n = (int)(id % NDB);
     id /= NDB;
-    const int sub = (int)(id % (4 * RW));
-    id /= 4 * RW;
+    const int sub = (int)(id % 4);
+    id /= 4;
     const int rbi = (int)(id % nrb);
     const int64_t bh = id / nrb;
     if (bh >= (int64_t)p.B * p.Hq) return;  // (whole waves)
@@ -1338,7 +1326,7 @@ __global__ __launch_bounds__(256) void prefill_combine_kernel(PrefillParams p) {
     }
     if (n_ranges == 1) return;
     auto record = [&](int i) {
-        return p.ws + ((bh * p.items_per_head + item0 + i) * (4 * RW) + sub) * prefill_record_floats(D);
+        return p.ws + ((bh * p.items_per_head + item0 + i) * 4 + sub) * prefill_record_floats(D);
     };
     float m = kNegInf;
 #pragma unroll 8
@@ -1382,9 +1370,56 @@ __global__ __launch_bounds__(256) void prefill_combine_kernel(PrefillParams p) {
         }
 }
 
+// What a launch costs, in units of one 64-key tile of a workgroup that has a compute unit to itself (1.2 us at
+// d = 128, 0.72 at d = 64): to start and finish a workgroup, and per workgroup and tile of the chip's load (d = 64:
+// two share a unit, which hides most of a start and delivers a tile every 0.95 us).
+struct PrefillCosts {
+    double unit, start, load_start, load_tile;
+    int resident;                                              // workgroups per compute unit
+    double pair_start, pair_tile, pair_load_start, pair_load_tile;  // 64 rows per workgroup (PAIR)
+};
+static PrefillCosts prefill_costs(int d) {
+    return d == 128 ? PrefillCosts{1.2, 4.0, 4.0, 1.0, 1, 5.7, 0.55, 6.2, 0.55}
+                    : PrefillCosts{0.72, 7.8, 4.2, 1.32, 2, 7.9, 0.64, 2.5, 0.76};
+}
+// 64 rows per workgroup (PAIR) or 128, from the longest workgroup and the load dealt over the chip, for the causal
+// forms. Measured us, 128 rows / 64: 16 query heads, d = 128, 200 rows 11.5 / 10.7, 777 20.8 / 16.9, 1000 24.1 / 18.8,
+// 1500 32.9 / 28.3, 2048 44.4 / 41.4, but 128 8.4 / 8.8, 2500 59 / 64; 32 heads, 500 16.3 / 14.0, 777 22.1 / 23.1; 32 heads
+// x 300 behind 2700 keys 61 / 38.5; 32 heads, d = 64, 300 9.3 / 8.2, 777 15.8 / 13.1, 1500 28.1 / 28.8, 64 heads, 777
+// 20.5 / 21.6, 8 heads, 2000 28.6 / 20.4. From 4096 rows on always 128: the two add in different orders, and there a
+// sequence's outputs are to have the same bits whatever else is in the launch.
+struct PrefillForms {
+    bool pair;
+    double best_us;
+};
+static PrefillForms choose_form(const PrefillParams &p, int num_cus) {
+    const PrefillCosts c = prefill_costs(p.d);
+    const double heads = (double)p.B * p.Hq, off = (double)p.Tk - p.T;
+    const bool windowed = p.window > 0 && p.window < p.Tk;
+    auto form = [&](int rows, double start, double tile, double load_start, double load_tile, double tail) {
+        const double blocks = (p.T + rows - 1) / rows;
+        double longest = (p.Tk + kBC - 1) / kBC, mean = longest;
+        if (p.causal) mean = std::min(longest, (off + 0.5 * rows * (blocks + 1)) / kBC);
+        if (windowed) longest = std::min(longest, (p.window + rows - 1.0) / kBC + 1), mean = std::min(mean, longest);
+        const double n = heads * blocks;
+        // (the key tiles of all workgroups come out of the L2 and the cache behind it at 9.5 TB/s, at d = 64 at 6.8: 16
+        // heads x 1024 rows over 16384 keys, d = 128, by 64 rows 229 us, in two key ranges by 128 rows 213; 32 heads x
+        // 512, d = 64, 157 and 129)
+        const double traffic = n * mean * (4.0 * kBC * p.d) / ((p.d == 128 ? 9.5e6 : 6.8e6) * c.unit);
+        const double widest = std::max(start + tile * longest, traffic);
+        if (n <= (double)c.resident * num_cus) return widest;
+        return std::max(widest, n * (load_start + load_tile * mean) / num_cus + tail * widest);
+    };
+    const double whole = form(128, c.start, 1.0, c.load_start, c.load_tile, p.d == 128 ? 0.25 : 0.0);
+    if (!p.causal || !p.use_r || p.sparse_row_ptr != nullptr || p.T >= 4096 || (p.d == 128 && p.Tk <= 2 * kBC))
+        return {false, whole * c.unit};
+    const double pair = form(64, c.pair_start, c.pair_tile, c.pair_load_start, c.pair_load_tile, 0.1);
+    return {pair < whole, std::min(pair, whole) * c.unit};
+}
+
 // Key ranges of a launch that leaves compute units idle: the tiles per range with the smallest
-// estimate, in units of one 64-key tile of a workgroup (1.2 us at d = 128, 1.5 at d = 64, where it
-// serves twice as many rows): 4 to start and finish a workgroup, one workgroup per compute unit at a
+// estimate, in units of one 64-key tile of a workgroup (1.2 us at d = 128; d = 64: 1.5 for 256 rows, two workgroups
+// of the launch sharing a unit): 4 to start and finish a workgroup, one workgroup per compute unit at a
 // time; what a launch with more items than units loses at its end is taken as half an item. Merging
 // costs a launch (4) and the records' bytes there and back (4.2 MB per unit, what the sweeps below show).
 // With fewer than 16 tiles to cut, the records are few and dearer than that: the split has to win with 9
@@ -1396,13 +1431,16 @@ __global__ __launch_bounds__(256) void prefill_combine_kernel(PrefillParams p) {
 // of ranges of the longest row block, 16 heads, d = 128: 512 rows over 16384 keys whole 267, 2 160, 3 128,
 // 4 (the rule) 114, 5 160, 8 135; 1024 over 16384 whole 302, 2 (the rule) 207, 3 250, 4 226; 256 over 2000
 // whole 41, 2 34, 3 31, 4 33; 17 over 5000 whole 86, 8 30, 16 34; square prompts of 300 ... 3000 rows whole
-// (the rule) 13 ... 75, 2 18 ... 108; 8 heads, 1000 square whole (the rule) 24, 2 25, 4 29; d = 64, 8 heads,
-// 2000 square whole 50, 2 39, 3 37, 6 36, 8 47.
+// (the rule) 13 ... 75, 2 18 ... 108; 8 heads, 1000 square whole (the rule) 24, 2 25, 4 29; d = 64: 32 heads x 512 over
+// 16384 whole 190, 2 129, 4 (the rule) 129, 8 138; 17 over 17000 whole 195, 4 61, 8 42, 12 51; 8 heads x 700 over 9000
+// whole 106, 3 50, 5 43, 8 46. Where halved chains without records (choose_form) are quicker still, best_form is
+// false and the split is not taken: 2 x 16 heads, 300 rows over 3000 keys 46 against 38; d = 64, 32 heads, 300
+// over 4000 58 against 50.
 // The plan is made on every call, on the host, so it estimates no more than it has to: once for row
 // blocks that see the same keys (full attention) and for range counts that come to the same tiles, and
 // only those counts whose lower bound (as if tiles divided evenly) can still win (8 heads x 3900 rows,
 // causal: 7.5 -> 0.5 us on the host; 2 x 8192: 16 -> 1.9, full attention 14 -> 0.2).
-static int choose_split_tiles(const PrefillParams &p, int num_cus, int *items_per_head) {
+static int choose_split_tiles(const PrefillParams &p, int num_cus, int *items_per_head, double *cost_us) {
     const int rows = p.d == 64 ? 256 : 128, nrb = (p.T + rows - 1) / rows;
     const int64_t heads = (int64_t)p.B * p.Hq;
     *items_per_head = nrb;
@@ -1450,28 +1488,39 @@ static int choose_split_tiles(const PrefillParams &p, int num_cus, int *items_pe
     // Short chains: the merge of their few records is bound by its start instead of its bytes
     if (best > 0 && longest < 16 && (p.d == 64 ? estimate(best, &items, 5.0, 0.7) : estimate(best, &items, 9.0, 0.3)) >= limit)
         best = 0, *items_per_head = nrb;
+    *cost_us = best_cost * (p.d == 64 ? 1.5 : 1.2);
     return best;
 }
 
-size_t plan_prefill_split_bf16(PrefillParams &p, int num_cus) {
+size_t plan_prefill_split_bf16(PrefillParams &p, int num_cus, bool *best_form) {
     p.split_tiles = 0;
+    *best_form = false;
     if (p.sparse_row_ptr != nullptr || p.window > 0 || p.prep.gamma_q != nullptr) return 0;
-    p.split_tiles = choose_split_tiles(p, num_cus, &p.items_per_head);
+    double cost_us;
+    p.split_tiles = choose_split_tiles(p, num_cus, &p.items_per_head, &cost_us);
     if (p.split_tiles == 0) return 0;
-    return (size_t)p.B * p.Hq * p.items_per_head * (p.d == 64 ? 8 : 4) * prefill_record_floats(p.d) * sizeof(float);
+    *best_form = cost_us <= choose_form(p, num_cus).best_us;
+    const size_t bytes = (size_t)p.B * p.Hq * p.items_per_head * (p.d == 64 ? 8 : 4) * prefill_record_floats(p.d) * sizeof(float);
+    if (p.d == 64) {  // (the items of the 128-row blocks, at most two to one of 256 rows)
+        const int nrb = (p.T + 127) / 128;
+        p.items_per_head = 0;
+        for (int i = 0; i < nrb; ++i)
+            p.items_per_head += PrefillRanges(p.causal ? std::min(p.Tk, (nrb - i) * 128 + (p.Tk - p.T)) : p.Tk, p.split_tiles).count;
+    }
+    return bytes;
 }
 
-template <int D, int RW>
+template <int D>
 static hipError_t launch_prefill_split(const PrefillParams &p, hipStream_t stream) {
     const long long total = (long long)p.items_per_head * p.Hq * p.B;
-    const int rows = 128 * RW;
-    const long long waves = (long long)((p.T + rows - 1) / rows) * p.Hq * p.B * (4 * RW) * (D / 32);
+    const int rows = 128;
+    const long long waves = (long long)((p.T + rows - 1) / rows) * p.Hq * p.B * 4 * (D / 32);
     const dim3 grid((unsigned)total), merge((unsigned)((waves + 3) / 4)), block(256);
     auto run = [&](auto use_r, auto causal, auto stats) {
         constexpr bool R = decltype(use_r)::value, C = decltype(causal)::value, ST = decltype(stats)::value;
-        hipLaunchKernelGGL((prefill_bf16_kernel<D, R, C, false, ST, false, RW, false, true>), grid, block, 0, stream, p);
+        hipLaunchKernelGGL((prefill_bf16_kernel<D, R, C, false, ST, false, false, true>), grid, block, 0, stream, p);
         if (hipError_t err = hipGetLastError()) return err;
-        hipLaunchKernelGGL((prefill_combine_kernel<D, R, ST, RW>), merge, block, 0, stream, p);
+        hipLaunchKernelGGL((prefill_combine_kernel<D, R, ST>), merge, block, 0, stream, p);
         return hipGetLastError();
     };
     const std::true_type yes;
@@ -1501,52 +1550,73 @@ static hipError_t launch_prefill_sparse(const PrefillParams &p, hipStream_t stre
     return hipGetLastError();
 }
 
-// Dense kernels: RW = 2 (256 query rows per workgroup) at d = 64, RW = 1 at d = 128.
-template <int D, int RW>
+// Dense causal forward, 64 rows per workgroup
+template <int D>
+static hipError_t launch_prefill_pair(const PrefillParams &p, hipStream_t stream) {
+    const long long total = (long long)((p.T + 63) / 64) * p.Hq * p.B;
+    if (total > 0x7fffffffLL) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)total), block(256);
+    if (p.prep.gamma_q != nullptr)
+        hipLaunchKernelGGL((prefill_bf16_kernel<D, true, true, false, false, false, true, false, true>), grid, block, 0, stream, p);
+    else if (p.row_stats != nullptr && p.window > 0)
+        hipLaunchKernelGGL((prefill_bf16_kernel<D, true, true, true, true, false, false, false, true>), grid, block, 0, stream, p);
+    else if (p.row_stats != nullptr)
+        hipLaunchKernelGGL((prefill_bf16_kernel<D, true, true, false, true, false, false, false, true>), grid, block, 0, stream, p);
+    else if (p.window > 0)
+        hipLaunchKernelGGL((prefill_bf16_kernel<D, true, true, true, false, false, false, false, true>), grid, block, 0, stream, p);
+    else
+        hipLaunchKernelGGL((prefill_bf16_kernel<D, true, true, false, false, false, false, false, true>), grid, block, 0, stream, p);
+    return hipGetLastError();
+}
+
+// Dense kernels, 128 rows per workgroup
+template <int D>
 static hipError_t launch_prefill_dense(const PrefillParams &p, hipStream_t stream) {
-    const int rows = 128 * RW;
+    const int rows = 128;
     const long long total = (long long)((p.T + rows - 1) / rows) * p.Hq * p.B;
     if (total > 0x7fffffffLL) return hipErrorInvalidValue;
     const dim3 grid((unsigned)total), block(256);
     if (p.prep.gamma_q != nullptr) {  // RMSNorm + RoPE on q, rho in the prologue (use_r, no window, no row cache)
         if (p.causal)
-            hipLaunchKernelGGL((prefill_bf16_kernel<D, true, true, false, false, false, RW, true>), grid, block, 0, stream, p);
+            hipLaunchKernelGGL((prefill_bf16_kernel<D, true, true, false, false, false, true>), grid, block, 0, stream, p);
         else
-            hipLaunchKernelGGL((prefill_bf16_kernel<D, true, false, false, false, false, RW, true>), grid, block, 0, stream, p);
+            hipLaunchKernelGGL((prefill_bf16_kernel<D, true, false, false, false, false, true>), grid, block, 0, stream, p);
         return hipGetLastError();
     }
     if (p.row_stats != nullptr && p.window > 0) {  // row cache + sliding window (causal, use_r)
-        hipLaunchKernelGGL((prefill_bf16_kernel<D, true, true, true, true, false, RW>), grid, block, 0, stream, p);
+        hipLaunchKernelGGL((prefill_bf16_kernel<D, true, true, true, true, false>), grid, block, 0, stream, p);
     } else if (p.row_stats != nullptr) {  // with the row cache of the backward pass (use_r)
         if (p.causal)
-            hipLaunchKernelGGL((prefill_bf16_kernel<D, true, true, false, true, false, RW>), grid, block, 0, stream, p);
+            hipLaunchKernelGGL((prefill_bf16_kernel<D, true, true, false, true, false>), grid, block, 0, stream, p);
         else
-            hipLaunchKernelGGL((prefill_bf16_kernel<D, true, false, false, true, false, RW>), grid, block, 0, stream, p);
+            hipLaunchKernelGGL((prefill_bf16_kernel<D, true, false, false, true, false>), grid, block, 0, stream, p);
     } else if (p.window > 0) {  // causal only (checked by the caller)
         if (p.use_r)
-            hipLaunchKernelGGL((prefill_bf16_kernel<D, true, true, true, false, false, RW>), grid, block, 0, stream, p);
+            hipLaunchKernelGGL((prefill_bf16_kernel<D, true, true, true, false, false>), grid, block, 0, stream, p);
         else
-            hipLaunchKernelGGL((prefill_bf16_kernel<D, false, true, true, false, false, RW>), grid, block, 0, stream, p);
+            hipLaunchKernelGGL((prefill_bf16_kernel<D, false, true, true, false, false>), grid, block, 0, stream, p);
     } else if (p.use_r) {
         if (p.causal)
-            hipLaunchKernelGGL((prefill_bf16_kernel<D, true, true, false, false, false, RW>), grid, block, 0, stream, p);
+            hipLaunchKernelGGL((prefill_bf16_kernel<D, true, true, false, false, false>), grid, block, 0, stream, p);
         else
-            hipLaunchKernelGGL((prefill_bf16_kernel<D, true, false, false, false, false, RW>), grid, block, 0, stream, p);
+            hipLaunchKernelGGL((prefill_bf16_kernel<D, true, false, false, false, false>), grid, block, 0, stream, p);
     } else {
         if (p.causal)
-            hipLaunchKernelGGL((prefill_bf16_kernel<D, false, true, false, false, false, RW>), grid, block, 0, stream, p);
+            hipLaunchKernelGGL((prefill_bf16_kernel<D, false, true, false, false, false>), grid, block, 0, stream, p);
         else
-            hipLaunchKernelGGL((prefill_bf16_kernel<D, false, false, false, false, false, RW>), grid, block, 0, stream, p);
+            hipLaunchKernelGGL((prefill_bf16_kernel<D, false, false, false, false, false>), grid, block, 0, stream, p);
     }
     return hipGetLastError();
 }
 
-hipError_t launch_prefill_bf16(const PrefillParams &p, hipStream_t stream) {
+hipError_t launch_prefill_bf16(const PrefillParams &p, int num_cus, hipStream_t stream) {
     if (p.ws != nullptr)  // (planned and sized by plan_prefill_split_bf16)
-        return p.d == 128 ? launch_prefill_split<128, 1>(p, stream) : launch_prefill_split<64, 2>(p, stream);
+        return p.d == 128 ? launch_prefill_split<128>(p, stream) : launch_prefill_split<64>(p, stream);
     if (p.sparse_row_ptr != nullptr)
         return p.d == 128 ? launch_prefill_sparse<128>(p, stream) : launch_prefill_sparse<64>(p, stream);
-    return p.d == 128 ? launch_prefill_dense<128, 1>(p, stream) : launch_prefill_dense<64, 2>(p, stream);
+    if (choose_form(p, num_cus).pair)
+        return p.d == 128 ? launch_prefill_pair<128>(p, stream) : launch_prefill_pair<64>(p, stream);
+    return p.d == 128 ? launch_prefill_dense<128>(p, stream) : launch_prefill_dense<64>(p, stream);
 }
 
 }  // namespace plx

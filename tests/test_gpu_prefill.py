@@ -124,6 +124,31 @@ def test_head_dim_64_two_row_sub_blocks_per_wave(plx, synth, oracle, T, Tkv, cau
         assert rel_l2(gotb, refb) <= BF16_REL_L2
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,T,Tkv,d,causal,window", [
+    # many heads: 128 rows per workgroup, two workgroups per compute unit at d = 64
+    (40, 16, 8, 130, 130, 128, True, 0), (40, 16, 8, 65, 200, 128, True, 50), (48, 16, 8, 129, 129, 64, True, 0),
+    (48, 16, 8, 100, 257, 64, False, 0), (48, 16, 8, 190, 190, 64, True, 33),
+    # few heads: 64 rows per workgroup, waves by twos on the halves of a tile; odd and even numbers of tiles
+    (1, 4, 2, 193, 193, 128, True, 0), (1, 4, 2, 65, 260, 128, True, 0), (1, 4, 2, 320, 320, 128, True, 90),
+    (2, 4, 4, 64, 64, 64, True, 0), (1, 4, 2, 63, 321, 64, True, 0), (1, 4, 2, 257, 257, 64, True, 70)])
+def test_forms_of_a_launch(plx, synth, oracle, B, Hq, Hkv, T, Tkv, d, causal, window):
+    """Every form of the kernel at the edges of its blocks, first and last batch entry, with and without the row
+    cache; then the same rows with scores hundreds of binades apart (the online update and its merge)."""
+    y = synth.prefill_inputs(B, Hq, Hkv, Tkv, d, seed=900 + T + d, device=DEV)
+    y["q"], y["r"] = y["q"][:, :, Tkv - T:].contiguous(), y["r"][:, :, Tkv - T:].contiguous()
+    ramp = torch.linspace(0.2, 3.0, Tkv, device=DEV).view(1, 1, Tkv, 1)
+    wide = dict(y, q=(y["q"].float() * 30.0).to(torch.bfloat16), k=(y["k"].float() * ramp).to(torch.bfloat16))
+    for x in (y, wide):
+        out = plx.parallax_prefill(x["q"], x["r"], x["k"], x["v"], x["scale"], causal=causal, window=window)
+        cached = plx.parallax_prefill(x["q"], x["r"], x["k"], x["v"], x["scale"], causal=causal, window=window,
+                                      save_for_backward=True)[0]
+        for b in {0, B - 1}:
+            ref = oracle.forward(*(host(x[n][b:b + 1]) for n in "qrkv"), x["scale"], causal=causal, window=window)
+            for got in (out, cached):
+                assert np.isfinite(host(got[b:b + 1])).all()
+                assert rel_l2(host(got[b:b + 1]), ref) <= BF16_REL_L2, (b, x is wide)
+
+
 def test_scale_zero_is_uniform_weighting(plx, synth, oracle):
     """scale = 0 is the wide-bandwidth limit (uniform softmax weights)."""
     y = synth.prefill_inputs(1, 4, 2, 260, 128, seed=821, device=DEV, r_scale=0.2)
