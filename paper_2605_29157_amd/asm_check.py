@@ -140,6 +140,35 @@ def find_early_reads_of_asm_mfma_results(asm_text: str) -> list[str]:
     return bad
 
 
+def find_early_writes_over_asm_mfma_results(asm_text: str) -> list[str]:
+    """The other half of the hazard above: a block that nothing reads any more (the scores that a
+    pipeline's last step makes for a tile that is not there) is free to the register allocator at
+    once, and what a vector instruction puts there before the MFMA has written back is lost."""
+    bad, pending, inside = [], [], False  # pending: (line, registers, wait states so far)
+    for n, line in enumerate(asm_text.splitlines(), 1):
+        t = line.strip()
+        if t.startswith(";;#ASMSTART") or t.startswith(";;#ASMEND"):
+            inside = t.startswith(";;#ASMSTART")
+            continue
+        if not _is_instruction(line):
+            continue
+        ins = t.split(";")[0].strip()
+        if ins.endswith(":") or ins.startswith("s_endpgm"):
+            pending = []
+            continue
+        parts = ins.split(None, 1)
+        dst = _regs(parts[1].split(",")[0]) if len(parts) == 2 else set()
+        mfma = ins.startswith("v_mfma")
+        if ins.startswith("v_") and not mfma:
+            bad += ["line %d: '%s' overwrites the result of the assembly MFMA at line %d after only %d wait states"
+                    % (n, ins, m, w) for m, regs, w in pending if regs & dst]
+        step = MFMA_PASSES if mfma else _wait_states(ins)
+        pending = [(m, regs, w + step) for m, regs, w in pending if w + step < MFMA_RESULT_WAIT_STATES]
+        if mfma and inside:
+            pending = [p for p in pending if p[1] != dst] + [(n, dst, 0)]
+    return bad
+
+
 DOT_RESULT_WAIT_STATES = 3  # a dot-product result may be read by a different instruction after 3
 
 
@@ -224,6 +253,7 @@ def check_file(path: str) -> None:
     with open(path) as f:
         text = f.read()
     bad = (find_violations(text) + find_m0_uses_outside_inline_asm(text)
-           + find_early_reads_of_asm_mfma_results(text) + find_early_reads_of_asm_dot_results(text))
+           + find_early_reads_of_asm_mfma_results(text) + find_early_reads_of_asm_dot_results(text)
+           + find_early_writes_over_asm_mfma_results(text))
     if bad:
         raise RuntimeError("MFMA source hazard in %s:\n  %s" % (path, "\n  ".join(bad[:20])))

@@ -59,6 +59,7 @@ def _check_pipelined_assembly(src: str, full: bool) -> None:
     with open(asm) as f:
         text = f.read()
     bad = (asm_check.find_early_reads_of_asm_mfma_results(text)
+           + asm_check.find_early_writes_over_asm_mfma_results(text)
            + asm_check.find_m0_uses_outside_inline_asm(text)
            + asm_check.find_foreign_uses_of_asm_loaded_registers(text))
     if bad:

@@ -70,6 +70,16 @@ def test_late_reads_chained_mfmas_and_writes_pass():
     assert check(OTHER_MFMA + "\tv_accvgpr_read_b32 v1, a0\n") == []
 
 
+def test_early_write_over_the_result_is_flagged():
+    check = asm_check.find_early_writes_over_asm_mfma_results
+    write = "\tv_cvt_pk_bf16_f32 v36, v1, v2\n"
+    assert len(check(ASM_MFMA + write)) == 1
+    assert len(check(ASM_MFMA + OTHER_MFMA + write)) == 1
+    assert check(ASM_MFMA + OTHER_MFMA + OTHER_MFMA + write) == []
+    assert check(ASM_MFMA + ASM_MFMA) == []
+    assert check(ASM_MFMA + "\tv_cvt_pk_bf16_f32 v60, v1, v2\n") == []
+
+
 def test_foreign_use_of_an_assembly_loaded_register_is_reported():
     """Registers written by inline-assembly global loads may only be touched by inline assembly
     until the last inline-assembly LDS store: a compiler-made copy in between is reported."""
