@@ -66,14 +66,17 @@ __global__ __launch_bounds__(256, 1) void decode_mla_kernel(MlaDecodeParams p) {
     int Lb = p.seq_lens ? p.seq_lens[b] : p.Lmax;
     Lb = min(max(Lb, 0), p.Lmax);
     // tokens [key_lo, key_end) of this lane's column: row t of a head is at position Lb - Tq + t
-    const int key_end = live ? max(Lb - p.Tq + (head % p.Tq) + 1, 0) : 0;
+    // (one row per head: every live column ends at Lb, nothing to divide or to agree on)
+    const int key_end = !live ? 0 : p.Tq == 1 ? Lb : max(Lb - p.Tq + (head % p.Tq) + 1, 0);
     const int key_lo = p.window > 0 ? max(key_end - p.window, 0) : 0;
     // the workgroup's tiles: the union over its live columns (the same value in every wave)
     int wg_end = key_end, wg_lo = live && key_end > 0 ? key_lo : 0x7fffffff;
+    if (p.Tq > 1) {  // (lane 0's column is live otherwise and speaks for all)
 #pragma unroll
-    for (int off = 1; off < 16; off <<= 1) {
-        wg_end = max(wg_end, __shfl_xor(wg_end, off, 64));
-        wg_lo = min(wg_lo, __shfl_xor(wg_lo, off, 64));
+        for (int off = 1; off < 16; off <<= 1) {
+            wg_end = max(wg_end, __shfl_xor(wg_end, off, 64));
+            wg_lo = min(wg_lo, __shfl_xor(wg_lo, off, 64));
+        }
     }
     wg_end = __builtin_amdgcn_readfirstlane(wg_end);
     wg_lo = __builtin_amdgcn_readfirstlane(min(wg_lo, wg_end));

@@ -83,28 +83,6 @@ __global__ __launch_bounds__(256, 1) void decode_mla_wide_kernel(MlaDecodeParams
     const int scol = cgroup * CG + 16 * ch + c16, ocol = cgroup * CG + c32;  // in [0, Hq * Tq)
     const bool live_s = scol < n_cols, live_o = ocol < n_cols;
 
-    int Lb = p.seq_lens ? p.seq_lens[b] : p.Lmax;
-    Lb = min(max(Lb, 0), p.Lmax);
-    // tokens [key_lo, key_end) of a column: row t of a head is at position Lb - Tq + t
-    auto col_end = [&](int col, bool live) { return live ? max(Lb - p.Tq + (col % p.Tq) + 1, 0) : 0; };
-    auto col_lo = [&](int end) { return p.window > 0 ? max(end - p.window, 0) : 0; };
-    const int key_end = col_end(scol, live_s), key_lo = col_lo(key_end);  // of the score column
-    // the workgroup's tiles: the union over its live columns (the same value in every wave)
-    const int oend = col_end(ocol, live_o);
-    int wg_end = oend, wg_lo = live_o && oend > 0 ? col_lo(oend) : 0x7fffffff;
-#pragma unroll
-    for (int off = 1; off < CG; off <<= 1) {
-        wg_end = max(wg_end, __shfl_xor(wg_end, off, 64));
-        wg_lo = min(wg_lo, __shfl_xor(wg_lo, off, 64));
-    }
-    wg_end = __builtin_amdgcn_readfirstlane(wg_end);
-    wg_lo = __builtin_amdgcn_readfirstlane(min(wg_lo, wg_end));
-    const int tile0 = wg_lo / kMlaTileKeys;
-    const int n_tiles = (wg_end + kMlaTileKeys - 1) / kMlaTileKeys - tile0;
-    const int tiles_per_split = (n_tiles + S - 1) / S;
-    const int t_lo = tile0 + split * tiles_per_split;
-    const int t_hi = min(t_lo + tiles_per_split, tile0 + n_tiles);
-
     // ---- B operands of the scores: q and rho of the score column (zero if it is dead), k-step s
     // = dimensions 32 s + 8 g .. + 7, resident for the whole kernel
     u32x4 qf[kMlaKSteps], rf[kMlaKSteps];
@@ -119,6 +97,31 @@ __global__ __launch_bounds__(256, 1) void decode_mla_wide_kernel(MlaDecodeParams
             rf[s] = live_s ? *(const u32x4 *)(rrow + 32 * s + 8 * g) : z;
         }
     }
+
+    int Lb = p.seq_lens ? p.seq_lens[b] : p.Lmax;
+    Lb = min(max(Lb, 0), p.Lmax);
+    // tokens [key_lo, key_end) of a column: row t of a head is at position Lb - Tq + t
+    // (one row per head: every live column ends at Lb, nothing to divide or to agree on)
+    auto col_end = [&](int col, bool live) { return !live ? 0 : p.Tq == 1 ? Lb : max(Lb - p.Tq + (col % p.Tq) + 1, 0); };
+    auto col_lo = [&](int end) { return p.window > 0 ? max(end - p.window, 0) : 0; };
+    const int key_end = col_end(scol, live_s), key_lo = col_lo(key_end);  // of the score column
+    // the workgroup's tiles: the union over its live columns (the same value in every wave)
+    const int oend = col_end(ocol, live_o);
+    int wg_end = oend, wg_lo = live_o && oend > 0 ? col_lo(oend) : 0x7fffffff;
+    if (p.Tq > 1) {  // (lane 0's column is live otherwise and speaks for all)
+#pragma unroll
+        for (int off = 1; off < CG; off <<= 1) {
+            wg_end = max(wg_end, __shfl_xor(wg_end, off, 64));
+            wg_lo = min(wg_lo, __shfl_xor(wg_lo, off, 64));
+        }
+    }
+    wg_end = __builtin_amdgcn_readfirstlane(wg_end);
+    wg_lo = __builtin_amdgcn_readfirstlane(min(wg_lo, wg_end));
+    const int tile0 = wg_lo / kMlaTileKeys;
+    const int n_tiles = (wg_end + kMlaTileKeys - 1) / kMlaTileKeys - tile0;
+    const int tiles_per_split = (n_tiles + S - 1) / S;
+    const int t_lo = tile0 + split * tiles_per_split;
+    const int t_hi = min(t_lo + tiles_per_split, tile0 + n_tiles);
 
     // ---- global -> LDS tile loads -------------------------------------------------------------
     // A load fills 64 consecutive chunk slots of the tile: four rows of a latent column block or
