@@ -206,7 +206,8 @@ __device__ __forceinline__ void swap_halves(f32x16 (&first)[D / 32], f32x16 (&se
 }
 // 32 rows, times `scale`, to base + row * stride (rows < n_rows only). A lane owns one ROW: stored from the
 // registers, an instruction would touch 32 rows, 16 bytes each; the wave turns its block through its own
-// piece of the LDS and writes whole rows. (4 x 4096 rows, d = 128: 5.1 -> 2.5 us at the end of a workgroup.)
+// piece of the LDS and writes whole rows. (16 heads, d = 128: 1 x 300 rows 35.2 -> 33.1 us, 4 x
+// 4096 1458 -> 1439.)
 template <int D>
 __device__ __forceinline__ void store_rows(const f32x16 (&acc)[D / 32], float scale, __bf16 *base, int64_t stride,
                                            int n_rows, int w, int lane, u32x4 *lds) {
