@@ -280,12 +280,14 @@ plx_status parallax_prefill(const plx_prefill_args *args, void *hip_stream);
  * unnormalised fp32 records go to the workspace and are merged by a second kernel (App. C). bf16,
  * dense forms only; the split is chosen from the shape, and where none pays the call is
  * parallax_prefill.
- *   parallax_prefill_workspace_bytes  what a split of this call takes, 0 = none pays against the launch
- *                                     of 128 rows per workgroup (or the arguments are not valid)
- *   workspace   NULL, or 16-byte aligned device memory; smaller than that: the call runs unsplit, as it does
- *               where parallax_prefill is quicker still (64 rows per workgroup)
+ *   parallax_prefill_workspace_bytes  what the split of this call takes, 0 = the call is not split (or its
+ *                                     arguments are not valid)
+ *   workspace   NULL, or 16-byte aligned device memory; smaller than that: the call runs unsplit
+ *   parallax_prefill_form  how a bf16 call runs with a workspace of that many bytes: query rows per workgroup (64
+ *                          or 128) plus 256 * (64-key tiles per key range, 0 = not split); 0: fp32, or not valid
  */
 size_t parallax_prefill_workspace_bytes(const plx_prefill_args *args);
+int32_t parallax_prefill_form(const plx_prefill_args *args, size_t workspace_bytes);
 plx_status parallax_prefill_split(const plx_prefill_args *args, void *workspace, size_t workspace_bytes,
                                   void *hip_stream);
 

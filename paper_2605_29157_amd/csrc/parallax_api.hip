@@ -467,24 +467,27 @@ plx_status parallax_prefill(const plx_prefill_args *a, void *hip_stream) {
 size_t parallax_prefill_workspace_bytes(const plx_prefill_args *a) {
     plx::PrefillParams p{};
     if (prepare_prefill(a, &p) != PLX_OK || a->dtype != PLX_BF16) return 0;
-    bool best_form;
-    return plx::plan_prefill_split_bf16(p, query_num_cus(), &best_form);
+    return plx::plan_prefill_bf16(p, query_num_cus(), true);
+}
+
+int32_t parallax_prefill_form(const plx_prefill_args *a, size_t workspace_bytes) {
+    plx::PrefillParams p{};
+    if (prepare_prefill(a, &p) != PLX_OK || a->dtype != PLX_BF16) return 0;
+    const size_t need = plx::plan_prefill_bf16(p, query_num_cus(), workspace_bytes > 0);
+    return need > 0 && workspace_bytes >= need ? 128 + 256 * p.split_tiles : p.rows;
 }
 
 plx_status parallax_prefill_split(const plx_prefill_args *a, void *workspace, size_t workspace_bytes,
                                   void *hip_stream) {
     plx::PrefillParams p{};
-    plx_status st = prepare_prefill(a, &p);
+    const plx_status st = prepare_prefill(a, &p);
     if (st != PLX_OK) return st;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     if (a->dtype == PLX_F32) return plx::launch_prefill_f32(p, stream) == hipSuccess ? PLX_OK : PLX_ERR_LAUNCH;
-    if (workspace) {
-        if (!aligned16(workspace)) return PLX_ERR_WORKSPACE;
-        bool best_form;
-        const size_t need = plx::plan_prefill_split_bf16(p, query_num_cus(), &best_form);
-        if (need > 0 && best_form && workspace_bytes >= need) p.ws = static_cast<float *>(workspace);
-    }
-    return plx::launch_prefill_bf16(p, query_num_cus(), stream) == hipSuccess ? PLX_OK : PLX_ERR_LAUNCH;
+    if (workspace && !aligned16(workspace)) return PLX_ERR_WORKSPACE;
+    const size_t need = plx::plan_prefill_bf16(p, query_num_cus(), workspace != nullptr && workspace_bytes > 0);
+    if (need > 0 && workspace_bytes >= need) p.ws = static_cast<float *>(workspace);
+    return plx::launch_prefill_bf16(p, stream) == hipSuccess ? PLX_OK : PLX_ERR_LAUNCH;
 }
 
 size_t parallax_decode_mla_workspace_bytes(int32_t B, int32_t Hq) {

@@ -58,10 +58,11 @@ struct PrefillParams {
     const int32_t *sparse_row_ptr, *sparse_tile_idx;
     int32_t sparse_batch, sparse_heads;
     QrPrep prep;
-    // bf16, launches with idle compute units: records of row blocks whose keys are split over workgroups
-    // (ws != nullptr: take this form, at most split_tiles 64-key tiles per range)
+    // bf16, the form of the launch (plan_prefill_bf16): query rows per workgroup, and for launches with idle compute
+    // units key ranges of at most split_tiles 64-key tiles, a workgroup each, with their records in ws
+    // (ws != nullptr: take them)
     float *ws;
-    int32_t split_tiles, items_per_head;
+    int32_t rows, split_tiles, items_per_head;
 };
 
 // Decode over an MLA-style latent cache: one row [latent 512 | rope 64] per token shared by all
@@ -134,10 +135,10 @@ struct NormRopeParams {
 // Each returns hipSuccess or the launch error. No allocation, no synchronisation.
 hipError_t launch_decode_bf16(const DecodeParams &p, hipStream_t stream);
 hipError_t launch_decode_combine(const DecodeParams &p, hipStream_t stream);
-hipError_t launch_prefill_bf16(const PrefillParams &p, int num_cus, hipStream_t stream);
-// Plans the split of a call over key ranges: 0 = none pays against the whole launch, else the bytes of p.ws that its
-// launch takes; best_form: nor is another form without a workspace quicker
-size_t plan_prefill_split_bf16(PrefillParams &p, int num_cus, bool *best_form);
+hipError_t launch_prefill_bf16(const PrefillParams &p, hipStream_t stream);
+// Plans a call: p.rows for a launch without a workspace and, with_ranges, p.split_tiles > 0 where key ranges are
+// quicker still. Returns the bytes of p.ws that these take, 0 = there are none.
+size_t plan_prefill_bf16(PrefillParams &p, int num_cus, bool with_ranges);
 hipError_t launch_prefill_bwd_bf16(const PrefillBwdParams &p, int num_cus, hipStream_t stream);
 hipError_t launch_prefill_bwd_f32(const PrefillBwdParams &p, hipStream_t stream);
 hipError_t launch_decode_f32(const DecodeParams &p, hipStream_t stream);

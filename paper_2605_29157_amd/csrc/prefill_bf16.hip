@@ -1370,144 +1370,166 @@ __global__ __launch_bounds__(256) void prefill_combine_kernel(PrefillParams p) {
         }
 }
 
-// What a launch costs, in units of one 64-key tile of a workgroup that has a compute unit to itself (1.2 us at
-// d = 128, 0.72 at d = 64): to start and finish a workgroup, and per workgroup and tile of the chip's load (d = 64:
-// two share a unit, which hides most of a start and delivers a tile every 0.95 us).
+// ---- which form a launch takes -------------------------------------------------------------------
+// The estimates below are in us, from three quantities of a launch: its longest workgroup, the load dealt over
+// the chip, and what the last round of workgroups finds left to do. Fitted to (and the choice checked on) 2100 launches of
+// every form: 1 - 64 heads, 17 - 16384 rows behind 0 - 16384 keys, causal and full, windows, K and V not in the
+// L2. The form taken is 0.6 % (d = 64) and 0.3 % (d = 128) behind the fastest one on average, and more than a tenth in 20
+// of 1456 and 1 of 631 launches.
+struct LaunchCosts {
+    double start, tile;            // a workgroup alone on its compute unit: to start and finish, per 64-key tile
+    double shared;                 // per tile of a second workgroup on the unit (d = 64)
+    double load_start, load_tile;  // per workgroup and tile of a chip that is full
+    double tail;                   // of the longest workgroup (in tiles at d = 64), where there are more than fit at once
+    double bandwidth;              // bytes per us at which all workgroups get their tiles
+};
 struct PrefillCosts {
-    double unit, start, load_start, load_tile;
-    int resident;                                              // workgroups per compute unit
-    double pair_start, pair_tile, pair_load_start, pair_load_tile;  // 64 rows per workgroup (PAIR)
+    LaunchCosts whole, pair;                       // 128 rows per workgroup; 64 (PAIR)
+    double merge, merge_byte, merge_range;         // key ranges: the second launch, per byte of records written or read, per range of a row
+    int resident;                                  // workgroups per compute unit
 };
-static PrefillCosts prefill_costs(int d) {
-    return d == 128 ? PrefillCosts{1.2, 4.0, 4.0, 1.0, 1, 5.7, 0.55, 6.2, 0.55}
-                    : PrefillCosts{0.72, 7.8, 4.2, 1.32, 2, 7.9, 0.64, 2.5, 0.76};
-}
-// 64 rows per workgroup (PAIR) or 128, from the longest workgroup and the load dealt over the chip, for the causal
-// forms. Measured us, 128 rows / 64: 16 query heads, d = 128, 200 rows 11.5 / 10.7, 777 20.8 / 16.9, 1000 24.1 / 18.8,
-// 1500 32.9 / 28.3, 2048 44.4 / 41.4, but 128 8.4 / 8.8, 2500 59 / 64; 32 heads, 500 16.3 / 14.0, 777 22.1 / 23.1; 32 heads
-// x 300 behind 2700 keys 61 / 38.5; 32 heads, d = 64, 300 9.3 / 8.2, 777 15.8 / 13.1, 1500 28.1 / 28.8, 64 heads, 777
-// 20.5 / 21.6, 8 heads, 2000 28.6 / 20.4. From 4096 rows on always 128: the two add in different orders, and there a
-// sequence's outputs are to have the same bits whatever else is in the launch.
-struct PrefillForms {
-    bool pair;
-    double best_us;
-};
-static PrefillForms choose_form(const PrefillParams &p, int num_cus) {
-    const PrefillCosts c = prefill_costs(p.d);
-    const double heads = (double)p.B * p.Hq, off = (double)p.Tk - p.T;
-    const bool windowed = p.window > 0 && p.window < p.Tk;
-    auto form = [&](int rows, double start, double tile, double load_start, double load_tile, double tail) {
-        const double blocks = (p.T + rows - 1) / rows;
-        double longest = (p.Tk + kBC - 1) / kBC, mean = longest;
-        if (p.causal) mean = std::min(longest, (off + 0.5 * rows * (blocks + 1)) / kBC);
-        if (windowed) longest = std::min(longest, (p.window + rows - 1.0) / kBC + 1), mean = std::min(mean, longest);
-        const double n = heads * blocks;
-        // (the key tiles of all workgroups come out of the L2 and the cache behind it at 9.5 TB/s, at d = 64 at 6.8: 16
-        // heads x 1024 rows over 16384 keys, d = 128, by 64 rows 229 us, in two key ranges by 128 rows 213; 32 heads x
-        // 512, d = 64, 157 and 129)
-        const double traffic = n * mean * (4.0 * kBC * p.d) / ((p.d == 128 ? 9.5e6 : 6.8e6) * c.unit);
-        const double widest = std::max(start + tile * longest, traffic);
-        if (n <= (double)c.resident * num_cus) return widest;
-        return std::max(widest, n * (load_start + load_tile * mean) / num_cus + tail * widest);
-    };
-    const double whole = form(128, c.start, 1.0, c.load_start, c.load_tile, p.d == 128 ? 0.25 : 0.0);
-    if (!p.causal || !p.use_r || p.sparse_row_ptr != nullptr || p.T >= 4096 || (p.d == 128 && p.Tk <= 2 * kBC))
-        return {false, whole * c.unit};
-    const double pair = form(64, c.pair_start, c.pair_tile, c.pair_load_start, c.pair_load_tile, 0.1);
-    return {pair < whole, std::min(pair, whole) * c.unit};
+static constexpr PrefillCosts kPrefillCosts64 = {{5.7, 0.765, 0.715, 0.0, 0.82, 0.31, 7.7e6},
+                                                 {5.3, 0.61, 0.125, 1.8, 0.473, 0.02, 9.1e6}, 4.7, 0.15e-6, 0.89, 2};
+static constexpr PrefillCosts kPrefillCosts128 = {{7.2, 1.145, 0.0, 6.0, 1.43, 0.25, 13.0e6},
+                                                  {8.3, 0.755, 0.0, 7.2, 0.70, 0.18, 8.5e6}, 5.0, 0.134e-6, 0.95, 1};
+
+// n workgroups, the longest and the mean of them in tiles; at(rank): tiles of the workgroup of that rank, long ones first
+template <class At>
+static double launch_us(const LaunchCosts &c, int resident, int num_cus, double n, double longest, double mean,
+                        double tile_bytes, At at) {
+    const double alone = std::max(c.start + c.tile * longest, n * mean * tile_bytes / c.bandwidth);
+    if (n <= num_cus) return alone;
+    if (resident == 1) {
+        // (workgroup k * num_cus starts behind k others, none of them shorter)
+        const double rounds = std::floor((n - 1) / num_cus);
+        return std::max({alone, n * (c.load_start + mean * c.load_tile) / num_cus + c.tail * alone,
+                         (rounds + 1) * (c.start + c.tile * at(rounds * num_cus))});
+    }
+    const double both = c.tile + c.shared;  // a unit's two workgroups, per tile of each
+    double us = std::max(alone + c.shared * at(num_cus), c.start + n * (c.load_start + mean * c.load_tile) / num_cus +
+                                                              (n > 2.0 * num_cus ? c.tail * longest : 0.0));
+    const double rounds = std::floor((n - 1) / (2.0 * num_cus)), left = n - 2.0 * rounds * num_cus;
+    if (rounds > 0) {
+        const double last = at(2.0 * rounds * num_cus);
+        us = std::max(us, c.start + rounds * both * last + c.tile * last +
+                              (left > num_cus ? c.shared * at((2.0 * rounds + 1) * num_cus) : 0.0));
+    }
+    return us;
 }
 
-// Key ranges of a launch that leaves compute units idle: the tiles per range with the smallest
-// estimate, in units of one 64-key tile of a workgroup (1.2 us at d = 128; d = 64: 1.5 for 256 rows, two workgroups
-// of the launch sharing a unit): 4 to start and finish a workgroup, one workgroup per compute unit at a
-// time; what a launch with more items than units loses at its end is taken as half an item. Merging
-// costs a launch (4) and the records' bytes there and back (4.2 MB per unit, what the sweeps below show).
-// With fewer than 16 tiles to cut, the records are few and dearer than that: the split has to win with 9
-// units and 0.3 of the bytes' share (d = 64: 5 and 0.7) as well. (Over 488 splits that the first form alone
-// makes, 1 - 1000 rows over 0 - 3000 keys before them, 2 - 64 heads, 52 were slower than the whole launch, by
-// up to 18 % -- 16 rows over 616 keys, 32 heads: whole 18.3, split 21.6. With the second one
-// 13 of 432 are, by up to 5 %, and a dozen gains of up to 10 % are not taken.)
-// 0 = leave the launch whole (also when the gain would be under a tenth). Measured us against the number
-// of ranges of the longest row block, 16 heads, d = 128: 512 rows over 16384 keys whole 267, 2 160, 3 128,
-// 4 (the rule) 114, 5 160, 8 135; 1024 over 16384 whole 302, 2 (the rule) 207, 3 250, 4 226; 256 over 2000
-// whole 41, 2 34, 3 31, 4 33; 17 over 5000 whole 86, 8 30, 16 34; square prompts of 300 ... 3000 rows whole
-// (the rule) 13 ... 75, 2 18 ... 108; 8 heads, 1000 square whole (the rule) 24, 2 25, 4 29; d = 64: 32 heads x 512 over
-// 16384 whole 190, 2 129, 4 (the rule) 129, 8 138; 17 over 17000 whole 195, 4 61, 8 42, 12 51; 8 heads x 700 over 9000
-// whole 106, 3 50, 5 43, 8 46. Where halved chains without records (choose_form) are quicker still, best_form is
-// false and the split is not taken: 2 x 16 heads, 300 rows over 3000 keys 46 against 38; d = 64, 32 heads, 300
-// over 4000 58 against 50.
+// A launch without key ranges, `rows` query rows per workgroup
+static double unsplit_us(const PrefillParams &p, int num_cus, int rows, const LaunchCosts &c, int resident) {
+    const double heads = (double)p.B * p.Hq, blocks = (p.T + rows - 1) / rows, all = (p.Tk + kBC - 1) / kBC;
+    const double span = p.window > 0 ? (p.window + rows - 1.0) / kBC + 1 : 1e30;
+    // row block j (from 1) sees `before` + j * `step` tiles under a causal mask
+    const double before = (p.Tk - p.T + kBC - 1) / kBC, step = rows / kBC, longest = std::min(all, span);
+    double sum = blocks * longest;
+    if (p.causal) {
+        const double inside = std::min(std::max(std::floor((longest - before) / step), 0.0), blocks);  // blocks below `longest`
+        sum = inside * before + step * inside * (inside + 1) / 2 + (blocks - inside) * longest;
+    }
+    auto at = [&](double rank) {
+        return p.causal ? std::min(longest, before + step * (blocks - std::floor(rank / heads))) : longest;
+    };
+    return launch_us(c, resident, num_cus, heads * blocks, longest, sum / blocks, 4.0 * kBC * p.d, at);
+}
+
+// 64 rows per workgroup (PAIR) or 128. Measured us, 128 rows / 64: 16 query heads, d = 128, 200 rows 11.5 / 10.7, 777
+// 20.8 / 16.9, 1000 24.1 / 18.8, 1500 32.9 / 28.3, 2048 44.4 / 41.4, but 128 8.4 / 8.8, 2500 59 / 64; 8 heads, 4096 rows
+// 82 / 74, 6000 134 / 145; 64 heads, 267 rows over 7471 keys (320 workgroups of 64 rows: two rounds) 152 / 197; d = 64,
+// 32 heads, 300 9.3 / 8.2, 777 15.8 / 13.1, 1500 28.1 / 28.8; 8 heads, 4096 54 / 47, 16 x 250 rows over 6188 keys 75 / 65.
+// From 4096 rows on always 128: the two add in different orders, and there a sequence's outputs are to have the same bits
+// whatever else is in the launch.
+static bool pair_possible(const PrefillParams &p) {
+    return p.causal && p.use_r && p.sparse_row_ptr == nullptr && p.T < 4096 && !(p.d == 128 && p.Tk <= 2 * kBC);
+}
+
+// Key ranges: the tiles per range with the smallest estimate, where that is below `limit`; 0 = none is.
+// A range's workgroup costs what one of 128 rows costs; merging costs a launch, the records' bytes there and
+// back, and a step per range of a row. Measured us against the number of ranges of the longest row block, 16 heads, d =
+// 128: 512 rows over 16384 keys whole 267, 2 160, 3 128, 4 (the rule) 114, 5 160, 8 135; 1024 over 16384 whole
+// 302, 2 (the rule) 207, 3 250, 4 226; 17 over 5000 whole 86, 8 30, 16 34; d = 64 (whole, PAIR, ranges): 8 heads, 28
+// rows over 3678 keys 47, 42, 4 24, 6 (the rule) 22, 29 42; 694 over 4540 64, 55, 3 37, 5 (the rule) 36, 9 40; 32 heads, 272 over 13224
+// 157, 135, 3 92, 5 (the rule) 86, 8 95; 4 x 8 heads, 250 over 5938 75, 65, 3 40, 4 (the rule) 39, 8 44. A split has to be 3 % ahead.
 // The plan is made on every call, on the host, so it estimates no more than it has to: once for row
 // blocks that see the same keys (full attention) and for range counts that come to the same tiles, and
-// only those counts whose lower bound (as if tiles divided evenly) can still win (8 heads x 3900 rows,
-// causal: 7.5 -> 0.5 us on the host; 2 x 8192: 16 -> 1.9, full attention 14 -> 0.2).
-static int choose_split_tiles(const PrefillParams &p, int num_cus, int *items_per_head, double *cost_us) {
-    const int rows = p.d == 64 ? 256 : 128, nrb = (p.T + rows - 1) / rows;
-    const int64_t heads = (int64_t)p.B * p.Hq;
-    *items_per_head = nrb;
-    if (heads * nrb >= 2 * (int64_t)num_cus || nrb > 64) return 0;
+// only those counts whose lower bound (the longest and the load alone, as if tiles divided evenly) can still win.
+static int choose_split_tiles(const PrefillParams &p, int num_cus, const PrefillCosts &c, double limit, int *items_per_head) {
+    constexpr int rows = 128;
+    const int nrb = (p.T + rows - 1) / rows;
+    const double heads = (double)p.B * p.Hq;
+    // A launch that keeps more than half of the units busy leaves most of them two ranges: at d = 128 none of 130 such
+    // gained 3 %; at d = 64 a few do where the estimate is well ahead, and more of those with more row blocks than units
+    // (3 x 32 heads, 383 rows over 13721 keys 315 whole, 259).
+    const double n_whole = heads * nrb;
+    if (nrb > 128 || n_whole >= 2.0 * num_cus || (c.resident == 1 && 2 * n_whole > num_cus)) return 0;
+    if (2 * n_whole > num_cus) limit *= n_whole <= num_cus ? 0.9 : 0.97;
     const int kinds = p.causal ? nrb : 1, alike = p.causal ? 1 : nrb;  // row blocks by the keys they see
     auto keys = [&](int i) { return p.causal ? std::min(p.Tk, (nrb - i) * rows + (p.Tk - p.T)) : p.Tk; };
     auto tiles_of = [&](int i) { return (keys(i) + kBC - 1) / kBC; };
     // records of 32 rows of a range, all row blocks of the kind together
     auto subs_of = [&](int i) { return p.causal ? (std::min(rows, p.T - (nrb - 1 - i) * rows) + 31) / 32 : (p.T + 31) / 32; };
-    const int longest = tiles_of(0);
-    auto cost = [&](double widest, double n, double work, double records, double start, double part) {
-        const double t = std::max(widest, (double)heads * work / num_cus + (heads * n > num_cus ? 0.5 * widest : 0.0));
-        return records > 0 ? t + start + part * heads * records * (2.0 * 32 * (2 * p.d + 5) * 4.0 / 4.2e6) : t;
-    };
-    auto estimate = [&](int tiles, int *items, double start, double part) {
-        double work = 0, widest = 0;
+    const double record_us = 2 * c.merge_byte * (double)prefill_record_floats(p.d) * sizeof(float), tile_bytes = 4.0 * kBC * p.d;
+    double all = 0;
+    for (int i = 0; i < kinds; ++i) all += alike * tiles_of(i);
+    auto estimate = [&](int tiles, int *items) {
         int64_t n = 0, records = 0;
         for (int i = 0; i < kinds; ++i) {
             const PrefillRanges r(keys(i), tiles);
-            work += alike * r.count * (4.0 + r.tiles);
-            widest = std::max(widest, 4.0 + r.tiles);
             n += alike * r.count, records += r.count > 1 ? r.count * subs_of(i) : 0;
         }
+        auto at = [&](double rank) {
+            double before = 0;
+            for (int i = 0;; ++i) {
+                const PrefillRanges r(keys(i), tiles);
+                before += heads * alike * r.count;
+                if (rank < before || i == kinds - 1) return (double)r.tiles;
+            }
+        };
         *items = (int)n;
-        return cost(widest, (double)n, work, (double)records, start, part);
+        const PrefillRanges longest(keys(0), tiles);
+        return launch_us(c.whole, c.resident, num_cus, heads * n, longest.tiles, all / n, tile_bytes, at) + c.merge +
+               record_us * heads * records + c.merge_range * longest.count;
     };
-    int items = 0, best = 0, last = longest, cut = 0;
-    const double limit = 0.9 * estimate(longest, &items, 4.0, 1.0);
-    double best_cost = limit;
-    int64_t all = 0, cut_tiles = 0, cut_subs = 0;  // tiles; of the row blocks with more than one range: tiles, tiles x records
-    for (int i = 0; i < kinds; ++i) all += alike * tiles_of(i);
+    int best = 0, last = tiles_of(0), cut = 0;
+    double cut_tiles = 0, cut_records = 0;  // of the row blocks with more than one range: tiles, tiles x records
     for (int ranges = 2; ranges <= 32; ++ranges) {
-        const int tiles = (longest + ranges - 1) / ranges;
+        const int tiles = (tiles_of(0) + ranges - 1) / ranges;
         if (tiles < 2) break;
         if (tiles == last) continue;
         last = tiles;
         for (; cut < kinds && tiles_of(cut) > tiles; ++cut)  // (ever fewer tiles from row block to row block)
-            cut_tiles += alike * tiles_of(cut), cut_subs += (int64_t)tiles_of(cut) * subs_of(cut);
-        const double n = (double)cut_tiles / tiles + alike * (kinds - cut);
-        const double least = cost(4.0 + PrefillRanges(keys(0), tiles).tiles, n, all + 4.0 * n, (double)cut_subs / tiles, 4.0, 1.0);
-        if (least * (1.0 - 1e-9) >= best_cost) continue;
-        const double t = estimate(tiles, &items, 4.0, 1.0);
-        if (t < best_cost) best_cost = t, best = tiles, *items_per_head = items;
+            cut_tiles += alike * tiles_of(cut), cut_records += (double)tiles_of(cut) * subs_of(cut);
+        const PrefillRanges longest(keys(0), tiles);
+        const double n = heads * (cut_tiles / tiles + alike * (kinds - cut));
+        double least = c.whole.start + c.whole.tile * longest.tiles;
+        if (n > num_cus)
+            least = std::max(least, (n * c.whole.load_start + heads * all * c.whole.load_tile) / num_cus);
+        least += c.merge + record_us * heads * cut_records / tiles + c.merge_range * longest.count;
+        if (least * (1.0 - 1e-9) >= limit) continue;
+        int items;
+        const double us = estimate(tiles, &items);
+        if (us < limit) limit = us, best = tiles, *items_per_head = items;
     }
-    // Short chains: the merge of their few records is bound by its start instead of its bytes
-    if (best > 0 && longest < 16 && (p.d == 64 ? estimate(best, &items, 5.0, 0.7) : estimate(best, &items, 9.0, 0.3)) >= limit)
-        best = 0, *items_per_head = nrb;
-    *cost_us = best_cost * (p.d == 64 ? 1.5 : 1.2);
     return best;
 }
 
-size_t plan_prefill_split_bf16(PrefillParams &p, int num_cus, bool *best_form) {
+size_t plan_prefill_bf16(PrefillParams &p, int num_cus, bool with_ranges) {
+    p.rows = 128;
     p.split_tiles = 0;
-    *best_form = false;
-    if (p.sparse_row_ptr != nullptr || p.window > 0 || p.prep.gamma_q != nullptr) return 0;
-    double cost_us;
-    p.split_tiles = choose_split_tiles(p, num_cus, &p.items_per_head, &cost_us);
-    if (p.split_tiles == 0) return 0;
-    *best_form = cost_us <= choose_form(p, num_cus).best_us;
-    const size_t bytes = (size_t)p.B * p.Hq * p.items_per_head * (p.d == 64 ? 8 : 4) * prefill_record_floats(p.d) * sizeof(float);
-    if (p.d == 64) {  // (the items of the 128-row blocks, at most two to one of 256 rows)
-        const int nrb = (p.T + 127) / 128;
-        p.items_per_head = 0;
-        for (int i = 0; i < nrb; ++i)
-            p.items_per_head += PrefillRanges(p.causal ? std::min(p.Tk, (nrb - i) * 128 + (p.Tk - p.T)) : p.Tk, p.split_tiles).count;
+    if (p.sparse_row_ptr != nullptr) return 0;
+    const PrefillCosts &c = p.d == 128 ? kPrefillCosts128 : kPrefillCosts64;
+    const bool ranges = with_ranges && p.window <= 0 && p.prep.gamma_q == nullptr;
+    if (!ranges && !pair_possible(p)) return 0;
+    double us = unsplit_us(p, num_cus, 128, c.whole, c.resident);
+    if (pair_possible(p)) {
+        const double pair = unsplit_us(p, num_cus, 64, c.pair, c.resident);
+        if (pair < us) us = pair, p.rows = 64;
     }
-    return bytes;
+    if (!ranges) return 0;
+    p.split_tiles = choose_split_tiles(p, num_cus, c, 0.97 * us, &p.items_per_head);
+    if (p.split_tiles == 0) return 0;
+    return (size_t)p.B * p.Hq * p.items_per_head * 4 * prefill_record_floats(p.d) * sizeof(float);
 }
 
 template <int D>
@@ -1609,13 +1631,12 @@ static hipError_t launch_prefill_dense(const PrefillParams &p, hipStream_t strea
     return hipGetLastError();
 }
 
-hipError_t launch_prefill_bf16(const PrefillParams &p, int num_cus, hipStream_t stream) {
-    if (p.ws != nullptr)  // (planned and sized by plan_prefill_split_bf16)
+hipError_t launch_prefill_bf16(const PrefillParams &p, hipStream_t stream) {  // (planned by plan_prefill_bf16)
+    if (p.ws != nullptr)
         return p.d == 128 ? launch_prefill_split<128>(p, stream) : launch_prefill_split<64>(p, stream);
     if (p.sparse_row_ptr != nullptr)
         return p.d == 128 ? launch_prefill_sparse<128>(p, stream) : launch_prefill_sparse<64>(p, stream);
-    if (choose_form(p, num_cus).pair)
-        return p.d == 128 ? launch_prefill_pair<128>(p, stream) : launch_prefill_pair<64>(p, stream);
+    if (p.rows == 64) return p.d == 128 ? launch_prefill_pair<128>(p, stream) : launch_prefill_pair<64>(p, stream);
     return p.d == 128 ? launch_prefill_dense<128>(p, stream) : launch_prefill_dense<64>(p, stream);
 }
 

@@ -465,58 +465,125 @@ def test_packed_arguments_land_in_their_fields(binding):
         assert list(leaves(args.from_buffer_copy(layout.pack(*range(1, n + 1))))) == list(range(1, n + 1)), args
 
 
-def _prefill_split_by_search(B, Hq, T, Tk, d, causal, cus=256):
-    """Workspace of the split with the smallest estimate over all range counts, every row block of every
-    count estimated: units of one 64-key tile of a workgroup."""
-    rows = 64 * (4 if d == 64 else 2)
-    nrb, heads = -(-T // rows), B * Hq
-    if heads * nrb >= 2 * cus or nrb > 64:
-        return 0
-    blocks = []  # (key tiles seen, records of 32 rows)
-    for i in range(nrb):
-        keys = min(Tk, (i + 1) * rows + Tk - T) if causal else Tk
-        blocks.append((-(-keys // 64), -(-min(rows, T - i * rows) // 32)))
-    longest = max(t for t, _ in blocks)
+# us: (start, per tile, per tile of a second workgroup on the unit, load per workgroup, load per tile, tail, bytes per
+# us) of 128 rows per workgroup and of 64; (second launch, per byte of records, per range)
+_PREFILL_COSTS = {64: ((5.7, 0.765, 0.715, 0.0, 0.82, 0.31, 7.7e6), (5.3, 0.61, 0.125, 1.8, 0.473, 0.02, 9.1e6),
+                       (4.7, 0.15e-6, 0.89)),
+                  128: ((7.2, 1.145, 0.0, 6.0, 1.43, 0.25, 13.0e6), (8.3, 0.755, 0.0, 7.2, 0.70, 0.18, 8.5e6),
+                        (5.0, 0.134e-6, 0.95))}
 
-    def estimate(tiles, start=4.0, part=1.0):
-        n = records = work = widest = 0
-        for t, subs in blocks:
-            per = -(-t // -(-t // tiles))
-            count = -(-t // per)
-            n, work, widest = n + count, work + count * (4 + per), max(widest, 4 + per)
-            records += count * subs if count > 1 else 0
-        cost = max(widest, heads * work / cus + (0.5 * widest if heads * n > cus else 0))
-        return cost + (start + part * heads * records * (2 * 32 * (2 * d + 5) * 4 / 4.2e6) if records else 0), n
 
-    limit = 0.9 * estimate(longest)[0]
-    best, items, few = limit, 0, 0
+def _launch_us(costs, d, tiles, load, cus=256):
+    """Estimate of a launch whose workgroups walk tiles[0], tiles[1], .. (in the order they start), `load` in all."""
+    start, tile, shared, load_start, load_tile, tail, bandwidth = costs
+    n, longest = len(tiles), tiles[0]
+    alone = max(start + tile * longest, load * 256 * d / bandwidth)
+    if n <= cus:
+        return alone
+    if d == 128:
+        rounds = (n - 1) // cus
+        return max(alone, (n * load_start + load * load_tile) / cus + tail * alone, (rounds + 1) * (start + tile * tiles[rounds * cus]))
+    us = max(alone + shared * tiles[cus], start + (n * load_start + load * load_tile) / cus + (tail * longest if n > 2 * cus else 0))
+    rounds = (n - 1) // (2 * cus)
+    if rounds:
+        last = tiles[2 * rounds * cus]
+        us = max(us, start + rounds * (tile + shared) * last + tile * last
+                 + (shared * tiles[(2 * rounds + 1) * cus] if n > (2 * rounds + 1) * cus else 0))
+    return us
+
+
+def _prefill_plan_by_search(B, Hq, T, Tk, d, causal, window=0, cus=256):
+    """(rows per workgroup, workspace, tiles per key range) of the form with the smallest estimate: every row block of every
+    form and of all range counts estimated."""
+    whole, pair, (merge, merge_byte, merge_range) = _PREFILL_COSTS[d]
+    heads = B * Hq
+
+    def seen(rows):  # tiles of a head's row blocks, long ones first
+        nrb = -(-T // rows)
+        tiles = [-(-(min(Tk, i * rows + Tk - T) if causal else Tk) // 64) for i in range(nrb, 0, -1)]
+        return [min(t, (window + rows - 1) / 64 + 1) for t in tiles] if window else tiles
+
+    def unsplit(rows, costs):
+        return _launch_us(costs, d, [t for t in seen(rows) for _ in range(heads)], heads * sum(seen(rows)))
+
+    rows, us = 128, unsplit(128, whole)
+    if causal and T < 4096 and not (d == 128 and Tk <= 128):
+        us, rows = min((us, -128), (unsplit(64, pair), -64))
+        rows = -rows
+    blocks = [(t, -(-min(128, T - 128 * (i if not causal else len(seen(128)) - 1 - i)) // 32)) for i, t in enumerate(seen(128))]
+    n = heads * len(blocks)
+    if window or len(blocks) > 128 or n >= 2 * cus or (d == 128 and 2 * n > cus):
+        return rows, 0, 0
+    best, items, at = us * 0.97 * (1 if 2 * n <= cus else 0.9 if n <= cus else 0.97), 0, 0
     for ranges in range(2, 33):
-        tiles = -(-longest // ranges)
-        if tiles >= 2 and estimate(tiles)[0] < best:
-            best, items = estimate(tiles)
-            few = estimate(tiles, *((5.0, 0.7) if d == 64 else (9.0, 0.3)))[0]  # short chains: the merge's start
-    if longest < 16 and few >= limit:
-        return 0
-    return heads * items * (rows // 32) * (64 * d + 160) * 4
+        most = -(-blocks[0][0] // ranges)
+        if most < 2:
+            break
+        tiles, records = [], 0
+        for t, subs in blocks:
+            per = -(-t // -(-t // most))
+            count = -(-t // per)
+            tiles += count * heads * [per]
+            records += count * subs if count > 1 else 0
+        longest = -(-blocks[0][0] // tiles[0])
+        t = (_launch_us(whole, d, tiles, heads * sum(t for t, _ in blocks)) + merge + merge_range * longest
+             + merge_byte * 2 * heads * records * (64 * d + 160) * 4)
+        if t < best:
+            best, items, at = t, len(tiles), most
+    return rows, items * 4 * (64 * d + 160) * 4, at
 
 
-def test_prefill_split_is_the_cheapest_of_all_range_counts(binding):
-    """The plan leaves out what cannot win; it has to find what the whole search finds."""
-    import ctypes
+def _prefill_shape(binding, B, Hq, Hkv, T, Tk, d, causal, window=0):
+    a = binding.plx_prefill_args()
+    a.q = a.r = a.k = a.v = a.o = 1 << 20
+    a.B, a.Hq, a.Hkv, a.T, a.Tkv, a.d = B, Hq, Hkv, T, Tk, d
+    a.scale, a.causal, a.use_r, a.dtype, a.window = 0.1, int(causal), 1, binding.PLX_BF16, window
+    for name, H, L in (("q", Hq, T), ("r", Hq, T), ("k", Hkv, Tk), ("v", Hkv, Tk), ("o", Hq, T)):
+        setattr(a, name + "_stride", (ctypes.c_int64 * 3)(H * L * d, L * d, d))
+    return a
+
+
+def test_prefill_plan_is_the_cheapest_of_all_forms(binding):
+    """The plan leaves out what cannot win; it has to find what the whole search finds. No scratch is asked for that the
+    call would not use, and without it the call runs in the quicker of the other two forms."""
     import random
 
-    rng, lib, n_split = random.Random(5), binding.load_library(), 0
-    for _ in range(400):
+    rng, lib, seen = random.Random(5), binding.load_library(), {64: 0, 128: 0, "split": 0}
+    for _ in range(500):
         B, Hq, d, causal = rng.randint(1, 3), rng.choice([1, 2, 7, 8, 16, 40]), rng.choice([64, 128]), rng.random() < 0.6
         T = rng.randint(1, rng.choice([600, 8000]))
         Tk = T + rng.choice([0, rng.randint(0, 20000)])
-        a = binding.plx_prefill_args()
-        a.q = a.r = a.k = a.v = a.o = 1 << 20
-        a.B, a.Hq, a.Hkv, a.T, a.Tkv, a.d = B, Hq, Hq, T, Tk, d
-        a.scale, a.causal, a.use_r, a.dtype = 0.1, int(causal), 1, binding.PLX_BF16
-        for name, L in (("q", T), ("r", T), ("k", Tk), ("v", Tk), ("o", T)):
-            setattr(a, name + "_stride", (ctypes.c_int64 * 3)(Hq * L * d, L * d, d))
-        want = _prefill_split_by_search(B, Hq, T, Tk, d, causal)
-        assert lib.parallax_prefill_workspace_bytes(ctypes.byref(a)) == want, (B, Hq, T, Tk, d, causal)
-        n_split += want > 0
-    assert 100 < n_split < 300
+        window = rng.randint(1, Tk) if causal and rng.random() < 0.15 else 0
+        window = window if window < Tk else 0
+        a = ctypes.byref(_prefill_shape(binding, B, Hq, Hq, T, Tk, d, causal, window))
+        rows, need, tiles = _prefill_plan_by_search(B, Hq, T, Tk, d, causal, window)
+        case = (B, Hq, T, Tk, d, causal, window)
+        assert lib.parallax_prefill_workspace_bytes(a) == need, case
+        assert lib.parallax_prefill_form(a, need) == (128 + 256 * tiles if need else rows), case
+        assert lib.parallax_prefill_form(a, max(need - 1, 0)) == rows, case
+        assert lib.parallax_prefill_form(a, 0) == rows, case
+        seen["split" if need else rows] += 1
+    assert min(seen.values()) > 60, seen
+
+
+# us measured with 128 rows per workgroup, with 64, and by 64-key tiles per key range; K and V not in the L2
+@pytest.mark.parametrize("shape,measured", [
+    ((4, 8, 8, 250, 6188, 64, True), {128: 75.2, 64: 65.4, 49: 49.2, 33: 40.0, 25: 39.1, 20: 46.6, 13: 44.2, 7: 59.2}),
+    ((1, 16, 8, 484, 6648, 64, True), {128: 80.0, 64: 69.0, 52: 54.2, 35: 44.9, 26: 43.9, 18: 49.0, 11: 52.8, 7: 59.9}),
+    ((2, 8, 8, 619, 8316, 64, True), {128: 97.8, 64: 85.1, 65: 62.2, 44: 52.5, 33: 62.3, 22: 55.8, 11: 70.2}),
+    ((1, 32, 16, 272, 13496, 64, True), {128: 156.9, 64: 135.4, 106: 95.9, 71: 109.4, 53: 92.4, 43: 85.8, 27: 90.2}),
+    ((1, 8, 8, 694, 5234, 64, True), {128: 64.1, 64: 55.1, 41: 44.6, 28: 36.9, 21: 35.6, 17: 35.5, 11: 39.9, 6: 48.7}),
+    ((1, 8, 8, 28, 3706, 64, True), {128: 46.8, 64: 41.6, 20: 25.7, 12: 22.9, 10: 22.3, 8: 22.7, 6: 23.1, 3: 32.1}),
+    ((3, 32, 16, 383, 14104, 64, True), {128: 315.5, 64: 329.2, 111: 277.2, 74: 260.0, 56: 258.7, 37: 264.1}),
+    ((1, 8, 8, 43, 7029, 64, False), {128: 81.4, 37: 37.8, 22: 31.3, 14: 27.8, 11: 28.8, 10: 29.2, 5: 39.1}),
+    ((1, 32, 16, 300, 2300, 64, True), {128: 31.6, 64: 27.4, 18: 30.7, 9: 34.5, 5: 36.9}),
+    ((1, 8, 8, 2789, 2789, 64, True), {128: 37.9, 64: 31.8, 22: 38.8, 11: 40.1}),
+    ((1, 64, 16, 267, 7471, 128, True), {128: 151.8, 64: 197.1, 59: 173.1, 30: 168.9}),
+    ((1, 32, 16, 539, 1790, 128, True), {128: 39.0, 64: 46.0, 14: 58.4}),
+    ((4, 8, 8, 751, 863, 128, True), {128: 24.5, 64: 26.5, 7: 42.6}),
+    ((1, 16, 8, 28, 1173, 128, True), {128: 26.9, 64: 22.1, 10: 24.0, 7: 21.9, 5: 22.5, 3: 24.5})])
+def test_prefill_takes_a_form_close_to_the_fastest_measured(binding, shape, measured):
+    a = ctypes.byref(_prefill_shape(binding, *shape))
+    lib = binding.load_library()
+    form = lib.parallax_prefill_form(a, lib.parallax_prefill_workspace_bytes(a))
+    assert measured[form // 256 or form] <= 1.05 * min(measured.values())

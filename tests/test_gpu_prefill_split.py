@@ -1,7 +1,7 @@
 """Prefill with the keys of a row block split over workgroups, against the oracle and against the
 whole launch (parallax_prefill through the C ABI), at the shapes where a range can go wrong: ranges that
 start on the diagonal (rows that see nothing of them), a last range of one key, one range only for the
-short row blocks, both row-block sizes."""
+short row blocks."""
 import ctypes
 
 import numpy as np
@@ -42,14 +42,45 @@ def _whole(plx, y, causal=True, use_r=True, stats=False):
     st = torch.empty(y["q"].shape[:3] + (2,), dtype=torch.float32, device=DEV)
     if stats:
         a.vbar, a.row_stats = vbar.data_ptr(), st.data_ptr()
-    need = plx.load_library().parallax_prefill_workspace_bytes(ctypes.byref(a))
-    assert plx.load_library().parallax_prefill(ctypes.byref(a), None) == 0
+    lib = plx.load_library()
+    need = lib.parallax_prefill_workspace_bytes(ctypes.byref(a))
+    assert (lib.parallax_prefill_form(ctypes.byref(a), need) >= 256) == (need > 0)  # scratch is asked for by calls that are split
+    assert lib.parallax_prefill(ctypes.byref(a), None) == 0
     return (out, vbar, st) if stats else out, need
 
 
 # (B, Hq, Hkv, T, Tkv, d): heads * row blocks leave most of the chip idle
-SHAPES = [(1, 2, 2, 997, 997, 128), (1, 2, 1, 1024, 1025, 128), (1, 2, 2, 130, 5000, 128), (2, 4, 4, 17, 3001, 128),
-          (1, 4, 2, 1111, 1111, 64), (1, 4, 4, 300, 2049, 64), (1, 2, 2, 512, 1600, 128)]
+SHAPES = [(1, 1, 1, 1500, 1501, 128), (1, 2, 1, 300, 1281, 128), (1, 2, 2, 130, 5000, 128), (2, 4, 4, 17, 3001, 128),
+          (1, 2, 2, 512, 1600, 128), (1, 1, 1, 1500, 1500, 64), (1, 2, 1, 700, 2625, 64), (1, 4, 4, 300, 2049, 64)]
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,T,Tkv,d", SHAPES)
+def test_the_records_are_written(plx, synth, B, Hq, Hkv, T, Tkv, d):
+    """A call that says it is split goes through its scratch: every row's record is there afterwards; one that is
+    given too little leaves it alone."""
+    y = _inputs(synth, B, Hq, Hkv, T, Tkv, d, 4050 + T)
+    whole, need = _whole(plx, y)
+    out, lib = torch.empty_like(whole), plx.load_library()
+    a = plx.prefill_args(y["q"], y["r"], y["k"], y["v"], out, y["scale"], True, True)
+    form = lib.parallax_prefill_form(ctypes.byref(a), need)
+    ws = torch.full((need // 4,), -7.25, dtype=torch.float32, device=DEV)
+    assert lib.parallax_prefill_split(ctypes.byref(a), ws.data_ptr(), need - 4, None) == 0
+    assert bool((ws == -7.25).all()) and torch.equal(out, whole)
+    assert lib.parallax_prefill_split(ctypes.byref(a), ws.data_ptr(), need, None) == 0
+    torch.cuda.synchronize()
+    assert torch.equal(out, plx.parallax_prefill(y["q"], y["r"], y["k"], y["v"], y["scale"]))
+    # records [B * Hq][items][4 x 32 rows][64 d + 160]: those of row blocks with more than one range
+    rec = ws.reshape(B * Hq, -1, 4, 64 * d + 160)
+    item, nrb = 0, -(-T // 128)
+    for rb in range(nrb - 1, -1, -1):
+        tiles = -(-min(Tkv, (rb + 1) * 128 + Tkv - T) // 64)
+        count = -(-tiles // (form // 256))
+        waves = -(-min(128, T - rb * 128) // 32)
+        written = rec[:, item:item + count] != -7.25
+        assert bool(written[:, :, :waves, :64 * d + 96].all()) == (count > 1)
+        assert not bool(written[:, :, waves:].any()) and (count > 1 or not bool(written.any()))
+        item += count
+    assert item == rec.shape[1]
 
 
 @pytest.mark.parametrize("B,Hq,Hkv,T,Tkv,d", SHAPES)
@@ -122,7 +153,7 @@ def test_ranges_whose_sums_come_close_to_the_end_of_fp32(plx, synth, oracle, d, 
     T, Tkv = 32, 4096
     y = _inputs(synth, 1, 2, 2, T, Tkv, d, 4500)
     _, need = _whole(plx, y)
-    ranges = need // (2 * (128 if d == 128 else 256) // 32 * (64 * d + 160) * 4)
+    ranges = need // (2 * 4 * (64 * d + 160) * 4)
     tiles = -(-(Tkv // 64) // ranges)
     assert ranges >= 4 and tiles >= 2
     first = [64 * tiles * i for i in range(ranges)]
