@@ -285,6 +285,8 @@ plx_status parallax_prefill(const plx_prefill_args *args, void *hip_stream);
  *   workspace   NULL, or 16-byte aligned device memory; smaller than that: the call runs unsplit
  *   parallax_prefill_form  how a bf16 call runs with a workspace of that many bytes: query rows per workgroup (64
  *                          or 128) plus 256 * (64-key tiles per key range, 0 = not split); 0: fp32, or not valid
+ * The form is the quickest for the launch, so it depends on B and Hq, and a sequence's outputs may differ in
+ * their rounding with what else is in the launch. Two launches of the same form give a sequence the same bits.
  */
 size_t parallax_prefill_workspace_bytes(const plx_prefill_args *args);
 int32_t parallax_prefill_form(const plx_prefill_args *args, size_t workspace_bytes);

@@ -1438,10 +1438,11 @@ static double unsplit_us(const PrefillParams &p, int num_cus, int rows, const La
 // 20.8 / 16.9, 1000 24.1 / 18.8, 1500 32.9 / 28.3, 2048 44.4 / 41.4, but 128 8.4 / 8.8, 2500 59 / 64; 8 heads, 4096 rows
 // 82 / 74, 6000 134 / 145; 64 heads, 267 rows over 7471 keys (320 workgroups of 64 rows: two rounds) 152 / 197; d = 64,
 // 32 heads, 300 9.3 / 8.2, 777 15.8 / 13.1, 1500 28.1 / 28.8; 8 heads, 4096 54 / 47, 16 x 250 rows over 6188 keys 75 / 65.
-// From 4096 rows on always 128: the two add in different orders, and there a sequence's outputs are to have the same bits
-// whatever else is in the launch.
+// The forms differ in the last bits: they add the keys' fp32 terms in different orders, and a tile that only some row of a
+// workgroup sees in part (so: other tiles, as workgroups have other rows) is summed after the rounding of P, the others
+// before it. 1 x 16 heads x 777 rows, d = 128: 4e-4 apart (relative L2), each 1.7e-3 from 64 bits.
 static bool pair_possible(const PrefillParams &p) {
-    return p.causal && p.use_r && p.sparse_row_ptr == nullptr && p.T < 4096 && !(p.d == 128 && p.Tk <= 2 * kBC);
+    return p.causal && p.use_r && p.sparse_row_ptr == nullptr && !(p.d == 128 && p.Tk <= 2 * kBC);
 }
 
 // Key ranges: the tiles per range with the smallest estimate, where that is below `limit`; 0 = none is.

@@ -507,7 +507,7 @@ def _prefill_plan_by_search(B, Hq, T, Tk, d, causal, window=0, cus=256):
         return _launch_us(costs, d, [t for t in seen(rows) for _ in range(heads)], heads * sum(seen(rows)))
 
     rows, us = 128, unsplit(128, whole)
-    if causal and T < 4096 and not (d == 128 and Tk <= 128):
+    if causal and not (d == 128 and Tk <= 128):
         us, rows = min((us, -128), (unsplit(64, pair), -64))
         rows = -rows
     blocks = [(t, -(-min(128, T - 128 * (i if not causal else len(seen(128)) - 1 - i)) // 32)) for i, t in enumerate(seen(128))]
@@ -578,6 +578,11 @@ def test_prefill_plan_is_the_cheapest_of_all_forms(binding):
     ((1, 8, 8, 43, 7029, 64, False), {128: 81.4, 37: 37.8, 22: 31.3, 14: 27.8, 11: 28.8, 10: 29.2, 5: 39.1}),
     ((1, 32, 16, 300, 2300, 64, True), {128: 31.6, 64: 27.4, 18: 30.7, 9: 34.5, 5: 36.9}),
     ((1, 8, 8, 2789, 2789, 64, True), {128: 37.9, 64: 31.8, 22: 38.8, 11: 40.1}),
+    ((1, 8, 8, 4095, 4095, 64, True), {128: 55.3, 64: 47.5, 22: 55.2}),
+    ((1, 8, 8, 4096, 4096, 64, True), {128: 52.7, 64: 45.9, 22: 54.9}),
+    ((1, 4, 4, 8192, 8192, 64, True), {128: 100.9, 64: 88.9, 43: 96.4}),
+    ((1, 8, 8, 4096, 4096, 128, True), {128: 80.1, 64: 71.7, 22: 96.7}),
+    ((1, 8, 8, 6000, 6000, 128, True), {128: 136.6, 64: 144.4}),
     ((1, 64, 16, 267, 7471, 128, True), {128: 151.8, 64: 197.1, 59: 173.1, 30: 168.9}),
     ((1, 32, 16, 539, 1790, 128, True), {128: 39.0, 64: 46.0, 14: 58.4}),
     ((4, 8, 8, 751, 863, 128, True), {128: 24.5, 64: 26.5, 7: 42.6}),

@@ -149,6 +149,48 @@ def test_forms_of_a_launch(plx, synth, oracle, B, Hq, Hkv, T, Tkv, d, causal, wi
                 assert rel_l2(host(got[b:b + 1]), ref) <= BF16_REL_L2, (b, x is wide)
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,T,d,window,rows", [(4, 16, 8, 4096, 128, 0, 128), (2, 8, 8, 4200, 128, 0, 128), (2, 8, 4, 700, 128, 90, 64),
+                                                      (2, 8, 4, 2000, 64, 0, 64), (3, 32, 16, 1111, 64, 0, 128), (2, 4, 4, 4500, 64, 0, 64)])
+def test_two_launches_of_one_form_agree_bit_for_bit(plx, synth, B, Hq, Hkv, T, d, window, rows):
+    """The last sequence's heads from the second key head on by themselves: a workgroup's arithmetic does not depend
+    on the work item it is (one pair count takes the mapping onto the XCDs, the other the plain one)."""
+    import ctypes
+
+    lib = plx.load_library()
+    y = synth.prefill_inputs(B, Hq, Hkv, T, d, seed=950 + T, device=DEV)
+    G = Hq // Hkv
+
+    def run(q, r, k, v):
+        out, vbar = torch.empty_like(q), torch.empty_like(q)
+        stats = torch.empty(q.shape[:3] + (2,), dtype=torch.float32, device=DEV)
+        a = plx.prefill_args(q, r, k, v, out, y["scale"], True, True, window)
+        a.vbar, a.row_stats = vbar.data_ptr(), stats.data_ptr()
+        assert lib.parallax_prefill(ctypes.byref(a), None) == 0
+        return lib.parallax_prefill_form(ctypes.byref(a), 0), out, vbar, stats
+
+    full = run(*(y[n] for n in "qrkv"))
+    first = B - 1 if rows == 64 else 0  # (halved chains are for few workgroups, the others for many)
+    part = run(*(y[n][first:, (G if n in "qr" else 1):].contiguous() for n in "qrkv"))
+    assert full[0] == part[0] == rows
+    for a, b in zip(full[1:], part[1:]):
+        assert torch.equal(a[first:, G:], b)
+
+
+@pytest.mark.parametrize("Hq,T,d", [(2, 4133, 64), (2, 4200, 128)])
+def test_halved_chains_of_long_sequences(plx, synth, oracle, Hq, T, d):
+    """Few heads: 64 rows per workgroup also beyond 4096 rows; first, last and border rows and a sample between."""
+    import ctypes
+
+    y = synth.prefill_inputs(1, Hq, Hq, T, d, seed=960, device=DEV)
+    out = torch.empty_like(y["q"])
+    a = plx.prefill_args(y["q"], y["r"], y["k"], y["v"], out, y["scale"], True, True)
+    lib = plx.load_library()
+    assert lib.parallax_prefill_form(ctypes.byref(a), 0) == 64 and lib.parallax_prefill(ctypes.byref(a), None) == 0
+    rows = _sample_rows(1, Hq, T, 300, seed=6, tile=64)
+    got = host(out)[rows[:, 0], rows[:, 1], rows[:, 2]]
+    assert rel_l2(got, oracle_prefill(oracle, y, rows=rows)) <= BF16_REL_L2
+
+
 def test_scale_zero_is_uniform_weighting(plx, synth, oracle):
     """scale = 0 is the wide-bandwidth limit (uniform softmax weights)."""
     y = synth.prefill_inputs(1, 4, 2, 260, 128, seed=821, device=DEV, r_scale=0.2)
