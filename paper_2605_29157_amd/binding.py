@@ -27,7 +27,8 @@ EXPORTED_SYMBOLS = (
     "parallax_decode_partials", "parallax_decode_combine", "parallax_decode_fused",
     "parallax_decode_static", "parallax_decode_static_scratch_bytes",
     "parallax_decode_mla", "parallax_decode_mla_workspace_bytes", "parallax_decode_mla_num_splits",
-    "parallax_prefill", "parallax_prefill_split", "parallax_prefill_workspace_bytes", "parallax_prefill_form", "parallax_prefill_backward", "parallax_prefill_backward_workspace_bytes",
+    "parallax_prefill", "parallax_prefill_split", "parallax_prefill_workspace_bytes", "parallax_prefill_form", "parallax_prefill_backward", "parallax_prefill_backward_form",
+    "parallax_prefill_backward_workspace_bytes",
     "parallax_block_lists", "parallax_norm_rope", "parallax_rope_table", "parallax_util_copy", "parallax_util_read",
     "parallax_util_read_grid", "parallax_util_read_sink_slots", "parallax_util_mfma", "parallax_strerror", "parallax_version",
 )
@@ -215,6 +216,8 @@ def load_library() -> ctypes.CDLL:
         lib.parallax_prefill_split.restype = ctypes.c_int
         lib.parallax_prefill_backward.argtypes = [ctypes.POINTER(plx_prefill_bwd_args), ctypes.c_void_p]
         lib.parallax_prefill_backward.restype = ctypes.c_int
+        lib.parallax_prefill_backward_form.argtypes = [ctypes.POINTER(plx_prefill_bwd_args)]
+        lib.parallax_prefill_backward_form.restype = ctypes.c_int32
         lib.parallax_prefill_backward_workspace_bytes.argtypes = [ctypes.c_int32] * 3
         lib.parallax_prefill_backward_workspace_bytes.restype = ctypes.c_size_t
         lib.parallax_block_lists.argtypes = [ctypes.POINTER(plx_block_list_args), ctypes.c_void_p]

@@ -612,7 +612,10 @@ size_t parallax_prefill_backward_workspace_bytes(int32_t B, int32_t Hq, int32_t 
     return (size_t)B * Hq * T * 4 * sizeof(float);
 }
 
-plx_status parallax_prefill_backward(const plx_prefill_bwd_args *a, void *hip_stream) {
+namespace {
+
+// Validation of a backward call; fills the launch parameters.
+plx_status prepare_prefill_backward(const plx_prefill_bwd_args *a, plx::PrefillBwdParams *out) {
     if (!a) return PLX_ERR_NULL;
     const void *ptrs[12] = {a->q, a->r, a->k, a->v, a->o, a->vbar, a->row_stats, a->d_o,
                             a->dq, a->dr, a->dk, a->dv};
@@ -681,10 +684,26 @@ plx_status parallax_prefill_backward(const plx_prefill_bwd_args *a, void *hip_st
             p.sparse_batch = a->sparse_batch, p.sparse_heads = a->sparse_heads;
         }
     }
+    *out = p;
+    return PLX_OK;
+}
+
+}  // namespace
+
+plx_status parallax_prefill_backward(const plx_prefill_bwd_args *a, void *hip_stream) {
+    plx::PrefillBwdParams p{};
+    const plx_status st = prepare_prefill_backward(a, &p);
+    if (st != PLX_OK) return st;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     const hipError_t err = a->dtype == PLX_F32 ? plx::launch_prefill_bwd_f32(p, stream)
                                                : plx::launch_prefill_bwd_bf16(p, query_num_cus(), stream);
     return err == hipSuccess ? PLX_OK : PLX_ERR_LAUNCH;
+}
+
+int32_t parallax_prefill_backward_form(const plx_prefill_bwd_args *a) {
+    plx::PrefillBwdParams p{};
+    if (prepare_prefill_backward(a, &p) != PLX_OK || a->dtype != PLX_BF16) return 0;
+    return plx::backward_form_bf16(p, query_num_cus());
 }
 
 plx_status parallax_norm_rope(const plx_norm_rope_args *a, void *hip_stream) {

@@ -139,6 +139,8 @@ hipError_t launch_prefill_bf16(const PrefillParams &p, hipStream_t stream);
 // Plans a call: p.rows for a launch without a workspace and, with_ranges, p.split_tiles > 0 where key ranges are
 // quicker still. Returns the bytes of p.ws that these take, 0 = there are none.
 size_t plan_prefill_bf16(PrefillParams &p, int num_cus, bool with_ranges);
+// keys per workgroup of the column pass, plus 256 * rows per workgroup of the row pass
+int32_t backward_form_bf16(const PrefillBwdParams &p, int num_cus);
 hipError_t launch_prefill_bwd_bf16(const PrefillBwdParams &p, int num_cus, hipStream_t stream);
 hipError_t launch_prefill_bwd_f32(const PrefillBwdParams &p, hipStream_t stream);
 hipError_t launch_decode_f32(const DecodeParams &p, hipStream_t stream);

@@ -1167,8 +1167,8 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void bwd_passes_kernel(Prefil
 // 2048: 218 -> 231, 4 x 4096 1508 -> 1655), at half of the tiles and below it gains (2 x 2048: a half 176 -> 153, a
 // quarter 141 -> 115, 0.15 101 -> 99): taken from a chain of half the load on (as if all were listed), and
 // always at d = 64 (3 x 2048 a quarter 162 -> 154, all 326 -> 348; the one-per-unit form 223 and 406).
-// From 4096 rows on every launch takes the whole form: the two add a gradient's terms in different orders, and
-// there a sequence's gradients are to have the same bits whatever else is in the launch.
+// The forms add a gradient's terms in different orders, so gradients differ in their rounding with the form.
+// 8 / 8 heads, d = 64, 4096 rows 139 / 123, both 112; 4 / 2 heads, d = 128, 5129 rows 347 / 237.
 struct BackwardPlan {
     bool pair_c, pair_r;
 };
@@ -1186,13 +1186,17 @@ static BackwardPlan backward_plan(const PrefillBwdParams &p, int num_cus) {
     const double load = (heads * ((cells + (p.causal ? key_blocks : 0)) * per_item + (cells + (p.causal ? row_blocks : 0)) * per_tile) +
                          fixed * (heads * row_blocks + kv_heads * key_blocks)) / num_cus;
     BackwardPlan plan{};
-    if (p.T >= 4096) return plan;
     if (sparse)
         plan.pair_c = p.d == 64 || chain > 0.5 * load;
     else
         plan.pair_c = chain > (p.d == 128 ? 1.3 : 0.6) * load && chain >= row_chain;
     plan.pair_r = plan.pair_c && !sparse && p.window <= 0 && 3 * row_tiles > 2 * G * col_tiles;
     return plan;
+}
+
+int32_t backward_form_bf16(const PrefillBwdParams &p, int num_cus) {
+    const BackwardPlan plan = backward_plan(p, num_cus);
+    return (plan.pair_c ? 64 : 128) + 256 * (plan.pair_r ? 64 : 128);
 }
 
 template <int D>

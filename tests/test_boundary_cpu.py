@@ -592,3 +592,29 @@ def test_prefill_takes_a_form_close_to_the_fastest_measured(binding, shape, meas
     lib = binding.load_library()
     form = lib.parallax_prefill_form(a, lib.parallax_prefill_workspace_bytes(a))
     assert measured[form // 256 or form] <= 1.05 * min(measured.values())
+
+
+def _backward_shape(binding, B, Hq, Hkv, T, Tk, d, causal, window=0, lists=False):
+    a = binding.plx_prefill_bwd_args()
+    for name in ("q", "r", "k", "v", "o", "vbar", "row_stats", "d_o", "dq", "dr", "dk", "dv", "workspace"):
+        setattr(a, name, 1 << 20)
+    a.B, a.Hq, a.Hkv, a.T, a.Tkv, a.d = B, Hq, Hkv, T, Tk, d
+    a.scale, a.causal, a.dtype, a.window, a.workspace_bytes = 0.1, int(causal), binding.PLX_BF16, window, 1 << 60
+    if lists:
+        a.sparse_row_ptr = a.sparse_tile_idx = a.sparse_col_ptr = a.sparse_col_idx = 1 << 20
+        a.sparse_batch = a.sparse_heads = 1
+    return a
+
+
+# us measured with 128 keys and rows per workgroup (0), with 64 keys (1), with 64 keys and 64 rows (2)
+@pytest.mark.parametrize("shape,measured", [
+    ((1, 8, 8, 4095, 4095, 64, True), {0: 140.9, 1: 122.3, 2: 111.6}),
+    ((1, 8, 8, 4096, 4096, 64, True), {0: 138.9, 1: 123.5, 2: 111.5}),
+    ((1, 4, 2, 5129, 5129, 128, True), {0: 346.6, 1: 236.5, 2: 234.2}),
+    ((1, 16, 4, 5486, 5486, 64, True), {0: 633.9, 1: 440.6, 2: 439.2}),
+    ((1, 16, 8, 6265, 6265, 64, True, 0, True), {0: 247.3, 1: 156.3}),  # a quarter of the tiles listed
+    ((4, 16, 8, 4096, 4096, 128, True), {0: 1415.9, 1: 1509.1, 2: 1606.0}),
+    ((1, 8, 8, 1619, 1619, 128, True), {0: 66.5, 1: 51.3, 2: 48.3})])
+def test_backward_takes_a_form_close_to_the_fastest_measured(binding, shape, measured):
+    form = binding.load_library().parallax_prefill_backward_form(ctypes.byref(_backward_shape(binding, *shape)))
+    assert measured[{128 + 256 * 128: 0, 64 + 256 * 128: 1, 64 + 256 * 64: 2}[form]] <= 1.05 * min(measured.values())

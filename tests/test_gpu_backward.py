@@ -250,23 +250,56 @@ def test_backward_config4_launch_against_the_oracle(plx, synth, bwd_oracle):
 
 def test_backward_config4_launch_equals_its_slices(plx, synth):
     """Benchmark configuration 4 as bench.py launches it (B=4, 16 query / 8 KV heads, T=4096, d=128):
-    a workgroup's arithmetic does not depend on which work item it is, so the gradients of one
-    batch entry and two KV heads' groups must equal, bit for bit, those of a call on just that
-    slice (one pair count takes the XCD mapping, the other the plain one; the slice-sized call is
-    what test_backward_config4_shape_sampled checks against the oracle)."""
+    a workgroup's arithmetic does not depend on which work item it is, so the gradients of two
+    batch entries and seven KV heads' groups must equal, bit for bit, those of a call on just that
+    slice, which runs in the same form (one pair count takes the XCD mapping, the other the plain one)."""
     B, Hq, Hkv, T, d = 4, 16, 8, 4096, 128
     y, g = _inputs(synth, B, Hq, Hkv, T, T, d, 2680)
-    o, vbar, stats, full = _run(plx, y, g, True)
-    for b, hk0 in ((0, 0), (3, 6), (2, 2)):
-        hq0, sl_b = 2 * hk0, slice(b, b + 1)
-        sub = {"q": y["q"][sl_b, hq0:hq0 + 4], "r": y["r"][sl_b, hq0:hq0 + 4],
-               "k": y["k"][sl_b, hk0:hk0 + 2], "v": y["v"][sl_b, hk0:hk0 + 2], "scale": y["scale"]}
-        part = plx.parallax_prefill_backward(sub["q"], sub["r"], sub["k"], sub["v"], o[sl_b, hq0:hq0 + 4],
-                                             vbar[sl_b, hq0:hq0 + 4], stats[sl_b, hq0:hq0 + 4].contiguous(),
-                                             g[sl_b, hq0:hq0 + 4], y["scale"], causal=True)
+    _equals_its_slices(plx, y, g, True, 0, [(slice(0, 2), slice(0, 7)), (slice(2, 4), slice(1, 8))], 128 + 256 * 128)
+
+
+def _form(plx, y, causal, window):
+    import ctypes
+
+    q, k = y["q"], y["k"]
+    stats = torch.empty(q.shape[:3] + (2,), dtype=torch.float32, device=DEV)
+    ws = torch.empty(q.shape[:3] + (4,), dtype=torch.float32, device=DEV)
+    a = plx.prefill_bwd_args(q, y["r"], k, y["v"], q, q, stats, q, q, q, k, k, y["scale"], causal, ws, window)
+    return plx.load_library().parallax_prefill_backward_form(ctypes.byref(a))
+
+
+def _equals_its_slices(plx, y, g, causal, window, slices, form):
+    G = y["q"].shape[1] // y["k"].shape[1]
+    o, vbar, stats, full = _run(plx, y, g, causal, window)
+    assert _form(plx, y, causal, window) == form
+    for sb, sk in slices:
+        sq = slice(G * sk.start, G * sk.stop)
+        sub = {"q": y["q"][sb, sq], "r": y["r"][sb, sq], "k": y["k"][sb, sk], "v": y["v"][sb, sk], "scale": y["scale"]}
+        assert _form(plx, sub, causal, window) == form
+        part = plx.parallax_prefill_backward(sub["q"], sub["r"], sub["k"], sub["v"], o[sb, sq], vbar[sb, sq],
+                                             stats[sb, sq].clone(), g[sb, sq], y["scale"], causal=causal, window=window)
         torch.cuda.synchronize()
-        for name, got, ref, h0, n in zip(("dq", "dr", "dk", "dv"), part, full, (hq0, hq0, hk0, hk0), (4, 4, 2, 2)):
-            assert torch.equal(got, ref[sl_b, h0:h0 + n]), (name, b, hk0)
+        for name, got, ref, heads in zip(("dq", "dr", "dk", "dv"), part, full, (sq, sq, sk, sk)):
+            assert torch.equal(got, ref[sb, heads]), (name, sb, sk)
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,T,d,window,form", [(2, 8, 4, 1000, 128, 0, 64 + 256 * 128), (1, 8, 8, 4133, 64, 0, 64 + 256 * 64),
+                                                      (2, 8, 8, 700, 128, 0, 64 + 256 * 64), (2, 4, 2, 1500, 64, 200, 64 + 256 * 128),
+                                                      (3, 32, 16, 1111, 64, 0, 128 + 256 * 128)])
+def test_two_launches_of_one_form_agree_bit_for_bit(plx, synth, B, Hq, Hkv, T, d, window, form):
+    y, g = _inputs(synth, B, Hq, Hkv, T, T, d, 2690 + T)
+    _equals_its_slices(plx, y, g, True, window, [(slice(0, B), slice(1, Hkv))], form)
+
+
+@pytest.mark.parametrize("Hq,Hkv,T,d", [(2, 2, 4133, 64), (2, 1, 4200, 128)])
+def test_halved_chains_of_long_sequences(plx, synth, bwd_oracle, Hq, Hkv, T, d):
+    """Few heads take 64 keys per workgroup also beyond 4096 rows."""
+    y, g = _inputs(synth, 1, Hq, Hkv, T, T, d, 2695)
+    assert _form(plx, y, True, 0) % 256 == 64
+    _, _, _, grads = _run(plx, y, g, True)
+    want = bwd_oracle.backward(*(host(y[n]) for n in "qrkv"), host(g), y["scale"], causal=True)
+    for name, got, ref in zip(("dq", "dr", "dk", "dv"), grads, want):
+        assert_gradient_close(name, host(got), ref, BF16_REL_L2, (Hq, Hkv, T, d))
 
 
 @pytest.mark.parametrize("B,Hq,Hkv,T,Tkv,d,causal", [(1, 2, 2, 128, 128, 64, True), (2, 4, 2, 77, 77, 32, True),
