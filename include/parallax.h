@@ -402,7 +402,8 @@ size_t parallax_prefill_backward_workspace_bytes(int32_t B, int32_t Hq, int32_t 
 plx_status parallax_prefill_backward(const plx_prefill_bwd_args *args, void *hip_stream);
 /* How a bf16 call runs: keys per workgroup of the pass for dk and dv (64 or 128), plus 256 * query rows per workgroup of the
  * pass for dq and dr; 0: fp32, or not valid. As in the forward the form is the quickest for the launch and depends on B
- * and the heads; two launches of the same form give a sequence the same bits. */
+ * and the heads; two launches of the same form give a sequence the same bits. Plus 65536: block lists, and what share
+ * of the cells they name decides, read by the kernels, between the 64 keys and 128. */
 int32_t parallax_prefill_backward_form(const plx_prefill_bwd_args *args);
 
 /*

@@ -103,6 +103,9 @@ struct PrefillBwdParams {
     // ceil(Tk / 128) + cb, each 4 * row block + flags (bit t: the row block lists key tile 2 cb + t)
     const int32_t *sparse_row_ptr, *sparse_tile_idx, *sparse_col_ptr, *sparse_col_idx;
     int32_t sparse_batch, sparse_heads;
+    // > 0 (set by the launcher): both forms are launched, that of 64 keys per workgroup runs if the row lists hold at most
+    // this many entries, the other one if they hold more
+    int32_t list_limit;
 };
 
 // Block mask [lists, n_row_blocks, n_tiles] (bytes, nonzero = listed) -> the lists of PrefillParams and,
@@ -139,7 +142,7 @@ hipError_t launch_prefill_bf16(const PrefillParams &p, hipStream_t stream);
 // Plans a call: p.rows for a launch without a workspace and, with_ranges, p.split_tiles > 0 where key ranges are
 // quicker still. Returns the bytes of p.ws that these take, 0 = there are none.
 size_t plan_prefill_bf16(PrefillParams &p, int num_cus, bool with_ranges);
-// keys per workgroup of the column pass, plus 256 * rows per workgroup of the row pass
+// keys per workgroup of the column pass, plus 256 * rows per workgroup of the row pass, plus 65536 where the lists decide
 int32_t backward_form_bf16(const PrefillBwdParams &p, int num_cus);
 hipError_t launch_prefill_bwd_bf16(const PrefillBwdParams &p, int num_cus, hipStream_t stream);
 hipError_t launch_prefill_bwd_f32(const PrefillBwdParams &p, hipStream_t stream);

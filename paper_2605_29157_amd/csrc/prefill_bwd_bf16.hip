@@ -1143,6 +1143,14 @@ template <int D, bool CAUSAL, bool WINDOW, bool SPARSE, bool PAIR_C, bool PAIR_R
 __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void bwd_passes_kernel(PrefillBwdParams p, int n_columns) {
     __shared__ u32x4 lds[kBwdLdsChunks<D>];
     const int id = blockIdx.x;
+    if constexpr (SPARSE) {
+        if (p.list_limit > 0) {  // (two launches: the number of entries says which of them runs)
+            using const_i32 = const __attribute__((address_space(4))) int32_t;
+            const_i32 *row_ptr = (const_i32 *)(uintptr_t)p.sparse_row_ptr;
+            const int64_t lines = (int64_t)p.sparse_batch * p.sparse_heads * ((p.T + 127) / 128);
+            if ((row_ptr[lines] - row_ptr[0] <= p.list_limit) != PAIR_C) return;
+        }
+    }
     if (id >= n_columns) {
         bwd_dq_dr<D, CAUSAL, WINDOW, SPARSE, PAIR_R>(p, id - n_columns, lds);
         return;
@@ -1163,14 +1171,23 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void bwd_passes_kernel(Prefil
 // One query head per key head: the row workgroups' chains are then as long, and are halved too (8 / 8 heads,
 // whole / columns / both: d = 64, 2 x 2000 73 / 67 / 61, 1 x 3000 92 / 78 / 68; d = 128, 1 x 2000 81 / 73 / 66),
 // but for a sliding window (d = 64, 1 x 2500, 500 keys: 31 / 28 / 32).
-// Block lists: what share is listed the host does not know. With full lists PAIR costs up to a tenth (d = 128, 2 x
-// 2048: 218 -> 231, 4 x 4096 1508 -> 1655), at half of the tiles and below it gains (2 x 2048: a half 176 -> 153, a
-// quarter 141 -> 115, 0.15 101 -> 99): taken from a chain of half the load on (as if all were listed), and
-// always at d = 64 (3 x 2048 a quarter 162 -> 154, all 326 -> 348; the one-per-unit form 223 and 406).
+// A launch of the whole form that fits the units at once, where the halved chains do not, trades one round for two:
+// there they have to be worth more (d = 128, n / CUs in brackets; 8 / 8 heads, 2 x 651 full attention (0.75, 1.4) 40 / 50, both
+// 45; 4 x 366 over 502 keys (0.9, 1.4) 28 / 35; 1641 rows, window 431 (0.8, 1.3) 34 / 45; chain / load 1.3 - 1.8 in all of these;
+// 1 x 1619 (0.8, 1.2; 2.4) 66 / 51, 4 / 4 heads, 1 x 3759 (0.9, 1.4; 2.3) 137 / 104).
+// Block lists: what share is listed the host does not know; the estimate counts all. PAIR gains where few are listed and
+// costs where all are, unless the chain decides in any case (d = 128, chain / load in brackets, share listed; 2 x 2048
+// (0.97) a quarter 119 / 109, a half 164 / 151, 0.9 202 / 219, all 209 / 226; 8 / 8 heads, 3774 (1.1) 116 / 96, 161 / 132, 180 /
+// 210, 187 / 226; 2 x 1000 (1.8) 67 / 54 ... 99 / 74; d = 64, 4 x 4096 (0.13) 318 / 276, 509 / 455, 740 / 760, 777 / 833). Between
+// these both forms are launched and the number of entries in the lists tells every workgroup whether its form
+// is the one that runs: 2 - 3 us for the launch that does not (2 x 2048 a quarter 111, all 212; 4 x 4096 of either d up to
+// 15 in 1480). Short chains at d = 128 lose with PAIR at any share as long as the load decides (8 / 8 heads, 3 x 616 over
+// 1506 (0.6) a quarter 49 / 60, 32 / 16, 4 x 316 (0.8) all 55 / 64).
 // The forms add a gradient's terms in different orders, so gradients differ in their rounding with the form.
 // 8 / 8 heads, d = 64, 4096 rows 139 / 123, both 112; 4 / 2 heads, d = 128, 5129 rows 347 / 237.
 struct BackwardPlan {
     bool pair_c, pair_r;
+    int32_t list_limit;  // > 0: pair_c up to so many entries in the row lists
 };
 static BackwardPlan backward_plan(const PrefillBwdParams &p, int num_cus) {
     const bool sparse = p.sparse_row_ptr != nullptr, windowed = p.causal && p.window > 0 && p.window < p.Tk;
@@ -1185,39 +1202,59 @@ static BackwardPlan backward_plan(const PrefillBwdParams &p, int num_cus) {
     const double chain = G * col_tiles * per_item + fixed, row_chain = row_tiles * per_tile + fixed;
     const double load = (heads * ((cells + (p.causal ? key_blocks : 0)) * per_item + (cells + (p.causal ? row_blocks : 0)) * per_tile) +
                          fixed * (heads * row_blocks + kv_heads * key_blocks)) / num_cus;
+    const double rows_n = heads * row_blocks;
+    const bool one_round = rows_n + kv_heads * key_blocks <= num_cus && rows_n + kv_heads * std::ceil(Tk / 64) > num_cus;
     BackwardPlan plan{};
-    if (sparse)
-        plan.pair_c = p.d == 64 || chain > 0.5 * load;
-    else
-        plan.pair_c = chain > (p.d == 128 ? 1.3 : 0.6) * load && chain >= row_chain;
+    bool by_length = false;
+    if (sparse) {
+        const bool long_chains = col_tiles >= 16;
+        if (p.d == 64) {
+            plan.pair_c = true;
+            by_length = long_chains && chain <= 0.6 * load;
+        } else if (long_chains) {
+            plan.pair_c = chain > 0.5 * load;
+            by_length = plan.pair_c && chain <= 1.5 * load;
+        } else {
+            plan.pair_c = chain > (one_round ? 1.8 : 1.1) * load;
+        }
+    } else if (p.d == 64) {
+        plan.pair_c = chain > 0.6 * load && chain >= row_chain;
+    } else {
+        plan.pair_c = chain > (one_round ? 1.8 : 1.3) * load && chain >= row_chain;
+    }
+    if (by_length) {
+        const double seen = cells + (p.causal ? row_blocks : 0);  // list cells that some row sees
+        const double limit = (p.d == 128 ? 0.65 : 0.8) * seen * p.sparse_batch * p.sparse_heads;
+        plan.list_limit = (int32_t)std::min(std::max(limit, 1.0), 2147483647.0);
+    }
     plan.pair_r = plan.pair_c && !sparse && p.window <= 0 && 3 * row_tiles > 2 * G * col_tiles;
     return plan;
 }
 
 int32_t backward_form_bf16(const PrefillBwdParams &p, int num_cus) {
     const BackwardPlan plan = backward_plan(p, num_cus);
-    return (plan.pair_c ? 64 : 128) + 256 * (plan.pair_r ? 64 : 128);
+    return (plan.pair_c ? 64 : 128) + 256 * (plan.pair_r ? 64 : 128) + (plan.list_limit > 0 ? 65536 : 0);
 }
 
 template <int D>
 static hipError_t launch_bwd_d(const PrefillBwdParams &p, int num_cus, hipStream_t stream) {
     const BackwardPlan plan = backward_plan(p, num_cus);
-    const int keys = plan.pair_c ? 64 : 128, rows = plan.pair_r ? 64 : 128;
     const long long n_rows = (long long)p.B * p.Hq * p.T;
     constexpr int kPrepRows = 2048 / D;  // rows per workgroup of the rows-prepare kernel
     const long long g0 = (n_rows + kPrepRows - 1) / kPrepRows;
-    const long long g1 = (long long)((p.T + rows - 1) / rows) * p.Hq * p.B;
-    const long long g2 = (long long)((p.Tk + keys - 1) / keys) * p.Hkv * p.B;
-    if (g0 > 0x7fffffffLL || g1 + g2 > 0x7fffffffLL) return hipErrorInvalidValue;
+    auto columns = [&](bool pair) { return (long long)((p.Tk + (pair ? 63 : 127)) / (pair ? 64 : 128)) * p.Hkv * p.B; };
+    auto row_groups = [&](bool pair) { return (long long)((p.T + (pair ? 63 : 127)) / (pair ? 64 : 128)) * p.Hq * p.B; };
+    if (g0 > 0x7fffffffLL || columns(plan.pair_c) + row_groups(plan.pair_r) > 0x7fffffffLL) return hipErrorInvalidValue;
     hipLaunchKernelGGL((bwd_rows_prepare_kernel<D>), dim3((unsigned)g0), dim3(256), 0, stream, p);
-    const dim3 grid((unsigned)(g1 + g2)), block(256);
-    const int cols = (int)g2;
+    PrefillBwdParams q = p;
+    q.list_limit = plan.list_limit;
     const std::true_type yes;
     const std::false_type no;
     auto run = [&](auto causal, auto window, auto sparse, auto pair_c, auto pair_r) {
-        hipLaunchKernelGGL((bwd_passes_kernel<D, decltype(causal)::value, decltype(window)::value, decltype(sparse)::value,
-                                              decltype(pair_c)::value, decltype(pair_r)::value>),
-                           grid, block, 0, stream, p, cols);
+        constexpr bool PC = decltype(pair_c)::value, PR = decltype(pair_r)::value;
+        const long long cols = columns(PC);
+        hipLaunchKernelGGL((bwd_passes_kernel<D, decltype(causal)::value, decltype(window)::value, decltype(sparse)::value, PC, PR>),
+                           dim3((unsigned)(cols + row_groups(PR))), dim3(256), 0, stream, q, (int)cols);
         return hipGetLastError();
     };
     auto dense = [&](auto causal) {
@@ -1225,7 +1262,8 @@ static hipError_t launch_bwd_d(const PrefillBwdParams &p, int num_cus, hipStream
         return plan.pair_c ? run(causal, no, no, yes, no) : run(causal, no, no, no, no);
     };
     auto lists = [&](auto causal) {
-        return plan.pair_c ? run(causal, no, yes, yes, no) : run(causal, no, yes, no, no);
+        const hipError_t err = plan.pair_c ? run(causal, no, yes, yes, no) : run(causal, no, yes, no, no);
+        return err == hipSuccess && plan.list_limit > 0 ? run(causal, no, yes, no, no) : err;
     };
     if (p.sparse_row_ptr != nullptr) return p.causal ? lists(yes) : lists(no);  // (no window; checked by the caller)
     if (p.causal && p.window > 0)

@@ -614,7 +614,28 @@ def _backward_shape(binding, B, Hq, Hkv, T, Tk, d, causal, window=0, lists=False
     ((1, 16, 4, 5486, 5486, 64, True), {0: 633.9, 1: 440.6, 2: 439.2}),
     ((1, 16, 8, 6265, 6265, 64, True, 0, True), {0: 247.3, 1: 156.3}),  # a quarter of the tiles listed
     ((4, 16, 8, 4096, 4096, 128, True), {0: 1415.9, 1: 1509.1, 2: 1606.0}),
-    ((1, 8, 8, 1619, 1619, 128, True), {0: 66.5, 1: 51.3, 2: 48.3})])
+    ((1, 8, 8, 1619, 1619, 128, True), {0: 66.5, 1: 51.3, 2: 48.3}),
+    # the whole form fits the units at once, the halved chains do not
+    ((2, 8, 8, 651, 651, 128, False), {0: 39.6, 1: 50.4, 2: 45.5}),
+    ((4, 8, 8, 366, 502, 128, True), {0: 28.0, 1: 34.9, 2: 33.7}),
+    ((1, 8, 8, 1641, 1703, 128, True, 431), {0: 34.5, 1: 44.9}),
+    ((2, 4, 4, 1634, 1634, 128, True), {0: 66.2, 1: 51.8, 2: 48.1}),
+    # lists with short chains: 0.15, a quarter, a half of the tiles
+    ((8, 8, 8, 210, 210, 128, True, 0, True), {0: 17.6, 1: 26.7}),
+    ((3, 8, 8, 616, 1506, 128, True, 0, True), {0: 48.9, 1: 59.8}),
+    ((4, 32, 16, 182, 182, 128, True, 0, True), {0: 26.2, 1: 32.2}),
+    # the chain decides at any share: all of the tiles
+    ((2, 16, 8, 1000, 1000, 128, True, 0, True), {0: 98.8, 1: 74.3}),
+    ((1, 16, 8, 1500, 1500, 128, True, 0, True), {0: 138.3, 1: 95.5})])
 def test_backward_takes_a_form_close_to_the_fastest_measured(binding, shape, measured):
     form = binding.load_library().parallax_prefill_backward_form(ctypes.byref(_backward_shape(binding, *shape)))
     assert measured[{128 + 256 * 128: 0, 64 + 256 * 128: 1, 64 + 256 * 64: 2}[form]] <= 1.05 * min(measured.values())
+
+
+@pytest.mark.parametrize("shape", [(2, 16, 8, 2048, 2048, 128, True), (2, 16, 8, 2048, 2048, 128, False), (4, 16, 8, 906, 2000, 128, False),
+                                   (1, 8, 8, 3774, 3774, 128, True), (2, 32, 16, 4096, 4096, 64, True)])
+def test_backward_lets_the_lists_decide_where_a_share_does(binding, shape):
+    """Halved chains are 8 to 18 % quicker with a quarter of the tiles listed and 8 to 21 % slower with all."""
+    form = binding.load_library().parallax_prefill_backward_form(ctypes.byref(_backward_shape(binding, *shape, 0, True)))
+    assert (form == 64 + 256 * 128 + 65536) == (shape[3] >= 1024)
+    assert shape[3] >= 1024 or form == 128 + 256 * 128

@@ -321,6 +321,63 @@ def test_lists_built_on_the_device(plx, lists, nrb, nkt, density):
     assert torch.equal(buf[:len(want[0])], want[0]) and torch.equal(buf[first:first + int(want[0][-1])], want[1][:int(want[0][-1])])
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,T,Tkv,d,causal", [(3, 16, 8, 1100, 1100, 128, True), (2, 16, 8, 1024, 1500, 128, False),
+                                                     (2, 32, 16, 1030, 1030, 64, False)])
+@pytest.mark.parametrize("per_head", [False, True])
+def test_the_lists_decide_the_form(plx, synth, masked, B, Hq, Hkv, T, Tkv, d, causal, per_head):
+    """Launches whose form depends on the share listed: few cells, all but a few, all, and none. With few the gradients are
+    those of 64 keys per workgroup bit for bit (as a launch of two key heads' groups takes them in any case), with
+    many they are not; both within the bound of the oracle."""
+    import ctypes
+
+    y = synth.prefill_inputs(B, Hq, Hkv, Tkv, d, seed=3800 + T, device=DEV)
+    y["q"], y["r"] = y["q"][:, :, Tkv - T:].contiguous(), y["r"][:, :, Tkv - T:].contiguous()
+    g = synth.prefill_inputs(B, Hq, Hkv, T, d, seed=3801, device=DEV)["q"].contiguous()
+    G, nrb, nkt = Hq // Hkv, -(-T // 128), -(-Tkv // 64)
+    rng = np.random.default_rng(T)
+
+    def grads_of(qs, ks, bm):
+        t = {n: y[n][:, qs if n in "qr" else ks].contiguous() for n in "qrkv"}
+        mask = torch.as_tensor(bm[qs] if per_head else bm, device=DEV)
+        mask = mask[None] if per_head else mask
+        o, vbar, stats = plx.parallax_prefill(t["q"], t["r"], t["k"], t["v"], y["scale"], causal=causal, block_mask=mask,
+                                              save_for_backward=True)
+        up = g[:, qs].contiguous()
+        ws = torch.empty(o.shape[:3] + (4,), dtype=torch.float32, device=DEV)
+        a = plx.prefill_bwd_args(t["q"], t["r"], t["k"], t["v"], o, vbar, stats, up, o, o, t["k"], t["k"], y["scale"], causal, ws)
+        lists = plx.attach_block_lists(a, mask, torch.device(DEV), columns=True)
+        form = plx.load_library().parallax_prefill_backward_form(ctypes.byref(a))
+        del lists
+        return form, plx.parallax_prefill_backward(t["q"], t["r"], t["k"], t["v"], o, vbar, stats, up, y["scale"],
+                                                   causal=causal, block_mask=mask)
+
+    row, tile = np.arange(nrb)[:, None], np.arange(nkt)[None, :]
+    visible = (tile * 64 <= row * 128 + 127 + Tkv - T) if causal else np.ones((nrb, nkt), bool)
+    some = slice(2 * G, 4 * G), slice(2, 4)
+    for share in (0.3, 0.95, 1.0, 0.0):
+        bm = (rng.random((Hq, nrb, nkt) if per_head else (nrb, nkt)) < share) & visible
+        form, full = grads_of(slice(0, Hq), slice(0, Hkv), bm)
+        assert form == 64 + 256 * 128 + 65536
+        form, part = grads_of(*some, bm)
+        if d == 128:
+            assert form == 64 + 256 * 128
+            same = all(torch.equal(a[:, some[0] if i < 2 else some[1]], b) for i, (a, b) in enumerate(zip(full, part)))
+            assert same == (share < 0.5)
+        for b, hk in ((0, 2), (B - 1, 3)):
+            for h in range(G if per_head else 1):
+                qs = slice(G * hk, G * hk + G)
+                if per_head:
+                    qs = slice(G * hk + h, G * hk + h + 1)
+                dense = masked.block_mask_to_dense(bm[G * hk + h] if per_head else bm, T, Tkv, 128, 64, causal)
+                want = masked.masked_backward(host(y["q"][b:b + 1, qs]), host(y["r"][b:b + 1, qs]), host(y["k"][b:b + 1, hk:hk + 1]),
+                                              host(y["v"][b:b + 1, hk:hk + 1]), host(g[b:b + 1, qs]), y["scale"], dense)
+                sums = want if h == 0 else want[:2] + tuple(x + z for x, z in zip(sums[2:], want[2:]))
+                for name, got, ref in zip(("dq", "dr"), full[:2], want[:2]):
+                    assert_gradient_close(name, host(got[b:b + 1, qs]), ref, BF16_REL_L2, (share, b, hk, h))
+            for name, got, ref in zip(("dk", "dv"), full[2:], sums[2:]):
+                assert_gradient_close(name, host(got[b:b + 1, hk:hk + 1]), ref, BF16_REL_L2, (share, b, hk))
+
+
 # (from 8192 lines of a kind on the counts are scanned, 4096 to a round)
 @pytest.mark.parametrize("lists,nrb,nkt", [((8191, 1), 1, 1), ((8192, 1), 1, 1), ((2, 4097), 1, 3), ((300, 1), 30, 3),
                                            ((1000, 3), 2, 6), ((9, 1000), 1, 40)])
