@@ -1372,10 +1372,10 @@ __global__ __launch_bounds__(256) void prefill_combine_kernel(PrefillParams p) {
 
 // ---- which form a launch takes -------------------------------------------------------------------
 // The estimates below are in us, from three quantities of a launch: its longest workgroup, the load dealt over
-// the chip, and what the last round of workgroups finds left to do. Fitted to (and the choice checked on) 2100 launches of
+// the chip, and what the last round of workgroups finds left to do. Fitted to (and the choice checked on) 3000 launches of
 // every form: 1 - 64 heads, 17 - 16384 rows behind 0 - 16384 keys, causal and full, windows, K and V not in the
-// L2. The form taken is 0.6 % (d = 64) and 0.3 % (d = 128) behind the fastest one on average, and more than a tenth in 20
-// of 1456 and 1 of 631 launches.
+// L2. The form taken is 0.4 % (d = 64) and 0.2 % (d = 128) behind the fastest one on average, and more than a tenth in 8
+// of 2095 and 1 of 901 launches.
 struct LaunchCosts {
     double start, tile;            // a workgroup alone on its compute unit: to start and finish, per 64-key tile
     double shared;                 // per tile of a second workgroup on the unit (d = 64)
@@ -1388,8 +1388,8 @@ struct PrefillCosts {
     double merge, merge_byte, merge_range;         // key ranges: the second launch, per byte of records written or read, per range of a row
     int resident;                                  // workgroups per compute unit
 };
-static constexpr PrefillCosts kPrefillCosts64 = {{5.7, 0.765, 0.715, 0.0, 0.82, 0.31, 7.7e6},
-                                                 {5.3, 0.61, 0.125, 1.8, 0.473, 0.02, 9.1e6}, 4.7, 0.15e-6, 0.89, 2};
+static constexpr PrefillCosts kPrefillCosts64 = {{5.9, 0.765, 0.715, 0.0, 0.82, 0.31, 7.7e6},
+                                                 {5.3, 0.61, 0.125, 1.1, 0.50, 0.1, 9.1e6}, 4.7, 0.15e-6, 0.89, 2};
 static constexpr PrefillCosts kPrefillCosts128 = {{7.2, 1.145, 0.0, 6.0, 1.43, 0.25, 13.0e6},
                                                   {8.3, 0.755, 0.0, 7.2, 0.70, 0.18, 8.5e6}, 5.0, 0.134e-6, 0.95, 1};
 

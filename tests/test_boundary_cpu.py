@@ -467,7 +467,7 @@ def test_packed_arguments_land_in_their_fields(binding):
 
 # us: (start, per tile, per tile of a second workgroup on the unit, load per workgroup, load per tile, tail, bytes per
 # us) of 128 rows per workgroup and of 64; (second launch, per byte of records, per range)
-_PREFILL_COSTS = {64: ((5.7, 0.765, 0.715, 0.0, 0.82, 0.31, 7.7e6), (5.3, 0.61, 0.125, 1.8, 0.473, 0.02, 9.1e6),
+_PREFILL_COSTS = {64: ((5.9, 0.765, 0.715, 0.0, 0.82, 0.31, 7.7e6), (5.3, 0.61, 0.125, 1.1, 0.50, 0.1, 9.1e6),
                        (4.7, 0.15e-6, 0.89)),
                   128: ((7.2, 1.145, 0.0, 6.0, 1.43, 0.25, 13.0e6), (8.3, 0.755, 0.0, 7.2, 0.70, 0.18, 8.5e6),
                         (5.0, 0.134e-6, 0.95))}
@@ -576,6 +576,10 @@ def test_prefill_plan_is_the_cheapest_of_all_forms(binding):
     ((1, 8, 8, 28, 3706, 64, True), {128: 46.8, 64: 41.6, 20: 25.7, 12: 22.9, 10: 22.3, 8: 22.7, 6: 23.1, 3: 32.1}),
     ((3, 32, 16, 383, 14104, 64, True), {128: 315.5, 64: 329.2, 111: 277.2, 74: 260.0, 56: 258.7, 37: 264.1}),
     ((1, 8, 8, 43, 7029, 64, False), {128: 81.4, 37: 37.8, 22: 31.3, 14: 27.8, 11: 28.8, 10: 29.2, 5: 39.1}),
+    ((3, 16, 4, 609, 609, 64, True), {128: 14.1, 64: 12.6}),
+    ((4, 16, 4, 327, 327, 64, True), {128: 10.4, 64: 9.4}),
+    ((3, 16, 8, 637, 637, 64, True), {128: 13.8, 64: 12.3}),
+    ((1, 64, 16, 425, 425, 64, True), {128: 12.1, 64: 10.7}),
     ((1, 32, 16, 300, 2300, 64, True), {128: 31.6, 64: 27.4, 18: 30.7, 9: 34.5, 5: 36.9}),
     ((1, 8, 8, 2789, 2789, 64, True), {128: 37.9, 64: 31.8, 22: 38.8, 11: 40.1}),
     ((1, 8, 8, 4095, 4095, 64, True), {128: 55.3, 64: 47.5, 22: 55.2}),
