@@ -1207,7 +1207,7 @@ static BackwardPlan backward_plan(const PrefillBwdParams &p, int num_cus) {
     BackwardPlan plan{};
     bool by_length = false;
     if (sparse) {
-        const bool long_chains = col_tiles >= 16;
+        const bool long_chains = G * col_tiles >= 24;
         if (p.d == 64) {
             plan.pair_c = true;
             by_length = long_chains && chain <= 0.6 * load;
@@ -1215,7 +1215,7 @@ static BackwardPlan backward_plan(const PrefillBwdParams &p, int num_cus) {
             plan.pair_c = chain > 0.5 * load;
             by_length = plan.pair_c && chain <= 1.5 * load;
         } else {
-            plan.pair_c = chain > (one_round ? 1.8 : 1.1) * load;
+            plan.pair_c = chain > (one_round ? 1.8 : 1.5) * load;
         }
     } else if (p.d == 64) {
         plan.pair_c = chain > 0.6 * load && chain >= row_chain;
