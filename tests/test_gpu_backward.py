@@ -151,17 +151,19 @@ def test_backward_strided_views_equal_dense_tensors(plx, synth, T, Tkv, causal, 
         assert torch.equal(got.contiguous(), ref), name
 
 
-@pytest.mark.parametrize("B,Hq,Hkv,T,Tkv,d,causal,window", [
+@pytest.mark.parametrize("B,Hq,Hkv,T,Tkv,d,causal,window,keys,rows", [
     # many heads: the launch fills the chip and takes 128 keys and rows per workgroup
-    (64, 16, 8, 130, 130, 128, True, 0), (64, 16, 8, 65, 200, 128, False, 0), (48, 16, 8, 129, 129, 128, True, 40),
-    (96, 16, 8, 130, 130, 64, True, 0), (96, 8, 8, 193, 193, 64, False, 0), (96, 16, 8, 100, 150, 64, True, 33),
+    (64, 16, 8, 130, 130, 128, True, 0, 128, 128), (64, 16, 8, 65, 200, 128, False, 0, 128, 128),
+    (48, 16, 8, 129, 129, 128, True, 40, 128, 128), (96, 16, 8, 130, 130, 64, True, 0, 128, 128),
+    (96, 8, 8, 193, 193, 64, False, 0, 128, 128), (96, 16, 8, 100, 150, 64, True, 33, 128, 128),
     # few heads: 64 keys per workgroup, with one query head per key head also 64 rows; odd and even numbers of tiles
-    (1, 4, 2, 63, 63, 128, True, 0), (1, 4, 2, 65, 65, 64, True, 0), (1, 4, 2, 191, 191, 128, False, 0),
-    (2, 4, 4, 64, 64, 128, True, 0), (2, 4, 4, 129, 129, 64, True, 0), (1, 4, 4, 200, 200, 128, False, 0),
-    (1, 4, 4, 257, 257, 64, False, 0), (1, 4, 4, 320, 320, 128, True, 0), (1, 4, 4, 260, 260, 64, True, 70)])
-def test_backward_forms_of_a_launch(plx, synth, bwd_oracle, B, Hq, Hkv, T, Tkv, d, causal, window):
+    (1, 4, 2, 63, 63, 128, True, 0, 64, 128), (1, 4, 2, 65, 65, 64, True, 0, 64, 128), (1, 4, 2, 191, 191, 128, False, 0, 64, 128),
+    (2, 4, 4, 64, 64, 128, True, 0, 64, 64), (2, 4, 4, 129, 129, 64, True, 0, 64, 64), (1, 4, 4, 200, 200, 128, False, 0, 64, 64),
+    (1, 4, 4, 257, 257, 64, False, 0, 64, 64), (1, 4, 4, 320, 320, 128, True, 0, 64, 64), (1, 4, 4, 260, 260, 64, True, 70, 64, 128)])
+def test_backward_forms_of_a_launch(plx, synth, bwd_oracle, B, Hq, Hkv, T, Tkv, d, causal, window, keys, rows):
     """Every form of the passes at the edges of its blocks, first and last batch entry."""
     y, g = _inputs(synth, B, Hq, Hkv, T, Tkv, d, seed=2700 + T + d)
+    assert _form(plx, y, causal, window) == keys + 256 * rows
     _, _, _, grads = _run(plx, y, g, causal, window)
     for b in {0, B - 1}:
         want = bwd_oracle.backward(*(host(y[n][b:b + 1]) for n in "qrkv"), host(g[b:b + 1]), y["scale"], causal=causal,

@@ -178,6 +178,19 @@ def test_backward_random_block_masks_shared_by_all_heads(plx, synth, masked, T, 
     _check_backward(plx, synth, masked, y, bm, causal, seed=3600 + T)
 
 
+def _list_form(plx, y, mask, causal):
+    import ctypes
+
+    q, k = y["q"], y["k"]
+    stats = torch.empty(q.shape[:3] + (2,), dtype=torch.float32, device=DEV)
+    ws = torch.empty(q.shape[:3] + (4,), dtype=torch.float32, device=DEV)
+    a = plx.prefill_bwd_args(q, y["r"], k, y["v"], q, q, stats, q, q, q, k, k, 0.1, causal, ws)
+    lists = plx.attach_block_lists(a, mask, torch.device(DEV), columns=True)
+    form = plx.load_library().parallax_prefill_backward_form(ctypes.byref(a))
+    del lists
+    return form
+
+
 @pytest.mark.parametrize("B,T,Tkv,d,causal", [(96, 300, 300, 128, True), (96, 130, 200, 128, False), (2, 300, 300, 64, True),
                                               (2, 129, 385, 64, False), (2, 385, 385, 128, True)])
 def test_backward_forms_of_a_launch_with_lists(plx, synth, masked, B, T, Tkv, d, causal):
@@ -198,6 +211,7 @@ def test_backward_forms_of_a_launch_with_lists(plx, synth, masked, B, T, Tkv, d,
         m = torch.as_tensor(bm, device=DEV)
         o, vbar, stats = plx.parallax_prefill(t["q"], t["r"], t["k"], t["v"], y["scale"], causal=causal, block_mask=m,
                                               save_for_backward=True)
+        assert [_list_form(plx, x, m, causal) for x in (y, t)] == [64 + 256 * 128, 128 + 256 * 128]
         big = plx.parallax_prefill_backward(t["q"], t["r"], t["k"], t["v"], o, vbar, stats, g.repeat(B // 2, 1, 1, 1),
                                             y["scale"], causal=causal, block_mask=m)
         for name, got, ref in zip(("dq", "dr", "dk", "dv"), big, small):
@@ -328,8 +342,6 @@ def test_the_lists_decide_the_form(plx, synth, masked, B, Hq, Hkv, T, Tkv, d, ca
     """Launches whose form depends on the share listed: few cells, all but a few, all, and none. With few the gradients are
     those of 64 keys per workgroup bit for bit (as a launch of two key heads' groups takes them in any case), with
     many they are not; both within the bound of the oracle."""
-    import ctypes
-
     y = synth.prefill_inputs(B, Hq, Hkv, Tkv, d, seed=3800 + T, device=DEV)
     y["q"], y["r"] = y["q"][:, :, Tkv - T:].contiguous(), y["r"][:, :, Tkv - T:].contiguous()
     g = synth.prefill_inputs(B, Hq, Hkv, T, d, seed=3801, device=DEV)["q"].contiguous()
@@ -343,11 +355,7 @@ def test_the_lists_decide_the_form(plx, synth, masked, B, Hq, Hkv, T, Tkv, d, ca
         o, vbar, stats = plx.parallax_prefill(t["q"], t["r"], t["k"], t["v"], y["scale"], causal=causal, block_mask=mask,
                                               save_for_backward=True)
         up = g[:, qs].contiguous()
-        ws = torch.empty(o.shape[:3] + (4,), dtype=torch.float32, device=DEV)
-        a = plx.prefill_bwd_args(t["q"], t["r"], t["k"], t["v"], o, vbar, stats, up, o, o, t["k"], t["k"], y["scale"], causal, ws)
-        lists = plx.attach_block_lists(a, mask, torch.device(DEV), columns=True)
-        form = plx.load_library().parallax_prefill_backward_form(ctypes.byref(a))
-        del lists
+        form = _list_form(plx, t, mask, causal)
         return form, plx.parallax_prefill_backward(t["q"], t["r"], t["k"], t["v"], o, vbar, stats, up, y["scale"],
                                                    causal=causal, block_mask=mask)
 
@@ -376,6 +384,35 @@ def test_the_lists_decide_the_form(plx, synth, masked, B, Hq, Hkv, T, Tkv, d, ca
                     assert_gradient_close(name, host(got[b:b + 1, qs]), ref, BF16_REL_L2, (share, b, hk, h))
             for name, got, ref in zip(("dk", "dv"), full[2:], sums[2:]):
                 assert_gradient_close(name, host(got[b:b + 1, hk:hk + 1]), ref, BF16_REL_L2, (share, b, hk))
+
+
+def test_the_lists_decide_the_form_in_a_hip_graph(plx, synth):
+    """One captured backward, replayed with few, nearly all and few cells in the captured mask: each replay as eagerly."""
+    y = synth.prefill_inputs(3, 16, 8, 1100, 128, seed=3850, device=DEV)
+    g = synth.prefill_inputs(3, 16, 8, 1100, 128, seed=3851, device=DEV)["q"].contiguous()
+    mask = torch.zeros(9, 18, dtype=torch.bool, device=DEV)
+    assert _list_form(plx, y, mask, True) == 64 + 256 * 128 + 65536
+
+    def step():
+        o, vbar, stats = plx.parallax_prefill(y["q"], y["r"], y["k"], y["v"], y["scale"], causal=True, block_mask=mask,
+                                              save_for_backward=True)
+        return (o,) + plx.parallax_prefill_backward(y["q"], y["r"], y["k"], y["v"], o, vbar, stats, g, y["scale"],
+                                                    causal=True, block_mask=mask)
+
+    graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.graph(graph, stream=side):
+        out = step()
+    torch.cuda.current_stream().wait_stream(side)
+    rng = np.random.default_rng(3852)
+    for share in (0.3, 0.95, 0.3):
+        mask.copy_(torch.as_tensor(rng.random((9, 18)) < share))
+        for t in out:
+            t.fill_(5.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        for a, b in zip([t.clone() for t in out], step()):
+            assert torch.equal(a, b), share
 
 
 # (from 8192 lines of a kind on the counts are scanned, 4096 to a round)

@@ -90,10 +90,9 @@ def test_large_logit_range_takes_the_safe_path(plx, synth, oracle, gain, causal)
                                                    (513, 513, True, 0), (1100, 1100, True, 0), (200, 777, True, 0),
                                                    (5, 600, True, 0), (130, 515, False, 0), (700, 700, True, 1),
                                                    (700, 700, True, 40), (520, 1500, True, 300)])
-def test_head_dim_64_two_row_sub_blocks_per_wave(plx, synth, oracle, T, Tkv, causal, window):
-    """d = 64 runs 64 query rows per wave (256 per workgroup): lengths around and far from
-    multiples of 256, chunks behind a cache, windows, the softmax-only twin, the online-rescale
-    pass, and the row cache written by the same kernel family."""
+def test_head_dim_64(plx, synth, oracle, T, Tkv, causal, window):
+    """d = 64: lengths around and far from multiples of a workgroup's rows, chunks behind a cache, windows, the
+    softmax-only twin, the online-rescale pass, and the row cache written by the same kernel family."""
     from oracle import parallax_backward as pb
 
     y = synth.prefill_inputs(2, 4, 2, Tkv, 64, seed=860 + T + window, device=DEV, k_offset_sigma=0.5)
@@ -124,29 +123,44 @@ def test_head_dim_64_two_row_sub_blocks_per_wave(plx, synth, oracle, T, Tkv, cau
         assert rel_l2(gotb, refb) <= BF16_REL_L2
 
 
-@pytest.mark.parametrize("B,Hq,Hkv,T,Tkv,d,causal,window", [
-    # many heads: 128 rows per workgroup, two workgroups per compute unit at d = 64
-    (40, 16, 8, 130, 130, 128, True, 0), (40, 16, 8, 65, 200, 128, True, 50), (48, 16, 8, 129, 129, 64, True, 0),
-    (48, 16, 8, 100, 257, 64, False, 0), (48, 16, 8, 190, 190, 64, True, 33),
+@pytest.mark.parametrize("B,Hq,Hkv,T,Tkv,d,causal,window,rows", [
+    # many heads: 128 rows per workgroup, two workgroups per compute unit at d = 64; one row block and several
+    (40, 16, 8, 130, 130, 128, True, 0, 128), (40, 16, 8, 65, 200, 128, True, 50, 128), (48, 16, 8, 129, 129, 64, True, 0, 128),
+    (48, 16, 8, 100, 257, 64, False, 0, 128), (48, 16, 8, 190, 190, 64, True, 33, 128), (3, 32, 16, 1111, 1111, 64, True, 0, 128),
+    (3, 32, 16, 1111, 1111, 64, True, 300, 128), (2, 64, 16, 333, 600, 64, True, 100, 128),
     # few heads: 64 rows per workgroup, waves by twos on the halves of a tile; odd and even numbers of tiles
-    (1, 4, 2, 193, 193, 128, True, 0), (1, 4, 2, 65, 260, 128, True, 0), (1, 4, 2, 320, 320, 128, True, 90),
-    (2, 4, 4, 64, 64, 64, True, 0), (1, 4, 2, 63, 321, 64, True, 0), (1, 4, 2, 257, 257, 64, True, 70)])
-def test_forms_of_a_launch(plx, synth, oracle, B, Hq, Hkv, T, Tkv, d, causal, window):
+    (1, 4, 2, 193, 193, 128, True, 0, 64), (1, 4, 2, 65, 260, 128, True, 0, 64), (1, 4, 2, 320, 320, 128, True, 90, 64),
+    (2, 4, 4, 64, 64, 64, True, 0, 64), (1, 4, 2, 63, 321, 64, True, 0, 64), (1, 4, 2, 257, 257, 64, True, 70, 64)])
+def test_forms_of_a_launch(plx, synth, oracle, B, Hq, Hkv, T, Tkv, d, causal, window, rows):
     """Every form of the kernel at the edges of its blocks, first and last batch entry, with and without the row
-    cache; then the same rows with scores hundreds of binades apart (the online update and its merge)."""
+    cache (output, value mean and scalars); then the same rows with scores hundreds of binades apart (the
+    online update and its merge)."""
+    import ctypes
+
+    from oracle import parallax_backward as pb
+
     y = synth.prefill_inputs(B, Hq, Hkv, Tkv, d, seed=900 + T + d, device=DEV)
     y["q"], y["r"] = y["q"][:, :, Tkv - T:].contiguous(), y["r"][:, :, Tkv - T:].contiguous()
     ramp = torch.linspace(0.2, 3.0, Tkv, device=DEV).view(1, 1, Tkv, 1)
     wide = dict(y, q=(y["q"].float() * 30.0).to(torch.bfloat16), k=(y["k"].float() * ramp).to(torch.bfloat16))
+    a, lib = plx.prefill_args(y["q"], y["r"], y["k"], y["v"], y["q"], y["scale"], causal, True, window), plx.load_library()
+    assert lib.parallax_prefill_form(ctypes.byref(a), lib.parallax_prefill_workspace_bytes(ctypes.byref(a))) == rows
     for x in (y, wide):
         out = plx.parallax_prefill(x["q"], x["r"], x["k"], x["v"], x["scale"], causal=causal, window=window)
-        cached = plx.parallax_prefill(x["q"], x["r"], x["k"], x["v"], x["scale"], causal=causal, window=window,
-                                      save_for_backward=True)[0]
+        cached, vbar, stats = plx.parallax_prefill(x["q"], x["r"], x["k"], x["v"], x["scale"], causal=causal, window=window,
+                                                   save_for_backward=True)
         for b in {0, B - 1}:
             ref = oracle.forward(*(host(x[n][b:b + 1]) for n in "qrkv"), x["scale"], causal=causal, window=window)
             for got in (out, cached):
                 assert np.isfinite(host(got[b:b + 1])).all()
                 assert rel_l2(host(got[b:b + 1]), ref) <= BF16_REL_L2, (b, x is wide)
+        heads, kv = slice(Hq - Hq // Hkv, Hq), slice(Hkv - 1, Hkv)  # the last group of the last entry
+        _, vb, ub, lw = pb.forward_with_cache(*(host(x[n][B - 1:, heads if n in "qr" else kv]) for n in "qrkv"), x["scale"],
+                                              causal=causal, window=window)
+        assert rel_l2(host(vbar[B - 1:, heads]), vb) <= BF16_REL_L2
+        st = host(stats[B - 1:, heads])
+        np.testing.assert_allclose(st[..., 0], lw * 1.4426950408889634, rtol=1e-5, atol=2e-2)
+        assert np.linalg.norm(st[..., 1] - ub) <= BF16_REL_L2 * np.linalg.norm(ub) + 1e-6
 
 
 @pytest.mark.parametrize("B,Hq,Hkv,T,d,window,rows", [(4, 16, 8, 4096, 128, 0, 128), (2, 8, 8, 4200, 128, 0, 128), (2, 8, 4, 700, 128, 90, 64),
