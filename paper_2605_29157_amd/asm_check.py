@@ -92,6 +92,71 @@ MFMA_RESULT_WAIT_STATES = 12  # an 8-pass MFMA result may be read by the vector 
 MFMA_PASSES = 8               # v_mfma_f32_32x32x16_bf16: the pipe accepts the next one 8 states later
 
 
+def _basic_blocks(asm_text: str) -> tuple[list[list[tuple[int, str, bool]]], list[list[int]]]:
+    """The instructions (line number, text, inside inline assembly) between labels and branches, and which
+    blocks each of them can go on to: the one behind it and the target of its branch."""
+    blocks, labels, inside = [[]], {}, False
+    for n, line in enumerate(asm_text.splitlines(), 1):
+        t = line.strip()
+        if t.startswith(";;#ASMSTART") or t.startswith(";;#ASMEND"):
+            inside = t.startswith(";;#ASMSTART")
+            continue
+        if not _is_instruction(line):
+            continue
+        ins = t.split(";")[0].strip()
+        if ins.endswith(":"):
+            if blocks[-1]:
+                blocks.append([])
+            labels[ins[:-1]] = len(blocks) - 1
+            continue
+        blocks[-1].append((n, ins, inside))
+        if ins.startswith(("s_branch", "s_cbranch", "s_endpgm", "s_setpc")):
+            blocks.append([])
+    follow = []
+    for i, block in enumerate(blocks):
+        last = block[-1][1] if block else ""
+        nxt = [i + 1] if i + 1 < len(blocks) and not last.startswith(("s_branch", "s_endpgm", "s_setpc")) else []
+        if last.startswith(("s_branch", "s_cbranch")) and last.split()[-1] in labels:
+            nxt.append(labels[last.split()[-1]])
+        follow.append(nxt)
+    return blocks, follow
+
+
+def _with_pending_asm_mfmas(asm_text: str):
+    """Every instruction with the assembly MFMAs that may not have written back when it starts, on any way there:
+    (line number, text, [(line, result registers, wait states since)])."""
+    blocks, follow = _basic_blocks(asm_text)
+
+    def walk(block, state, out=None):
+        state = dict(state)  # (line, result registers) -> wait states since
+        for n, ins, inside in block:
+            if out is not None and state:
+                out.append((n, ins, [(m, regs, w) for (m, regs), w in state.items()]))
+            mfma = ins.startswith("v_mfma")
+            step = MFMA_PASSES if mfma else _wait_states(ins)
+            state = {k: w + step for k, w in state.items() if w + step < MFMA_RESULT_WAIT_STATES}
+            if mfma and inside:
+                dst = frozenset(_regs(ins.split(None, 1)[1].split(",")[0]))
+                state = {k: w for k, w in state.items() if k[1] != dst}  # (the next link of the same chain)
+                state[(n, dst)] = 0
+        return state
+
+    entry = [{} for _ in blocks]
+    todo = list(range(len(blocks)))
+    while todo:
+        i = todo.pop()
+        left = walk(blocks[i], entry[i])
+        for j in follow[i]:
+            grown = {k: w for k, w in left.items() if entry[j].get(k, MFMA_RESULT_WAIT_STATES) > w}
+            if grown:
+                entry[j].update(grown)
+                todo.append(j)
+    found = []
+    for block, state in zip(blocks, entry):
+        walk(block, state, found)
+    return found
+
+
 def find_early_reads_of_asm_mfma_results(asm_text: str) -> list[str]:
     """An MFMA written as inline assembly is invisible to the compiler, which therefore adds no
     wait states between it and the first instruction that reads its result. The kernels place
@@ -101,71 +166,37 @@ def find_early_reads_of_asm_mfma_results(asm_text: str) -> list[str]:
     per instruction (s_nop n: n + 1), MFMA_PASSES per further MFMA, which the matrix pipe only
     accepts once the previous one is through. (A later MFMA that reads the block as its
     accumulator input is the normal dependent chain.) This also catches register-allocator
-    copies or spills of a freshly written block."""
-    instrs = []  # (line number, text, inside inline assembly)
-    inside = False
-    for n, line in enumerate(asm_text.splitlines(), 1):
-        t = line.strip()
-        if t.startswith(";;#ASMSTART"):
-            inside = True
-            continue
-        if t.startswith(";;#ASMEND"):
-            inside = False
-            continue
-        if _is_instruction(line):
-            instrs.append((n, t.split(";")[0].strip(), inside))
+    copies or spills of a freshly written block. Branches are followed."""
     bad = []
-    for i, (n, ins, inside) in enumerate(instrs):
-        if not (inside and ins.startswith("v_mfma")):
+    for n, ins, pending in _with_pending_asm_mfmas(asm_text):
+        parts = ins.split(None, 1)
+        if ins.startswith("v_mfma") or len(parts) != 2:
             continue
-        dst = _regs(ins.split(None, 1)[1].split(",")[0])
-        states = 0
-        for pn, nxt, _ in instrs[i + 1:]:
-            if states >= MFMA_RESULT_WAIT_STATES or nxt.endswith(":") or nxt.startswith("s_endpgm"):
-                break
-            if nxt.startswith("v_mfma"):
-                states += MFMA_PASSES
-                continue
-            parts = nxt.split(None, 1)
-            if len(parts) == 2:
-                ops = parts[1].split(",")
-                # stores and LDS writes read every operand; everything else writes its first
-                stores = ("ds_write", "global_store", "scratch_store", "buffer_store")
-                reads = ops if parts[0].startswith(stores) else ops[1:]
-                if any(_regs(o) & dst for o in reads):
-                    bad.append("line %d: '%s' reads the result of the assembly MFMA at line %d after "
-                               "only %d wait states" % (pn, nxt, n, states))
-                    break
-            states += _wait_states(nxt)
+        ops = parts[1].split(",")
+        # stores and LDS writes read every operand; everything else writes its first
+        stores = ("ds_write", "global_store", "scratch_store", "buffer_store")
+        read = set().union(*(_regs(o) for o in (ops if parts[0].startswith(stores) else ops[1:])))
+        bad += ["line %d: '%s' reads the result of the assembly MFMA at line %d after only %d wait states"
+                % (n, ins, m, w) for m, regs, w in pending if regs & read]
     return bad
 
 
 def find_early_writes_over_asm_mfma_results(asm_text: str) -> list[str]:
     """The other half of the hazard above: a block that nothing reads any more (the scores that a
     pipeline's last step makes for a tile that is not there) is free to the register allocator at
-    once, and what a vector instruction puts there before the MFMA has written back is lost."""
-    bad, pending, inside = [], [], False  # pending: (line, registers, wait states so far)
-    for n, line in enumerate(asm_text.splitlines(), 1):
-        t = line.strip()
-        if t.startswith(";;#ASMSTART") or t.startswith(";;#ASMEND"):
-            inside = t.startswith(";;#ASMSTART")
-            continue
-        if not _is_instruction(line):
-            continue
-        ins = t.split(";")[0].strip()
-        if ins.endswith(":") or ins.startswith("s_endpgm"):
-            pending = []
-            continue
+    once, and what another instruction -- a vector one, or a load from the LDS, from memory or from
+    scratch -- puts there before the MFMA has written back is lost. Branches are followed."""
+    bad = []
+    for n, ins, pending in _with_pending_asm_mfmas(asm_text):
         parts = ins.split(None, 1)
-        dst = _regs(parts[1].split(",")[0]) if len(parts) == 2 else set()
-        mfma = ins.startswith("v_mfma")
-        if ins.startswith("v_") and not mfma:
-            bad += ["line %d: '%s' overwrites the result of the assembly MFMA at line %d after only %d wait states"
-                    % (n, ins, m, w) for m, regs, w in pending if regs & dst]
-        step = MFMA_PASSES if mfma else _wait_states(ins)
-        pending = [(m, regs, w + step) for m, regs, w in pending if w + step < MFMA_RESULT_WAIT_STATES]
-        if mfma and inside:
-            pending = [p for p in pending if p[1] != dst] + [(n, dst, 0)]
+        loads = ("ds_read", "ds_bpermute", "ds_permute", "ds_swizzle", "global_load", "buffer_load", "flat_load", "scratch_load")
+        writes = ins.startswith("v_") and not ins.startswith("v_mfma") or (ins.startswith(loads) and "_lds_" not in parts[0])
+        if not writes or len(parts) != 2:
+            continue
+        ops = parts[1].split(",")
+        dst = set().union(*(_regs(o) for o in ops[:2 if "swap" in parts[0] else 1]))  # (a swap writes both)
+        bad += ["line %d: '%s' overwrites the result of the assembly MFMA at line %d after only %d wait states"
+                % (n, ins, m, w) for m, regs, w in pending if regs & dst]
     return bad
 
 

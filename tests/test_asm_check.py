@@ -75,9 +75,36 @@ def test_early_write_over_the_result_is_flagged():
     write = "\tv_cvt_pk_bf16_f32 v36, v1, v2\n"
     assert len(check(ASM_MFMA + write)) == 1
     assert len(check(ASM_MFMA + OTHER_MFMA + write)) == 1
+    assert len(check(ASM_MFMA + "\tv_permlane32_swap_b32_e32 v60, v36\n")) == 1
     assert check(ASM_MFMA + OTHER_MFMA + OTHER_MFMA + write) == []
     assert check(ASM_MFMA + ASM_MFMA) == []
     assert check(ASM_MFMA + "\tv_cvt_pk_bf16_f32 v60, v1, v2\n") == []
+
+
+def test_early_load_over_the_result_is_flagged():
+    check = asm_check.find_early_writes_over_asm_mfma_results
+    for load in ("\tds_read_b128 v[36:39], v1 offset:32\n", "\tds_read_b64_tr_b16 v[34:35], v1\n",
+                 "\tscratch_load_dword v49, off, off offset:16\n", "\tglobal_load_dwordx4 v[40:43], v1, s[2:3]\n"):
+        assert len(check(ASM_MFMA + load)) == 1, load
+        assert check(ASM_MFMA + OTHER_MFMA + OTHER_MFMA + load) == []
+    # a load into the LDS names address registers only
+    assert check(ASM_MFMA + "\tglobal_load_lds_dwordx4 v36, s[2:3]\n") == []
+
+
+def test_results_are_followed_past_labels_and_branches():
+    writes, reads = asm_check.find_early_writes_over_asm_mfma_results, asm_check.find_early_reads_of_asm_mfma_results
+    write, read = "\tv_mov_b32_e32 v36, 0\n", "\tv_add_f32 v1, v34, v2\n"
+    for check, use in ((writes, write), (reads, read)):
+        # falling through a label; a branch taken to it; back to the top of a loop whose end issues the MFMA
+        assert len(check(ASM_MFMA + ".LBB0_1:\n" + use)) == 1
+        away = "\ts_cbranch_scc1 .LBB0_2\n\ts_nop 15\n\ts_endpgm\n.LBB0_2:\n"
+        assert len(check(ASM_MFMA + away + use)) == 1
+        loop = ".LBB0_1:\n" + use + OTHER_MFMA * 3 + ASM_MFMA + "\ts_cbranch_scc1 .LBB0_1\n\ts_endpgm\n"
+        assert len(check(loop)) == 1
+        assert check(loop.replace("\ts_cbranch", "\ts_nop 11\n\ts_cbranch")) == []
+        # behind an unconditional branch or the end of a kernel nothing of it is left
+        assert check(ASM_MFMA + "\ts_branch .LBB0_9\n.LBB0_3:\n" + use) == []
+        assert check(ASM_MFMA + "\ts_endpgm\nkernel_b:\n" + use) == []
 
 
 def test_foreign_use_of_an_assembly_loaded_register_is_reported():
