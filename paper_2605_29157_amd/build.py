@@ -104,6 +104,18 @@ def _check_f32_assembly() -> None:
         raise RuntimeError("generic_f32.hip: register spills in an fp32 kernel (%s)" % bad)
 
 
+def _check_prefill_assembly() -> None:
+    """At d = 64 two workgroups share a compute unit, with 256 registers a wave; a kernel that went over them once spilled
+    100 - 200 and took twice as long. The row-cache forms (their sums of the unrounded terms) park up to 17 registers
+    around their tile loops, the window form at d = 128 up to 5, the dense backward 3. Fail the build beyond that."""
+    row_cache_64 = ("ILi64ELb1ELb1ELb0ELb1E", "ILi64ELb1ELb0ELb0ELb1E", "ILi64ELb1ELb1ELb1ELb1E")
+    bad = {n: c for n, c in _spills("prefill_bf16.hip", "prefill_bf16_kernel").items()
+           if c > (20 if any(x in n for x in row_cache_64) else 6)}
+    bad.update({n: c for n, c in _spills("prefill_bwd_bf16.hip", "bwd_passes_kernel").items() if c > 4})
+    if bad:
+        raise RuntimeError("register spills in a prefill kernel (%s)" % bad)
+
+
 def build_library(extra_flags: list[str] | None = None, verbose: bool = True) -> str:
     """Compile every kernel file for gfx950 and link libparallax_hip.so next to this file."""
     os.makedirs(BUILD_DIR, exist_ok=True)
@@ -116,6 +128,7 @@ def build_library(extra_flags: list[str] | None = None, verbose: bool = True) ->
     _check_pipelined_assembly("decode_mla_wide_bf16.hip", False)
     _check_decode_assembly()
     _check_f32_assembly()
+    _check_prefill_assembly()
     tmp = LIB_PATH + ".tmp%d" % os.getpid()
     cmd = [_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs]
     res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)

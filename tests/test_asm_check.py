@@ -153,3 +153,23 @@ def test_early_read_of_an_assembly_dot_product_result_is_flagged():
     # overwriting the result early is reported too; other registers are nobody's business
     assert len(check(_asm_dot("v9", "v3") + "\tv_mov_b32_e32 v9, 0\n")) == 1
     assert check(_asm_dot("v9", "v3") + "\tv_mov_b32_e32 v8, v10\n" + dpp.replace("v9", "v7")) == []
+
+
+def test_spills_of_the_prefill_kernels_fail_the_build(monkeypatch):
+    import pytest
+
+    from paper_2605_29157_amd import build
+
+    row_cache = "_ZN3plx19prefill_bf16_kernelILi64ELb1ELb1ELb0ELb1ELb0ELb0ELb0ELb0EEEvNS_13PrefillParamsE"
+    plain = row_cache.replace("ELb0ELb1ELb0E", "ELb0ELb0ELb0E", 1)
+    for forward, backward, fails in ((20, 4, False), (21, 4, True), (20, 5, True)):
+        monkeypatch.setattr(build, "_spills", lambda src, kernel: {row_cache: forward, plain: 6} if kernel.startswith("prefill")
+                            else {"_ZN3plx17bwd_passes_kernelILi64ELb1ELb0ELb0ELb0ELb0EEEv": backward})
+        if fails:
+            with pytest.raises(RuntimeError):
+                build._check_prefill_assembly()
+        else:
+            build._check_prefill_assembly()
+    monkeypatch.setattr(build, "_spills", lambda src, kernel: {plain: 7})
+    with pytest.raises(RuntimeError):
+        build._check_prefill_assembly()
