@@ -49,7 +49,6 @@
 
 namespace plx {
 
-
 constexpr int kBC = 64;   // keys per LDS tile
 constexpr int kKB = 32;   // keys per inner block (one MFMA row block)
 
@@ -66,8 +65,6 @@ struct PrefillRanges {
 };
 // Split records of 32 rows: O1, O2 (2 * 32 * D floats) and five row scalars
 __host__ __device__ constexpr int64_t prefill_record_floats(int d) { return 64 * (int64_t)d + 5 * 32; }
-
-
 
 // Keeps two score blocks where they are up to this point.
 __device__ __forceinline__ void keep_blocks(const f32x16 &a, const f32x16 &b) { asm volatile("" ::"v"(a), "v"(b)); }
@@ -390,10 +387,7 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void prefill_bf16_kernel(Pref
     auto scores = [&](int stage, int kb, f32x16 &s1, f32x16 &s2) __attribute__((always_inline)) {
         const u32x4 *tk = lds + stage * STAGE_CHUNKS + col * KROW + h;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                s1[r] = 0.f;
-                s2[r] = 0.f;
-            }
+        for (int r = 0; r < 16; ++r) s1[r] = s2[r] = 0.f;
 #pragma unroll
         for (int ks = 0; ks < KSTEPS; ++ks) {
             const u32x4 kf = tk[kb * kKB * KROW + 2 * ks];
@@ -842,10 +836,10 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void prefill_bf16_kernel(Pref
         const u32x4 *zq = lds + QZONE + w * WAVE_TILE_CHUNKS + col * KROW + h;
         const u32x4 *zr = lds + RZONE + w * WAVE_TILE_CHUNKS + col * KROW + h;
 #pragma unroll
-            for (int ks = 0; ks < KSTEPS; ++ks) {
-                qf[ks] = zq[2 * ks];
-                if constexpr (USE_R) rf[ks] = zr[2 * ks];
-            }
+        for (int ks = 0; ks < KSTEPS; ++ks) {
+            qf[ks] = zq[2 * ks];
+            if constexpr (USE_R) rf[ks] = zr[2 * ks];
+        }
     }
     int stage = 0;
     f32x16 sa1, sa2, sb1, sb2;
@@ -1118,17 +1112,17 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void prefill_bf16_kernel(Pref
         for (int n = 0; n < NDB; ++n)
             if (owned(n))
 #pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) {
-                float y[4];
+                for (int q4 = 0; q4 < 4; ++q4) {
+                    float y[4];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int r = 4 * q4 + i;
-                    y[i] = o1[n][r] * gain - (USE_R ? o2[n][r] * inv2 : 0.f);
-                    chk = fmaf(y[i], 0.f, chk);
+                    for (int i = 0; i < 4; ++i) {
+                        const int r = 4 * q4 + i;
+                        y[i] = o1[n][r] * gain - (USE_R ? o2[n][r] * inv2 : 0.f);
+                        chk = fmaf(y[i], 0.f, chk);
+                    }
+                    const u32x2 packed = {pack_bf16(y[0], y[1]), pack_bf16(y[2], y[3])};
+                    *(u32x2 *)(otile16 + col * (OROW * 8) + 32 * n + 8 * q4 + 4 * h) = packed;
                 }
-                const u32x2 packed = {pack_bf16(y[0], y[1]), pack_bf16(y[2], y[3])};
-                *(u32x2 *)(otile16 + col * (OROW * 8) + 32 * n + 8 * q4 + 4 * h) = packed;
-            }
         return chk;
     };
     if constexpr (TWO && !PAIR) {  // (the staging tiles reach into ring stage 2)
@@ -1141,7 +1135,7 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void prefill_bf16_kernel(Pref
         // the row's own scores that the sum underflowed, take the exact path as well
         // (block-sparse: only for rows that do see a listed key -- the list is ascending, so that
         // is decided by its first tile)
-            if (my_row < T && (!SPARSE || tile_at(0) * kBC <= row_lim) && !(dsum1 > 1e-30f)) chk = 1.f;
+        if (my_row < T && (!SPARSE || tile_at(0) * kBC <= row_lim) && !(dsum1 > 1e-30f)) chk = 1.f;
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // tile loads past the end have landed
     const bool overflow = __syncthreads_or(chk != 0.f);  // NaN != 0 is true; all waves agree
@@ -1272,8 +1266,8 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void prefill_bf16_kernel(Pref
             __builtin_amdgcn_wave_barrier();
             if constexpr (PAIR) __syncthreads();  // (the other wave has read its rows)
 #pragma unroll
-                for (int n = 0; n < NDB; ++n)
-                    if (owned(n))
+            for (int n = 0; n < NDB; ++n)
+                if (owned(n))
 #pragma unroll
                     for (int q4 = 0; q4 < 4; ++q4) {
                         const u32x2 packed = {pack_bf16(o1[n][4 * q4] * inv, o1[n][4 * q4 + 1] * inv),

@@ -254,6 +254,7 @@ template <int D, bool CAUSAL, bool WINDOW, bool SPARSE, bool PAIR>
 __device__ __forceinline__ void bwd_dq_dr(const PrefillBwdParams &p, const int id, u32x4 *lds) {
     static_assert(CAUSAL || !WINDOW, "a sliding window is causal");
     static_assert(!(SPARSE && WINDOW), "block lists and a sliding window do not combine");
+    static_assert(!PAIR || (!SPARSE && !WINDOW), "halved row chains: dense, no window (backward_plan)");
     using TL = BwdTile<D>;
     constexpr int CPR = TL::CPR, KSTEPS = D / 16, NDB = D / 32;
     constexpr int STAGES = 3, STAGE_CHUNKS = 2 * TL::CHUNKS;  // ring of [K tile | V tile]
@@ -374,7 +375,7 @@ __device__ __forceinline__ void bwd_dq_dr(const PrefillBwdParams &p, const int i
     int n_list = 0;
     if constexpr (SPARSE) {
         const int sb = p.sparse_batch > 1 ? b : 0, sh = p.sparse_heads > 1 ? hq : 0;
-        const int64_t e = ((int64_t)sb * p.sparse_heads + sh) * ((T + 127) / 128) + rb * ROWS / 128;
+        const int64_t e = ((int64_t)sb * p.sparse_heads + sh) * nrb + rb;
         const_i32 *row_ptr = (const_i32 *)(uintptr_t)p.sparse_row_ptr;
         const int first = row_ptr[e];
         tile_list = (const_i32 *)(uintptr_t)p.sparse_tile_idx + first;
@@ -398,7 +399,7 @@ __device__ __forceinline__ void bwd_dq_dr(const PrefillBwdParams &p, const int i
     const int lim_row = CAUSAL ? min(my_row + off, Tk - 1) : Tk - 1;  // last key this lane's row sees
     if constexpr (SPARSE) {
         if (n_tiles == 0) {  // (workgroup-uniform) a row block that lists nothing: zero gradients
-            if (my_row < T && half == 0) {
+            if (my_row < T) {
                 __bf16 *dq_row = (__bf16 *)p.dq + b * p.dqs[0] + hq * p.dqs[1] + my_row * p.dqs[2];
                 __bf16 *dr_row = (__bf16 *)p.dr + b * p.drs[0] + hq * p.drs[1] + my_row * p.drs[2];
 #pragma unroll
@@ -606,7 +607,7 @@ __device__ __forceinline__ void bwd_dq_dr(const PrefillBwdParams &p, const int i
     if constexpr (WINDOW) {
         // leading tiles that hold a key before the window of the block's last row
         const int n_left = min(n_tiles, max(rb * ROWS + ROWS + off - p.window + kTileRows - 1, 0) / kTileRows);
-        run_tiles(std::true_type{}, std::false_type{}, t, PAIR ? min((n_left + 1) & ~1, n_tiles & ~1) : n_left, [] {});
+        run_tiles(std::true_type{}, std::false_type{}, t, n_left, [] {});
     }
     dma_k = (const char *)kbase + (t + 2) * k_tile_bytes;
     dma_v = (const char *)vbase + (t + 2) * v_tile_bytes;
@@ -1181,8 +1182,8 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void bwd_passes_kernel(Prefil
 // 210, 187 / 226; 2 x 1000 (1.8) 67 / 54 ... 99 / 74; d = 64, 4 x 4096 (0.13) 318 / 276, 509 / 455, 740 / 760, 777 / 833). Between
 // these both forms are launched and the number of entries in the lists tells every workgroup whether its form
 // is the one that runs: 2 - 3 us for the launch that does not (2 x 2048 a quarter 111, all 212; 4 x 4096 of either d up to
-// 15 in 1480). Short chains at d = 128 lose with PAIR at any share as long as the load decides (8 / 8 heads, 3 x 616 over
-// 1506 (0.6) a quarter 49 / 60, 32 / 16, 4 x 316 (0.8) all 55 / 64).
+// 15 in 1480). Chains of fewer than 24 tiles (over the heads of the group) lose with PAIR at any share at d = 128 as long
+// as the load decides (8 / 8 heads, 3 x 616 over 1506 (0.6) a quarter 49 / 60, 32 / 16, 4 x 316 (0.8) all 55 / 64).
 // The forms add a gradient's terms in different orders, so gradients differ in their rounding with the form.
 // 8 / 8 heads, d = 64, 4096 rows 139 / 123, both 112; 4 / 2 heads, d = 128, 5129 rows 347 / 237.
 struct BackwardPlan {
