@@ -12,8 +12,9 @@
 //     pass -- an MFMA can take its B operand from there -- and the vector registers hold scores,
 //     P and LDS fragments. d = 64: 256 registers and half of the LDS, two workgroups per compute unit, as the
 //     element-wise work takes as long as the matrix work there and one wave's runs under the other's
-//     matrix instructions (64 rows per wave, one workgroup per unit, before: 32 heads, 4 x 4096 rows 512 -> 492 us,
-//     3 x 1111 52 -> 40, 1 x 777 25 -> 16, 4 x 2048 with a window of 512 125 -> 84);
+//     matrix instructions (64 rows per wave, one workgroup per unit, before: 32 heads, 4 x 4096 rows 520 -> 503 us,
+//     3 x 1111 54 -> 42, 4 x 2048 with a window of 512 127 -> 88; 2 x 1024 over 16384 keys, whose workgroups all walk
+//     hundreds of tiles, 478 -> 489);
 //   * every global read is a direct global -> LDS load of whole rows (global_load_lds_dwordx4:
 //     no staging registers, no LDS write instructions): the wave's own Q and R rows once, then
 //     K/V tiles of 64 keys into a three-stage ring, fetched two tiles ahead, one load per MFMA
@@ -1428,10 +1429,11 @@ static double unsplit_us(const PrefillParams &p, int num_cus, int rows, const La
     return launch_us(c, resident, num_cus, heads * blocks, longest, sum / blocks, 4.0 * kBC * p.d, at);
 }
 
-// 64 rows per workgroup (PAIR) or 128. Measured us, 128 rows / 64: 16 query heads, d = 128, 200 rows 11.5 / 10.7, 777
-// 20.8 / 16.9, 1000 24.1 / 18.8, 1500 32.9 / 28.3, 2048 44.4 / 41.4, but 128 8.4 / 8.8, 2500 59 / 64; 8 heads, 4096 rows
-// 82 / 74, 6000 134 / 145; 64 heads, 267 rows over 7471 keys (320 workgroups of 64 rows: two rounds) 152 / 197; d = 64,
-// 32 heads, 300 9.3 / 8.2, 777 15.8 / 13.1, 1500 28.1 / 28.8; 8 heads, 4096 54 / 47, 16 x 250 rows over 6188 keys 75 / 65.
+// 64 rows per workgroup (PAIR) or 128. Measured us, 128 rows / 64, K and V not in the L2: 16 query heads, d = 128, 200
+// rows 11.6 / 10.9, 777 21.2 / 18.2, 1000 24.3 / 20.6, 1500 33.1 / 28.8, 2048 43.7 / 42.1, but 128 8.7 / 9.0, 2500 58.7 / 64.8; 32
+// heads, 500 16.5 / 14.8, 777 22.2 / 23.4, 300 over 3300 keys 59.5 / 46.4; 8 heads, 4096 79 / 71, 6000 136 / 144; 64 heads, 267
+// over 7471 keys (320 workgroups of 64 rows: two rounds) 152 / 197; d = 64, 32 heads, 300 9.6 / 8.6, 777 15.9 / 13.7, 1500 28.3 /
+// 28.5, 64 heads, 777 20.3 / 21.6; 8 heads, 2000 28.6 / 23.9, 4096 52.7 / 45.9, 4 x 250 over 6188 75 / 65.
 // The forms differ in the last bits: they add the keys' fp32 terms in different orders, and a tile that only some row of a
 // workgroup sees in part (so: other tiles, as workgroups have other rows) is summed after the rounding of P, the others
 // before it. 1 x 16 heads x 777 rows, d = 128: 4e-4 apart (relative L2), each 1.7e-3 from 64 bits.
@@ -1446,7 +1448,7 @@ static bool pair_possible(const PrefillParams &p) {
 // 302, 2 (the rule) 207, 3 250, 4 226; 17 over 5000 whole 86, 8 30, 16 34; d = 64 (whole, PAIR, ranges): 8 heads, 28
 // rows over 3678 keys 47, 42, 4 24, 6 (the rule) 22, 29 42; 694 over 4540 64, 55, 3 37, 5 (the rule) 36, 9 40; 32 heads, 272 over 13224
 // 157, 135, 3 92, 5 (the rule) 86, 8 95; 4 x 8 heads, 250 over 5938 75, 65, 3 40, 4 (the rule) 39, 8 44. A split has to be 3 % ahead.
-// The plan is made on every call, on the host, so it estimates no more than it has to: once for row
+// The plan is made on every call, on the host (0.6 - 2 us, 7 for 16000 rows), so it estimates no more than it has to: once for row
 // blocks that see the same keys (full attention) and for range counts that come to the same tiles, and
 // only those counts whose lower bound (the longest and the load alone, as if tiles divided evenly) can still win.
 static int choose_split_tiles(const PrefillParams &p, int num_cus, const PrefillCosts &c, double limit, int *items_per_head) {

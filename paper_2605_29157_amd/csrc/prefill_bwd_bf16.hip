@@ -1133,7 +1133,7 @@ __device__ __forceinline__ void bwd_dk_dv(const PrefillBwdParams &p, const int c
 // 1 x 1000 117 -> 87, 1 x 2048 212 -> 162, 4 x 1000 152 -> 133, 4 x 4096 1419 -> 1401; same bits.
 // d = 64: two workgroups per compute unit (77 KB of LDS, 256 registers a wave), so that the vector work of one,
 // which takes as long as its matrix work there, runs under the matrix instructions of the other: 32 / 16
-// heads, 4 x 4096 1677 -> 1430 us, 3 x 1111 137 -> 111, 2 x 2048 with a quarter of the tiles listed 146 -> 104.
+// heads, 4 x 4096 1760 -> 1505 us, 3 x 1111 142 -> 117, 2 x 2048 with a quarter of the tiles listed 166 -> 121 (PAIR 109).
 // PAIR: a workgroup owns 64 keys (column pass) or 64 rows (row pass) instead of 128, two waves share 32 of them,
 // and each takes one 32-row half of every tile it streams; their sums are added at the end. The
 // chain of a workgroup is half as long for twice as many workgroups, and with block lists a column
@@ -1165,13 +1165,13 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void bwd_passes_kernel(Prefil
 // The form of a launch, from estimates in us: `chain`, the longest column workgroup (2.4 us per 64 rows x 128
 // keys at d = 128 and 9 to start and end; 1.3 and 5 at d = 64), against `load`, all workgroups dealt evenly over the
 // chip (row pass: 1.75 and 1.0 per tile). Halved chains pay where the longest one is what the launch waits for. us
-// in the whole form / with PAIR columns, chain / load in brackets; 16 / 8 heads, d = 128: 4 x 4096 (0.26) 1337 /
-// 1430, 2 x 2048 full attention (0.56) 324 / 348, 3 x 1111 (1.03) 107 / 118, 4 x 600 (1.19) 63 / 66; 1 x 3000 (1.36)
-// 237 / 217, 1 x 2000 (1.93) 154 / 109, 4 x 300 (1.62) 37 / 30, 1 x 1000 (3.4) 79 / 55; 32 / 16, d = 64: 3 x 1111 (0.50)
-// 111 / 114; 1 x 3000 (0.67) 229 / 224, 4 x 500 (0.68) 48 / 43, 1 x 1000 (1.65) 65 / 46.
+// in the whole form / with PAIR columns, chain / load in brackets; 16 / 8 heads, d = 128: 4 x 4096 (0.26) 1395 /
+// 1486, 2 x 2048 full attention (0.56) 328 / 353, 3 x 1111 (1.03) 109 / 120, 4 x 600 (1.19) 64 / 67; 1 x 3000 (1.36)
+// 240 / 220, 1 x 2000 (1.93) 156 / 111, 4 x 300 (1.62) 37 / 30, 1 x 1000 (3.4) 79 / 56; 32 / 16, d = 64: 3 x 1111 (0.53)
+// 115 / 117; 1 x 3000 (0.67) 235 / 226, 4 x 500 (0.68) 50 / 45, 1 x 1000 (1.65) 66 / 47.
 // One query head per key head: the row workgroups' chains are then as long, and are halved too (8 / 8 heads,
-// whole / columns / both: d = 64, 2 x 2000 73 / 67 / 61, 1 x 3000 92 / 78 / 68; d = 128, 1 x 2000 81 / 73 / 66),
-// but for a sliding window (d = 64, 1 x 2500, 500 keys: 31 / 28 / 32).
+// whole / columns / both: d = 64, 2 x 2000 74 / 67 / 62, 1 x 3000 94 / 79 / 68; d = 128, 1 x 2000 81 / 73 / 65),
+// but for a sliding window (d = 64, 1 x 2500, 500 keys: 31 / 27 / 32).
 // A launch of the whole form that fits the units at once, where the halved chains do not, trades one round for two:
 // there they have to be worth more (d = 128, n / CUs in brackets; 8 / 8 heads, 2 x 651 full attention (0.75, 1.4) 40 / 50, both
 // 45; 4 x 366 over 502 keys (0.9, 1.4) 28 / 35; 1641 rows, window 431 (0.8, 1.3) 34 / 45; chain / load 1.3 - 1.8 in all of these;
