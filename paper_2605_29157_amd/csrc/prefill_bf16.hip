@@ -1369,7 +1369,7 @@ __global__ __launch_bounds__(256) void prefill_combine_kernel(PrefillParams p) {
 // The estimates below are in us, from three quantities of a launch: its longest workgroup, the load dealt over
 // the chip, and what the last round of workgroups finds left to do. Fitted to (and the choice checked on) 3000 launches of
 // every form: 1 - 64 heads, 17 - 16384 rows behind 0 - 16384 keys, causal and full, windows, K and V not in the
-// L2. The form taken is 0.4 % (d = 64) and 0.2 % (d = 128) behind the fastest one on average, and more than a tenth in 8
+// L2. The form taken is 0.4 % (d = 64) and 0.2 % (d = 128) behind the fastest one on average, and more than a tenth in 6
 // of 2095 and 1 of 901 launches.
 struct LaunchCosts {
     double start, tile;            // a workgroup alone on its compute unit: to start and finish, per 64-key tile
@@ -1457,10 +1457,12 @@ static int choose_split_tiles(const PrefillParams &p, int num_cus, const Prefill
     const double heads = (double)p.B * p.Hq;
     // A launch that keeps more than half of the units busy leaves most of them two ranges: at d = 128 none of 130 such
     // gained 3 %; at d = 64 a few do where the estimate is well ahead, and more of those with more row blocks than units
-    // (3 x 32 heads, 383 rows over 13721 keys 315 whole, 259).
+    // (3 x 32 heads, 383 rows over 13721 keys 315 whole, 259) unless the row blocks see keys of all lengths: the ranges of the
+    // long ones come first, whole long ones behind them (4 heads, 14891 rows square 226, 294).
     const double n_whole = heads * nrb;
     if (nrb > 128 || n_whole >= 2.0 * num_cus || (c.resident == 1 && 2 * n_whole > num_cus)) return 0;
-    if (2 * n_whole > num_cus) limit *= n_whole <= num_cus ? 0.9 : 0.97;
+    if (n_whole > num_cus && p.causal && p.T > p.Tk / 4) return 0;
+    if (2 * n_whole > num_cus) limit *= n_whole <= num_cus ? 0.88 : 0.97;
     const int kinds = p.causal ? nrb : 1, alike = p.causal ? 1 : nrb;  // row blocks by the keys they see
     auto keys = [&](int i) { return p.causal ? std::min(p.Tk, (nrb - i) * rows + (p.Tk - p.T)) : p.Tk; };
     auto tiles_of = [&](int i) { return (keys(i) + kBC - 1) / kBC; };

@@ -512,9 +512,9 @@ def _prefill_plan_by_search(B, Hq, T, Tk, d, causal, window=0, cus=256):
         rows = -rows
     blocks = [(t, -(-min(128, T - 128 * (i if not causal else len(seen(128)) - 1 - i)) // 32)) for i, t in enumerate(seen(128))]
     n = heads * len(blocks)
-    if window or len(blocks) > 128 or n >= 2 * cus or (d == 128 and 2 * n > cus):
+    if window or len(blocks) > 128 or n >= 2 * cus or (d == 128 and 2 * n > cus) or (n > cus and causal and T > Tk // 4):
         return rows, 0, 0
-    best, items, at = us * 0.97 * (1 if 2 * n <= cus else 0.9 if n <= cus else 0.97), 0, 0
+    best, items, at = us * 0.97 * (1 if 2 * n <= cus else 0.88 if n <= cus else 0.97), 0, 0
     for ranges in range(2, 33):
         most = -(-blocks[0][0] // ranges)
         if most < 2:
@@ -585,6 +585,7 @@ def test_prefill_plan_is_the_cheapest_of_all_forms(binding):
     ((1, 8, 8, 4095, 4095, 64, True), {128: 55.3, 64: 47.5, 22: 55.2}),
     ((1, 8, 8, 4096, 4096, 64, True), {128: 52.7, 64: 45.9, 22: 54.9}),
     ((1, 4, 4, 8192, 8192, 64, True), {128: 100.9, 64: 88.9, 43: 96.4}),
+    ((1, 4, 2, 14891, 14891, 64, True), {64: 225.7, 78: 294.4}),
     ((1, 8, 8, 4096, 4096, 128, True), {128: 80.1, 64: 71.7, 22: 96.7}),
     ((1, 8, 8, 6000, 6000, 128, True), {128: 136.6, 64: 144.4}),
     ((1, 64, 16, 267, 7471, 128, True), {128: 151.8, 64: 197.1, 59: 173.1, 30: 168.9}),
