@@ -1179,11 +1179,13 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void bwd_passes_kernel(Prefil
 // Block lists: what share is listed the host does not know; the estimate counts all. PAIR gains where few are listed and
 // costs where all are, unless the chain decides in any case (d = 128, chain / load in brackets, share listed; 2 x 2048
 // (0.97) a quarter 119 / 109, a half 164 / 151, 0.9 202 / 219, all 209 / 226; 8 / 8 heads, 3774 (1.1) 116 / 96, 161 / 132, 180 /
-// 210, 187 / 226; 2 x 1000 (1.8) 67 / 54 ... 99 / 74; d = 64, 4 x 4096 (0.13) 318 / 276, 509 / 455, 740 / 760, 777 / 833). Between
-// these both forms are launched and the number of entries in the lists tells every workgroup whether its form
-// is the one that runs: 2 - 3 us for the launch that does not (2 x 2048 a quarter 111, all 212; 4 x 4096 of either d up to
-// 15 in 1480). Chains of fewer than 24 tiles (over the heads of the group) lose with PAIR at any share at d = 128 as long
-// as the load decides (8 / 8 heads, 3 x 616 over 1506 (0.6) a quarter 49 / 60, 32 / 16, 4 x 316 (0.8) all 55 / 64).
+// 210, 187 / 226; 2 x 1000 (1.8) 67 / 54 ... 99 / 74, 64 / 16, 1213 (1.45) 0.7 201 / 162; d = 64, 4 x 4096 (0.13) 318 / 276, 509 /
+// 455, 740 / 760, 777 / 833). Between these both forms are launched and the number of entries in the lists tells every
+// workgroup whether its form is the one that runs: 2 - 3 us for the launch that does not (2 x 2048 a quarter 111, all 212; 4
+// x 4096 of either d up to 15 in 1480). Chains of fewer than 24 tiles (over the heads of the group) lose with PAIR at any
+// share as long as the load decides (d = 128, 8 / 8 heads, 3 x 616 over 1506 (0.6) a quarter 49 / 60, 32 / 16, 4 x 316 (0.8) all
+// 55 / 64; d = 64, 4 / 4 heads, 4 x 606 over 3287 (0.4) 0.7 75 / 100). Over 700 launches the form that runs is 1.0 % (d = 128) and
+// 0.5 % behind the faster one on average, the launch that does not run included.
 // The forms add a gradient's terms in different orders, so gradients differ in their rounding with the form.
 // 8 / 8 heads, d = 64, 4096 rows 139 / 123, both 112; 4 / 2 heads, d = 128, 5129 rows 347 / 237.
 struct BackwardPlan {
@@ -1210,11 +1212,11 @@ static BackwardPlan backward_plan(const PrefillBwdParams &p, int num_cus) {
     if (sparse) {
         const bool long_chains = G * col_tiles >= 24;
         if (p.d == 64) {
-            plan.pair_c = true;
             by_length = long_chains && chain <= 0.6 * load;
+            plan.pair_c = by_length || chain > 0.6 * load;
         } else if (long_chains) {
             plan.pair_c = chain > 0.5 * load;
-            by_length = plan.pair_c && chain <= 1.5 * load;
+            by_length = plan.pair_c && chain <= (G > 1 ? 1.2 : 1.5) * load;
         } else {
             plan.pair_c = chain > (one_round ? 1.8 : 1.5) * load;
         }
@@ -1225,7 +1227,7 @@ static BackwardPlan backward_plan(const PrefillBwdParams &p, int num_cus) {
     }
     if (by_length) {
         const double seen = cells + (p.causal ? row_blocks : 0);  // list cells that some row sees
-        const double limit = (p.d == 128 ? 0.65 : 0.8) * seen * p.sparse_batch * p.sparse_heads;
+        const double limit = (p.d == 128 ? 0.75 : 0.8) * seen * p.sparse_batch * p.sparse_heads;
         plan.list_limit = (int32_t)std::min(std::max(limit, 1.0), 2147483647.0);
     }
     plan.pair_r = plan.pair_c && !sparse && p.window <= 0 && 3 * row_tiles > 2 * G * col_tiles;

@@ -631,7 +631,12 @@ def _backward_shape(binding, B, Hq, Hkv, T, Tk, d, causal, window=0, lists=False
     ((4, 32, 16, 182, 182, 128, True, 0, True), {0: 26.2, 1: 32.2}),
     # the chain decides at any share: all of the tiles
     ((2, 16, 8, 1000, 1000, 128, True, 0, True), {0: 98.8, 1: 74.3}),
-    ((1, 16, 8, 1500, 1500, 128, True, 0, True), {0: 138.3, 1: 95.5})])
+    ((1, 16, 8, 1500, 1500, 128, True, 0, True), {0: 138.3, 1: 95.5}),
+    # the chain decides: 0.5, 0.7; short chains at d = 64: 0.7, 0.9
+    ((2, 64, 16, 549, 549, 128, True, 0, True), {0: 130.1, 1: 101.7}),
+    ((1, 64, 16, 1213, 1213, 128, True, 0, True), {0: 200.6, 1: 161.7}),
+    ((4, 4, 4, 606, 3287, 64, False, 0, True), {0: 74.5, 1: 100.2}),
+    ((2, 32, 16, 161, 4094, 64, False, 0, True), {0: 133.2, 1: 177.0})])
 def test_backward_takes_a_form_close_to_the_fastest_measured(binding, shape, measured):
     form = binding.load_library().parallax_prefill_backward_form(ctypes.byref(_backward_shape(binding, *shape)))
     assert measured[{128 + 256 * 128: 0, 64 + 256 * 128: 1, 64 + 256 * 64: 2}[form]] <= 1.05 * min(measured.values())
