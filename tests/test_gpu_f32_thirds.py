@@ -1,0 +1,117 @@
+"""Large fp32 prefill launches at d = 64 (bf16 thirds) at the edges of their tiles (32 columns x 32 keys, two tiles at a
+time): against the double-precision oracle, and against the fp32 matrix kernels that a launch of one key head runs."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+from parity import host, rel_l2
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+# Three thirds hold 24 bits, the products left out are below 3 * 2^-24 of one, and about 400 roundings at 2^-24 of
+# random sign make 20 * 2^-24 = 1.2e-6 of a sum.
+REL = 1.2e-6
+
+
+@pytest.fixture(scope="module")
+def plx():
+    from paper_2605_29157_amd import binding
+
+    binding.load_library()
+    return binding
+
+
+def _inputs(B, Hq, Hkv, T, Tkv, seed):
+    gen = torch.Generator(device=DEV).manual_seed(seed)
+    shapes = dict(q=(B, Hq, T, 64), r=(B, Hq, T, 64), k=(B, Hkv, Tkv, 64), v=(B, Hkv, Tkv, 64), g=(B, Hq, T, 64))
+    return {n: torch.randn(s, generator=gen, device=DEV) for n, s in shapes.items()}
+
+
+def _step(plx, x, causal=True, window=0):
+    o, vbar, st = plx.parallax_prefill(x["q"], x["r"], x["k"], x["v"], 0.125, causal=causal, window=window, save_for_backward=True)
+    return [o, *plx.parallax_prefill_backward(x["q"], x["r"], x["k"], x["v"], o, vbar, st, x["g"], 0.125, causal=causal,
+                                              window=window)]
+
+
+def _one_head(x, b, hk):
+    G = x["q"].shape[1] // x["k"].shape[1]
+    heads = lambda n: slice(hk, hk + 1) if n in "kv" else slice(hk * G, hk * G + G)
+    return {n: torch.empty_like(t[b:b + 1, heads(n)], memory_format=torch.contiguous_format).copy_(t[b:b + 1, heads(n)]) for n, t in x.items()}
+
+
+def _head_of(outs, b, hk, G):
+    return [t[b:b + 1, hk:hk + 1] if n > 2 else t[b:b + 1, hk * G:hk * G + G] for n, t in enumerate(outs)]
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,T,Tkv,causal,window", [
+    (8, 16, 16, 128, 128, True, 0), (4, 32, 32, 129, 129, True, 0), (4, 32, 16, 161, 161, True, 0), (4, 32, 32, 159, 223, True, 0),
+    (5, 26, 26, 130, 131, False, 0), (4, 32, 32, 190, 128, False, 0), (4, 32, 32, 200, 200, True, 1), (4, 32, 32, 193, 320, True, 37)])
+def test_thirds_at_the_edges(plx, B, Hq, Hkv, T, Tkv, causal, window):
+    from oracle import parallax_backward
+
+    x = _inputs(B, Hq, Hkv, T, Tkv, seed=T + Tkv)
+    outs, G = _step(plx, x, causal, window), Hq // Hkv
+    for b, hk in ((0, 0), (B - 1, Hkv - 1)):
+        one = _one_head(x, b, hk)
+        few = _step(plx, one, causal, window)
+        args = [host(one[n]) for n in "qrkv"]
+        want = [parallax_backward.forward_with_cache(*args, 0.125, causal=causal, window=window)[0],
+                *parallax_backward.backward(*args, host(one["g"]), 0.125, causal=causal, window=window)]
+        for name, got, fp32, ref in zip(("o", "dq", "dr", "dk", "dv"), _head_of(outs, b, hk, G), few, want):
+            if np.linalg.norm(ref) <= 1e-9 * got.numel():  # (window 1: a single key has no query and no probe gradient;
+                # what is left is the rounding of sums of 64 products of N(0, 1), 64 * 2^-24 of their size of 8 at most)
+                assert float(got.abs().max()) <= 64 * 2.0 ** -24 * 8, name
+                continue
+            assert rel_l2(host(got), ref) <= REL, (name, rel_l2(host(got), ref))
+            if window != 1 and Hkv * B * -(-Tkv // 32) >= 512:
+                assert not torch.equal(got, fp32), (name, "the launch did not run the kernels under test")
+                assert rel_l2(host(got), ref) <= rel_l2(host(fp32), ref), name
+
+
+def test_forward_without_probe_and_with_strided_rows(plx):
+    x = _inputs(4, 32, 32, 200, 200, seed=5)
+    y = {n: t[:, :, 40:] if n in "qr" else t for n, t in x.items()}
+    for use_r in (True, False):
+        got = plx.parallax_prefill(y["q"], y["r"] if use_r else None, y["k"], y["v"], 0.125, use_r=use_r)
+        one = {n: t[3:, 31:] for n, t in y.items()}
+        few = plx.parallax_prefill(one["q"], one["r"] if use_r else None, one["k"], one["v"], 0.125, use_r=use_r)
+        assert rel_l2(host(got[3:, 31:]), host(few).astype(np.float64)) <= REL
+
+
+@pytest.mark.parametrize("scales", [dict(v=1e-30), dict(v=1e35, g=1e-30), dict(g=1e-28), dict(k=1e-18, q=1e18), dict(v=3e-36),
+                                    dict(g=1e-36)])
+def test_small_and_large_values(plx, scales):
+    """Powers of ten that leave thirds below the smallest number, or near the largest."""
+    x = _inputs(4, 32, 32, 130, 130, seed=9)
+    for n, f in scales.items():
+        x[n] *= f
+    outs, few = _step(plx, x), _step(plx, _one_head(x, 2, 7))
+    for name, got, ref in zip(("o", "dq", "dr", "dk", "dv"), _head_of(outs, 2, 7, 1), few):
+        a, b = host(got).astype(np.float64), host(ref).astype(np.float64)
+        assert np.isfinite(a).all() and np.isfinite(b).all(), name
+        size = np.abs(b).max() or 1.0
+        assert rel_l2(a / size, b / size) <= 2 * REL, name
+
+
+@pytest.mark.parametrize("bad", [math.nan, math.inf, -math.inf])
+@pytest.mark.parametrize("name", list("qrkvg"))
+@pytest.mark.parametrize("window", [0, 30])
+def test_not_finite_as_the_fp32_kernels_have_it(plx, name, bad, window):
+    """One value that is not finite: the results are infinite or NaN where those of the fp32 kernels are, and as
+    close to them as ever everywhere else."""
+    x = _inputs(4, 32, 32, 150, 150, seed=21)
+    x[name][2, 7, 70, 3] = bad
+    outs, few = _step(plx, x, window=window), _step(plx, _one_head(x, 2, 7), window=window)
+    for n, got, ref in zip(("o", "dq", "dr", "dk", "dv"), _head_of(outs, 2, 7, 1), few):
+        a, b = host(got).astype(np.float64), host(ref).astype(np.float64)
+        ok = np.isfinite(b)
+        assert (np.isfinite(a) == ok).all(), n
+        if n != "dk":  # (there two infinities may meet in either order)
+            assert np.array_equal(a[~ok], b[~ok], equal_nan=True), n
+        if ok.any():
+            assert rel_l2(a[ok], b[ok]) <= 2 * REL, n
+    rest = _step(plx, _one_head(x, 1, 7), window=window)
+    for got, ref in zip(_head_of(outs, 1, 7, 1), rest):
+        assert rel_l2(host(got), host(ref).astype(np.float64)) <= 2 * REL
