@@ -155,10 +155,13 @@ _PACK = {
     plx_prefill_bwd_args: struct.Struct("@12P6if3iPN33q4P2i0P"),
     plx_decode_mla_args: struct.Struct("@5P3i3i2qfiPNP3i2i0P"),
     plx_norm_rope_args: struct.Struct("@" + 3 * "3P2i" + "4iP2fiPi0P"),
+    plx_block_list_args: struct.Struct("@P3i5P"),
 }
 for _args, _format in _PACK.items():
     assert _format.size == ctypes.sizeof(_args), _args
 _NO_PREP = (0,) * 8
+_ROW_LISTS, _ALL_LISTS = struct.Struct("@2P2i"), struct.Struct("@4P2i")  # from sparse_row_ptr on
+_ROW_CACHE = struct.Struct("@2P")  # from vbar on
 
 
 def _filled(args, *values):
@@ -547,12 +550,11 @@ def attach_block_lists(a, block_mask, device, stream=None, columns=False):
     backward) arguments `a` at them, for a launch on `stream`. Returns the buffer that holds them
     (several tensors for a mask beyond what parallax_block_lists takes): keep it until the call has
     been enqueued."""
-    m = block_mask.to(device=device, dtype=torch.bool)
-    while m.dim() < 4:
-        m = m.unsqueeze(0)
-    Bs, Hs, nrb, nkt = m.shape
+    m = block_mask
+    if m.dtype != torch.bool or m.device != device:
+        m = m.to(device=device, dtype=torch.bool)
+    Bs, Hs, nrb, nkt = (1,) * (4 - m.dim()) + tuple(m.shape)
     rows, cols = Bs * Hs * nrb, Bs * Hs * ((nkt + 1) // 2)
-    current = torch.cuda.current_stream()
     col_ptr = col_idx = 0
     if rows * nkt > _MAX_LIST_CELLS or rows + cols > _MAX_LIST_LINES:
         held = list(block_mask_lists(m)[:2])
@@ -564,25 +566,26 @@ def attach_block_lists(a, block_mask, device, stream=None, columns=False):
         if not columns:
             cols = 0
         # [row_ptr | col_ptr | counts | tile_idx | col_idx]
-        sizes = [rows + 1, cols + 1 if columns else 0, rows + cols, rows * nkt, cols * nrb]
-        held = [torch.empty(sum(sizes), dtype=torch.int32, device=device)]
-        row_ptr, col_ptr, counts, tile_idx, col_idx = (held[0].data_ptr() + 4 * sum(sizes[:i]) for i in range(5))
-        la = plx_block_list_args()
-        la.mask, la.lists, la.n_row_blocks, la.n_tiles = m.data_ptr(), Bs * Hs, nrb, nkt
-        la.row_ptr, la.counts, la.tile_idx = row_ptr, counts, tile_idx
+        counts = rows + 1 + (cols + 1 if columns else 0)
+        tiles = counts + rows + cols
+        held = [torch.empty(tiles + rows * nkt + cols * nrb, dtype=torch.int32, device=device)]
+        row_ptr = held[0].data_ptr()
+        tile_idx = row_ptr + 4 * tiles
         if columns:
-            la.col_ptr, la.col_idx = col_ptr, col_idx
-        st = load_library().parallax_block_lists(ctypes.byref(la), current.cuda_stream)
+            col_ptr, col_idx = row_ptr + 4 * (rows + 1), tile_idx + 4 * rows * nkt
+        la = _filled(plx_block_list_args, m.data_ptr(), Bs * Hs, nrb, nkt, row_ptr + 4 * counts, row_ptr, tile_idx, col_ptr, col_idx)
+        st = load_library().parallax_block_lists(ctypes.byref(la), _stream_ptr(None))
         if st != PLX_OK:
             raise ParallaxError(st, "parallax_block_lists")
-    a.sparse_row_ptr, a.sparse_tile_idx, a.sparse_batch, a.sparse_heads = row_ptr, tile_idx, Bs, Hs
     if columns:
-        a.sparse_col_ptr, a.sparse_col_idx = col_ptr, col_idx
+        _ALL_LISTS.pack_into(a, plx_prefill_bwd_args.sparse_row_ptr.offset, row_ptr, tile_idx, col_ptr, col_idx, Bs, Hs)
+    else:
+        _ROW_LISTS.pack_into(a, type(a).sparse_row_ptr.offset, row_ptr, tile_idx, Bs, Hs)
     other = _other_stream(stream, device)
     if other is not None:  # read there: after the lists are built, and not reused here before
         for t in held:
             t.record_stream(other)
-        other.wait_stream(current)
+        other.wait_stream(torch.cuda.current_stream())
     return held[0] if len(held) == 1 else held
 
 
@@ -612,8 +615,9 @@ def parallax_prefill(q, r, k, v, scale, causal=True, use_r=True, out=None, strea
         vbar = _result_maker(stream, torch.empty_like)(out)
         if vbar.stride() != out.stride():  # (out has gaps: the kernel writes vbar with out's strides)
             vbar = _result_maker(stream, torch.empty_strided)(out.shape, out.stride(), dtype=out.dtype, device=out.device)
-        row_stats = _result_maker(stream, torch.empty)(q.shape[:3] + (2,), dtype=torch.float32, device=q.device)
-        a.vbar, a.row_stats = vbar.data_ptr(), row_stats.data_ptr()
+        B, Hq, T, _ = q.shape
+        row_stats = _result_maker(stream, torch.empty)(B, Hq, T, 2, dtype=torch.float32, device=q.device)
+        _ROW_CACHE.pack_into(a, plx_prefill_args.vbar.offset, vbar.data_ptr(), row_stats.data_ptr())
     lib, where = load_library(), _stream_ptr(stream)
     split_bytes = lib.parallax_prefill_workspace_bytes(ctypes.byref(a))
     if split_bytes:  # few row blocks, many keys: split over key ranges
@@ -633,14 +637,17 @@ def parallax_prefill_backward_workspace_bytes(B, Hq, T) -> int:
 def prefill_bwd_args(q, r, k, v, o, vbar, row_stats, d_o, dq, dr, dk, dv, scale, causal, workspace, window=0):
     """Fill a plx_prefill_bwd_args: [B, H, T, d] tensors (views with any batch / head / row strides,
     last dimension contiguous); row_stats and the workspace dense."""
-    for t in (q, r, k, v, o, vbar, row_stats, d_o, dq, dr, dk, dv, workspace):
-        if not t.is_cuda or t.stride(-1) != 1:
-            raise ValueError("parallax_prefill_backward needs device tensors with a contiguous last dimension")
+    strides, ok = [], row_stats.is_cuda and workspace.is_cuda and row_stats.stride(-1) == workspace.stride(-1) == 1
+    for t in (q, r, k, v, o, vbar, d_o, dq, dr, dk, dv):
+        at = t.stride()
+        ok = ok and t.is_cuda and at[-1] == 1
+        strides += at[:3]
+    if not ok:
+        raise ValueError("parallax_prefill_backward needs device tensors with a contiguous last dimension")
     if not row_stats.is_contiguous() or not workspace.is_contiguous():
         raise ValueError("row_stats and the workspace must be contiguous")
     B, Hq, T, d = q.shape
     ptrs = [t.data_ptr() for t in (q, r, k, v, o, vbar, row_stats, d_o, dq, dr, dk, dv)]
-    strides = [x for t in (q, r, k, v, o, vbar, d_o, dq, dr, dk, dv) for x in t.stride()[:3]]
     return _filled(plx_prefill_bwd_args, *ptrs, B, Hq, k.shape[1], T, k.shape[2], d, _f32(scale), 1 if causal else 0,
                    _dtype_code(q), _i32(window), workspace.data_ptr(), _bytes(workspace), *strides, 0, 0, 0, 0, 0, 0)
 
