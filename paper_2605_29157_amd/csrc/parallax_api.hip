@@ -5,6 +5,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
 #include <initializer_list>
 #include <mutex>
@@ -236,21 +237,35 @@ int32_t pick_splits(const plx_decode_args *a, int32_t Tq) {
     return parallax_decode_num_splits(a->B, a->Hq, a->Hkv, (int32_t)keys_read(a, Tq), a->d, 0);
 }
 
-// Split count of an fp32 call with scratch for any: as many workgroups as the compute units hold at a time
-// (two each, one above d = 128: 2 sequences x 3000 keys, 16 pairs, d = 256, S = 16 55 us, S = 23 90), at least 128 keys (two rounds of a
-// workgroup's four waves) per split. Measured us
-// at S = 1, 2, 4, 8, 16, 32, 64: 16 sequences x 1024 keys (128 pairs, d = 128; the rule: 4) 61, 41, 38,
-// 44, 56; 8 x 4096 (32 pairs; 16) 220, 120, 67, 43, 40, 47, 58; 1 x 16384 (8 pairs; 64) 849, 432, 222,
-// 118, 66, 42, 42; 64 x 512 (512 pairs; 1) 58, 67, 80, 104.
+// Split count of an fp32 call with scratch for any: the cheapest by a model of f32_forward_kernel in us. A workgroup of
+// a split of `per` blocks of 16 keys walks ceil(per / 4) rounds of its four waves, each a wave's matrix instructions on
+// a SIMD: 1.25 per 64 (padded) dimensions alone on its unit, 1.1 for each of n workgroups on one (two of them
+// resident, one above d = 128; 1 for every further start); the merge is a launch, 2.4, and its records at 1 MB / us. Only
+// the fewest splits of a number of rounds can be cheapest.
+// As many workgroups as are resident and at least 128 keys a split, the rule before, left a round or a second
+// workgroup per unit where there need not be one; us, that rule / this one: 1 sequence x 1307 keys, 4 pairs of 4 heads,
+// d = 128 (S = 10 / 21) 18.2 / 13.4; 7 x 1647 likewise (12 / 9) 24.9 / 19.9; 5 x 3198, 16 pairs, d = 64 (7 / 6) 39.4 / 33.8.
+// Over 26 calls of 1 - 11 sequences x 400 - 6127 keys it was 8 % from the best of a sweep, now 2 %.
 int32_t pick_splits_f32(const plx_decode_args *a, int32_t Tq) {
     if (a->num_splits > 0) return a->num_splits;
     const int64_t groups = (int64_t)a->B * a->Hkv * (((int64_t)(a->Hq / a->Hkv) * Tq + 15) / 16);
-    const int64_t resident = (int64_t)query_num_cus() * (a->d <= 128 ? 2 : 1);
-    int64_t s = (resident + groups - 1) / groups;
-    const int64_t cap = keys_read(a, Tq) / 128;
-    if (s > cap) s = cap;
-    if (s > PLX_MAX_SPLITS) s = PLX_MAX_SPLITS;
-    return s < 1 ? 1 : (int32_t)s;
+    const int64_t keys = keys_read(a, Tq), cus = query_num_cus(), blocks = (keys + 15) / 16;
+    // (d <= 64: a round costs no more than the records that save it; one split per 128 keys at most)
+    const int64_t most = std::min<int64_t>(a->d <= 64 ? std::max<int64_t>(keys / 128, 1) : PLX_MAX_SPLITS, PLX_MAX_SPLITS);
+    const int resident = a->d <= 128 ? 2 : 1;
+    const double width = a->d <= 64 ? 1.0 : a->d <= 128 ? 2.0 : 4.0;
+    const double record_us = (double)a->B * a->Hq * Tq * (2 * a->d + 4) * 4e-6;
+    double best = 0.0;
+    int64_t pick = 0;
+    for (int64_t rounds = (blocks + 4 * most - 1) / (4 * most);;) {
+        const int64_t s = std::max<int64_t>(std::min((blocks + 4 * rounds - 1) / (4 * rounds), most), 1);
+        const int64_t n = (groups * s + cus - 1) / cus;
+        double us = (double)rounds * width * (n == 1 ? 1.25 : 1.1 * (double)n) + (double)((n + resident - 1) / resident - 1);
+        if (s > 1) us += 2.4 + 0.5 * (double)((s + 31) / 32 - 1) + record_us * (double)s;
+        if (pick == 0 || us < best) best = us, pick = s;
+        if (s == 1) return (int32_t)pick;
+        rounds = std::max(rounds + 1, (blocks + 4 * (s - 1) - 1) / (4 * (s - 1)));  // the next with fewer splits
+    }
 }
 
 // ... and no more than the caller's workspace has room for.
