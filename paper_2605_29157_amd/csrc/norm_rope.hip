@@ -42,7 +42,8 @@ struct Chunk<float> {
 // A wave that walked all 40 heads of a layer alone would compute sine and cosine of a (position, pair)
 // once, but is a chain of 10 dependent memory round trips: two trips a wave are faster at every size
 // (many positions are bound by memory, 4.9 - 5.4 TB/s), one where there are few positions.
-// q, rho [1,16,777,128] and k [1,8,777,128]: 11.2 -> 7.0 us; one row each, 10.3 -> 5.2 us; [4,..,4096,128] 66.
+// q, rho [1,16,777,128] and k [1,8,777,128]: 6.2 us, 6.9 with the powers taken here and sums by lane shuffles; one row
+// each 4.5 (5.2), [4,..,4096,128] 67 - 69 either way.
 template <typename T>
 __global__ __launch_bounds__(256) void norm_rope_kernel(NormRopeParams p) {
     constexpr int E = Chunk<T>::E;
@@ -93,10 +94,11 @@ __global__ __launch_bounds__(256) void norm_rope_kernel(NormRopeParams p) {
             cs[j] = v[0], sn[j] = v[1], cs[j + 1] = v[2], sn[j + 1] = v[3];
         }
     } else {
-        // theta^(-dim/d) for this lane's first pair, then pair by pair times theta^(-2/d) (both in double
-        // precision: at most three roundings more than a power per pair, 4e-16 of the angle)
+        // theta^(-dim/d) for this lane's first pair (from the host: a power in double precision per lane took 0.5 us of
+        // a small launch), then pair by pair times theta^(-2/d) (at most four roundings more than a power per pair,
+        // 5e-16 of the angle)
         const double pos = (double)((p.pos0 ? p.pos0[b] : 0) + ld_t);
-        double freq = exp2(-(double)(lr * E) / (double)p.d * p.log2_theta);
+        double freq = p.freq[lr];
 #pragma unroll
         for (int j = 0; j < E / 2; ++j) {
             double ang = pos * freq;
@@ -113,7 +115,12 @@ __global__ __launch_bounds__(256) void norm_rope_kernel(NormRopeParams p) {
             float ss = 0.f;
 #pragma unroll
             for (int e = 0; e < E; ++e) ss = fmaf(c[u].get(e), c[u].get(e), ss);
-            for (int off = 1; off < lpr; off <<= 1) ss += __shfl_xor(ss, off, 64);
+            if (lpr == 16)  // (uniform; the same sums in the same order, without a trip through the LDS)
+                ss = lane_group_sum<16>(ss);
+            else if (lpr == 8)
+                ss = lane_group_sum<8>(ss);
+            else
+                for (int off = 1; off < lpr; off <<= 1) ss += __shfl_xor(ss, off, 64);
             const float rinv = 1.0f / sqrtf(ss * inv_d + p.eps);
 #pragma unroll
             for (int j = 0; j < E / 2; ++j) {
@@ -178,8 +185,14 @@ hipError_t launch_norm_rope(const NormRopeParams &p_in, bool f32, hipStream_t st
     if (chunks > trips) chunks = trips;
     p.trips_per_wave = (trips + (int)chunks - 1) / (int)chunks;
     p.trip_chunks = (trips + p.trips_per_wave - 1) / p.trips_per_wave;
-    p.log2_theta = std::log2((double)p.theta);
-    p.pair_ratio = std::exp2(-2.0 / (double)p.d * p.log2_theta);
+    const double log2_theta = std::log2((double)p.theta);
+    p.pair_ratio = std::exp2(-2.0 / (double)p.d * log2_theta);
+    double step[4] = {1.0};  // (every fourth lane by a power, one rounding more in between: six powers a call, not sixteen)
+    for (int i = 1; i < 4; ++i) step[i] = std::exp2(-(double)(i * elems) / (double)p.d * log2_theta);
+    for (int i = 0; i < p.d / elems; i += 4) {
+        const double first = i == 0 ? 1.0 : std::exp2(-(double)(i * elems) / (double)p.d * log2_theta);
+        for (int k = 0; k < 4; ++k) p.freq[i + k] = first * step[k];
+    }
     const int64_t waves = groups * p.trip_chunks;
     const int64_t blocks = (waves + 3) / 4;
     if (blocks <= 0 || blocks > 0x7fffffffLL) return hipErrorInvalidValue;

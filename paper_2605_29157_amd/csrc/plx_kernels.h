@@ -132,7 +132,7 @@ struct NormRopeParams {
     const float *table;   // optional (cos, sin) per (position, pair); NULL = evaluate in the kernel
     int32_t n_pos;        // positions in the table
     int32_t trips_per_wave, trip_chunks;  // set by the launcher, like
-    double log2_theta, pair_ratio;        // ... log2(theta) and theta^(-2/d)
+    double pair_ratio, freq[64];          // ... theta^(-2/d), and theta^(-dim/d) of the first pair of every lane of a row
 };
 
 // Each returns hipSuccess or the launch error. No allocation, no synchronisation.
