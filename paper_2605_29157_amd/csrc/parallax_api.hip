@@ -520,7 +520,7 @@ int32_t parallax_decode_mla_num_splits(int32_t B, int32_t Hq, int32_t Lmax, int3
     // tile's chain of phases) when W < num_cus workgroups share the memory; merging splits costs
     // one more launch (about 6 us). The split count is the one with the smallest
     //     (rounds - 1) * (tiles * 3.2 + 10) + (tiles * max(2.4, 3.2 * W_last / num_cus) + 10) + (S > 1 ? 6 : 0)
-    // with at least 256 keys per split, or 128 as long as there are few splits to merge (32; 12 of the
+    // with at least 256 keys per split (rounded to tiles), or 128 as long as there are few splits to merge (32; 12 of the
     // 32-column kernel, whose records are eight times the bytes at 128 heads). 16 heads, 1 x 4096 tokens: 16 splits
     // 22.9 us, 32 19.9; 1 x 2000: 7 22.3, 15 17.8; 16 x 1500: 5 25.9, 11 21.2; 128 heads, 1 x 1000: 4 24.6,
     // 8 21.8, but 1 x 4000: 15 25.0, 16 26.7, 31 28.1. Against sweeps of S on MI355X (model / measured us):
@@ -535,8 +535,15 @@ int32_t parallax_decode_mla_num_splits(int32_t B, int32_t Hq, int32_t Lmax, int3
     const int64_t pairs = (int64_t)B * (wide ? (Hq + 31) / 32 : 1);
     const int64_t n_tiles = ((int64_t)Lmax + 63) / 64;
     const int64_t few = wide ? 12 : 32;
-    int64_t cap = n_tiles >= 8 ? n_tiles / 4 : 1;
-    if (n_tiles >= 8 && cap < few) cap = n_tiles / 2 < few ? n_tiles / 2 : few;
+    int64_t cap = n_tiles >= 8 ? (n_tiles + 3) / 4 : 1;
+    if (n_tiles >= 8 && cap < few) cap = std::min((n_tiles + 1) / 2, few);
+    // (rounded up: 47 tiles in 23 splits are three a workgroup, in 24 two; 8 heads, 1 x 3005: 20.1 -> 17.9 us, 16 heads, 6 x 1171:
+    // 9 20.4, 10 18.2.) Up to 1024 tokens down to a tile per split where that is one round and little to merge: 8 heads,
+    // 2 x 781: 6 18.3, 13 14.8; 16 heads, 14 x 277: 1 20.6, 5 16.3; 25 x 313: 1 20.8, 5 18.4; 32 heads, 2 x 388: 1 20.4, 7
+    // 16.6; but 128 heads, 2 rows each, 2 x 200: 1 16.5, 4 20.1, 32 heads, 23 x 799: 6 26.6, 10 27.4.
+    if (n_tiles >= (wide ? 6 : 4) && n_tiles <= 16 && pairs * n_tiles <= num_cus &&
+        (int64_t)B * Hq * n_tiles <= (wide ? 512 : 2048))
+        cap = n_tiles;
     if (cap > PLX_MAX_SPLITS) cap = PLX_MAX_SPLITS;
     auto cost_of = [&](int64_t s) {
         const int64_t rounds = (pairs * s + num_cus - 1) / num_cus;
