@@ -510,7 +510,10 @@ size_t parallax_decode_mla_workspace_bytes(int32_t B, int32_t Hq) {
     return (size_t)B * Hq * PLX_MAX_SPLITS * (2 * 512 + 4) * sizeof(float);
 }
 
-int32_t parallax_decode_mla_num_splits(int32_t B, int32_t Hq, int32_t Lmax, int32_t num_cus) {
+namespace {
+// Split count of a latent-cache call. `small_splits` false: at least 256 (128) whole keys a split, as calls had it that
+// bring no workspace because they ran unsplit, or one of so many records.
+int32_t mla_splits(int32_t B, int32_t Hq, int32_t Lmax, int32_t num_cus, bool small_splits) {
     if (B <= 0 || Hq <= 0 || Lmax <= 0) return 1;
     if (num_cus <= 0) num_cus = query_num_cus();
     // One workgroup per compute unit is resident (tile, q / rho fragments and the two register
@@ -535,13 +538,14 @@ int32_t parallax_decode_mla_num_splits(int32_t B, int32_t Hq, int32_t Lmax, int3
     const int64_t pairs = (int64_t)B * (wide ? (Hq + 31) / 32 : 1);
     const int64_t n_tiles = ((int64_t)Lmax + 63) / 64;
     const int64_t few = wide ? 12 : 32;
-    int64_t cap = n_tiles >= 8 ? (n_tiles + 3) / 4 : 1;
-    if (n_tiles >= 8 && cap < few) cap = std::min((n_tiles + 1) / 2, few);
+    const int64_t up = small_splits ? 1 : 0;
+    int64_t cap = n_tiles >= 8 ? (n_tiles + 3 * up) / 4 : 1;
+    if (n_tiles >= 8 && cap < few) cap = std::min((n_tiles + up) / 2, few);
     // (rounded up: 47 tiles in 23 splits are three a workgroup, in 24 two; 8 heads, 1 x 3005: 20.1 -> 17.9 us, 16 heads, 6 x 1171:
     // 9 20.4, 10 18.2.) Up to 1024 tokens down to a tile per split where that is one round and little to merge: 8 heads,
     // 2 x 781: 6 18.3, 13 14.8; 16 heads, 14 x 277: 1 20.6, 5 16.3; 25 x 313: 1 20.8, 5 18.4; 32 heads, 2 x 388: 1 20.4, 7
     // 16.6; but 128 heads, 2 rows each, 2 x 200: 1 16.5, 4 20.1, 32 heads, 23 x 799: 6 26.6, 10 27.4.
-    if (n_tiles >= (wide ? 6 : 4) && n_tiles <= 16 && pairs * n_tiles <= num_cus &&
+    if (small_splits && n_tiles >= (wide ? 6 : 4) && n_tiles <= 16 && pairs * n_tiles <= num_cus &&
         (int64_t)B * Hq * n_tiles <= (wide ? 512 : 2048))
         cap = n_tiles;
     if (cap > PLX_MAX_SPLITS) cap = PLX_MAX_SPLITS;
@@ -563,6 +567,11 @@ int32_t parallax_decode_mla_num_splits(int32_t B, int32_t Hq, int32_t Lmax, int3
     for (int64_t s = best + 1; s <= cap && (pairs * s + num_cus - 1) / num_cus == best_rounds; ++s)
         if (cost_of(s) <= limit) best = s;
     return (int32_t)best;
+}
+}  // namespace
+
+int32_t parallax_decode_mla_num_splits(int32_t B, int32_t Hq, int32_t Lmax, int32_t num_cus) {
+    return mla_splits(B, Hq, Lmax, num_cus, true);
 }
 
 plx_status parallax_decode_mla(const plx_decode_mla_args *a, void *hip_stream) {
@@ -600,12 +609,18 @@ plx_status parallax_decode_mla(const plx_decode_mla_args *a, void *hip_stream) {
         p.page_size = a->page_size, p.table_stride = a->block_table_stride, p.num_pages = a->num_pages;
     }
     int32_t S = a->num_splits;
-    if (S == 0) S = parallax_decode_mla_num_splits(a->B, (int32_t)n_cols, a->Lmax, 0);
+    auto has_room = [&](int32_t splits) {
+        return a->workspace && aligned16(a->workspace) &&
+               a->workspace_bytes >= (size_t)a->B * n_cols * splits * (2 * 512 + 4) * sizeof(float);
+    };
+    if (S == 0) {
+        S = mla_splits(a->B, (int32_t)n_cols, a->Lmax, 0, true);
+        if (S > 1 && !has_room(S)) S = mla_splits(a->B, (int32_t)n_cols, a->Lmax, 0, false);
+    }
     p.S = S;
     p.direct_out = S == 1;
     if (S > 1) {
-        if (!a->workspace || !aligned16(a->workspace)) return PLX_ERR_WORKSPACE;
-        if (a->workspace_bytes < (size_t)a->B * n_cols * S * (2 * 512 + 4) * sizeof(float)) return PLX_ERR_WORKSPACE;
+        if (!has_room(S)) return PLX_ERR_WORKSPACE;
         p.ws = static_cast<float *>(a->workspace);
     }
     return plx::launch_decode_mla(p, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? PLX_OK

@@ -380,3 +380,22 @@ def test_many_heads_and_rows_at_the_benchmark_launches(plx, synth, mla):
         ref2 += float((one ** 2).sum())
         assert np.linalg.norm(out[0, h, t] - one) <= 4e-2 * np.linalg.norm(one), (h, t)
     assert (err2 / ref2) ** 0.5 <= BF16_REL_L2
+
+
+@pytest.mark.parametrize("B,Hq,L,before", [(1, 32, 400, 1), (14, 16, 277, 1), (4, 16, 900, 7), (1, 8, 3005, 23)])
+def test_a_workspace_for_fewer_splits_is_taken_as_it_was(B, Hq, L, before):
+    """A call of no given count whose workspace holds the records of 256 (128) whole keys a split, or none where those are one
+    split, runs with that count, bit for bit; one record less is refused."""
+    from paper_2605_29157_amd import binding as plx
+
+    gen = torch.Generator(device="cuda").manual_seed(L)
+    q, r = (torch.randn(B, Hq, 576, generator=gen, device="cuda", dtype=torch.bfloat16) for _ in range(2))
+    ckv = torch.randn(B, L, 576, generator=gen, device="cuda", dtype=torch.bfloat16)
+    assert plx.parallax_decode_mla_num_splits(B, Hq, L) > before
+    record = B * Hq * (2 * 512 + 4)
+    few = torch.empty(max(record * before, 4) if before > 1 else 4, dtype=torch.float32, device="cuda")
+    got = plx.parallax_decode_mla(q, r, ckv, 0.04, workspace=few)
+    assert torch.equal(got, plx.parallax_decode_mla(q, r, ckv, 0.04, num_splits=before))
+    if before > 1:
+        with pytest.raises(plx.ParallaxError):
+            plx.parallax_decode_mla(q, r, ckv, 0.04, workspace=few[:-4])
