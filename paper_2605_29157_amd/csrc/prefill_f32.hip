@@ -29,8 +29,13 @@
 // every accumulator it reaches (also from a key that no column sees: 0 * NaN). A workgroup that ends with
 // an accumulator that is not finite walks its tiles again with care: scores of operands that are not
 // finite on the fp32 instruction, such values zero in the output operand, and what they do to the columns
-// that see them added as sums of products that overflow. If none of the accumulators of an output reaches 2^-100 it takes the fp32
-// instruction for everything, too: the last thirds of values below 2^-109 are lost.
+// that see them added as sums of products that overflow.
+// Small values: the last thirds of what is below 2^-110 are lost (bf16 ends at 2^-133). A workgroup that cut such a
+// value of q, rho, k, v or dO, whatever it is multiplied with, walks again with every product on the fp32 instruction;
+// so does one with a column whose largest gradient weight is that small. Softmax weights are not looked at (the
+// largest of a column is 1, and a small one loses 2^-134 at most). Looking is half an instruction a value (exact zeros,
+// which hide others from the minimum, two). Forward / backward of 8 x 8 x 512, us: 40.0 / 102 without it, 40.4 / 107 with it,
+// 41.6 / 109 where a tenth of the values and every fifth row are zeros, 40.2 / 200 where every head has a row of dO at 1e-36.
 #include "plx_f32.h"
 
 namespace plx {
@@ -45,7 +50,7 @@ struct Thirds {
 };
 
 // Eight fp32 values in thirds. The first is cut off (a finite value stays finite), the others rounded:
-// what is left of 24 bits fits the third one exactly.
+// what is left of 24 bits fits the third one exactly (from kThirdsExact on).
 __device__ __forceinline__ Thirds f32_cut(const f32x4 &lo, const f32x4 &hi) {
     Thirds t;
 #pragma unroll
@@ -87,6 +92,23 @@ __device__ __forceinline__ void add_thirds(const Thirds *const (&a)[N], const Th
     for (int i = 0; i < N; ++i) *acc[i] += t[i];
 }
 
+// The smallest magnitude whose thirds hold it exactly, its last bit being no less than the smallest bf16, 2^-133; zero is
+// exact too. The minimum is NaN where a value is.
+constexpr float kThirdsExact = 0x1p-110f;
+__device__ __forceinline__ float smallest(float low, const f32x4 &a, const f32x4 &b) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) low = __builtin_elementwise_minimum(__builtin_elementwise_minimum(low, fabsf(a[i])), fabsf(b[i]));
+    return low;
+}
+// (without sign, less one: a zero is the largest)
+__device__ __forceinline__ uint32_t size_or_most(float x) { return 2 * __builtin_bit_cast(uint32_t, x) - 1; }
+__device__ __forceinline__ bool any_lost(const f32x4 &a, const f32x4 &b) {
+    uint32_t low = 0xffffffffu;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) low = min(low, min(size_or_most(a[i]), size_or_most(b[i])));
+    return low < size_or_most(kThirdsExact);
+}
+
 __device__ __forceinline__ bool finite4(const f32x4 &x) {
     return fmaf(x[0], 0.f, fmaf(x[1], 0.f, fmaf(x[2], 0.f, x[3] * 0.f))) == 0.f;
 }
@@ -108,6 +130,16 @@ __device__ __forceinline__ bool part_finite(const RowPart &a) {
 #pragma unroll
     for (int j = 0; j < DP / 32; ++j) ok &= finite4(a.x[j][0]) && finite4(a.x[j][1]);
     return ok;
+}
+__device__ __forceinline__ bool part_lost(const RowPart &a) {
+    float low = kThirdsExact;
+#pragma unroll
+    for (int j = 0; j < DP / 32; ++j) low = smallest(low, a.x[j][0], a.x[j][1]);
+    if (!__any(!(low >= kThirdsExact))) return false;
+    bool lost = false;
+#pragma unroll
+    for (int j = 0; j < DP / 32; ++j) lost |= any_lost(a.x[j][0], a.x[j][1]);
+    return lost;
 }
 struct CutPart {
     Thirds x[DP / 32];
@@ -160,10 +192,20 @@ __device__ __forceinline__ void stage(Staged &st, int tid, RowOf row_of) {
         st.x[i][0] = *(const f32x4 *)(at + dim), st.x[i][1] = *(const f32x4 *)(at + dim + 4);
     }
 }
-// Returns whether the thread met a value that is not finite; with care such values become zeros.
+// Returns whether the thread met a value that its thirds do not hold; with care one that is not finite, and such values
+// become zeros.
 template <bool CARE>
 __device__ __forceinline__ bool put(Staged &st, CutTile &tile, int tid) {
     bool odd = false;
+    if constexpr (!CARE) {
+        float low = kThirdsExact;
+#pragma unroll
+        for (int i = 0; i < Staged::kChunks; ++i) low = smallest(low, st.x[i][0], st.x[i][1]);
+        if (__builtin_expect(__any(!(low >= kThirdsExact)), 0)) {
+#pragma unroll
+            for (int i = 0; i < Staged::kChunks; ++i) odd |= any_lost(st.x[i][0], st.x[i][1]);
+        }
+    }
 #pragma unroll
     for (int i = 0; i < Staged::kChunks; ++i) {
         const int e = tid + i * kF32Threads, row = e / (DP / 8), chunk = e % (DP / 8);
@@ -239,21 +281,45 @@ __device__ __forceinline__ void add_products_f32(f32x4 (&acc)[NA], const f32x4 (
 }
 __device__ __forceinline__ bool wave_finite(const f32x4 (&w)[2]) { return __all(finite4(w[0]) && finite4(w[1])); }
 
-// What a wave's accumulators say about its walk: 1 = one of them is not finite, 2 = none of a set reaches 2^-100 (and not all are
-// zero): thirds of such operands fall under the smallest bf16.
-enum { kFine = 0, kNotFinite = 1, kTiny = 2 };
-__device__ __forceinline__ int verdict(const f32x4 (&a)[NA], const f32x4 (&b)[NA], float more) {
-    float chk = more * 0.f, size_a = 0.f, size_b = 0.f;
+// What a walk leaves to be said about it: an accumulator that is not finite, or operands that their thirds do not hold
+enum { kNotFinite = 1, kLost = 2 };
+__device__ __forceinline__ int verdict(const f32x4 (&a)[NA], const f32x4 (&b)[NA], float more, bool lost) {
+    float chk = more * 0.f;
 #pragma unroll
     for (int n = 0; n < NA; ++n)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            chk = fmaf(a[n][i], 0.f, fmaf(b[n][i], 0.f, chk));
-            size_a = fmaxf(size_a, fabsf(a[n][i])), size_b = fmaxf(size_b, fabsf(b[n][i]));
-        }
-    if (__any(!(chk == 0.f))) return kNotFinite;
-    auto tiny = [](float size) { return __any(size > 0.f) && !__any(size >= 0x1p-100f); };
-    return tiny(size_a) || tiny(size_b) ? kTiny : kFine;
+        for (int i = 0; i < 4; ++i) chk = fmaf(a[n][i], 0.f, fmaf(b[n][i], 0.f, chk));
+    return (__any(!(chk == 0.f)) ? kNotFinite : 0) | (__any(lost) ? kLost : 0);
+}
+
+// Sizes of the weights of an output, one after another: the bits of their first thirds on top of each other. An exponent
+// of 16 or more, 2^-111, leaves a bit above the lowest four that no smaller ones make together.
+struct WeightSizes {
+    uint32_t bits = 0;
+    __device__ __forceinline__ void add(const Thirds &w) {
+        bits |= w.x[0][0] | w.x[0][1];
+        bits |= w.x[0][2] | w.x[0][3];
+    }
+    // bit c: column c has weights that are not zero; bit 16 + c: a large one
+    __device__ __forceinline__ unsigned columns() const {
+        auto fold = [](unsigned long long lanes) {
+            const unsigned x = (unsigned)lanes | (unsigned)(lanes >> 32);
+            return (x | x >> 16) & 0xffffu;
+        };
+        return fold(__ballot((bits & 0x7fff7fffu) != 0)) | fold(__ballot((bits & 0x78007800u) != 0)) << 16;
+    }
+};
+// kLost if a column has weights, all of them small, over the waves that share it
+__device__ __forceinline__ int small_columns(const unsigned (&sizes)[kF32Waves]) {
+    int said = 0;
+#pragma unroll
+    for (int cg = 0; cg < CG; ++cg) {
+        unsigned x = 0;
+#pragma unroll
+        for (int kg = 0; kg < KG; ++kg) x |= sizes[kg * CG + cg];
+        if (x & 0xffffu & ~(x >> 16)) said = kLost;
+    }
+    return said;
 }
 
 // The two halves of the keys (waves CG .. 2 CG - 1 hand theirs to waves 0 .. CG - 1)
@@ -312,9 +378,16 @@ __global__ __launch_bounds__(kF32Threads, 2) void f32_prefill_kernel(PrefillPara
         stage(vs, tid, [&](int i, int row) { return v_row(32 * (first + i) + row); });
     };
     if (lo < hi) load(lo);
-    const CutPart q = cut_part(load_part(qcol, g));
-    CutPart rho;
-    if constexpr (USE_R) rho = cut_part(load_part(rcol, g));
+    CutPart q, rho;
+    bool lost;  // a value that its thirds do not hold
+    {
+        const RowPart x = load_part(qcol, g);
+        lost = part_lost(x), q = cut_part(x);
+    }
+    if constexpr (USE_R) {
+        const RowPart x = load_part(rcol, g);
+        lost |= part_lost(x), rho = cut_part(x);
+    }
 
     const float scale_log2 = p.scale * kLog2e;
     float m_run, d1, d2;  // the sums over this lane's keys only
@@ -340,7 +413,7 @@ __global__ __launch_bounds__(kF32Threads, 2) void f32_prefill_kernel(PrefillPara
                 odd_k = put<true>(ks, lds.tile[0], tid), odd_v = put<true>(vs, lds.tile[1], tid);
                 odd_k = __syncthreads_or(odd_k), odd_v = __syncthreads_or(odd_v);
             } else {
-                put<false>(ks, lds.tile[0], tid), put<false>(vs, lds.tile[1], tid);
+                lost |= put<false>(ks, lds.tile[0], tid), lost |= put<false>(vs, lds.tile[1], tid);
                 __syncthreads();
                 if (first + KG < hi) load(first + KG);
             }
@@ -424,14 +497,14 @@ __global__ __launch_bounds__(kF32Threads, 2) void f32_prefill_kernel(PrefillPara
             }
         }
         d1 = rows_sum(d1), d2 = rows_sum(d2);
-        const int said = verdict(o1, o2, d1 + d2);
+        const int said = verdict(o1, o2, d1 + d2, lost);
         if (lane == 0) odd[w] = said;
         if (g == 0) sm[0][w][c] = m_run, sm[1][w][c] = d1, sm[2][w][c] = d2;
     };
     walk(std::false_type{});
     __syncthreads();
     if (const int said = odd[0] | odd[1] | odd[2] | odd[3]) {
-        all_f32 = said & kTiny;
+        all_f32 = said & kLost;
         __syncthreads();
         walk(std::true_type{});
         __syncthreads();
@@ -482,6 +555,7 @@ __global__ __launch_bounds__(kF32Threads, 2) void f32_prefill_kernel(PrefillPara
 __global__ __launch_bounds__(kF32Threads, 2) void f32_prefill_rows_kernel(PrefillBwdParams p) {
     __shared__ Lds<2> lds;  // k, v
     __shared__ int odd[kF32Waves];
+    __shared__ unsigned sizes[2][kF32Waves];
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int c = lane & 15, g = lane >> 4, cg = w % CG, kg = w / CG, off = p.Tk - p.T;
     const int n_blocks = (p.T + COLS - 1) / COLS;
@@ -510,15 +584,23 @@ __global__ __launch_bounds__(kF32Threads, 2) void f32_prefill_rows_kernel(Prefil
     if (lo < hi) load(lo);
     float lse, ubar, tau, beta;
     CutPart q, rho, up;
+    bool lost;
     {
         const RowPart x = load_part(gcol, g);
+        lost = part_lost(x);
         tau = column_dot(x, load_part((const float *)p.o + row * DP, g));
         beta = column_dot(x, load_part((const float *)p.vbar + row * DP, g));
         lse = p.row_stats[2 * row], ubar = p.row_stats[2 * row + 1];
         if (kg == 0 && g == 0 && t0 + 16 * cg + c <= t1) ((f32x4 *)p.row_cache)[row] = f32x4{lse, ubar, tau, beta};
         up = cut_part(x);
-        q = cut_part(load_part(qcol, g));
-        rho = cut_part(load_part(rcol, g));
+    }
+    {
+        const RowPart x = load_part(qcol, g);
+        lost |= part_lost(x), q = cut_part(x);
+    }
+    {
+        const RowPart x = load_part(rcol, g);
+        lost |= part_lost(x), rho = cut_part(x);
     }
     f32x4 dq[NA], dr[NA];
     const float scale_log2 = p.scale * kLog2e;
@@ -527,6 +609,7 @@ __global__ __launch_bounds__(kF32Threads, 2) void f32_prefill_rows_kernel(Prefil
         constexpr bool CARE = decltype(with_care)::value;
 #pragma unroll
         for (int n = 0; n < NA; ++n) dq[n] = dr[n] = f32x4{0.f, 0.f, 0.f, 0.f};
+        WeightSizes size1, size2;
         bool odd_cols = false;
         if constexpr (CARE) {
             odd_cols = !part_finite(load_part(qcol, g)) || !part_finite(load_part(rcol, g)) ||
@@ -541,7 +624,7 @@ __global__ __launch_bounds__(kF32Threads, 2) void f32_prefill_rows_kernel(Prefil
                 odd_k = put<true>(ks, lds.tile[0], tid), odd_v = put<true>(vs, lds.tile[1], tid);
                 odd_k = __syncthreads_or(odd_k), odd_v = __syncthreads_or(odd_v);
             } else {
-                put<false>(ks, lds.tile[0], tid), put<false>(vs, lds.tile[1], tid);
+                lost |= put<false>(ks, lds.tile[0], tid), lost |= put<false>(vs, lds.tile[1], tid);
                 __syncthreads();
                 if (first + KG < hi) load(first + KG);
             }
@@ -597,19 +680,21 @@ __global__ __launch_bounds__(kF32Threads, 2) void f32_prefill_rows_kernel(Prefil
                     continue;
                 }
             const Thirds w1 = f32_cut(g1[0], g1[1]), w2 = f32_cut(g2[0], g2[1]);
+            if constexpr (!CARE) size1.add(w1), size2.add(w2);
 #pragma unroll
             for (int n = 0; n < NA; n += 2) {
                 const Thirds x0 = transposed(lds.tile[0], 32 * kg, n, c, g), x1 = transposed(lds.tile[0], 32 * kg, n + 1, c, g);
                 add_thirds<4>({&x0, &x0, &x1, &x1}, {&w1, &w2, &w1, &w2}, {&dq[n], &dr[n], &dq[n + 1], &dr[n + 1]});
             }
         }
-        const int said = verdict(dq, dr, 0.f);
-        if (lane == 0) odd[w] = said;
+        const int said = verdict(dq, dr, 0.f, lost);
+        const unsigned columns[2] = {size1.columns(), size2.columns()};
+        if (lane == 0) odd[w] = said, sizes[0][w] = columns[0], sizes[1][w] = columns[1];
     };
     walk(std::false_type{});
     __syncthreads();
-    if (const int said = odd[0] | odd[1] | odd[2] | odd[3]) {
-        all_f32 = said & kTiny;
+    if (const int said = odd[0] | odd[1] | odd[2] | odd[3] | small_columns(sizes[0]) | small_columns(sizes[1])) {
+        all_f32 = said & kLost;
         __syncthreads();
         walk(std::true_type{});
     }
@@ -627,6 +712,7 @@ __global__ __launch_bounds__(kF32Threads, 2) void f32_prefill_rows_kernel(Prefil
 __global__ __launch_bounds__(kF32Threads, 2) void f32_prefill_cols_kernel(PrefillBwdParams p) {
     __shared__ Lds<3> lds;  // q, rho, dO
     __shared__ int odd[kF32Waves];
+    __shared__ unsigned sizes[3][kF32Waves];
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int c = lane & 15, g = lane >> 4, cg = w % CG, kg = w / CG, off = p.Tk - p.T;
     const int n_blocks = (p.Tk + COLS - 1) / COLS;
@@ -659,7 +745,16 @@ __global__ __launch_bounds__(kF32Threads, 2) void f32_prefill_cols_kernel(Prefil
         stage(xg, tid, [&](int i, int r) { return row_of(p.d_o, first + i, r); });
     };
     if (n_items > 0) load(0);
-    const CutPart kk = cut_part(load_part(kcol, g)), vv = cut_part(load_part(vcol, g));
+    CutPart kk, vv;
+    bool lost;
+    {
+        const RowPart x = load_part(kcol, g);
+        lost = part_lost(x), kk = cut_part(x);
+    }
+    {
+        const RowPart x = load_part(vcol, g);
+        lost |= part_lost(x), vv = cut_part(x);
+    }
     f32x4 dk[NA], dv[NA];
     const float scale_log2 = p.scale * kLog2e;
     bool all_f32 = false;  // with care: every product on the fp32 instruction
@@ -667,6 +762,7 @@ __global__ __launch_bounds__(kF32Threads, 2) void f32_prefill_cols_kernel(Prefil
         constexpr bool CARE = decltype(with_care)::value;
 #pragma unroll
         for (int n = 0; n < NA; ++n) dk[n] = dv[n] = f32x4{0.f, 0.f, 0.f, 0.f};
+        WeightSizes size_w, size1, size2;
         bool odd_cols = false;
         if constexpr (CARE) {
             odd_cols = !part_finite(load_part(kcol, g)) || !part_finite(load_part(vcol, g));
@@ -681,7 +777,8 @@ __global__ __launch_bounds__(kF32Threads, 2) void f32_prefill_cols_kernel(Prefil
                 odd_g = put<true>(xg, lds.tile[2], tid);
                 odd_q = __syncthreads_or(odd_q), odd_r = __syncthreads_or(odd_r), odd_g = __syncthreads_or(odd_g);
             } else {
-                put<false>(xq, lds.tile[0], tid), put<false>(xr, lds.tile[1], tid), put<false>(xg, lds.tile[2], tid);
+                lost |= put<false>(xq, lds.tile[0], tid), lost |= put<false>(xr, lds.tile[1], tid);
+                lost |= put<false>(xg, lds.tile[2], tid);
                 __syncthreads();
                 if (first + KG < n_items) load(first + KG);
             }
@@ -733,7 +830,7 @@ __global__ __launch_bounds__(kF32Threads, 2) void f32_prefill_cols_kernel(Prefil
                         if (!(i >= my_lo && i < my_end)) wt[s][r] = g1[s][r] = g2[s][r] = 0.f, seen &= ~(1u << (4 * s + r));
                     }
                 }
-            auto add = [&](int tensor, const void *base, int is_odd, const f32x4(&weights)[2], f32x4(&acc)[NA]) {
+            auto add = [&](int tensor, const void *base, int is_odd, const f32x4(&weights)[2], WeightSizes &sizes_of, f32x4(&acc)[NA]) {
                 if constexpr (CARE) {
                     auto at = [&](int s, int r) { return row_of(base, item, 16 * s + 4 * g + r); };
                     if (is_odd) add_not_finite(acc, weights, seen, c, at);
@@ -743,6 +840,7 @@ __global__ __launch_bounds__(kF32Threads, 2) void f32_prefill_cols_kernel(Prefil
                     }
                 }
                 const Thirds y = f32_cut(weights[0], weights[1]);
+                if constexpr (!CARE) sizes_of.add(y);
 #pragma unroll
                 for (int n = 0; n < NA; n += 4) {
                     Thirds x[4];
@@ -751,17 +849,19 @@ __global__ __launch_bounds__(kF32Threads, 2) void f32_prefill_cols_kernel(Prefil
                     add_thirds<4>({&x[0], &x[1], &x[2], &x[3]}, {&y, &y, &y, &y}, {&acc[n], &acc[n + 1], &acc[n + 2], &acc[n + 3]});
                 }
             };
-            add(0, p.q, odd_q, g1, dk);
-            add(1, p.r, odd_r, g2, dk);
-            add(2, p.d_o, odd_g, wt, dv);
+            add(0, p.q, odd_q, g1, size1, dk);
+            add(1, p.r, odd_r, g2, size2, dk);
+            add(2, p.d_o, odd_g, wt, size_w, dv);
         }
-        const int said = verdict(dk, dv, 0.f);
-        if (lane == 0) odd[w] = said;
+        const int said = verdict(dk, dv, 0.f, lost);
+        const unsigned columns[3] = {size1.columns(), size2.columns(), size_w.columns()};
+        if (lane == 0) odd[w] = said, sizes[0][w] = columns[0], sizes[1][w] = columns[1], sizes[2][w] = columns[2];
     };
     walk(std::false_type{});
     __syncthreads();
-    if (const int said = odd[0] | odd[1] | odd[2] | odd[3]) {
-        all_f32 = said & kTiny;
+    if (const int said = odd[0] | odd[1] | odd[2] | odd[3] | small_columns(sizes[0]) | small_columns(sizes[1]) |
+                         small_columns(sizes[2])) {
+        all_f32 = said & kLost;
         __syncthreads();
         walk(std::true_type{});
     }

@@ -95,6 +95,59 @@ def test_small_and_large_values(plx, scales):
         assert rel_l2(a / size, b / size) <= 2 * REL, name
 
 
+def _times(x, factor, *names):
+    for n in names:
+        x[n] *= factor
+
+
+# What is scaled by tiny and huge factors, and which parts of which results are looked at (those that do not underflow).
+# Thirds end at 2^-133 = 1e-40: a value at 1e-36 keeps 13 to 16 of its 24 bits in them.
+SMALL_BESIDE_LARGE = {
+    "scores of tiny rows and huge keys": (lambda x: (_times(x, 1e-36, "q", "r"), _times(x, 1e36, "k")), [("o",), ("dq",), ("dr",), ("dk",), ("dv",)]),
+    "scores of huge rows and tiny keys": (lambda x: (_times(x, 1e36, "q", "r"), _times(x, 1e-36, "k")), [("o",), ("dq",), ("dr",), ("dk",), ("dv",)]),
+    "a tiny probe alone": (lambda x: (_times(x, 1e-37, "r"), _times(x, 1e15, "k"), _times(x, 1e-15, "q")), [("o",), ("dq",), ("dr",), ("dk",), ("dv",)]),
+    "tiny upstream, huge values": (lambda x: (_times(x, 1e-36, "g"), _times(x, 1e36, "v")), [("o",), ("dq",), ("dr",), ("dk",)]),
+    "huge upstream, tiny values": (lambda x: (_times(x, 1e36, "g"), _times(x, 1e-36, "v")), [("dq",), ("dr",), ("dk",), ("dv",)]),
+    "one tiny column of v": (lambda x: x["v"][..., 5].mul_(1e-36), [("o",), ("o", Ellipsis, 5), ("dq",), ("dv",)]),
+    "one tiny row of dO": (lambda x: x["g"][:, :, 70].mul_(1e-36), [("dq",), ("dq", 70), ("dr", 70), ("dk",), ("dv",)]),
+    "a tiny row of q, a huge dimension of k": (lambda x: (x["q"][..., 3].mul_(1e-36), x["q"][:, :, 70, :3].zero_(), x["q"][:, :, 70, 4:].zero_(),
+                                                         x["r"][..., 3].mul_(1e-36), x["k"][..., 3].mul_(1e36)), [("o",), ("o", 70), ("dr", 70)]),
+    "weights of tiny factors, huge rows": (lambda x: (_times(x, 1e-25, "g"), _times(x, 1e-10, "v"), _times(x, 1e20, "q", "r"),
+                                                      _times(x, 1e-20, "k")), [("o",), ("dk",), ("dv",)]),
+    "weights of tiny factors, huge keys": (lambda x: (_times(x, 1e-25, "g"), _times(x, 1e-10, "v"), _times(x, 1e-20, "q", "r"),
+                                                      _times(x, 1e20, "k")), [("o",), ("dq",), ("dr",), ("dv",)]),
+    "zeros among them": (lambda x: (_times(x, 1e-36, "q", "r"), _times(x, 1e36, "k"), x["k"][:, :, ::3].zero_(), x["q"][..., ::5].zero_(),
+                                    x["v"][:, :, :, 7].zero_(), x["g"][:, :, ::7].zero_()), [("o",), ("dq",), ("dr",), ("dk",), ("dv",)]),
+}
+
+
+@pytest.mark.parametrize("what", list(SMALL_BESIDE_LARGE))
+def test_small_values_beside_large_ones(plx, what):
+    """Values that three thirds do not hold, times large ones or next to ordinary ones: no less exact than elsewhere."""
+    from oracle import parallax_backward
+
+    scale, looked_at = SMALL_BESIDE_LARGE[what]
+    x = _inputs(4, 32, 32, 150, 150, seed=31)
+    scale(x)
+    outs = _step(plx, x)
+    one = _one_head(x, 2, 7)
+    few = _step(plx, one)
+    args = [host(one[n]) for n in "qrkv"]
+    want = [parallax_backward.forward_with_cache(*args, 0.125)[0], *parallax_backward.backward(*args, host(one["g"]), 0.125)]
+    names = ("o", "dq", "dr", "dk", "dv")
+    bad = []
+    for name, *part in looked_at:
+        at = (0, 0, *part)
+        got, fp32, ref = (np.asarray(t[names.index(name)], np.float64)[at] for t in
+                          ([host(t) for t in _head_of(outs, 2, 7, 1)], [host(t) for t in few], want))
+        size = np.abs(ref).max()
+        errs = [rel_l2(t / size, ref / size) for t in (got, fp32)]
+        print(what, name, part, "%.2g, fp32 instruction %.2g" % tuple(errs))
+        if errs[0] > max(REL, 1.5 * errs[1]):
+            bad.append((name, part, errs))
+    assert not bad
+
+
 @pytest.mark.parametrize("bad", [math.nan, math.inf, -math.inf])
 @pytest.mark.parametrize("name", list("qrkvg"))
 @pytest.mark.parametrize("window", [0, 30])
