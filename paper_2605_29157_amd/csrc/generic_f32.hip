@@ -426,7 +426,7 @@ hipError_t launch_decode_f32(const DecodeParams &p, hipStream_t stream) {
 }
 
 hipError_t launch_prefill_f32(const PrefillParams &p, hipStream_t stream) {
-    if (f32_thirds_pay(p.d, p.T, p.Tk, f32_thirds_blocks(p.T, p.B, p.Hq))) return launch_forward_thirds(p, stream);
+    if (f32_thirds_pay(p.d, p.T, p.Tk, p.causal, p.window, f32_thirds_blocks(p.T, p.B, p.Hq))) return launch_forward_thirds(p, stream);
     F32Forward g{};
     g.q = (const float *)p.q, g.r = (const float *)p.r, g.k = (const float *)p.k, g.v = (const float *)p.v;
     g.o = (float *)p.o;
@@ -669,13 +669,14 @@ template <int DP, bool FULL>
 static hipError_t launch_backward(const PrefillBwdParams &p, hipStream_t stream) {
     const int64_t row_blocks = (p.T + 15) / 16, key_blocks = (p.Tk + 15) / 16;
     // (each pass by itself: with several query heads to a key head there are fewer key blocks)
-    if (f32_thirds_pay(p.d, p.T, p.Tk, f32_thirds_blocks(p.T, p.B, p.Hq))) {
+    auto thirds_pay = [&](int n, int heads) { return f32_thirds_pay(p.d, p.T, p.Tk, p.causal, p.window, f32_thirds_blocks(n, p.B, heads)); };
+    if (thirds_pay(p.T, p.Hq)) {
         if (hipError_t err = launch_bwd_rows_thirds(p, stream)) return err;
     } else {
         hipLaunchKernelGGL((f32_bwd_rows_kernel<DP, FULL>), f32_grid(row_blocks * p.B * p.Hq), dim3(kF32Threads), 0, stream, p);
         if (hipError_t err = hipGetLastError()) return err;
     }
-    if (f32_thirds_pay(p.d, p.T, p.Tk, f32_thirds_blocks(p.Tk, p.B, p.Hkv))) return launch_bwd_cols_thirds(p, stream);
+    if (thirds_pay(p.Tk, p.Hkv)) return launch_bwd_cols_thirds(p, stream);
     hipLaunchKernelGGL((f32_bwd_cols_kernel<DP, FULL>), f32_grid(key_blocks * p.B * p.Hkv), dim3(kF32Threads), 0, stream, p);
     return hipGetLastError();
 }

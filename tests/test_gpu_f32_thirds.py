@@ -46,8 +46,8 @@ def _head_of(outs, b, hk, G):
 
 
 @pytest.mark.parametrize("B,Hq,Hkv,T,Tkv,causal,window", [
-    (8, 16, 16, 128, 128, True, 0), (4, 32, 32, 129, 129, True, 0), (4, 32, 16, 161, 161, True, 0), (4, 32, 32, 159, 223, True, 0),
-    (5, 26, 26, 130, 131, False, 0), (4, 32, 32, 190, 128, False, 0), (4, 32, 32, 200, 200, True, 1), (4, 32, 32, 193, 320, True, 37)])
+    (8, 16, 16, 128, 128, True, 0), (4, 32, 32, 257, 257, True, 0), (4, 32, 16, 161, 225, True, 0), (4, 32, 32, 159, 223, True, 0),
+    (5, 26, 26, 160, 161, False, 0), (4, 32, 32, 190, 128, False, 0), (4, 32, 32, 230, 230, True, 96), (4, 32, 32, 193, 320, True, 101)])
 def test_thirds_at_the_edges(plx, B, Hq, Hkv, T, Tkv, causal, window):
     from oracle import parallax_backward
 
@@ -60,18 +60,26 @@ def test_thirds_at_the_edges(plx, B, Hq, Hkv, T, Tkv, causal, window):
         want = [parallax_backward.forward_with_cache(*args, 0.125, causal=causal, window=window)[0],
                 *parallax_backward.backward(*args, host(one["g"]), 0.125, causal=causal, window=window)]
         for name, got, fp32, ref in zip(("o", "dq", "dr", "dk", "dv"), _head_of(outs, b, hk, G), few, want):
-            if np.linalg.norm(ref) <= 1e-9 * got.numel():  # (window 1: a single key has no query and no probe gradient;
-                # what is left is the rounding of sums of 64 products of N(0, 1), 64 * 2^-24 of their size of 8 at most)
-                assert float(got.abs().max()) <= 64 * 2.0 ** -24 * 8, name
-                continue
             assert rel_l2(host(got), ref) <= REL, (name, rel_l2(host(got), ref))
-            if window != 1 and Hkv * B * -(-Tkv // 32) >= 512:
+            if name in ("o", "dq", "dr") or Hkv * B * -(-Tkv // 32) >= 512:
                 assert not torch.equal(got, fp32), (name, "the launch did not run the kernels under test")
                 assert rel_l2(host(got), ref) <= rel_l2(host(fp32), ref), name
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,T,Tkv,causal,window", [
+    (16, 8, 8, 129, 129, True, 0), (16, 8, 8, 176, 176, True, 0), (16, 16, 16, 208, 208, True, 0), (8, 16, 16, 144, 144, False, 0),
+    (8, 16, 16, 128, 140, True, 0), (4, 8, 8, 1024, 1024, True, 1), (4, 8, 8, 1024, 1024, True, 64)])
+def test_launches_of_half_empty_tiles_stay_on_the_fp32_instruction(plx, B, Hq, Hkv, T, Tkv, causal, window):
+    """Just above a pair of tiles, few keys to a row, or a narrow window: up to half as long again in thirds. Bits of the
+    kernels that a launch of one head runs."""
+    x = _inputs(B, Hq, Hkv, T, Tkv, seed=T)
+    few = _step(plx, _one_head(x, B - 1, 3), causal, window)
+    for name, got, want in zip(("o", "dq", "dr", "dk", "dv"), _head_of(_step(plx, x, causal, window), B - 1, 3, 1), few):
+        assert torch.equal(got, want), name
+
+
 def test_forward_without_probe_and_with_strided_rows(plx):
-    x = _inputs(4, 32, 32, 200, 200, seed=5)
+    x = _inputs(4, 32, 32, 300, 300, seed=5)
     y = {n: t[:, :, 40:] if n in "qr" else t for n, t in x.items()}
     for use_r in (True, False):
         got = plx.parallax_prefill(y["q"], y["r"] if use_r else None, y["k"], y["v"], 0.125, use_r=use_r)
@@ -84,7 +92,7 @@ def test_forward_without_probe_and_with_strided_rows(plx):
                                     dict(g=1e-36)])
 def test_small_and_large_values(plx, scales):
     """Powers of ten that leave thirds below the smallest number, or near the largest."""
-    x = _inputs(4, 32, 32, 130, 130, seed=9)
+    x = _inputs(4, 32, 32, 226, 226, seed=9)
     for n, f in scales.items():
         x[n] *= f
     outs, few = _step(plx, x), _step(plx, _one_head(x, 2, 7))
@@ -127,7 +135,7 @@ def test_small_values_beside_large_ones(plx, what):
     from oracle import parallax_backward
 
     scale, looked_at = SMALL_BESIDE_LARGE[what]
-    x = _inputs(4, 32, 32, 150, 150, seed=31)
+    x = _inputs(4, 32, 32, 230, 230, seed=31)
     scale(x)
     outs = _step(plx, x)
     one = _one_head(x, 2, 7)
@@ -150,11 +158,11 @@ def test_small_values_beside_large_ones(plx, what):
 
 @pytest.mark.parametrize("bad", [math.nan, math.inf, -math.inf])
 @pytest.mark.parametrize("name", list("qrkvg"))
-@pytest.mark.parametrize("window", [0, 30])
+@pytest.mark.parametrize("window", [0, 100])
 def test_not_finite_as_the_fp32_kernels_have_it(plx, name, bad, window):
     """One value that is not finite: the results are infinite or NaN where those of the fp32 kernels are, and as
     close to them as ever everywhere else."""
-    x = _inputs(4, 32, 32, 150, 150, seed=21)
+    x = _inputs(4, 32, 32, 230, 230, seed=21)
     x[name][2, 7, 70, 3] = bad
     outs, few = _step(plx, x, window=window), _step(plx, _one_head(x, 2, 7), window=window)
     for n, got, ref in zip(("o", "dq", "dr", "dk", "dv"), _head_of(outs, 2, 7, 1), few):
