@@ -116,6 +116,26 @@ def test_split_heuristic_is_sane(binding):
     assert f(32, 16, 8, 8192, 128, 256) == 2
 
 
+def test_splits_of_an_fp32_call(binding):
+    """On 256 compute units (what the library counts on without a GPU, too)."""
+    def splits(B, Hkv, G, d, L):
+        a = _good_decode_args(binding)
+        a.B, a.Hq, a.Hkv, a.Lmax, a.d, a.num_splits, a.dtype = B, Hkv * G, Hkv, L, d, 0, binding.PLX_F32
+        a.k_stride_b, a.k_stride_h, a.k_stride_l = Hkv * L * d, L * d, d
+        a.v_stride_b, a.v_stride_h, a.v_stride_l = Hkv * L * d, L * d, d
+        return binding.load_library().parallax_decode_call_splits(ctypes.byref(a))
+
+    # above d = 128 one workgroup is resident on a unit: a second round of them only where it saves the work of one
+    for d in (132, 256):
+        assert [splits(B, 8, 2, d, L) for B, L in ((4, 3000), (8, 1500), (8, 6000), (2, 6000))] == [8, 4, 4, 16]
+        assert splits(3, 8, 2, d, 6000) == 10 and splits(6, 8, 2, d, 3000) == 5    # 240 workgroups, not 264 or 768
+        assert splits(1, 8, 2, d, 500) == 8 and splits(8, 8, 2, d, 500) == 4       # a round of the four waves each
+    # caches that one or two rounds of a workgroup walk are not worth a merge, three are
+    assert [splits(1, 8, 2, 128, L) for L in (16, 80, 100, 128, 160)] == [1, 1, 1, 1, 3]
+    assert [splits(1, 8, 2, 64, L) for L in (80, 200, 260, 350)] == [1, 1, 1, 2]
+    assert splits(4, 8, 2, 64, 2048) == 16 and splits(7, 4, 4, 128, 1647) == 9 and splits(1, 4, 4, 128, 1307) == 21
+
+
 def test_static_scratch_entry_point_checks_its_limit_on_the_host(binding):
     lib = binding.load_library()
     static = lambda a: lib.parallax_decode_static(ctypes.byref(a), None)
