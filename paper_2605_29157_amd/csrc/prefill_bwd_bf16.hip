@@ -129,32 +129,43 @@ __device__ __forceinline__ f32x16 zero16() {
 
 // ---- rows prepare: (lse, ubar, tau, beta) per query row ---------------------------------------
 // Memory bound: three rows in, 16 bytes out. 16 bytes per lane, D / 8 lanes share a row; a workgroup takes kPrepRows
-// rows of one head, each lane two of them, all its loads in flight (the row's statistics among them: asked for behind the
-// sums they are another trip), and the head is divided out once per workgroup. 4 x 16 heads x 4096 rows, d = 128: 33.2 ->
-// 30.5 us (one row per lane 33.2, four 31.8); 3 x 32 x 1111, d = 64: 8.4 -> 7.8.
+// consecutive rows of any heads (its lanes are all busy for few rows and many heads, too), each lane two of them, all its
+// loads in flight (the row's statistics among them: asked for behind the sums they are another trip); the head is divided out
+// once per workgroup, and once more per row only where a head is shorter than what a workgroup takes. Us, one row per lane
+// and 64-bit divisions / two rows of one head / here: 4 x 16 heads x 4096 rows, d = 128, 37.0 / 36.3 / 35.8; 3 x 32 x 1111, d = 64,
+// 8.8 / 8.3 / 8.2; 512 x 32 x 16 19.9 / 25.4 / 17.7; 256 x 32 x 65 39.0 / 45.5 / 37.8; 512 x 16 x 33, d = 128, 38.2 / 45.2 / 36.7.
 template <int D>
 constexpr int kPrepRows = 2 * 2048 / D;
 template <int D>
 __global__ __launch_bounds__(256) void bwd_rows_prepare_kernel(PrefillBwdParams p) {
     constexpr int LPR = D / 8, ROWS = 256 / LPR, PER = kPrepRows<D> / ROWS;
     const int sub = threadIdx.x % LPR;
-    const unsigned per_head = (unsigned)(p.T + kPrepRows<D> - 1) / kPrepRows<D>;
-    const unsigned bh = blockIdx.x / per_head;
-    const int b = (int)(bh / (unsigned)p.Hq), h = (int)(bh - (unsigned)b * (unsigned)p.Hq);
-    const int t0 = (int)(blockIdx.x - bh * per_head) * kPrepRows<D> + threadIdx.x / LPR;
-    const __bf16 *d_o = (const __bf16 *)p.d_o + b * p.gs[0] + h * p.gs[1];
-    const __bf16 *out = (const __bf16 *)p.o + b * p.os[0] + h * p.os[1];
-    const __bf16 *vbar = (const __bf16 *)p.vbar + b * p.vbs[0] + h * p.vbs[1];
-    const int64_t row0 = (int64_t)bh * p.T;
+    const unsigned T = (unsigned)p.T, Hq = (unsigned)p.Hq, n_rows = (unsigned)p.B * Hq * T;  // (fits 31 bits: checked)
+    const unsigned first = blockIdx.x * kPrepRows<D>, bh0 = first / T, b0 = bh0 / Hq;
+    struct Row {
+        int64_t b, h, t;
+    };
+    auto row_at = [&](unsigned row) {
+        unsigned t = row - bh0 * T, h = bh0 - b0 * Hq, b = b0;
+        if (T >= kPrepRows<D>) {  // (uniform)
+            if (t >= T) t -= T, ++h;
+            if (h == Hq) h = 0, ++b;
+        } else {
+            h += t / T, t %= T;
+            b += h / Hq, h %= Hq;
+        }
+        return Row{(int64_t)b, (int64_t)h, (int64_t)t};
+    };
     u32x4 g[PER], o[PER], vb[PER];
     float lse[PER], ubar[PER];
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
-        const int64_t t = min(t0 + k * ROWS, p.T - 1);  // (every lane takes part in the sums)
-        g[k] = ((const u32x4 *)(d_o + t * p.gs[2]))[sub];
-        o[k] = ((const u32x4 *)(out + t * p.os[2]))[sub];
-        vb[k] = ((const u32x4 *)(vbar + t * p.vbs[2]))[sub];
-        lse[k] = p.row_stats[2 * (row0 + t)], ubar[k] = p.row_stats[2 * (row0 + t) + 1];
+        const unsigned row = min(first + k * ROWS + threadIdx.x / LPR, n_rows - 1);  // (every lane takes part in the sums)
+        const Row at = row_at(row);
+        g[k] = ((const u32x4 *)((const __bf16 *)p.d_o + at.b * p.gs[0] + at.h * p.gs[1] + at.t * p.gs[2]))[sub];
+        o[k] = ((const u32x4 *)((const __bf16 *)p.o + at.b * p.os[0] + at.h * p.os[1] + at.t * p.os[2]))[sub];
+        vb[k] = ((const u32x4 *)((const __bf16 *)p.vbar + at.b * p.vbs[0] + at.h * p.vbs[1] + at.t * p.vbs[2]))[sub];
+        lse[k] = p.row_stats[2 * (int64_t)row], ubar[k] = p.row_stats[2 * (int64_t)row + 1];
     }
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
@@ -165,8 +176,8 @@ __global__ __launch_bounds__(256) void bwd_rows_prepare_kernel(PrefillBwdParams 
             beta += bf16_lo_f32(g[k][i]) * bf16_lo_f32(vb[k][i]) + bf16_hi_f32(g[k][i]) * bf16_hi_f32(vb[k][i]);
         }
         tau = lane_group_sum<LPR>(tau), beta = lane_group_sum<LPR>(beta);
-        const int t = t0 + k * ROWS;
-        if (t < p.T && sub == 0) ((f32x4 *)p.row_cache)[row0 + t] = f32x4{lse[k], 1.f + ubar[k], beta - tau, beta};
+        const unsigned row = first + k * ROWS + threadIdx.x / LPR;
+        if (row < n_rows && sub == 0) ((f32x4 *)p.row_cache)[row] = f32x4{lse[k], 1.f + ubar[k], beta - tau, beta};
     }
 }
 
@@ -1254,7 +1265,7 @@ int32_t backward_form_bf16(const PrefillBwdParams &p, int num_cus) {
 template <int D>
 static hipError_t launch_bwd_d(const PrefillBwdParams &p, int num_cus, hipStream_t stream) {
     const BackwardPlan plan = backward_plan(p, num_cus);
-    const long long g0 = (long long)p.B * p.Hq * ((p.T + kPrepRows<D> - 1) / kPrepRows<D>);
+    const long long g0 = ((long long)p.B * p.Hq * p.T + kPrepRows<D> - 1) / kPrepRows<D>;
     auto columns = [&](bool pair) { return (long long)((p.Tk + (pair ? 63 : 127)) / (pair ? 64 : 128)) * p.Hkv * p.B; };
     auto row_groups = [&](bool pair) { return (long long)((p.T + (pair ? 63 : 127)) / (pair ? 64 : 128)) * p.Hq * p.B; };
     if (g0 > 0x7fffffffLL || columns(plan.pair_c) + row_groups(plan.pair_r) > 0x7fffffffLL) return hipErrorInvalidValue;

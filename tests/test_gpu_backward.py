@@ -363,3 +363,28 @@ def test_forward_and_backward_in_a_hip_graph(plx, synth):
         _, _, _, eager = _run(plx, y, g, True)
         for a, b in zip(got, eager):
             assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("B,Hq,T,d", [(3, 5, 1, 64), (70, 3, 1, 128), (3, 4, 16, 64), (2, 6, 33, 64), (5, 3, 63, 64), (5, 3, 64, 64),
+                                      (2, 3, 65, 64), (3, 4, 31, 128), (3, 4, 32, 128), (2, 5, 33, 128), (2, 3, 97, 128)])
+def test_row_scalars_at_the_edges_of_a_workgroup(plx, B, Hq, T, d):
+    """(lse, 1 + ubar, beta - tau, beta) that the first launch of a bf16 backward leaves in the workspace: workgroups of 32 or 64
+    consecutive rows that hold several heads and sequences, one wrap, or a last part; d_o and o with strides of their own."""
+    gen = torch.Generator(DEV).manual_seed(100 * T + d)
+    normal = lambda *s: torch.randn(s, generator=gen, device=DEV, dtype=torch.bfloat16)
+    q, r, k, v = (normal(B, Hq, T, d) for _ in range(4))
+    o, vbar, stats = plx.parallax_prefill(q, r, k, v, 0.1, save_for_backward=True)
+    g = normal(B, T, Hq, d).transpose(1, 2)
+    wide = torch.zeros(B, Hq, T, d + 8, device=DEV, dtype=torch.bfloat16)
+    wide[..., :d] = o
+    ws = torch.full((B * Hq * T * 4 + 64,), 7.0, dtype=torch.float32, device=DEV)
+    plx.parallax_prefill_backward(q, r, k, v, wide[..., :d], vbar, stats, g, 0.1, workspace=ws)
+    rows = ws[:-64].view(B, Hq, T, 4).double()
+    gd, od, vd = g.double(), o.double(), vbar.double()
+    tau, beta = (gd * od).sum(-1), (gd * vd).sum(-1)
+    bound = d * 2.0 ** -24 * ((gd * od).abs() + (gd * vd).abs()).sum(-1)  # fp32 sums of d exact products
+    assert torch.equal(rows[..., 0], stats[..., 0].double())
+    assert torch.equal(rows[..., 1].float(), 1 + stats[..., 1])
+    assert bool(((rows[..., 2] - (beta - tau)).abs() <= 2 * bound).all())
+    assert bool(((rows[..., 3] - beta).abs() <= bound).all())
+    assert bool((ws[-64:] == 7.0).all())
