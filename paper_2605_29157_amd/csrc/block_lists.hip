@@ -2,12 +2,12 @@
 // patterns of the paper's Sec. 5, no arithmetic).
 //
 // A line is a row block (entries: its listed key tiles) or a key block of two key tiles (entries:
-// 4 * row block + flags); lines are independent but for where their entries go. Up to kOneLaunchCells
-// one launch does all: every workgroup counts the cells in front of its lines. Above, one launch
+// 4 * row block + flags); lines are independent but for where their entries go. Up to kOneLaunchCells (and
+// kOneLaunchLines) one launch does all: every workgroup counts the cells in front of its lines. Above, one launch
 // counts and a second places: every workgroup adds up the counts in front of its lines itself
 // (reads that the L2 holds) instead of a third launch scanning them. With many lines (kScanLines) those
 // reads, quadratic in the number of lines, would cost more than the launch, and the scan is made. What
-// bounds it otherwise is the two launches; the host never learns the number of entries, so nothing waits for the GPU. Built from
+// bounds it otherwise is the launches, one or two; the host never learns the number of entries, so nothing waits for the GPU. Built from
 // tensor operations instead (a scan, a compaction whose size the host reads back, casts: 40 launches
 // and three waits per training step), the lists took 310 us of a 537 us step over 2 sequences x
 // 2048 rows, 16 heads, a quarter of the cells; with these kernels the whole step took 220 us.
@@ -27,7 +27,9 @@ constexpr int64_t kScanLines = 8192;
 // work quadratic in the cells, against a launch. Two launches / one in a replayed graph, us, row lists alone and with key
 // lists: 16 x 32 cells 4.4 / 2.7 and 4.7 / 3.2; 64 x 128 5.2 / 4.1 and 5.0 / 5.0; 16 lists of 16 x 32 4.6 / 3.9 and
 // 5.1 / 5.0; 16 of 32 x 64 4.9 / 7.2 and 5.7 / 9.6. (On a stream two launches cost another gap and their host time.)
-constexpr int64_t kOneLaunchCells = 8192;
+// And lines: each four of them count. In a trace with 1 us a gap, 8192 lists of one cell (16384 lines with the key lists)
+// 16.1 (a scan) / 18.8, 4096 of 1 x 2 (8192) 11.3 / 9.3, one list of 8192 x 1 65 / 47.
+constexpr int64_t kOneLaunchCells = 8192, kOneLaunchLines = 12288;
 
 // Entry n of a line: 0 = not listed, else 1 + the value that goes into the list.
 struct LineReader {
@@ -83,7 +85,7 @@ __global__ __launch_bounds__(64 * kLinesPerGroup) void block_list_count_kernel(B
     if (lane == 0) p.counts[line] = count;
 }
 
-// Few cells (kOneLaunchCells; so their indices fit 32 bits)
+// Few cells and lines (so their indices fit 32 bits)
 __global__ __launch_bounds__(64 * kLinesPerGroup) void block_list_kernel(BlockListParams p) {
     __shared__ int before[kLinesPerGroup], own[kLinesPerGroup];
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -211,7 +213,7 @@ hipError_t launch_block_lists(const BlockListParams &p, hipStream_t stream) {
     const int64_t groups = (lines + kLinesPerGroup - 1) / kLinesPerGroup;
     if (groups > (1 << 23)) return hipErrorInvalidValue;
     const dim3 grid((unsigned)groups), block(64 * kLinesPerGroup);
-    if ((int64_t)p.lists * p.n_row_blocks * p.n_tiles <= kOneLaunchCells) {
+    if ((int64_t)p.lists * p.n_row_blocks * p.n_tiles <= kOneLaunchCells && lines <= kOneLaunchLines) {
         hipLaunchKernelGGL(block_list_kernel, grid, block, 0, stream, p);
         return hipGetLastError();
     }

@@ -434,7 +434,9 @@ def test_masked_call_on_another_stream(plx, synth):
     assert torch.equal(got, want)
 
 
-@pytest.mark.parametrize("lists,nrb,nkt", [((1, 1), 64, 128), ((1, 1), 91, 91), ((3, 2), 25, 129), ((2, 3), 13, 105)])
+@pytest.mark.parametrize("lists,nrb,nkt", [((1, 1), 64, 128), ((1, 1), 91, 91), ((3, 2), 25, 129), ((2, 3), 13, 105),
+                                           ((96, 64), 1, 1), ((97, 64), 1, 1)])
 def test_lists_around_the_cells_of_one_launch(plx, lists, nrb, nkt):
-    """8192 cells in one launch, 8190 in six lists, and the two launches just above with odd lines."""
+    """8192 cells in one launch, 8190 in six lists, and the two launches just above with odd lines; 12288 lines in one launch,
+    and 12416."""
     test_lists_built_on_the_device(plx, lists, nrb, nkt, 0.3)
