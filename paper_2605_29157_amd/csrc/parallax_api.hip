@@ -517,8 +517,9 @@ size_t parallax_decode_mla_workspace_bytes(int32_t B, int32_t Hq) {
 }
 
 namespace {
-// Split count of a latent-cache call. `small_splits` false: at least 256 (128) whole keys a split, as calls had it that
-// bring no workspace because they ran unsplit, or one of so many records.
+// Split count of a latent-cache call. `small_splits` false: at least 256 (128) whole keys a split, for calls that bring no
+// workspace because that is one split, or one of so many records, and under a sliding window, whose keys are few of Lmax
+// (2 sequences x 32 heads, the last 53 of 399 tokens: 1 split 14.5 us, 7 16.4).
 int32_t mla_splits(int32_t B, int32_t Hq, int32_t Lmax, int32_t num_cus, bool small_splits) {
     if (B <= 0 || Hq <= 0 || Lmax <= 0) return 1;
     if (num_cus <= 0) num_cus = query_num_cus();
@@ -620,7 +621,8 @@ plx_status parallax_decode_mla(const plx_decode_mla_args *a, void *hip_stream) {
                a->workspace_bytes >= (size_t)a->B * n_cols * splits * (2 * 512 + 4) * sizeof(float);
     };
     if (S == 0) {
-        S = mla_splits(a->B, (int32_t)n_cols, a->Lmax, 0, true);
+        const bool windowed = a->window > 0 && (int64_t)a->window + Tq - 1 < a->Lmax;
+        S = mla_splits(a->B, (int32_t)n_cols, a->Lmax, 0, !windowed);
         if (S > 1 && !has_room(S)) S = mla_splits(a->B, (int32_t)n_cols, a->Lmax, 0, false);
     }
     p.S = S;

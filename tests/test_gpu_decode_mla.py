@@ -399,3 +399,18 @@ def test_a_workspace_for_fewer_splits_is_taken_as_it_was(B, Hq, L, before):
     if before > 1:
         with pytest.raises(plx.ParallaxError):
             plx.parallax_decode_mla(q, r, ckv, 0.04, workspace=few[:-4])
+
+
+@pytest.mark.parametrize("B,Hq,L,window,before", [(2, 32, 399, 53, 1), (1, 16, 350, 44, 1), (3, 32, 3942, 59, 15)])
+def test_a_windowed_call_splits_as_the_whole_keys_allow(B, Hq, L, window, before):
+    """A window reads few of the keys that a tile per split would be for: the count of 256 (128) whole keys a split, bit for
+    bit. A window as long as the cache is none."""
+    from paper_2605_29157_amd import binding as plx
+
+    gen = torch.Generator(device="cuda").manual_seed(L)
+    q, r = (torch.randn(B, Hq, 576, generator=gen, device="cuda", dtype=torch.bfloat16) for _ in range(2))
+    ckv = torch.randn(B, L, 576, generator=gen, device="cuda", dtype=torch.bfloat16)
+    assert plx.parallax_decode_mla_num_splits(B, Hq, L) > before
+    got = plx.parallax_decode_mla(q, r, ckv, 0.04, window=window)
+    assert torch.equal(got, plx.parallax_decode_mla(q, r, ckv, 0.04, window=window, num_splits=before))
+    assert torch.equal(plx.parallax_decode_mla(q, r, ckv, 0.04, window=L), plx.parallax_decode_mla(q, r, ckv, 0.04))
