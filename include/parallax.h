@@ -28,8 +28,8 @@
  *     outputs and workspace as undefined. No call aborts or throws.
  *   - GQA: G = Hq / Hkv must be an integer; query head h reads KV head h / G.
  *   - Supported: dtype bf16 (MFMA kernels, d in {64, 128}, G <= 16) and fp32 (fp32 MFMA
- *     kernels, d <= 256). Innermost dimension contiguous; base pointers and
- *     row strides 16-byte aligned. Output dtype = input dtype; all running state is fp32.
+ *     kernels, d <= 256; large prefill launches at d = 64 on bf16 MFMA with three parts per value). Innermost dimension
+ *     contiguous; base pointers and row strides 16-byte aligned. Output dtype = input dtype; all running state is fp32.
  */
 #ifndef PARALLAX_H
 #define PARALLAX_H
@@ -283,10 +283,11 @@ plx_status parallax_prefill(const plx_prefill_args *args, void *hip_stream);
  *   parallax_prefill_workspace_bytes  what the split of this call takes, 0 = the call is not split (or its
  *                                     arguments are not valid)
  *   workspace   NULL, or 16-byte aligned device memory; smaller than that: the call runs unsplit
- *   parallax_prefill_form  how a bf16 call runs with a workspace of that many bytes: query rows per workgroup (64
- *                          or 128) plus 256 * (64-key tiles per key range, 0 = not split); 0: fp32, or not valid
+ *   parallax_prefill_form  how a call runs with a workspace of that many bytes: query rows per workgroup (64
+ *                          or 128) plus 256 * (64-key tiles per key range, 0 = not split); fp32: 32 for a large
+ *                          launch at d = 64 (bf16 thirds), else 0; 0 too: not valid
  * The form is the quickest for the launch, so it depends on B and Hq, and a sequence's outputs may differ in
- * their rounding with what else is in the launch. Two launches of the same form give a sequence the same bits.
+ * their rounding with what else is in the launch (fp32 too). Two launches of the same form give a sequence the same bits.
  */
 size_t parallax_prefill_workspace_bytes(const plx_prefill_args *args);
 int32_t parallax_prefill_form(const plx_prefill_args *args, size_t workspace_bytes);
@@ -400,8 +401,8 @@ typedef struct {
 
 size_t parallax_prefill_backward_workspace_bytes(int32_t B, int32_t Hq, int32_t T);
 plx_status parallax_prefill_backward(const plx_prefill_bwd_args *args, void *hip_stream);
-/* How a bf16 call runs: keys per workgroup of the pass for dk and dv (64 or 128), plus 256 * query rows per workgroup of the
- * pass for dq and dr; 0: fp32, or not valid. As in the forward the form is the quickest for the launch and depends on B
+/* How a call runs: keys per workgroup of the pass for dk and dv (64 or 128; fp32: 32 in bf16 thirds, else 0), plus 256 *
+ * query rows per workgroup of the pass for dq and dr (likewise); 0: fp32 and neither in thirds, or not valid. As in the forward the form is the quickest for the launch and depends on B
  * and the heads; two launches of the same form give a sequence the same bits. Plus 65536: block lists, and what share
  * of the cells they name decides, read by the kernels, between the 64 keys and 128. */
 int32_t parallax_prefill_backward_form(const plx_prefill_bwd_args *args);

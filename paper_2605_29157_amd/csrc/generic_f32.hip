@@ -425,8 +425,12 @@ hipError_t launch_decode_f32(const DecodeParams &p, hipStream_t stream) {
     return launch_forward(g, stream);
 }
 
+int32_t prefill_form_f32(const PrefillParams &p) {
+    return f32_thirds_pay(p.d, p.T, p.Tk, p.causal, p.window, f32_thirds_blocks(p.T, p.B, p.Hq)) ? kF32ThirdsColumns : 0;
+}
+
 hipError_t launch_prefill_f32(const PrefillParams &p, hipStream_t stream) {
-    if (f32_thirds_pay(p.d, p.T, p.Tk, p.causal, p.window, f32_thirds_blocks(p.T, p.B, p.Hq))) return launch_forward_thirds(p, stream);
+    if (prefill_form_f32(p)) return launch_forward_thirds(p, stream);
     F32Forward g{};
     g.q = (const float *)p.q, g.r = (const float *)p.r, g.k = (const float *)p.k, g.v = (const float *)p.v;
     g.o = (float *)p.o;
@@ -665,18 +669,23 @@ __global__ __launch_bounds__(kF32Threads, DP <= 128 ? 2 : 1) void f32_bwd_cols_k
         }
 }
 
+int32_t backward_form_f32(const PrefillBwdParams &p) {
+    // (each pass by itself: with several query heads to a key head there are fewer key blocks)
+    auto pay = [&](int n, int heads) { return f32_thirds_pay(p.d, p.T, p.Tk, p.causal, p.window, f32_thirds_blocks(n, p.B, heads)); };
+    return (pay(p.Tk, p.Hkv) ? kF32ThirdsColumns : 0) + 256 * (pay(p.T, p.Hq) ? kF32ThirdsColumns : 0);
+}
+
 template <int DP, bool FULL>
 static hipError_t launch_backward(const PrefillBwdParams &p, hipStream_t stream) {
+    const int32_t form = backward_form_f32(p);
     const int64_t row_blocks = (p.T + 15) / 16, key_blocks = (p.Tk + 15) / 16;
-    // (each pass by itself: with several query heads to a key head there are fewer key blocks)
-    auto thirds_pay = [&](int n, int heads) { return f32_thirds_pay(p.d, p.T, p.Tk, p.causal, p.window, f32_thirds_blocks(n, p.B, heads)); };
-    if (thirds_pay(p.T, p.Hq)) {
+    if (form / 256) {
         if (hipError_t err = launch_bwd_rows_thirds(p, stream)) return err;
     } else {
         hipLaunchKernelGGL((f32_bwd_rows_kernel<DP, FULL>), f32_grid(row_blocks * p.B * p.Hq), dim3(kF32Threads), 0, stream, p);
         if (hipError_t err = hipGetLastError()) return err;
     }
-    if (thirds_pay(p.Tk, p.Hkv)) return launch_bwd_cols_thirds(p, stream);
+    if (form % 256) return launch_bwd_cols_thirds(p, stream);
     hipLaunchKernelGGL((f32_bwd_cols_kernel<DP, FULL>), f32_grid(key_blocks * p.B * p.Hkv), dim3(kF32Threads), 0, stream, p);
     return hipGetLastError();
 }

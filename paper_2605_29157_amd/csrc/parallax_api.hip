@@ -493,7 +493,8 @@ size_t parallax_prefill_workspace_bytes(const plx_prefill_args *a) {
 
 int32_t parallax_prefill_form(const plx_prefill_args *a, size_t workspace_bytes) {
     plx::PrefillParams p{};
-    if (prepare_prefill(a, &p) != PLX_OK || a->dtype != PLX_BF16) return 0;
+    if (prepare_prefill(a, &p) != PLX_OK) return 0;
+    if (a->dtype == PLX_F32) return plx::prefill_form_f32(p);
     const size_t need = plx::plan_prefill_bf16(p, query_num_cus(), workspace_bytes > 0);
     return need > 0 && workspace_bytes >= need ? 128 + 256 * p.split_tiles : p.rows;
 }
@@ -747,8 +748,8 @@ plx_status parallax_prefill_backward(const plx_prefill_bwd_args *a, void *hip_st
 
 int32_t parallax_prefill_backward_form(const plx_prefill_bwd_args *a) {
     plx::PrefillBwdParams p{};
-    if (prepare_prefill_backward(a, &p) != PLX_OK || a->dtype != PLX_BF16) return 0;
-    return plx::backward_form_bf16(p, query_num_cus());
+    if (prepare_prefill_backward(a, &p) != PLX_OK) return 0;
+    return a->dtype == PLX_F32 ? plx::backward_form_f32(p) : plx::backward_form_bf16(p, query_num_cus());
 }
 
 plx_status parallax_norm_rope(const plx_norm_rope_args *a, void *hip_stream) {

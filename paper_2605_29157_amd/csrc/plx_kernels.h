@@ -145,6 +145,9 @@ size_t plan_prefill_bf16(PrefillParams &p, int num_cus, bool with_ranges);
 // keys per workgroup of the column pass, plus 256 * rows per workgroup of the row pass, plus 65536 where the lists decide
 int32_t backward_form_bf16(const PrefillBwdParams &p, int num_cus);
 hipError_t launch_prefill_bwd_bf16(const PrefillBwdParams &p, int num_cus, hipStream_t stream);
+// 32 for a pass in bf16 thirds (prefill_f32.hip), 0 on the fp32 instruction; the backward as backward_form_bf16
+int32_t prefill_form_f32(const PrefillParams &p);
+int32_t backward_form_f32(const PrefillBwdParams &p);
 hipError_t launch_prefill_bwd_f32(const PrefillBwdParams &p, hipStream_t stream);
 hipError_t launch_decode_f32(const DecodeParams &p, hipStream_t stream);
 hipError_t launch_prefill_f32(const PrefillParams &p, hipStream_t stream);

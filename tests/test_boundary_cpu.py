@@ -670,3 +670,45 @@ def test_backward_lets_the_lists_decide_where_a_share_does(binding, shape, decid
     """Halved chains are 8 to 18 % quicker with a quarter of the tiles listed and 8 to 21 % slower with all."""
     form = binding.load_library().parallax_prefill_backward_form(ctypes.byref(_backward_shape(binding, *shape, 0, True)))
     assert (form == 64 + 256 * 128 + 65536) == decide
+
+
+# us of the fp32 forward and backward on the fp32 instruction and in bf16 thirds; d = 64
+@pytest.mark.parametrize("shape,instruction,thirds", [
+    ((4, 8, 8, 500, 500, 64, True), (31.0, 76.4), (26.6, 66.8)), ((8, 8, 8, 256, 256, 64, True), (19.0, 47.3), (16.9, 42.2)),
+    ((16, 8, 8, 100, 100, 64, True), (12.4, 26.8), (12.2, 29.1)), ((16, 8, 8, 128, 128, 64, True), (13.5, 32.6), (12.2, 29.4)),
+    ((16, 8, 8, 129, 129, 64, True), (16.6, 38.6), (17.3, 44.2)), ((16, 8, 8, 176, 176, 64, True), (21.5, 50.6), (21.4, 53.8)),
+    ((16, 8, 8, 192, 192, 64, True), (23.1, 54.9), (21.7, 52.3)), ((16, 16, 16, 208, 208, 64, True), (45.4, 108.4), (45.1, 116.8)),
+    ((16, 8, 8, 257, 257, 64, True), (35.9, 88.5), (33.7, 83.9)), ((8, 16, 8, 225, 225, 64, True), (31.0, 73.1), (26.6, 70.9)),
+    ((8, 16, 16, 144, 144, 64, False), (23.7, 56.8), (24.6, 61.3)), ((8, 16, 16, 160, 160, 64, False), (27.4, 65.5), (24.4, 62.3)),
+    ((8, 16, 16, 128, 140, 64, True), (14.8, 35.8), (14.9, 38.0)), ((8, 16, 16, 128, 600, 64, True), (51.4, 136.7), (38.3, 108.4)),
+    ((8, 16, 16, 600, 128, 64, False), (62.7, 145.0), (51.0, 118.0)), ((4, 8, 8, 1024, 1024, 64, True, 1), (15.5, 29.3), (19.6, 45.6)),
+    ((4, 8, 8, 1024, 1024, 64, True, 16), (18.1, 40.6), (19.9, 46.9)), ((16, 16, 16, 300, 300, 64, True, 64), (51.1, 120.9), (51.6, 124.3)),
+    ((4, 8, 8, 1024, 1024, 64, True, 128), (32.8, 83.3), (30.3, 77.5)), ((1, 8, 8, 2048, 2048, 64, True), (102.7, 238.9), (82.8, 218.1))])
+def test_fp32_launches_take_thirds_where_they_were_quicker(binding, shape, instruction, thirds):
+    """Both directions, and the sum of a step within 2 % of the quicker."""
+    lib = binding.load_library()
+    a, b = _prefill_shape(binding, *shape), _backward_shape(binding, *shape)
+    a.dtype = b.dtype = binding.PLX_F32
+    forward, backward = lib.parallax_prefill_form(ctypes.byref(a), 0), lib.parallax_prefill_backward_form(ctypes.byref(b))
+    assert forward in (0, 32) and backward in (0, 32 + 256 * 32)
+    took = (thirds if forward else instruction)[0] + (thirds if backward else instruction)[1]
+    assert took <= 1.02 * min(sum(instruction), sum(thirds))
+
+
+def test_fp32_form_of_each_pass_and_what_stays_on_the_fp32_instruction(binding):
+    """512 workgroups of 32 columns a pass; d = 64 alone. What a form of its own decides is decided for each pass."""
+    lib = binding.load_library()
+
+    def forms(*shape):
+        a, b = _prefill_shape(binding, *shape), _backward_shape(binding, *shape)
+        a.dtype = b.dtype = binding.PLX_F32
+        back = lib.parallax_prefill_backward_form(ctypes.byref(b))
+        return lib.parallax_prefill_form(ctypes.byref(a), 0), back // 256, back % 256
+
+    assert forms(4, 8, 8, 512, 512, 64, True) == (32, 32, 32) and forms(3, 8, 8, 512, 512, 64, True) == (0, 0, 0)
+    assert forms(8, 16, 8, 224, 224, 64, True) == (32, 32, 0)        # 448 workgroups of keys
+    assert forms(2, 8, 8, 512, 2048, 64, True) == (0, 0, 32)         # 256 of rows
+    for d in (32, 60, 68, 128, 256):
+        assert forms(8, 8, 8, 512, 512, d, True) == (0, 0, 0)
+    assert forms(8, 8, 8, 512, 512, 64, True, 95) == (0, 0, 0) and forms(8, 8, 8, 512, 512, 64, True, 96) == (32, 32, 32)
+    assert forms(8, 8, 8, 512, 512, 64, True, 512) == (32, 32, 32)   # as long as the keys: none
