@@ -314,8 +314,11 @@ plx_status parallax_prefill_split(const plx_prefill_args *args, void *workspace,
  *              576 <= ckv_stride_l <= 2^23), last dimension contiguous
  *   o          [B, Hq, 512] contiguous (the value up-projection is the caller's)
  *   seq_lens   int32 [B] on the device or NULL (= Lmax); 0 gives a zero row
- *   num_splits 0 = heuristic, else 1 .. PLX_MAX_SPLITS
- *   workspace  fp32 scratch for num_splits > 1, >= parallax_decode_mla_workspace_bytes(B, Hq)
+ *   num_splits 0 = heuristic, else 1 .. PLX_MAX_SPLITS. The heuristic's count is that of
+ *              parallax_decode_mla_num_splits if the workspace has room for its records and no window hides keys;
+ *              else one of at least 256 keys a split (128 up to 12 or 32 splits), which may be 1 and then needs none
+ *   workspace  fp32 scratch for num_splits > 1, >= parallax_decode_mla_workspace_bytes(B, Hq), or the records of the
+ *              splits: B * Hq * num_splits * (2 * 512 + 4) floats
  *   block_table  NULL, or int32 [B, block_table_stride] on the device: the cache is then a pool
  *              ckv [num_pages, page_size, 576] (ckv_stride_b = page stride) and token j of
  *              sequence b is row j % page_size of page block_table[b][j / page_size]; entries
@@ -346,7 +349,8 @@ typedef struct {
 } plx_decode_mla_args;
 
 size_t parallax_decode_mla_workspace_bytes(int32_t B, int32_t Hq);
-/* The split count the heuristic picks (num_cus <= 0: ask the device). */
+/* The split count the heuristic picks (num_cus <= 0: ask the device) for a call with room for it and no window; a call
+ * may use fewer, see num_splits above. */
 int32_t parallax_decode_mla_num_splits(int32_t B, int32_t Hq, int32_t Lmax, int32_t num_cus);
 plx_status parallax_decode_mla(const plx_decode_mla_args *args, void *hip_stream);
 
