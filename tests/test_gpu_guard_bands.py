@@ -167,6 +167,38 @@ def test_prefill_output_row_cache_and_gradients(plx, synth, T, Tkv, d, causal, w
     g.check(("parallax_prefill_backward reads", T, Tkv, d, causal, window))
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,T,Tkv,causal,window", [(4, 32, 32, 225, 259, True, 0), (4, 64, 32, 129, 223, True, 0),
+                                                           (5, 26, 26, 161, 193, False, 0), (4, 32, 32, 257, 257, True, 97)])
+def test_large_fp32_launches_in_thirds(plx, B, Hq, Hkv, T, Tkv, causal, window):
+    """Rows and keys that are no multiples of the tiles of 32; inputs in bands of NaN, which reach a result that reads them."""
+    gen, nan = torch.Generator(DEV).manual_seed(7450 + T), float("nan")
+
+    def banded(*shape):
+        n = int(np.prod(shape))
+        raw = torch.full((n + 2 * 4096,), nan, device=DEV)
+        raw[4096:4096 + n] = torch.randn(n, generator=gen, device=DEV)
+        return raw[4096:4096 + n].view(shape)
+
+    q, r, k, v, d_o = banded(B, Hq, T, 64), banded(B, Hq, T, 64), banded(B, Hkv, Tkv, 64), banded(B, Hkv, Tkv, 64), banded(B, Hq, T, 64)
+    g = Guarded()
+    out, vbar, stats = g.like(q), g.like(q), g.empty((B, Hq, T, 2), torch.float32)
+    a = plx.prefill_args(q, r, k, v, out, 0.125, causal, True, window)
+    a.vbar, a.row_stats = vbar.data_ptr(), stats.data_ptr()
+    assert plx.load_library().parallax_prefill_form(ctypes.byref(a), 0) == 32
+    _call(plx, "parallax_prefill", a)
+    g.check(("fp32 thirds", T, Tkv, causal, window))
+    g2 = Guarded()
+    dq, dr, dk, dv = g2.like(q), g2.like(q), g2.like(k), g2.like(k)
+    ws = g2.empty((B * Hq * T * 4,), torch.float32)
+    a = plx.prefill_bwd_args(q, r, k, v, out, vbar, stats, d_o, dq, dr, dk, dv, 0.125, causal, ws, window)
+    assert plx.load_library().parallax_prefill_backward_form(ctypes.byref(a)) == 32 + 256 * 32
+    _call(plx, "parallax_prefill_backward", a)
+    g2.check(("fp32 thirds, backward", T, Tkv, causal, window))
+    g.check(("fp32 thirds, backward reads", T, Tkv, causal, window))
+    for t in (out, vbar, stats, dq, dr, dk, dv):
+        assert bool(torch.isfinite(t).all())
+
+
 def test_prefill_fp32_block_sparse_and_norm_rope(plx, synth):
     # fp32 forward + backward
     y = synth.prefill_inputs(1, 2, 2, 70, 64, seed=7500, dtype=torch.float32, device=DEV)
