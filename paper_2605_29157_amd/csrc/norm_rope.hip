@@ -5,7 +5,7 @@
 //     y = x / sqrt(mean_c(x_c^2) + eps) * gamma
 //     (y_2i, y_2i+1) rotated by pos * theta^(-2i/d)   (adjacent pairs)
 // HBM bound: every element is read once and written once, 16 bytes per lane; the lanes of one row
-// (d * element size / 16 of them) share the sum of squares through lane shuffles. The angle is
+// (d * element size / 16 of them) share the sum of squares, rows of 8 and 16 lanes without a trip through the LDS. The angle is
 // formed and reduced modulo 2 pi in double precision (pos * frequency reaches 1e5 and more, where
 // fp32 would lose the fraction), sine and cosine are taken in single precision -- once per
 // (position, pair), for all heads of all tensors.
@@ -187,7 +187,7 @@ hipError_t launch_norm_rope(const NormRopeParams &p_in, bool f32, hipStream_t st
     p.trip_chunks = (trips + p.trips_per_wave - 1) / p.trips_per_wave;
     const double log2_theta = std::log2((double)p.theta);
     p.pair_ratio = std::exp2(-2.0 / (double)p.d * log2_theta);
-    double step[4] = {1.0};  // (every fourth lane by a power, one rounding more in between: six powers a call, not sixteen)
+    double step[4] = {1.0};  // (every fourth lane by a power, one rounding more in between: six powers for 16 lanes, not fifteen)
     for (int i = 1; i < 4; ++i) step[i] = std::exp2(-(double)(i * elems) / (double)p.d * log2_theta);
     for (int i = 0; i < p.d / elems; i += 4) {
         const double first = i == 0 ? 1.0 : std::exp2(-(double)(i * elems) / (double)p.d * log2_theta);
