@@ -7,9 +7,9 @@
 //
 // Against 64 bits the results are closer than those of generic_f32.hip (relative error of o, dq, dr, dk, dv, 8
 // sequences x 8 heads x 512 rows: 2.0, 3.2, 2.9, 3.2, 2.8e-7 against 2.9, 4.1, 3.7, 5.0, 4.2e-7).
-// Time, forward / backward, us, generic_f32.hip -> here: 8 x 8 x 512 58.7 / 131.7 -> 44.0 / 102; 4 x 8 x 512 31.4 / 76.0
-// -> 25.4 / 63.8; 8 heads x 2048 104.5 / 239 -> 82.2 / 212; 4 x 8 x 512 not causal 47.9 / 114.7 -> 33.0 / 85.7.
-// What bounds it: vector ALU and matrix pipe one after the other, 39k and 26k clocks of the 82k that a SIMD
+// Time, forward / backward, us, generic_f32.hip -> here: 8 x 8 x 512 53.2 / 131 -> 40.4 / 107; 4 x 8 x 512 31.0 / 75.9
+// -> 26.3 / 67.3; 8 heads x 2048 103 / 238 -> 83.6 / 222; 4 x 8 x 512 not causal 47.4 / 115 -> 33.9 / 89.9.
+// What bounds it: vector ALU and matrix pipe one after the other, 40k and 26k clocks of the 85k that a SIMD
 // of the forward of 8 x 8 x 512 takes: cutting is 5.5 instructions a value, and with 2 waves per SIMD (256
 // registers) the two hardly overlap. Tried and slower: three waves per SIMD (spills; 45 -> 55), every wave cutting its own
 // tiles without LDS (forward 46, backward 141), remainders by v_dot2 (copies and waits eat what it saves),
