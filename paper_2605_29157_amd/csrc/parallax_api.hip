@@ -241,7 +241,7 @@ int32_t pick_splits(const plx_decode_args *a, int32_t Tq) {
 // a split of `per` blocks of 16 keys walks ceil(per / 4) rounds of its four waves, each a wave's matrix instructions on
 // a SIMD: 1.25 per 64 (padded) dimensions alone on its unit. Of n workgroups on one, up to d = 128 two are resident: 1.1 a
 // round for each, 1 for every further start; above one is: they follow one another, 5.5 for every further start. The
-// merge is a launch, 2.7, and its records at 1 MB / us. Only the fewest splits of a number of rounds can be cheapest.
+// merge is a launch, 2.4, 2.7 and 3.3, and its records at 1 MB / us. Only the fewest splits of a number of rounds can be cheapest.
 // As many workgroups as are resident and at least 128 keys a split, the rule before, left a round or a second
 // workgroup per unit where there need not be one; us, that rule / this one: 1 sequence x 1307 keys, 4 pairs of 4 heads,
 // d = 128 (S = 10 / 21) 18.2 / 13.4; 7 x 1647 likewise (12 / 9) 24.9 / 19.9; 5 x 3198, 16 pairs, d = 64 (7 / 6) 39.4 / 33.8.
@@ -250,7 +250,7 @@ int32_t pick_splits(const plx_decode_args *a, int32_t Tq) {
 // 2 x 6000 131, 74, 47.7, 57.1; S = 10, 11, 20, 32: 3 x 6000 67.9, 104, 77.4, 82.6. Over 48 calls of 8 - 64 pairs x 500 - 6000
 // keys at d = 132 and 256 the model is 1 % from the best, the rule before 29 %; with the second workgroup of a unit at the
 // price of a resident one it was 6 %, and up to 20 % slower than the rule before.
-// Short caches: d = 128, 8 pairs, 100 keys, S = 1, 2: 11.4, 11.7; 160 keys, S = 1, 3: 14.5, 12.0; d = 64, 260 keys 12.7, 13.0.
+// Short caches: d = 128, 8 pairs, 100 keys, S = 1, 2: 11.4, 11.7; 160 keys, S = 1, 3: 14.5, 12.0; d = 64, 350 keys 14.5, 13.2.
 int32_t pick_splits_f32(const plx_decode_args *a, int32_t Tq) {
     if (a->num_splits > 0) return a->num_splits;
     const int64_t groups = (int64_t)a->B * a->Hkv * (((int64_t)(a->Hq / a->Hkv) * Tq + 15) / 16);
@@ -267,7 +267,7 @@ int32_t pick_splits_f32(const plx_decode_args *a, int32_t Tq) {
         const int64_t n = (groups * s + cus - 1) / cus;
         double us = pairs ? (double)rounds * width * (n == 1 ? 1.25 : 1.1 * (double)n) + (double)((n + 1) / 2 - 1)
                           : (double)rounds * width * 1.25 * (double)n + 5.5 * (double)(n - 1);
-        if (s > 1) us += 2.7 + 0.5 * (double)((s + 31) / 32 - 1) + record_us * (double)s;
+        if (s > 1) us += 2.1 + 0.3 * width + 0.5 * (double)((s + 31) / 32 - 1) + record_us * (double)s;
         if (pick == 0 || us < best) best = us, pick = s;
         if (s == 1) return (int32_t)pick;
         rounds = std::max(rounds + 1, (blocks + 4 * (s - 1) - 1) / (4 * (s - 1)));  // the next with fewer splits

@@ -130,9 +130,9 @@ def test_splits_of_an_fp32_call(binding):
         assert [splits(B, 8, 2, d, L) for B, L in ((4, 3000), (8, 1500), (8, 6000), (2, 6000))] == [8, 4, 4, 16]
         assert splits(3, 8, 2, d, 6000) == 10 and splits(6, 8, 2, d, 3000) == 5    # 240 workgroups, not 264 or 768
         assert splits(1, 8, 2, d, 500) == 8 and splits(8, 8, 2, d, 500) == 4       # a round of the four waves each
-    # caches that one or two rounds of a workgroup walk are not worth a merge, three are
+    # at d = 128 caches that one or two rounds of a workgroup walk are not worth a merge, three are
     assert [splits(1, 8, 2, 128, L) for L in (16, 80, 100, 128, 160)] == [1, 1, 1, 1, 3]
-    assert [splits(1, 8, 2, 64, L) for L in (80, 200, 260, 350)] == [1, 1, 1, 2]
+    assert [splits(1, 8, 2, 64, L) for L in (80, 200, 260, 350)] == [1, 1, 2, 2]
     assert splits(4, 8, 2, 64, 2048) == 16 and splits(7, 4, 4, 128, 1647) == 9 and splits(1, 4, 4, 128, 1307) == 21
 
 
