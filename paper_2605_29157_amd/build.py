@@ -100,7 +100,7 @@ def _check_f32_assembly() -> None:
     pass at d = 256: three row blocks, one of them turned round, and two accumulators are 450
     registers, and it parks 46 (ten stores in a loop of 448 matrix instructions)."""
     bad = {n: c for n, c in _spills("generic_f32.hip", "f32_").items() if c > (48 if "cols_kernelILi256" in n else 0)}
-    # (at two workgroups per unit, 256 registers a wave, the dQ / dR pass parks 19 around its loop)
+    # (at two workgroups per unit, 256 registers a wave, the dQ / dR pass parks 19 around its loop, the dK / dV pass 4)
     bad.update({n: c for n, c in _spills("prefill_f32.hip", "f32_").items() if c > 24})
     if bad:
         raise RuntimeError("register spills in an fp32 kernel (%s)" % bad)
